@@ -107,6 +107,11 @@ int static_scratch(void **ptr);
 // part = DEVICE memory of part_bytes bytes for fp32 partial sums when the columns are split.
 int launch_tile_small(const owq_layer_info_t &g, void *blob, void *part, uint64_t part_bytes, int32_t shape, const void *x,
                       void *y, int32_t ntok, void *stream);
+// More than 64 tokens of one task (defined in owq_tile_wide.hip): scratch = DEVICE memory of scratch_bytes bytes.
+// Returns a hipError_t as int, or -1 when that memory cannot hold the gathered activations of 128 tokens.
+int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, const void *x, void *y,
+                     int32_t batch, void *stream);
+int prepare_tile_wide_kernels(const owq_layer_info_t &g, int32_t lds_limit);   // LDS opt-in
 bool tile_small_split_ok(const owq_layer_info_t &g, int32_t split);
 int prepare_tile_small_kernels();   // LDS opt-in
 // scratch_bytes = size of the scratch memory in use, 0 = the blob's own scratch area

@@ -819,6 +819,11 @@ int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t s
 
   const _Float16 *xp = static_cast<const _Float16 *>(x);
   _Float16 *yp = static_cast<_Float16 *>(y);
+  // more tokens than a pass takes: the kernels that read the layer once per 128 tokens and need no such passes
+  if (batch > kScratchBatch && tasks.task_id == nullptr) {
+    const int r = launch_tile_wide(g, blob, scr, scr_bytes, x, y, batch, stream);
+    if (r >= 0) return r;
+  }
   for (int32_t t0 = 0; t0 < batch; t0 += kScratchBatch) {
     const int ntok = batch - t0 < kScratchBatch ? batch - t0 : kScratchBatch;
     const int nt = ntok > 32 ? 2 : 1;
