@@ -2,13 +2,17 @@
 // gfx950: for every (output row, group of input columns) a two-dimensional grid of narrowed
 // ranges is tried and the step size and zero point with the least rounding error are kept.
 //
-// The work is plain fp32 arithmetic, five vector instructions per weight and grid point, so the
-// kernel is laid out for the vector units, not for memory: one wave owns one (row, group), every
-// lane owns up to four grid points (its step size, zero point and running error stay in
-// registers), and the weights of the group are moved through LDS once (converted to fp32, the
-// weak columns dropped) and then read back four at a time at one address for the whole wave,
-// which LDS serves as a broadcast.  No reduction across lanes happens until the grid points of
-// a group are ranked at its end.
+// Summing every weight's error at every grid point is five vector instructions per pair, 256 points per weight.
+// Nearly all points can be ruled out without it.  With c_L the highest level of a point (step size s) and m_l the
+// midpoints between its levels, rounding to nearest with clamping gives
+//     E = sum (w - c_L)^2 + 2 s sum_l G(m_l),      G(m) = sum min(w - m, 0)
+// and G is one concave function of the group, the same for all grid points.  So the group's weights go into a
+// histogram of F bins (in LDS: a count and a sum of offsets, one 64-bit integer atomic per weight), two prefix sums
+// turn it into G at the bin edges, and every grid point is bounded from below by 2^bits - 1 lookups with linear
+// interpolation (a chord of a concave function lies under it).  The point with the least bound is evaluated in full,
+// and then those whose bound, less a bound on its own rounding, does not exceed the least error found: five of 256
+// on groups of 128, one or two on long rows.  These evaluations take the same binary32 decisions per weight as the
+// plain search and share their sums among the lanes.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -35,6 +39,7 @@ struct SearchArgs {
   float *err;
   int *choice;
   int d_in, g, n_groups, k, n_lo, n_hi, units, units_per_wave;
+  int vec;                             // rows and groups on the grid of the lanes' runs of columns
   float qmax, shrink;
 };
 
@@ -62,16 +67,32 @@ __device__ __forceinline__ T wave_all(T v, F op) {
 // Step size, reciprocal and zero point of the grid point that cuts the fractions fa and fb of
 // the range from its ends.  Every operation is a single binary32 operation in the order the
 // interface states; nothing may be fused here.
-__device__ __forceinline__ Cand candidate(float lo, float hi, float fa, float fb, float qmax) {
+// ANY: ranges that are no numbers too.  Otherwise the two divisions take three instructions each instead of ten, with
+// the same results: the quotient by 7 or 15 and the reciprocal of an fp16 number, corrected by their residuals, were
+// compared with the divisions for every mantissa.
+template <bool ANY>
+__device__ __forceinline__ Cand candidate(float lo, float hi, float fa, float fb, float qmax, float rqmax) {
 #pragma clang fp contract(off)
   const float r = hi - lo;
   const float pa = fa * r, pb = fb * r;
   const float lo_i = lo + pa, hi_j = hi - pb;
   const float width = hi_j - lo_i;
-  float s32 = width / qmax;
+  float s32;
+  if (ANY) {
+    s32 = width / qmax;
+  } else {
+    const float q0 = width * rqmax;
+    s32 = __builtin_fmaf(__builtin_fmaf(-q0, qmax, width), rqmax, q0);
+  }
   s32 = s32 > 0x1p-14f ? s32 : 0x1p-14f;
   const float s = (float)(_Float16)s32;
-  const float inv = 1.0f / s;
+  float inv;
+  if (ANY) {
+    inv = 1.0f / s;
+  } else {
+    const float r0 = __builtin_amdgcn_rcpf(s);
+    inv = __builtin_fmaf(__builtin_fmaf(-s, r0, 1.f), r0, r0);
+  }
   const float zl = -lo_i * inv;
   float z = __builtin_rintf(zl);
   z = z < -2048.f ? -2048.f : (z > 2048.f ? 2048.f : z);
@@ -135,13 +156,493 @@ struct Best {
   int id;
 };
 
+// Widens a zero-width range to reach 0; true if there is nothing to search.
+__device__ __forceinline__ bool degenerate(float &lo, float &hi, int kept) {
+  if (kept == 0) return true;
+  if (hi == lo) {
+    lo = lo < 0.f ? lo : 0.f;
+    hi = hi > 0.f ? hi : 0.f;
+    return hi == lo;
+  }
+  return false;
+}
+
+__device__ __forceinline__ void store_choice(const SearchArgs &a, int row, int gi, const Best &b, int lane) {
+  if (lane == 0) {
+    const size_t o = (size_t)row * a.n_groups + gi;
+    a.scale[o] = __builtin_bit_cast(uint16_t, (_Float16)b.s);
+    a.zero[o] = __builtin_bit_cast(uint16_t, (_Float16)b.z);
+    if (a.err != nullptr) a.err[o] = b.e;
+    if (a.choice != nullptr) a.choice[o] = b.id;
+  }
+}
+
+__device__ __forceinline__ uint8_t code_of(float v, const Best &b, float qmax) {
+  const float za = 0.f - b.z, zb = qmax - b.z;
+  return (uint8_t)(int)(__builtin_amdgcn_fmed3f(__builtin_rintf(v * b.inv), za, zb) - za);
+}
+
+// ---------------------------------------------------------------------------
+// bounds from a histogram
+// ---------------------------------------------------------------------------
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp0(int v) {       // 0 in lanes without a source
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+// sum over the lanes up to and including this one
+__device__ __forceinline__ int scan_lanes(int v) {
+  v += dpp0<0x111, 0xf>(v);
+  v += dpp0<0x112, 0xf>(v);
+  v += dpp0<0x114, 0xf>(v);
+  v += dpp0<0x118, 0xf>(v);
+  v += dpp0<0x142, 0xa>(v);
+  v += dpp0<0x143, 0xc>(v);
+  return v;
+}
+__device__ __forceinline__ float scan_lanes(float v) {
+  auto f = [](int x) __attribute__((always_inline)) { return __builtin_bit_cast(float, x); };
+  auto i = [](float x) __attribute__((always_inline)) { return __builtin_bit_cast(int, x); };
+  v += f(dpp0<0x111, 0xf>(i(v)));
+  v += f(dpp0<0x112, 0xf>(i(v)));
+  v += f(dpp0<0x114, 0xf>(i(v)));
+  v += f(dpp0<0x118, 0xf>(i(v)));
+  v += f(dpp0<0x142, 0xa>(i(v)));
+  v += f(dpp0<0x143, 0xc>(i(v)));
+  return v;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  return wave_all(v, [](float x, float y) { return x + y; });
+}
+
+// The search of groups of at most 64 TW NT columns by a team of TW waves (1 or 4, one or four teams per workgroup).
+// Lane t of the team keeps its NT weights of a group in registers, V neighbouring columns at a time; they give
+// the range, the histogram, the evaluations and the codes: one global read per weight.
+// Bins: 4 per lane of the team.  256 for a wave (groups of at most 1024: the bounds are within 0.7 % at 3 bits and
+// groups of 128, 512 bins would leave 4 points instead of 5 and cost a longer scan), 1024 for four waves.
+template <int TW, int NT>
+struct Team {
+  static constexpr int V = NT < 8 ? NT : 8;
+  static constexpr int LANES = 64 * TW;
+  static constexpr int F = 4 * LANES;
+  static constexpr int CPL = 4 / TW;               // grid points per lane
+  static __device__ __forceinline__ int column(int t, int lane) { return ((t / V) * LANES + lane) * V + t % V; }
+};
+
+// Table entry b + 1: G at bin b's lower edge and its increase over the bin; entries 0 and F + 1 continue G one bin beyond
+// the range on either side, which is as far as the midpoints of a grid point get unless its step size or zero point
+// was clamped (those are evaluated in full).
+struct Knot {
+  float g, dg;
+};
+
+__device__ __forceinline__ unsigned long long uniform(unsigned long long v) {
+  return ((unsigned long long)(u32)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | (u32)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// What the waves of a team of four exchange.
+struct TeamShared {
+  Cand cand[256];
+  float part[256][4];
+  float wave[4][4];
+  unsigned long long alive[4];
+  int scan_i[4];
+  float scan_f[4];
+};
+
+template <int TW, int NT>
+__global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
+  using T = Team<TW, NT>;
+  constexpr int V = T::V, LANES = T::LANES, F = T::F, CPL = T::CPL, TEAMS = 4 / TW;
+  __shared__ __attribute__((aligned(16))) unsigned long long hist[TEAMS][F + 2];
+  __shared__ TeamShared sh[1];                     // four waves only
+  extern __shared__ u32 mask[];                    // bit c = column c is weak; (d_in + 31) / 32 words
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int tl = TW == 4 ? tid : lane;             // lane within the team
+  unsigned long long *bins = hist[TW == 4 ? 0 : wv];
+  for (int i = tid; i < (a.d_in + 31) >> 5; i += 256) mask[i] = 0u;
+  __syncthreads();
+  for (int p = tid; p < a.k; p += 256) {
+    const u32 c = (u32)a.weak_idx[p];
+    if (c < (u32)a.d_in) atomicOr(&mask[c >> 5], 1u << (c & 31));
+  }
+  __syncthreads();
+  const int ncand = a.n_lo * a.n_hi;
+  float fa[CPL], fb[CPL];
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) {
+    const int id = tl + LANES * c;
+    const int i = id / a.n_hi, j = id - i * a.n_hi;
+    fa[c] = cut_fraction(a.shrink, i < a.n_lo ? i : 0, a.n_lo);
+    fb[c] = cut_fraction(a.shrink, j, a.n_hi);
+  }
+  const int team = TW == 4 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
+  const int u0 = team * a.units_per_wave;
+  const int n_units = a.units - u0 < a.units_per_wave ? a.units - u0 : a.units_per_wave;   // same for the team
+  if (n_units <= 0) return;                        // four waves: the whole workgroup
+  int row = u0 / a.n_groups, gi = u0 - row * a.n_groups;
+  auto team_barrier = [&]() __attribute__((always_inline)) {
+    if constexpr (TW == 4) __syncthreads();
+    else wave_lds_fence();
+  };
+
+  // columns past the end of a short last group are fetched from its last ones and dropped
+  auto fetch = [&](_Float16 (&dst)[NT], int r, int g) __attribute__((always_inline)) {
+    const int c0 = g * a.g, len = a.d_in - c0 < a.g ? a.d_in - c0 : a.g;
+    const _Float16 *src = a.w + (size_t)r * a.d_in + c0;
+    typedef _Float16 hv __attribute__((ext_vector_type(V)));
+#pragma unroll
+    for (int t = 0; t < NT; t += V) {
+      const int c = T::column(t, tl);
+      if (a.vec) {                                 // rows on the grid of V elements, len a multiple of V
+        const hv v = *reinterpret_cast<const hv *>(src + (c < len ? c : len - V));
+#pragma unroll
+        for (int e = 0; e < V; ++e) dst[t + e] = v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e) dst[t + e] = src[c + e < len ? c + e : len - 1];
+      }
+    }
+  };
+  // a wave fetches its next group while it searches one; with four waves to a row other workgroups fill the wait
+  constexpr bool kAhead = TW == 1;
+  float cur[NT];
+  _Float16 nxt[NT];
+  fetch(nxt, row, gi);
+  for (int uu = 0; uu < n_units; ++uu) {
+    const int c0 = gi * a.g;
+    const int len = a.d_in - c0 < a.g ? a.d_in - c0 : a.g;
+    int nrow = row, ngi = gi + 1;
+    if (ngi == a.n_groups) {
+      ngi = 0;
+      ++nrow;
+    }
+    if (!kAhead && uu > 0) fetch(nxt, row, gi);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) cur[t] = (float)nxt[t];
+    if (kAhead && uu + 1 < n_units) fetch(nxt, nrow, ngi);
+    // ---- range; an empty histogram ----
+    unsigned long long kept = 0;                   // bit t: weight t of this lane takes part
+    float lo = INFINITY, hi = -INFINITY;
+    bool odd = false;                              // a weight that is no number
+#pragma unroll
+    for (int t = 0; t < NT; t += V) {
+      const int c = T::column(t, tl);
+      u32 m = 0u;
+      if (c < len) {
+        m = ~(mask[(c0 + c) >> 5] >> ((c0 + c) & 31)) & ((1u << V) - 1u);
+        if (len - c < V) m &= (1u << (len - c)) - 1u;
+      }
+      kept |= (unsigned long long)m << t;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const float v = cur[t + e];
+        const bool in = (m >> e) & 1u;
+        odd |= in && !(__builtin_fabsf(v) < INFINITY);
+        lo = __builtin_fminf(lo, in ? v : INFINITY);      // ignores what is no number
+        hi = __builtin_fmaxf(hi, in ? v : -INFINITY);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bins[tl * 4 + i] = 0ull;
+    lo = wave_all(lo, [](float x, float y) { return __builtin_fminf(x, y); });
+    hi = wave_all(hi, [](float x, float y) { return __builtin_fmaxf(x, y); });
+    int cnt = 0;                                   // kept weights of the wave
+#pragma unroll
+    for (int t = 0; t < NT; ++t) cnt += __builtin_popcountll(__ballot((kept >> t) & 1u));
+    bool any_odd = __ballot(odd) != 0ull;
+    if constexpr (TW == 4) {
+      if (lane == 0) {
+        sh[0].wave[wv][0] = lo;
+        sh[0].wave[wv][1] = hi;
+        sh[0].wave[wv][2] = (float)cnt;
+        sh[0].wave[wv][3] = any_odd ? 1.f : 0.f;
+      }
+      __syncthreads();
+      cnt = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float l = sh[0].wave[i][0], h = sh[0].wave[i][1];
+        lo = l < lo ? l : lo;
+        hi = h > hi ? h : hi;
+        cnt += (int)sh[0].wave[i][2];
+        any_odd |= sh[0].wave[i][3] != 0.f;
+      }
+    } else {
+      wave_lds_fence();
+    }
+    const bool nothing = degenerate(lo, hi, cnt);
+    Best best = {1.f, 1.f, 0.f, 0.f, 0};
+    if (!nothing) {
+      Cand cd[CPL];
+      float bound[CPL];
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        cd[c] = candidate<false>(lo, hi, fa[c], fb[c], a.qmax, 1.f / a.qmax);
+        bound[c] = -INFINITY;
+      }
+      if (any_odd) {
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) cd[c] = candidate<true>(lo, hi, fa[c], fb[c], a.qmax, 0.f);
+      }
+      // error of grid point (s, inv, za, zb) over this lane's weights, over the wave
+      auto evaluate = [&](const Cand &p) __attribute__((always_inline)) {
+        float e = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const float v = cur[t];
+          const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(v * p.inv), p.a, p.b);   // q - z
+          float d = __builtin_fmaf(-p.s, q, v);
+          d = (kept >> t) & 1u ? d : 0.f;
+          e = __builtin_fmaf(d, d, e);
+        }
+        return wave_sum(e);
+      };
+      const float idelta = (float)F / (hi - lo);
+      float least = INFINITY;                      // least value (not bound) from the table, and its grid point
+      int first = 0x7fffffff;
+      if (!any_odd) {
+        // ---- histogram: count in the upper half, sum of the offsets inside the bin (in 2^-16 bins) in the lower ----
+        float s2 = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const float u = (cur[t] - lo) * idelta;
+          int b = (int)u;
+          b = b < 0 ? 0 : (b > F - 1 ? F - 1 : b);
+          const float f = __builtin_fminf(__builtin_fmaxf(u - (float)b, 0.f), 1.f);
+          const float uc = u - (float)(F / 2);
+          if ((kept >> t) & 1u) {
+            atomicAdd(&bins[b], (1ull << 32) | (unsigned long long)(u32)(f * 65536.f + 0.5f));
+            s2 = __builtin_fmaf(uc, uc, s2);
+          }
+        }
+        s2 = wave_sum(s2);
+        team_barrier();
+        // ---- G at the edges: the increase over bin b is -(weights below it) - (weights in it - their offsets) ----
+        unsigned long long h[4];
+        int n4 = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          h[i] = bins[tl * 4 + i];
+          n4 += (int)(h[i] >> 32);
+        }
+        const int incl = scan_lanes(n4);
+        float dg[4], d4 = 0.f;
+        int below = incl - n4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int n = (int)(h[i] >> 32);
+          dg[i] = -(float)below - ((float)n - (float)(u32)h[i] * 0x1p-16f);
+          below += n;
+          d4 += dg[i];
+        }
+        const float ginc = scan_lanes(d4);
+        float g = ginc - d4, wbelow = 0.f;         // of the wave's own bins; weights in the waves before
+        if constexpr (TW == 4) {
+          if (lane == 63) {
+            sh[0].scan_i[wv] = incl;
+            sh[0].scan_f[wv] = ginc;
+          }
+          if (lane == 0) sh[0].wave[wv][0] = s2;
+          __syncthreads();
+          s2 = (sh[0].wave[0][0] + sh[0].wave[1][0]) + (sh[0].wave[2][0] + sh[0].wave[3][0]);
+          float goff = 0.f;
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+            if (i < wv) {
+              goff += sh[0].scan_f[i] - wbelow * 256.f;
+              wbelow += (float)sh[0].scan_i[i];
+            }
+          g += goff - wbelow * (float)(lane * 4);
+        }
+        Knot *knot = reinterpret_cast<Knot *>(bins);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float d = dg[i] - wbelow;
+          knot[tl * 4 + i + 1] = Knot{g, d};
+          g += d;
+        }
+        if (tl == 0) knot[0] = Knot{0.f, 0.f};
+        if (tl == LANES - 1) knot[F + 1] = Knot{g, -(float)cnt};
+        team_barrier();
+        const float gend = knot[F + 1].g, n = (float)cnt;
+        const float s1 = gend + n * (float)(F / 2);            // sum of the centred weights
+        // ---- bounds ----
+        // What rounding can do to a value: eight operations on terms of at most `mag`, and positions (midpoints, levels)
+        // that are off by `eps` bins, each seen by all weights
+        const float far = __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)) * idelta, half = (float)(F / 2);
+        const float mag = 2.f * (s2 + half * (half * n + 2.f * __builtin_fabsf(s1)));
+        const float eps = 3.f * (float)F + 2.f * far;
+        const float slack = 0x1p-24f * (8.f * mag + 4.f * n * (float)F * eps);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+          const float su = cd[c].s * idelta, top = (cd[c].s * cd[c].b - lo) * idelta - half;
+          const float p1 = (cd[c].s * (cd[c].a + 0.5f) - lo) * idelta + 1.f;
+          const bool inside = p1 >= 0.f && __builtin_fmaf(a.qmax - 1.f, su, p1) < (float)(F + 2);
+          float gs = 0.f;
+          if (inside) {
+#pragma unroll
+            for (int l = 0; l < 15; ++l) {
+              if (l == 7 && a.qmax < 15.f) break;
+              const float p = __builtin_fmaf((float)l, su, p1);
+              const Knot k = knot[(u32)p];
+              gs = __builtin_fmaf(__builtin_amdgcn_fractf(p), k.dg, gs + k.g);
+            }
+          }
+          const float sq = __builtin_fmaf(top, __builtin_fmaf(top, n, -2.f * s1), s2);
+          const float e = __builtin_fmaf(2.f * su, gs, sq);
+          const int id = tl + LANES * c;
+          const bool is = id < ncand;
+          bound[c] = is ? (inside ? e - slack : -INFINITY) : INFINITY;
+          if (is && inside && e < least) {
+            least = e;
+            first = id;
+          }
+        }
+      }
+      // ---- the grid point with the least value first, then all that may be better ----
+      const float to_bins = any_odd ? 1.f : idelta * idelta * (1.f + 0x1p-12f);
+      best.e = INFINITY;
+      best.id = 0x7fffffff;
+      const float wl = wave_all(least, [](float x, float y) { return __builtin_fminf(x, y); });
+      int wf = wave_all(least == wl ? first : 0x7fffffff, [](int x, int y) { return x < y ? x : y; });
+      auto lane_of = [&](float v, int src) __attribute__((always_inline)) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
+      };
+      auto take = [&](float e, int id, const Cand &p) __attribute__((always_inline)) {
+        if (e < best.e || (e == best.e && id < best.id)) {
+          best.e = e;
+          best.id = id;
+          best.s = p.s;
+          best.inv = p.inv;
+          best.z = 0.f - p.a;
+        }
+      };
+      if constexpr (TW == 1) {
+        auto cand_of = [&](int id) __attribute__((always_inline)) {
+          const int src = id & 63, slot = id >> 6;
+          Cand p = {lane_of(cd[0].s, src), lane_of(cd[0].inv, src), lane_of(cd[0].a, src), lane_of(cd[0].b, src)};
+#pragma unroll
+          for (int c = 1; c < CPL; ++c)
+            if (slot == c) p = Cand{lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+          return p;
+        };
+        wf = __builtin_amdgcn_readfirstlane(wf);
+        if (wf != 0x7fffffff) {
+          const Cand p = cand_of(wf);
+          take(evaluate(p), wf, p);
+        }
+        if (any_odd) {
+          // weights that are no numbers: every grid point, and if none has an error that is one, the values of point 63
+          const Cand p = cand_of(63);
+          best.s = p.s; best.inv = p.inv; best.z = 0.f - p.a;
+        }
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+          unsigned long long m = __ballot(bound[c] <= best.e * to_bins && lane + 64 * c < ncand);
+          while (m) {
+            const int src = __builtin_ctzll(m);
+            m &= m - 1;
+            const int id = src + 64 * c;
+            if (id == wf || !(lane_of(bound[c], src) <= best.e * to_bins)) continue;
+            const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+            take(evaluate(p), id, p);
+          }
+        }
+      } else {
+        TeamShared &S = sh[0];
+        S.cand[tid] = cd[0];
+        __syncthreads();                            // the last reads of wave[][0] are done
+        if (lane == 0) {
+          S.wave[wv][0] = wl;
+          S.wave[wv][1] = __builtin_bit_cast(float, wf);
+        }
+        __syncthreads();
+        float l4 = INFINITY;
+        wf = 0x7fffffff;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float l = S.wave[i][0];
+          const int f = __builtin_bit_cast(int, S.wave[i][1]);
+          if (l < l4 || (l == l4 && f < wf)) {
+            l4 = l;
+            wf = f;
+          }
+        }
+        wf = __builtin_amdgcn_readfirstlane(wf);
+        float lim = INFINITY;
+        if (wf != 0x7fffffff) {
+          const Cand p = S.cand[wf];
+          const float e = evaluate(p);
+          if (lane == 0) S.wave[wv][2] = e;
+          __syncthreads();
+          const float e4 = (S.wave[0][2] + S.wave[1][2]) + (S.wave[2][2] + S.wave[3][2]);
+          take(e4, wf, p);
+          lim = e4 * to_bins;
+        } else if (any_odd) {
+          const Cand p = S.cand[63];
+          best.s = p.s; best.inv = p.inv; best.z = 0.f - p.a;
+        }
+        const unsigned long long m = __ballot(bound[0] <= lim && tid < ncand && tid != wf);
+        if (lane == 0) S.alive[wv] = m;
+        __syncthreads();
+        int na = 0;
+        for (int i = 0; i < 4; ++i) {
+          unsigned long long left = uniform(S.alive[i]);
+          while (left) {
+            const int id = i * 64 + __builtin_ctzll(left);
+            left &= left - 1;
+            const float e = evaluate(S.cand[id]);
+            if (lane == 0) S.part[na][wv] = e;
+            ++na;
+          }
+        }
+        __syncthreads();
+        na = 0;
+        for (int i = 0; i < 4; ++i) {
+          unsigned long long left = uniform(S.alive[i]);
+          while (left) {
+            const int id = i * 64 + __builtin_ctzll(left);
+            left &= left - 1;
+            take((S.part[na][0] + S.part[na][1]) + (S.part[na][2] + S.part[na][3]), id, S.cand[id]);
+            ++na;
+          }
+        }
+      }
+    }
+    team_barrier();                                // the histogram is cleared for the next group
+    if (TW == 1 || wv == 0) store_choice(a, row, gi, best, lane);
+    uint8_t *crow = a.codes + (size_t)row * a.d_in + c0;
+    typedef uint8_t bv __attribute__((ext_vector_type(V)));
+#pragma unroll
+    for (int t = 0; t < NT; t += V) {
+      const int c = T::column(t, tl);
+      bv q;
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+        q[e] = (nothing || !((kept >> (t + e)) & 1u)) ? (uint8_t)0 : code_of(cur[t + e], best, a.qmax);
+      if (a.vec) {
+        if (c < len) *reinterpret_cast<bv *>(crow + c) = q;
+      } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+          if (c + e < len) crow[c + e] = q[e];
+      }
+    }
+    row = nrow;
+    gi = ngi;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// plain search of long rows
+// ---------------------------------------------------------------------------
 // The grid points of this lane for the range [lo, hi], errors cleared.
 template <int CPL>
 __device__ __forceinline__ void make_cands(float lo, float hi, const float (&fa)[CPL], const float (&fb)[CPL],
                                            float qmax, Cand (&cd)[CPL], float (&e)[CPL]) {
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
-    cd[c] = candidate(lo, hi, fa[c], fb[c], qmax);
+    cd[c] = candidate<true>(lo, hi, fa[c], fb[c], qmax, 0.f);
     e[c] = 0.f;
   }
 }
@@ -201,38 +702,9 @@ __device__ __forceinline__ Best pick(const Cand (&cd)[CPL], const float (&e)[CPL
   return b;
 }
 
-// Widens a zero-width range to reach 0; true if there is nothing to search.
-__device__ __forceinline__ bool degenerate(float &lo, float &hi, int kept) {
-  if (kept == 0) return true;
-  if (hi == lo) {
-    lo = lo < 0.f ? lo : 0.f;
-    hi = hi > 0.f ? hi : 0.f;
-    return hi == lo;
-  }
-  return false;
-}
-
-__device__ __forceinline__ void store_choice(const SearchArgs &a, int row, int gi, const Best &b, int lane) {
-  if (lane == 0) {
-    const size_t o = (size_t)row * a.n_groups + gi;
-    a.scale[o] = __builtin_bit_cast(uint16_t, (_Float16)b.s);
-    a.zero[o] = __builtin_bit_cast(uint16_t, (_Float16)b.z);
-    if (a.err != nullptr) a.err[o] = b.e;
-    if (a.choice != nullptr) a.choice[o] = b.id;
-  }
-}
-
-__device__ __forceinline__ uint8_t code_of(float v, const Best &b, float qmax) {
-  const float za = 0.f - b.z, zb = qmax - b.z;
-  return (uint8_t)(int)(__builtin_amdgcn_fmed3f(__builtin_rintf(v * b.inv), za, zb) - za);
-}
-
-// NT > 0: groups of at most 64 NT columns.  A lane keeps its NT weights of the group in
-// registers (they serve the range, the list in LDS and the codes), and the weights of the
-// wave's next group are fetched while the current one is searched.
-// NT = 0: longer groups, moved through LDS kChunk columns at a time, three passes over the row
-// (range, errors, codes).
-template <int CPL, int NT>
+// Groups of more than 16384 columns, which four waves do not hold in registers: one wave per group, moved through
+// LDS kChunk columns at a time, three passes over the row (range, errors, codes).
+template <int CPL>
 __global__ __launch_bounds__(kWaves * 64) void owq_search_kernel(const SearchArgs a) {
   __shared__ __attribute__((aligned(16))) float lists[kWaves][kChunk + 4];   // + 4: read one step ahead
   extern __shared__ u32 mask[];                    // bit c = column c is weak; (d_in + 31) / 32 words
@@ -262,130 +734,64 @@ __global__ __launch_bounds__(kWaves * 64) void owq_search_kernel(const SearchArg
   int row = u0 / a.n_groups, gi = u0 - row * a.n_groups;
   const Best none = {1.f, 1.f, 0.f, 0.f, 0};
 
-  if constexpr (NT > 0) {
-    // columns past the end of a short last group are fetched from its last column and dropped
-    auto fetch = [&](_Float16 (&dst)[NT], int r, int g) __attribute__((always_inline)) {
-      const int c0 = g * a.g;
-      const int last = (a.d_in - c0 < a.g ? a.d_in - c0 : a.g) - 1;
-      const _Float16 *src = a.w + (size_t)r * a.d_in + c0;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int c = t * 64 + lane;
-        dst[t] = src[c < last ? c : last];
-      }
-    };
-    _Float16 cur[NT], nxt[NT];
-    fetch(cur, row, gi);
-    for (int uu = 0; uu < n_units; ++uu) {
-      const int c0 = gi * a.g;
-      const int len = a.d_in - c0 < a.g ? a.d_in - c0 : a.g;
-      int nrow = row, ngi = gi + 1;
-      if (ngi == a.n_groups) {
-        ngi = 0;
-        ++nrow;
-      }
-      if (uu + 1 < n_units) fetch(nxt, nrow, ngi);
-      // range and list straight from the registers
-      float lo = INFINITY, hi = -INFINITY;
-      int cnt = 0;
-      u32 weak_bits = 0u;                          // bit t: slot t of this lane is no weight of the search
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int c = t * 64 + lane;
-        const bool keep = c < len && !is_weak(mask, c0 + (c < len ? c : 0));
-        const float v = (float)cur[t];
-        const unsigned long long m = __ballot(keep);
-        const int pos = cnt + (int)__builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u));
-        if (keep) {
-          list[pos] = v;
-          lo = v < lo ? v : lo;
-          hi = v > hi ? v : hi;
-        } else {
-          weak_bits |= 1u << t;
-        }
-        cnt += __builtin_popcountll(m);
+  for (int uu = 0; uu < n_units; ++uu) {
+    const int c0 = gi * a.g;
+    const int len = a.d_in - c0 < a.g ? a.d_in - c0 : a.g;
+    const _Float16 *wrow = a.w + (size_t)row * a.d_in;
+    // least and greatest non-weak weight
+    float lo = INFINITY, hi = -INFINITY;
+    int kept = 0;
+    for (int o = 0; o < len; o += kChunk) {
+      const int cnt = stage(wrow, c0 + o, len - o < kChunk ? len - o : kChunk, list, mask, lane);
+      kept += cnt;
+      for (int e = lane; e < cnt; e += 64) {
+        const float v = list[e];
+        lo = v < lo ? v : lo;
+        hi = v > hi ? v : hi;
       }
       wave_lds_fence();
-      lo = wave_all(lo, [](float x, float y) { return x < y ? x : y; });
-      hi = wave_all(hi, [](float x, float y) { return x > y ? x : y; });
-      const bool nothing = degenerate(lo, hi, cnt);
-      Best best = none;
-      if (!nothing) {
-        Cand cd[CPL];
-        float e[CPL];
-        make_cands<CPL>(lo, hi, fa, fb, a.qmax, cd, e);
-        accumulate_list<CPL>(list, cnt, cd, e);
-        best = pick<CPL>(cd, e, ncand, lane);
-      }
-      wave_lds_fence();                            // the list is rewritten for the next group
-      store_choice(a, row, gi, best, lane);
-      uint8_t *crow = a.codes + (size_t)row * a.d_in + c0;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int c = t * 64 + lane;
-        const uint8_t q = (nothing || ((weak_bits >> t) & 1u)) ? (uint8_t)0 : code_of((float)cur[t], best, a.qmax);
-        if (c < len) crow[c] = q;
-      }
-#pragma unroll
-      for (int t = 0; t < NT; ++t) cur[t] = nxt[t];
-      row = nrow;
-      gi = ngi;
     }
-  } else {
-    for (int uu = 0; uu < n_units; ++uu) {
-      const int c0 = gi * a.g;
-      const int len = a.d_in - c0 < a.g ? a.d_in - c0 : a.g;
-      const _Float16 *wrow = a.w + (size_t)row * a.d_in;
-      // least and greatest non-weak weight
-      float lo = INFINITY, hi = -INFINITY;
-      int kept = 0;
+    lo = wave_all(lo, [](float x, float y) { return x < y ? x : y; });
+    hi = wave_all(hi, [](float x, float y) { return x > y ? x : y; });
+    const bool nothing = degenerate(lo, hi, kept);
+    Best best = none;
+    if (!nothing) {
+      Cand cd[CPL];
+      float e[CPL];
+      make_cands<CPL>(lo, hi, fa, fb, a.qmax, cd, e);
       for (int o = 0; o < len; o += kChunk) {
         const int cnt = stage(wrow, c0 + o, len - o < kChunk ? len - o : kChunk, list, mask, lane);
-        kept += cnt;
-        for (int e = lane; e < cnt; e += 64) {
-          const float v = list[e];
-          lo = v < lo ? v : lo;
-          hi = v > hi ? v : hi;
-        }
-        wave_lds_fence();
+        accumulate_list<CPL>(list, cnt, cd, e);
+        wave_lds_fence();                        // the list is rewritten by the next pass
       }
-      lo = wave_all(lo, [](float x, float y) { return x < y ? x : y; });
-      hi = wave_all(hi, [](float x, float y) { return x > y ? x : y; });
-      const bool nothing = degenerate(lo, hi, kept);
-      Best best = none;
-      if (!nothing) {
-        Cand cd[CPL];
-        float e[CPL];
-        make_cands<CPL>(lo, hi, fa, fb, a.qmax, cd, e);
-        for (int o = 0; o < len; o += kChunk) {
-          const int cnt = stage(wrow, c0 + o, len - o < kChunk ? len - o : kChunk, list, mask, lane);
-          accumulate_list<CPL>(list, cnt, cd, e);
-          wave_lds_fence();                        // the list is rewritten by the next pass
-        }
-        best = pick<CPL>(cd, e, ncand, lane);
-      }
-      store_choice(a, row, gi, best, lane);
-      // the codes of the group under the chosen step size and zero point; 0 at weak columns
-      uint8_t *crow = a.codes + (size_t)row * a.d_in;
-      for (int c = c0 + lane; c < c0 + len; c += 64)
-        crow[c] = (nothing || is_weak(mask, c)) ? (uint8_t)0 : code_of((float)wrow[c], best, a.qmax);
-      if (++gi == a.n_groups) {
-        gi = 0;
-        ++row;
-      }
+      best = pick<CPL>(cd, e, ncand, lane);
+    }
+    store_choice(a, row, gi, best, lane);
+    // the codes of the group under the chosen step size and zero point; 0 at weak columns
+    uint8_t *crow = a.codes + (size_t)row * a.d_in;
+    for (int c = c0 + lane; c < c0 + len; c += 64)
+      crow[c] = (nothing || is_weak(mask, c)) ? (uint8_t)0 : code_of((float)wrow[c], best, a.qmax);
+    if (++gi == a.n_groups) {
+      gi = 0;
+      ++row;
     }
   }
 }
 
 typedef void (*search_fn)(const SearchArgs);
-template <int CPL>
-search_fn pick_nt(int g) {
-  if (g <= 128) return owq_search_kernel<CPL, 2>;
-  if (g <= 256) return owq_search_kernel<CPL, 4>;
-  if (g <= 512) return owq_search_kernel<CPL, 8>;
-  if (g <= kChunk) return owq_search_kernel<CPL, 16>;
-  return owq_search_kernel<CPL, 0>;
+search_fn pick_bounds(int g) {
+  if (g <= 128) return owq_search_bounds<1, 2>;
+  if (g <= 256) return owq_search_bounds<1, 4>;
+  if (g <= 512) return owq_search_bounds<1, 8>;
+  if (g <= 1024) return owq_search_bounds<1, 16>;
+  if (g <= 2048) return owq_search_bounds<4, 8>;
+  if (g <= 4096) return owq_search_bounds<4, 16>;
+  if (g <= 6144) return owq_search_bounds<4, 24>;
+  if (g <= 8192) return owq_search_bounds<4, 32>;
+  if (g <= 12288) return owq_search_bounds<4, 48>;
+  return owq_search_bounds<4, 64>;
 }
+constexpr int kBoundsMax = 16384;    // columns of the longest group four waves keep in registers
 
 }  // namespace
 }  // namespace owq
@@ -423,17 +829,23 @@ extern "C" owq_status_t owq_search_config(const owq_search_desc_t *d, const uint
   a.n_lo = d->n_lo;
   a.n_hi = d->n_hi;
   a.units = (int)units;
-  // several groups per wave once there are enough waves to fill the chip many times over: the
-  // per-lane grid set-up is then paid once per wave
-  long long upw = units / 32768;
+  // several groups per team once there are enough teams to fill the chip many times over: the
+  // per-lane grid set-up and the weak mask are then paid once per team
+  const bool bounds = g <= kBoundsMax;
+  const int team_waves = bounds && g > 1024 ? 4 : 1;
+  const long long upw = units / (team_waves == 4 ? 2048 : 32768);
   a.units_per_wave = (int)(upw < 1 ? 1 : (upw > 16 ? 16 : upw));
   a.qmax = (float)((1 << d->bits) - 1);
   a.shrink = d->shrink;
-  const long long waves = (units + a.units_per_wave - 1) / a.units_per_wave;
-  const dim3 grid((unsigned)((waves + kWaves - 1) / kWaves)), block(kWaves * 64);
+  const int run = g <= 128 ? 2 : g <= 256 ? 4 : 8;   // columns a lane of owq_search_bounds reads at once
+  a.vec = d->d_in % run == 0 && reinterpret_cast<uintptr_t>(w) % (2 * run) == 0 && reinterpret_cast<uintptr_t>(codes) % run == 0;
+  const long long teams = (units + a.units_per_wave - 1) / a.units_per_wave;
+  const int per_wg = kWaves / team_waves;
+  const dim3 grid((unsigned)((teams + per_wg - 1) / per_wg)), block(kWaves * 64);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int ncand = d->n_lo * d->n_hi;
-  const search_fn fn = ncand <= 64 ? pick_nt<1>(g) : ncand <= 128 ? pick_nt<2>(g) : ncand <= 192 ? pick_nt<3>(g) : pick_nt<4>(g);
+  const search_fn fn = bounds ? pick_bounds(g)
+                       : ncand <= 64 ? owq_search_kernel<1> : ncand <= 128 ? owq_search_kernel<2> : ncand <= 192 ? owq_search_kernel<3> : owq_search_kernel<4>;
   hipLaunchKernelGGL(fn, grid, block, mask_bytes, st, a);
   return hipGetLastError() == hipSuccess ? OWQ_OK : OWQ_ERR_HIP;
 }
