@@ -25,7 +25,7 @@ static owq_status_t make_handle(const owq_layer_info_t &g, void *dev_buf, owq_ha
     if (e == (int)hipErrorInvalidValue) return OWQ_ERR_UNSUPPORTED;
     if (e != 0) return OWQ_ERR_HIP;
     if (prepare_tile_small_kernels() != 0) return OWQ_ERR_HIP;
-    if (prepare_tile_wide_kernels(g, lds_limit) != 0) return OWQ_ERR_HIP;
+    if (prepare_tile_wide_kernels(g, lds_limit) != 0 || prepare_backward_kernels(g, lds_limit) != 0) return OWQ_ERR_HIP;
   } else {
     shape = default_shape(g, lds_limit);
     if (shape.rtw < 1) return OWQ_ERR_UNSUPPORTED;

@@ -8,20 +8,17 @@
 // The dense part contracts over the rows i, while a lane of a packed tile holds eight
 // consecutive COLUMNS of one row, which is what the forward product wants as a matrix-core
 // operand and the wrong way round here.  The codes are therefore sent through the matrix core
-// twice.  First as the A operand against a selection matrix (ones on a diagonal): the result
-// is the same 32 x 32 block of codes, but in the accumulator layout, where a lane holds one
-// column and sixteen rows; starting the accumulator at minus the unpack constant 2^(10-o) of
-// the lane's column leaves the bare integer codes.  Converted to fp16 they are the B operand
-// of the real product, whose A operand is dy times the step size, staged in operand order.
-// No LDS and no shuffles are needed for the turn.  The zero-point term sum_i a[n, i] z[i] is
-// summed on the vector units beside the matrix instructions and taken off at the end.
+// twice.  First as the A operand against a selection matrix (ones on a diagonal): the result is
+// the same 32 x 32 block of q - z, but in the accumulator layout, where a lane holds one column
+// and sixteen rows.  Converted to fp16 (small integers, exact) they are the B operand of the real
+// product, whose A operand is dy times the step size, staged in operand order.  No LDS and no
+// shuffles are needed for the turn.
 //
-// Three launches per group of up to four passes of 128 tokens (staging: dy into operand order,
-// on the first group also the weak columns and the activations at the weak columns; product into
-// fp32 partial results per range of rows, the weak columns of dx riding along as one more tile of
-// columns per workgroup; sum of the partial results into fp16 dx), one more for dww over the whole
-// batch (a product with the tokens on the contraction axis).  A layer with more tiles of weak
-// columns than block pairs takes a plain kernel for the weak columns of dx instead.
+// Per group of up to four passes of 128 tokens: staging (dy into operand order, on the first group also the weak
+// columns and the activations at the weak columns); the small products (dww of the whole batch on the first group,
+// dx at the weak columns in partial results); the product into fp32 partial results per range of rows; the sum of
+// the partial results into fp16 dx.  A layer whose weak columns are more than an eighth of all takes a plain
+// kernel for the weak columns of dx instead.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -33,14 +30,10 @@ namespace owq {
 namespace {
 
 constexpr int kPassTokens = 128;     // tokens per pass: four accumulator tiles of 32 per wave
-constexpr int kBwdWaves = 4;         // one per quarter of a tile's 256 columns
 constexpr int kSplitMax = 16;        // most ranges of rows per block pair
+constexpr int kWeakSplit = 32;       // ranges of rows of the product with the weak columns
 constexpr int kLaunchPasses = 4;     // passes (of 128 tokens) that one set of launches takes
 constexpr size_t kScanBytes = 2048;  // end of the workspace: the magnitude scan's 256 words, then the exponent
-
-// bit offset of the pair of codes that column c (0..15) of K-step t holds, as in the packer
-__device__ const signed char kPairOffset3[4][4] = {{0, 3, 6, 1}, {4, 7, 2, 5}, {0, 3, 6, 1}, {4, 7, 4, 7}};
-__device__ const signed char kPairOffset4[4] = {0, 4, 2, 6};
 
 // N 2-byte loads whose results get a use of their own after all of them have been issued, so
 // that the compiler cannot move a load under the branch of a later select (loads under branches
@@ -71,9 +64,16 @@ __global__ __launch_bounds__(256) void owq_bwd_absmax(const u32x4 *dy, size_t n1
     const u32 lo = w & 0x7fffu, hi = (w >> 16) & 0x7fffu;
     m = max(m, max(lo, hi));
   };
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)kMaxBlocks * 256) {
-    const u32x4 v = dy[i];
-    take(v.x); take(v.y); take(v.z); take(v.w);
+  // eight loads in flight per thread (one at a time: 9.7 instead of 6.1 us on 27 MB); past the end the last one again
+  constexpr size_t kStep = (size_t)kMaxBlocks * 256;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += 8 * kStep) {
+    u32x4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = dy[i + j * kStep < n16 ? i + j * kStep : n16 - 1];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      take(v[j].x); take(v[j].y); take(v[j].z); take(v[j].w);
+    }
   }
   for (size_t i = n16 * 8 + (size_t)blockIdx.x * 256 + threadIdx.x; i < n_halves; i += (size_t)kMaxBlocks * 256)
     take(dy_h[i]);
@@ -89,16 +89,16 @@ __device__ __forceinline__ int scale_exponent(u32 max_bits) { return 24 - (int)(
 
 struct StageArgs {
   const _Float16 *dy;   // [batch][d_out]
-  u32x4 *a_st;          // [pass][n_rt][2][4 token tiles][64 lanes] units of 8 fp16
-  int d_out, n_rt, n0, batch, passes;
+  u32x4 *a_st;          // [pass][n_st][2][4 token tiles][64 lanes] units of 8 fp16
+  int d_out, n_st, n0, batch, passes;      // n_st: row tiles staged per pass, the last one all zeros
   const u32 *maxima;    // [kMaxBlocks] from owq_bwd_absmax
   int *kword;           // the exponent, for the kernel that scales the sums back
 };
 
-// One thread per unit: token 32 m + lane % 32 of the pass, rows 32 rt + 16 s + 4 h + {0..3} and
+// A unit: token 32 m + lane % 32 of the pass, rows 32 rt + 16 s + 4 h + {0..3} and
 // the same + 8 (h = lane / 32): the order in which the turned codes hold their rows.  Block b of
-// the staging takes one tile of 32 tokens and two row tiles: the 64 rows x 2 bytes that its four
-// waves read of a token are one 128-byte line, fetched by this block only.
+// the staging takes two row tiles of a pass, a thread one unit of each of its four tiles of 32 tokens: the 64 rows x
+// 2 bytes that its four waves read of a token are one 128-byte line, fetched by this block only.
 __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) {
   // the scale: every workgroup reduces the scan's 256 entries again (cheaper than one more launch)
   __shared__ u32 red[4];
@@ -110,42 +110,58 @@ __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) 
   const int kexp = scale_exponent(max(max(red[0], red[1]), max(red[2], red[3])));
   const float scale = __builtin_ldexpf(1.0f, kexp);
   if (b == 0 && t == 0) *a.kword = kexp;
-  const int pairs = (a.n_rt + 1) >> 1;
-  const int m = (int)(b & 3), pr = (int)((b >> 2) % (unsigned)pairs), pass = (int)((b >> 2) / (unsigned)pairs);
-  const int l = t & 63, s = (t >> 6) & 1, rt = 2 * pr + (t >> 7);
-  if (pass >= a.passes || rt >= a.n_rt) return;
-  const long long u = (long long)pass * a.n_rt * 512 + (((long long)rt * 2 + s) * 4 + m) * 64 + l;
-  const int n = a.n0 + kPassTokens * pass + 32 * m + (l & 31), h = l >> 5;
-  h8_t v;
+  const int pairs = (a.n_st + 1) >> 1;
+  const int pr = (int)(b % (unsigned)pairs), pass = (int)(b / (unsigned)pairs);
+  const int l = t & 63, s = (t >> 6) & 1, rt = 2 * pr + (t >> 7), h = l >> 5;
+  if (pass >= a.passes || rt >= a.n_st) return;
+  u32x4 *dst = a.a_st + (size_t)pass * a.n_st * 512 + ((size_t)rt * 2 + s) * 256 + l;
+  const int n0 = a.n0 + kPassTokens * pass + (l & 31);
+  h8_t v[4];
   const int ia = 32 * rt + 16 * s + 4 * h;          // rows ia .. ia + 3 and ia + 8 .. ia + 11
-  if (n < a.batch && ia + 11 < a.d_out && (a.d_out & 3) == 0) {
+  if (ia + 11 < a.d_out && (a.d_out & 3) == 0) {
     // both runs of four rows inside the matrix and 8-byte aligned (dy is 16-byte aligned)
     typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
-    const _Float16 *row = a.dy + (size_t)n * a.d_out + ia;
-    const h4_t lo = *reinterpret_cast<const h4_t *>(row), hi = *reinterpret_cast<const h4_t *>(row + 8);
+    h4_t lo[4], hi[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = lo[e];
-      v[4 + e] = hi[e];
+    for (int m = 0; m < 4; ++m) {
+      const int n = n0 + 32 * m;
+      const _Float16 *row = a.dy + (size_t)(n < a.batch ? n : a.batch - 1) * a.d_out + ia;
+      lo[m] = *reinterpret_cast<const h4_t *>(row);
+      hi[m] = *reinterpret_cast<const h4_t *>(row + 8);
     }
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = n0 + 32 * m < a.batch;
+        v[m][e] = in ? lo[m][e] : (_Float16)0.f;
+        v[m][4 + e] = in ? hi[m][e] : (_Float16)0.f;
+      }
   } else {
-    const _Float16 *p[8];
-    _Float16 x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i = ia + (e & 3) + 8 * (e >> 2);
-      p[e] = a.dy + (size_t)(n < a.batch ? n : a.batch - 1) * a.d_out + (i < a.d_out ? i : a.d_out - 1);
-    }
-    load_h<8>(p, x);
+    for (int m = 0; m < 4; ++m) {
+      const int n = n0 + 32 * m;
+      const _Float16 *p[8];
+      _Float16 x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i = ia + (e & 3) + 8 * (e >> 2);
-      v[e] = (n < a.batch && i < a.d_out) ? x[e] : (_Float16)0.f;
+      for (int e = 0; e < 8; ++e) {
+        const int i = ia + (e & 3) + 8 * (e >> 2);
+        p[e] = a.dy + (size_t)(n < a.batch ? n : a.batch - 1) * a.d_out + (i < a.d_out ? i : a.d_out - 1);
+      }
+      load_h<8>(p, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = ia + (e & 3) + 8 * (e >> 2);
+        v[m][e] = (n < a.batch && i < a.d_out) ? x[e] : (_Float16)0.f;
+      }
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = (_Float16)((float)v[e] * scale);      // a power of two, below 1024 afterwards: exact
-  a.a_st[u] = __builtin_bit_cast(u32x4, v);
+  for (int m = 0; m < 4; ++m) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[m][e] = (_Float16)((float)v[m][e] * scale);      // a power of two, below 1024 afterwards: exact
+    dst[m * 64] = __builtin_bit_cast(u32x4, v[m]);
+  }
 }
 
 struct StageWeakArgs {
@@ -180,34 +196,50 @@ struct ProdArgs {
   const u32 *codes;     // dwords of the packed tiles
   const u32 *sz;        // [G][d_out_pad] step size | zero point << 16
   const u32x4 *a_st;
-  float *part;          // [split][128][d_in_pad]
-  const u32x4 *wst;     // staged weak columns, or nullptr: the weak columns of dx are not made here
-  float *pw;            // [split][128][32 kp32]: their partial results
-  int n_rt, nbp, chunks, d_out_pad, d_in_pad, blocks_per_group, n_groups, split, rt_per_split, kp32;
+  float *part;          // [pass][split][128][d_in_pad]
+  int n_rt, nbp, chunks, d_out_pad, d_in_pad, blocks_per_group, n_groups, split, rt_per_split;
 };
 
-// HAS_W: the weak columns of dx ride along (every workgroup does the matrix instruction, those
-// without a tile of weak columns on a tile they do not store: a branch around it costs more).
-template <int BITS, bool HAS_W>
-__global__ __launch_bounds__(kBwdWaves * 64) void owq_bwd_product(const ProdArgs a) {
-  __shared__ float zbuf[kBwdWaves][4][32];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5, n32 = lane & 31;
+constexpr int kStepTiles = 4;                          // row tiles between two barriers
+constexpr int kStepBytes = kStepTiles * 8192;          // staged dy of a step: 128 tokens x 128 rows
+constexpr int kProdPlanes = 4 * kStepBytes;            // two buffers for either half of the rows; then per wave:
+constexpr int kProdPlane = kStepTiles * 32 * 6;        // step sizes and rests in operand order, zero points, of a step's rows
+constexpr int kProdLds = kProdPlanes + 8 * kProdPlane;
+
+// dx in partial results: a workgroup of eight waves takes 256 columns (a block pair) x 128 tokens x a range of row
+// tiles; waves 0..3 take 64 columns each over the first half of the range, waves 4..7 the same columns over the second.
+//
+// What bounds it: per 32 rows x 64 columns x 128 tokens a wave issues 16 matrix instructions for the product and 4 for
+// the turn, and about 100 vector instructions (mask-and-OR with -(2^(10-o) + z) added: 56, conversion of the turned
+// codes 16, dy times step size 32), so two waves per SIMD keep the matrix cores busy if nothing else is in the way.
+// Hence: staged dy comes in operand order by direct loads to LDS (no registers, no copies between register sets), step
+// sizes lie in LDS in the order a lane multiplies them, zero points leave with the unpack constant (exactly: integers
+// of at most 1024, what they lack is taken off by a side loop where a layer has other ones).  4096 -> 16384, 3-bit, 512
+// tokens: 92 us, 745 TFLOP/s beside a turn of a quarter more; with one wave per SIMD, all of that in registers and the
+// zero points summed beside the product 135 us.  5120 -> 13824, 4-bit, 512 tokens: 91 us against 175.
+template <int BITS>
+__global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
+  extern __shared__ u32x4 lds_units[];
+  unsigned char *lds = reinterpret_cast<unsigned char *>(lds_units);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cw = w & 3, kh = w >> 2;
+  const int h = lane >> 5, n32 = lane & 31;
   // Workgroups go to the eight dies (each with its own L2) in turn.  The workgroups that read the
   // same rows of the staged dy (same pass, same range of rows, different block pairs) are given
   // ids that land on one die: die d takes a contiguous eighth of the (pass, range, block pair) order.
-  int id = blockIdx.x;
-  const int total = gridDim.x;
-  if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+  const int N = gridDim.x, xcd = blockIdx.x & 7, id = xcd * (N >> 3) + min(xcd, N & 7) + (int)(blockIdx.x >> 3);
   const int bp = id % a.nbp, sp = (id / a.nbp) % a.split, pass = id / (a.nbp * a.split);
-  const u32x4 *a_st = a.a_st + (size_t)pass * a.n_rt * 512;
-  const int rt0 = sp * a.rt_per_split;
-  const int rt1 = rt0 + a.rt_per_split < a.n_rt ? rt0 + a.rt_per_split : a.n_rt;
+  const unsigned char *a_st = reinterpret_cast<const unsigned char *>(a.a_st) + (size_t)pass * (a.n_rt + 1) * 8192;
+  const int lo = sp * a.rt_per_split, hi = min(lo + a.rt_per_split, a.n_rt), mid = lo + (hi - lo + 1) / 2;
+  const int rt0 = kh ? mid : lo, rt1 = kh ? hi : mid;
+  const int steps = (mid - lo + kStepTiles - 1) / kStepTiles;             // of either half (the first is not the shorter)
+  const u32 ldsb = lds_address(lds);
+  _Float16 *splane = reinterpret_cast<_Float16 *>(lds + kProdPlanes + w * kProdPlane), *rplane = splane + kStepTiles * 32,
+           *zplane = rplane + kStepTiles * 32;
   Magic M;
   M.init();
   // this wave's 64 columns lie in one block (128 columns), hence in one group
-  const int blk = 2 * bp + (w >> 1);
-  int g = blk / a.blocks_per_group;
-  g = g < a.n_groups ? g : a.n_groups - 1;                          // columns past d_in: any group, their codes are 0
+  int g = (2 * bp + (cw >> 1)) / a.blocks_per_group;
+  g = g < a.n_groups ? g : a.n_groups - 1;                          // columns past d_in: any group, they are not stored
   const u32 *sz = a.sz + (size_t)g * a.d_out_pad;
   // selection matrices: K-step t of the forward numbering holds columns 16 t .. 16 t + 15 of the
   // block; two of them side by side make a 32-column tile
@@ -217,180 +249,215 @@ __global__ __launch_bounds__(kBwdWaves * 64) void owq_bwd_product(const ProdArgs
     sel0[e] = (n32 == 8 * h + e) ? (_Float16)1.f : (_Float16)0.f;
     sel1[e] = (n32 == 16 + 8 * h + e) ? (_Float16)1.f : (_Float16)0.f;
   }
-  // minus the unpack constant of this lane's column in either column tile of the wave
-  float cneg[2];
+  f16_t acc[4][2], zero;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int t = 2 * c + (n32 >> 4), i = (n32 & 7) >> 1;            // t & 3 of the K-step, pair in its octet
-    const int o = BITS == 3 ? kPairOffset3[t][i] : kPairOffset4[i];
-    cneg[c] = -(float)(1 << (10 - o));
-  }
-  f16_t acc[4][2];
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[m][c][r] = 0.f;
+  for (int m = 0; m < 4; ++m) acc[m][0] = acc[m][1] = zero;
   float zacc[4] = {0.f, 0.f, 0.f, 0.f};
-  // Weak columns of dx: the workgroup of block pair bp also takes tile bp of the weak columns
-  // (32 of them), each of its waves one tile of 32 tokens, from the same staged dy, unscaled.
-  const bool has_w = HAS_W && bp < a.kp32;
-  const int wtile = HAS_W ? (bp < a.kp32 ? bp : 0) : 0;
-  f16_t wacc;
+  u32 cd[kStepTiles][4];
+  u32 szr[2];
+  // codes of K-steps 4 cw .. 4 cw + 3 of the lane: 3 cw .. of its 12 or 4 cw .. of its 16 dwords.  Tiles past the range: the last
+  // tile's (their dy is zero)
+  auto fetch_codes = [&](int i, int rt) __attribute__((always_inline)) {
+    const u32 *tile = a.codes + (size_t)(min(rt, a.n_rt - 1) * a.nbp + bp) * (u32)(a.chunks * 256);
+    if (BITS == 4) {
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(tile + cw * 256 + lane * 4);
+      cd[i][0] = v.x; cd[i][1] = v.y; cd[i][2] = v.z; cd[i][3] = v.w;
+    } else {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) wacc[r] = 0.f;
-  constexpr int kDw = BITS == 3 ? 3 : 4;                              // dwords of the lane that hold this wave's columns
-  // What one row tile needs from memory besides its codes; fetched one tile ahead.
-  struct Fetched {
-    u32x4 q[2][2];      // step sizes and zero points of the lane's eight rows of either half
-    u32x4 raw[2][4];    // staged dy of the four token tiles
-    u32x4 wsu[2];       // staged weak columns
-    u32x4 raww[2];      // staged dy of token tile w once more (unscaled operand of the weak product)
-  };
-  // codes of K-steps 4 w .. 4 w + 3 of the lane: dwords kDw w .. of its 12 or 16; fetched two tiles ahead
-  struct Codes {
-    u32 cw[4];
-  };
-  auto fetch_codes = [&](Codes &c, int rt) __attribute__((always_inline)) {
-    const size_t tile = (size_t)rt * a.nbp + bp;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int dwi = kDw * w + (v < kDw ? v : 0);
-      c.cw[v] = a.codes[((tile * a.chunks + (dwi >> 2)) * 64 + lane) * 4 + (dwi & 3)];
+      for (int v = 0; v < 3; ++v) cd[i][v] = tile[((3 * cw + v) >> 2) * 256 + lane * 4 + ((3 * cw + v) & 3)];
+      cd[i][3] = 0u;
     }
   };
-  auto fetch = [&](Fetched &f, int rt) __attribute__((always_inline)) {
+  auto fetch_sz = [&](int rt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int i0 = 32 * rt + 16 * s + 4 * h;
-      f.q[s][0] = *reinterpret_cast<const u32x4 *>(sz + i0);
-      f.q[s][1] = *reinterpret_cast<const u32x4 *>(sz + i0 + 8);
+    for (int i = 0; i < 2; ++i) szr[i] = sz[min(32 * rt + 64 * i + lane, a.d_out_pad - 1)];
+  };
+  // the half's staged dy of a step: 8 KB per row tile, two of them by this wave
+  auto fetch_dy = [&](int rt, int buf) __attribute__((always_inline)) {
 #pragma unroll
-      for (int m = 0; m < 4; ++m) f.raw[s][m] = a_st[(((size_t)rt * 2 + s) * 4 + m) * 64 + lane];
-      if (HAS_W) {
-        f.wsu[s] = a.wst[(((size_t)rt * 2 + s) * a.kp32 + wtile) * 64 + lane];
-        f.raww[s] = a_st[(((size_t)rt * 2 + s) * 4 + w) * 64 + lane];
-      }
+    for (int i = 0; i < kStepTiles; ++i) {
+      const unsigned char *src = a_st + (size_t)(rt + i < rt1 ? rt + i : a.n_rt) * 8192;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        load_to_lds(src, (u32)((2 * cw + j) * 1024 + lane * 16), ldsb + (u32)((2 * kh + buf) * kStepBytes + i * 8192 + (2 * cw + j) * 1024));
     }
   };
-  // turned codes of the two column tiles: B operands for both halves of the 32 rows
-  struct Turned {
-    u32x4 wb[2][2];
-  };
-  auto turn = [&](const Codes &cd, Turned &o) __attribute__((always_inline)) {
+  fetch_dy(rt0, 0);
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      f16_t t;
+  for (int i = 0; i < kStepTiles; ++i) fetch_codes(i, rt0 + i);
+  fetch_sz(rt0);
+  for (int st = 0; st < steps; ++st) {
+    const int rt = rt0 + st * kStepTiles, nx = st + 1 < steps ? rt + kStepTiles : rt;
+    wait_loads<0>();
+    __syncthreads();
+    fetch_dy(nx, (st + 1) & 1);
+    // step sizes to where the lanes of either half of the wave read eight of them at once: row 16 s + 8 b + 4 h + e of
+    // a row tile is element 4 b + e of unit (s, h)
+    bool rest = false;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) t[r] = cneg[c];    // start from minus the unpack constant
-      if (c == 0) {
-        t = mma(a_operand<BITS, 0>(cd.cw, M), sel0, t);
-        t = mma(a_operand<BITS, 1>(cd.cw, M), sel1, t);
-      } else {
-        t = mma(a_operand<BITS, 2>(cd.cw, M), sel0, t);
-        t = mma(a_operand<BITS, 3>(cd.cw, M), sel1, t);
+    for (int i = 0; i < 2; ++i) {
+      const int r = 64 * i + lane, q = r & 15;
+      const int at = (r >> 4) * 16 + ((q >> 2) & 1) * 8 + (q >> 3) * 4 + (q & 3);
+      const float z = half_hi(szr[i]), z1 = __builtin_amdgcn_fmed3f(__builtin_rintf(z), -1024.f, 1024.f);
+      splane[at] = __builtin_bit_cast(_Float16, (unsigned short)szr[i]);
+      rplane[at] = (_Float16)(z - z1);
+      zplane[r] = (_Float16)z1;
+      rest |= z != z1;
+    }
+    fetch_sz(nx);
+    const unsigned char *dyb = lds + (2 * kh + (st & 1)) * kStepBytes + lane * 16;
+    if (__ballot(rest) != 0ull) {            // zero points that are no small integers: sum of dy s (z - rint z) per token
+      for (int i = 0; i < 2 * kStepTiles; ++i) {
+        const u32x4 s4 = *reinterpret_cast<const u32x4 *>(splane + (2 * i + h) * 8), r4 = *reinterpret_cast<const u32x4 *>(rplane + (2 * i + h) * 8);
+        const u32 sv[4] = {s4.x, s4.y, s4.z, s4.w}, rv[4] = {r4.x, r4.y, r4.z, r4.w};
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          const u32x4 d4 = *reinterpret_cast<const u32x4 *>(dyb + (i * 4 + m) * 1024);
+          const u32 dv[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+          for (int p = 0; p < 4; ++p)
+            zacc[m] = dot2(__builtin_bit_cast(u32, __builtin_bit_cast(h2_t, dv[p]) * __builtin_bit_cast(h2_t, sv[p])), rv[p], zacc[m]);
+        }
       }
+    }
+#pragma unroll
+    for (int i = 0; i < kStepTiles; ++i) {
+      // ---- turn: q - z of 32 rows x 64 columns from (row, eight columns) to (column, eight rows) per lane ----
+      const _Float16 z1 = zplane[32 * i + n32];
+      const u32 zz = (u32)__builtin_bit_cast(unsigned short, z1) * 0x00010001u ^ 0x80008000u;
+      u32 nb[8];
+#pragma unroll
+      for (int o = 0; o < 8; ++o) nb[o] = pk_sub(zz, M.m[o]);
+      u32x4 wb[2][2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        f16_t t;
+        if (c == 0) {
+          t = mma(a_exact<BITS, 0>(cd[i], M, nb), sel0, zero);
+          t = mma(a_exact<BITS, 1>(cd[i], M, nb), sel1, t);
+        } else {
+          t = mma(a_exact<BITS, 2>(cd[i], M, nb), sel0, zero);
+          t = mma(a_exact<BITS, 3>(cd[i], M, nb), sel1, t);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          u32 pk[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)       // small integers: exact whatever the rounding
+            pk[e] = __builtin_bit_cast(u32, __builtin_amdgcn_cvt_pkrtz(t[8 * s + 2 * e], t[8 * s + 2 * e + 1]));
+          wb[c][s] = (u32x4){pk[0], pk[1], pk[2], pk[3]};
+        }
+      }
+      fetch_codes(i, nx + i);
+      // ---- product: dy times step size (one rounding to fp16) against the turned codes ----
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        u32 pk[4];
+        const u32x4 s4 = *reinterpret_cast<const u32x4 *>(splane + ((2 * i + s) * 2 + h) * 8);
+        const u32 sv[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e)       // small integers: exact whatever the rounding
-          pk[e] = __builtin_bit_cast(u32, __builtin_amdgcn_cvt_pkrtz(t[8 * s + 2 * e], t[8 * s + 2 * e + 1]));
-        o.wb[c][s] = (u32x4){pk[0], pk[1], pk[2], pk[3]};
-      }
-    }
-  };
-  auto product = [&](const Fetched &f, const Turned &tw) __attribute__((always_inline)) {
+        for (int m = 0; m < 4; ++m) {
+          const u32x4 d4 = *reinterpret_cast<const u32x4 *>(dyb + ((2 * i + s) * 4 + m) * 1024);
+          const u32 dv[4] = {d4.x, d4.y, d4.z, d4.w};
+          u32 ap[4];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const u32x4 q0 = f.q[s][0], q1 = f.q[s][1];
-      const u32 d[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-      u32 sp2[4], zp2[4];
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        sp2[p] = __builtin_amdgcn_perm(d[2 * p + 1], d[2 * p], 0x05040100u);   // (lo of even, lo of odd)
-        zp2[p] = __builtin_amdgcn_perm(d[2 * p + 1], d[2 * p], 0x07060302u);   // (hi of even, hi of odd)
-      }
-      if (HAS_W)
-        wacc = mma(__builtin_bit_cast(h8_t, f.raww[s]), __builtin_bit_cast(h8_t, f.wsu[s]), wacc);
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const u32x4 raw = f.raw[s][m];
-        const u32 r[4] = {raw.x, raw.y, raw.z, raw.w};
-        u32 ap[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const h2_t prod = __builtin_bit_cast(h2_t, r[p]) * __builtin_bit_cast(h2_t, sp2[p]);   // one rounding to fp16
-          ap[p] = __builtin_bit_cast(u32, prod);
-          zacc[m] = dot2(ap[p], zp2[p], zacc[m]);
+          for (int p = 0; p < 4; ++p) ap[p] = __builtin_bit_cast(u32, __builtin_bit_cast(h2_t, dv[p]) * __builtin_bit_cast(h2_t, sv[p]));
+          const h8_t aop = __builtin_bit_cast(h8_t, (u32x4){ap[0], ap[1], ap[2], ap[3]});
+          acc[m][0] = mma(aop, __builtin_bit_cast(h8_t, wb[0][s]), acc[m][0]);
+          acc[m][1] = mma(aop, __builtin_bit_cast(h8_t, wb[1][s]), acc[m][1]);
         }
-        const u32x4 av = {ap[0], ap[1], ap[2], ap[3]};
-        const h8_t aop = __builtin_bit_cast(h8_t, av);
-        acc[m][0] = mma(aop, __builtin_bit_cast(h8_t, tw.wb[0][s]), acc[m][0]);
-        acc[m][1] = mma(aop, __builtin_bit_cast(h8_t, tw.wb[1][s]), acc[m][1]);
       }
     }
-  };
-  // Tile t's product runs while tile t + 1's codes are turned (its vector work under the product's
-  // matrix instructions), tile t + 1's operands are in flight and tile t + 2's codes are fetched.
-  const int last = rt1 - 1;
-  Fetched cur, nxt;
-  Codes c1, c2;
-  Turned tw, tn;
-  fetch_codes(c1, rt0);
-  fetch(cur, rt0);
-  fetch_codes(c2, rt0 + 1 < rt1 ? rt0 + 1 : last);
-  turn(c1, tw);
-  for (int rt = rt0; rt < rt1; ++rt) {
-    fetch(nxt, rt + 1 < rt1 ? rt + 1 : last);        // past the range: the last tile again, unused
-    c1 = c2;
-    fetch_codes(c2, rt + 2 < rt1 ? rt + 2 : last);
-    __builtin_amdgcn_sched_barrier(0);               // the loads above go out before the work below
-    product(cur, tw);
-    turn(c1, tn);
-    cur = nxt;
-    tw = tn;
   }
-  // zero-point term of every token: both halves of the rows, then from the operand layout
-  // (token = lane % 32) to the accumulator layout (tokens along the registers)
+  wait_loads<0>();
+  __syncthreads();
+  // The rest of the zero points per token: both halves of the lanes, then from the operand layout (token = lane % 32)
+  // to the accumulator layout (tokens along the registers); the planes of this wave have been read
+  float *zbuf = reinterpret_cast<float *>(splane);
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     const float z = zacc[m] + __shfl_xor(zacc[m], 32);
-    if (h == 0) zbuf[w][m][n32] = z;
+    if (h == 0) zbuf[m * 32 + n32] = z;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  // second half of the rows to LDS, the first adds it and stores
+  f4_t *xch = reinterpret_cast<f4_t *>(lds) + cw * 2048 + lane;
+  if (kh == 1) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          xch[((m * 2 + c) * 4 + q) * 64] = (f4_t){acc[m][c][4 * q], acc[m][c][4 * q + 1], acc[m][c][4 * q + 2], acc[m][c][4 * q + 3]};
+  }
+  __syncthreads();
+  if (kh == 1) return;
+  const float *zother = reinterpret_cast<const float *>(lds + kProdPlanes + (w + 4) * kProdPlane);
   float *part = a.part + ((size_t)pass * a.split + sp) * kPassTokens * a.d_in_pad;
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      const int j = 256 * bp + 64 * w + 32 * c + n32;
+      const int j = 256 * bp + 64 * cw + 32 * c + n32;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int nl = 8 * (r >> 2) + 4 * h + (r & 3);              // token of the tile that register r holds
-        part[(size_t)(32 * m + nl) * a.d_in_pad + j] = acc[m][c][r] - zbuf[w][m][nl];
+      for (int q = 0; q < 4; ++q) {
+        const f4_t o = xch[((m * 2 + c) * 4 + q) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int nl = 32 * m + 8 * q + 4 * h + e;                // token of the pass that register 4 q + e holds
+          part[(size_t)nl * a.d_in_pad + j] = (acc[m][c][4 * q + e] + o[e]) - (zbuf[nl] + zother[nl]);
+        }
       }
     }
-  if (has_w) {
-    float *pw = a.pw + ((size_t)pass * a.split + sp) * kPassTokens * (32 * a.kp32);
+}
+
+struct WeakProdArgs {
+  const u32x4 *a_st;
+  const u32x4 *wst;     // [n_rt][2][kp32][64 lanes]
+  float *pw;            // [pass][wsplit][128][32 kp32]
+  int n_rt, kp32, wsplit;
+};
+
+// dx at the weak columns in partial results: a workgroup takes a tile of 32 weak columns, 128 tokens and a range of row
+// tiles, a wave 32 of the tokens.  A small product that is all latency: the loads of four row tiles go out together.
+__device__ __forceinline__ void weak_product(const WeakProdArgs &a, int b) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5, n32 = lane & 31;
+  const int tt = b % a.kp32, sp = (b / a.kp32) % a.wsplit, pass = b / (a.kp32 * a.wsplit);
+  const int rt0 = (int)((long long)sp * a.n_rt / a.wsplit), rt1 = (int)((long long)(sp + 1) * a.n_rt / a.wsplit);
+  const u32x4 *a_st = a.a_st + (size_t)pass * (a.n_rt + 1) * 512 + w * 64 + lane;
+  const u32x4 *wst = a.wst + (size_t)tt * 64 + lane;
+  f16_t acc;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int nl = 8 * (r >> 2) + 4 * h + (r & 3);
-      pw[(size_t)(32 * w + nl) * (32 * a.kp32) + 32 * bp + n32] = wacc[r];
-    }
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  constexpr int kTiles = 4;
+  for (int rt = rt0; rt < rt1; rt += kTiles) {
+    u32x4 d[kTiles][2], q[kTiles][2];
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        d[i][s] = a_st[(size_t)(rt + i < rt1 ? rt + i : a.n_rt) * 512 + s * 256];     // past the range: the tile of zeros
+        q[i][s] = wst[(size_t)(2 * min(rt + i, a.n_rt - 1) + s) * a.kp32 * 64];
+      }
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) acc = mma(__builtin_bit_cast(h8_t, d[i][s]), __builtin_bit_cast(h8_t, q[i][s]), acc);
   }
+  float *pw = a.pw + ((size_t)pass * a.wsplit + sp) * kPassTokens * (32 * a.kp32);
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    pw[(size_t)(32 * w + 8 * (r >> 2) + 4 * h + (r & 3)) * (32 * a.kp32) + 32 * tt + n32] = acc[r];
 }
 
 struct SumArgs {
   const float *part;    // [pass][split][128][d_in_pad]
-  const float *pw;      // [pass][split][128][32 kp32], or nullptr
+  const float *pw;      // [pass][wsplit][128][32 kp32], or nullptr
   const uint8_t *wmask; // bit j = column j is weak
   const int *weak_idx;
   _Float16 *dx;         // [batch][d_in]
-  int d_in, d_in_pad, split, n0, ntok, k, kp32, dense_blocks;
+  int d_in, d_in_pad, split, wsplit, n0, ntok, k, kp32, dense_blocks;
   const int *kword;     // dy was scaled by 2^*kword
 };
 
@@ -404,9 +471,19 @@ __global__ __launch_bounds__(256) void owq_bwd_sum(const SumArgs a) {
   if ((int)blockIdx.x < a.dense_blocks) {
     const int j = (blockIdx.x * 256 + threadIdx.x) * 4;            // four columns per thread (d_in_pad is a multiple of 256)
     if (j >= a.d_in) return;
+    // four partial results in flight; past the last one it again, not added
     f4_t v = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < a.split; ++s)
-      v += *reinterpret_cast<const f4_t *>(a.part + (base + (size_t)s * kPassTokens + nl) * a.d_in_pad + j);
+    const float *src = a.part + (base + nl) * a.d_in_pad + j;
+    for (int s = 0; s < a.split; s += 4) {
+      f4_t r[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[i] = *reinterpret_cast<const f4_t *>(src + (size_t)min(s + i, a.split - 1) * kPassTokens * a.d_in_pad);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f4_t z = {0.f, 0.f, 0.f, 0.f};
+        v += s + i < a.split ? r[i] : z;
+      }
+    }
     const u32 weak = (a.wmask[j >> 3] >> (j & 7)) & 15u;          // j is a multiple of 4: the four bits sit in one byte
     _Float16 *out = a.dx + (size_t)(a.n0 + blockIdx.y) * a.d_in + j;
 #pragma unroll
@@ -418,7 +495,9 @@ __global__ __launch_bounds__(256) void owq_bwd_sum(const SumArgs a) {
     const int col = a.weak_idx[t];
     if ((unsigned)col >= (unsigned)a.d_in) return;
     float v = 0.f;
-    for (int s = 0; s < a.split; ++s) v += a.pw[(base + (size_t)s * kPassTokens + nl) * (32 * a.kp32) + t];
+    const size_t wbase = (size_t)pass * a.wsplit * kPassTokens;
+#pragma unroll 8
+    for (int s = 0; s < a.wsplit; ++s) v += a.pw[(wbase + (size_t)s * kPassTokens + nl) * (32 * a.kp32) + t];
     a.dx[(size_t)(a.n0 + blockIdx.y) * a.d_in + col] = (_Float16)(v * back);
   }
 }
@@ -528,10 +607,10 @@ struct DwwArgs {
 // through LDS in a fixed order.  The work is tiny and all latency: a wave sends out the loads of
 // eight of its token steps at once.
 template <int NTT>
-__global__ __launch_bounds__(256) void owq_bwd_dww(const DwwArgs a) {
+__device__ __forceinline__ void dww_product(const DwwArgs &a, int bx, int by) {
   __shared__ float red[4][16][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, h = lane >> 5;
-  const int i = blockIdx.x * 32 + (lane & 31), tt0 = blockIdx.y * NTT;
+  const int i = bx * 32 + (lane & 31), tt0 = by * NTT;
   const int ntt = a.kp32 - tt0 < NTT ? a.kp32 - tt0 : NTT;
   const int ic = i < a.d_out ? i : a.d_out - 1;
   f16_t acc[NTT];
@@ -597,10 +676,18 @@ __global__ __launch_bounds__(256) void owq_bwd_dww(const DwwArgs a) {
   }
 }
 
+// The two small products of a call in one launch: dww in the first blocks of the grid, dx at the weak columns in the
+// others (either may be absent).
+template <int NTT>
+__global__ __launch_bounds__(256) void owq_bwd_small(const DwwArgs da, const WeakProdArgs wa, int dww_rows, int dww_blocks) {
+  if ((int)blockIdx.x < dww_blocks) dww_product<NTT>(da, (int)blockIdx.x % dww_rows, (int)blockIdx.x / dww_rows);
+  else weak_product(wa, (int)blockIdx.x - dww_blocks);
+}
+
 struct BwdPlan {
   int passes;                    // passes per set of launches
-  int split, rt_per_split, kp32;
-  bool weak_in_product;          // every tile of 32 weak columns finds a block pair's workgroup
+  int split, rt_per_split, wsplit, kp32;
+  bool weak_staged;              // weak columns staged in operand order: at most an eighth of the columns
   int x_steps;                   // steps of 16 tokens of the whole batch
   size_t a_st_bytes, part_bytes, wst_bytes, pw_bytes, xw_bytes, total;
 };
@@ -609,16 +696,15 @@ BwdPlan plan(const owq_layer_info_t &g, int batch) {
   BwdPlan p;
   const int all_passes = (batch + kPassTokens - 1) / kPassTokens;
   p.passes = all_passes < kLaunchPasses ? (all_passes < 1 ? 1 : all_passes) : kLaunchPasses;
-  // Ranges of rows per block pair.  A compute unit holds one workgroup at a time (its registers), so
-  // the product takes rounds of 256 workgroups, each as long as a workgroup's row tiles (plus a fixed
-  // part: set-up and the store of its partial results); every further range costs the sum kernel about
-  // one row tile's time.  Cost in row tiles, fitted to measurements on MI355X.
+  // Ranges of rows per block pair.  A compute unit holds one workgroup at a time, so the product takes rounds of 256
+  // workgroups, each as long as its row tiles (0.7 us) and a fixed part; every range costs the sum kernel a read of its
+  // partial results.  In us, fitted to measurements on MI355X.
   int split = 1;
   double best = 1e30;
   for (int sp = 1; sp <= kSplitMax && sp <= g.n_rt; ++sp) {
     const long long wgs = (long long)g.nbp * sp * p.passes;
     const double rounds = (double)((wgs + 255) / 256);
-    const double cost = rounds * ((g.n_rt + sp - 1) / sp + 6.0) + 1.1 * sp;
+    const double cost = rounds * (0.7 * ((g.n_rt + sp - 1) / sp) + 6.0) + sp * (p.passes * kPassTokens * 256.0 * g.nbp * 8.0 / 4e6);
     if (cost < best) {
       best = cost;
       split = sp;
@@ -626,12 +712,13 @@ BwdPlan plan(const owq_layer_info_t &g, int batch) {
   }
   p.rt_per_split = (g.n_rt + split - 1) / split;
   p.split = (g.n_rt + p.rt_per_split - 1) / p.rt_per_split;
-  p.a_st_bytes = (size_t)p.passes * g.n_rt * 2 * 4 * 64 * 16;
+  p.a_st_bytes = (size_t)p.passes * (g.n_rt + 1) * 2 * 4 * 64 * 16;
   p.part_bytes = (size_t)p.passes * p.split * kPassTokens * ((size_t)g.nbp * 256) * 4;
   p.kp32 = (g.kp + 31) / 32;
-  p.weak_in_product = g.k > 0 && p.kp32 <= g.nbp;
-  p.wst_bytes = p.weak_in_product ? (size_t)g.n_rt * 2 * p.kp32 * 64 * 16 : 0;
-  p.pw_bytes = p.weak_in_product ? (size_t)p.passes * p.split * kPassTokens * 32 * p.kp32 * 4 : 0;
+  p.weak_staged = g.k > 0 && p.kp32 <= g.nbp;
+  p.wsplit = g.n_rt < kWeakSplit ? g.n_rt : kWeakSplit;
+  p.wst_bytes = p.weak_staged ? (size_t)g.n_rt * 2 * p.kp32 * 64 * 16 : 0;
+  p.pw_bytes = p.weak_staged ? (size_t)p.passes * p.wsplit * kPassTokens * 32 * p.kp32 * 4 : 0;
   p.x_steps = (batch + 15) / 16;
   p.xw_bytes = g.k > 0 ? (size_t)p.x_steps * p.kp32 * 64 * 16 : 0;
   p.total = p.a_st_bytes + p.part_bytes + p.wst_bytes + p.pw_bytes + p.xw_bytes + kScanBytes;
@@ -641,6 +728,13 @@ BwdPlan plan(const owq_layer_info_t &g, int batch) {
 bool live(owq_handle_t h) { return h && h->magic == kMagic; }
 
 }  // namespace
+
+int prepare_backward_kernels(const owq_layer_info_t &g, int32_t lds_limit) {
+  if (kProdLds > lds_limit) return (int)hipErrorInvalidValue;
+  return (int)hipFuncSetAttribute(reinterpret_cast<const void *>(g.bits == 3 ? owq_bwd_product<3> : owq_bwd_product<4>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, kProdLds);
+}
+
 }  // namespace owq
 
 extern "C" owq_status_t owq_backward_workspace_bytes(owq_handle_t h, int32_t batch, size_t *bytes) {
@@ -672,8 +766,8 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
   hipError_t err = hipSuccess;
   u32x4 *a_st = reinterpret_cast<u32x4 *>(ws);
   float *part = reinterpret_cast<float *>(ws + p.a_st_bytes);
-  u32x4 *wst = p.weak_in_product ? reinterpret_cast<u32x4 *>(ws + p.a_st_bytes + p.part_bytes) : nullptr;
-  float *pw = p.weak_in_product ? reinterpret_cast<float *>(ws + p.a_st_bytes + p.part_bytes + p.wst_bytes) : nullptr;
+  u32x4 *wst = p.weak_staged ? reinterpret_cast<u32x4 *>(ws + p.a_st_bytes + p.part_bytes) : nullptr;
+  float *pw = p.weak_staged ? reinterpret_cast<float *>(ws + p.a_st_bytes + p.part_bytes + p.wst_bytes) : nullptr;
   u32x4 *xw_st = reinterpret_cast<u32x4 *>(ws + p.a_st_bytes + p.part_bytes + p.wst_bytes + p.pw_bytes);
   u32 *maxima = reinterpret_cast<u32 *>(ws + p.total - kScanBytes);
   int *kword = reinterpret_cast<int *>(maxima + kMaxBlocks);
@@ -689,24 +783,31 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
     const int ntok = batch - n0 < per_launch ? batch - n0 : per_launch;
     const int passes = (ntok + kPassTokens - 1) / kPassTokens;
     StageAllArgs sa = {};
-    sa.dy = {static_cast<const _Float16 *>(dy), a_st, g.d_out, g.n_rt, n0, batch, passes, maxima, kword};
+    sa.dy = {static_cast<const _Float16 *>(dy), a_st, g.d_out, g.n_rt + 1, n0, batch, passes, maxima, kword};
     sa.weak = {reinterpret_cast<const _Float16 *>(blob + g.off_weak_w), wst, g.kp, p.kp32, g.n_rt};
     sa.x = {static_cast<const _Float16 *>(x), reinterpret_cast<const int *>(blob + g.off_weak_idx), xw_st,
             g.d_in, g.k, p.kp32, batch, p.x_steps};
-    sa.dy_blocks = dx ? (unsigned)(((g.n_rt + 1) / 2) * 4 * passes) : 0u;
-    sa.weak_blocks = dx && n0 == 0 && p.weak_in_product ? (unsigned)(((long long)g.n_rt * 2 * p.kp32 * 64 + 255) / 256) : 0u;
+    sa.dy_blocks = dx ? (unsigned)(((g.n_rt + 2) / 2) * passes) : 0u;
+    sa.weak_blocks = dx && n0 == 0 && p.weak_staged ? (unsigned)(((long long)g.n_rt * 2 * p.kp32 * 64 + 255) / 256) : 0u;
     const unsigned x_blocks = want_dww && n0 == 0 ? (unsigned)(((long long)p.x_steps * p.kp32 * 64 + 255) / 256) : 0u;
     if (sa.dy_blocks + sa.weak_blocks + x_blocks > 0)
       hipLaunchKernelGGL(owq_bwd_stage_all, dim3(sa.dy_blocks + sa.weak_blocks + x_blocks), dim3(256), 0, st, sa);
+    // the small products: dww of the whole batch with the first group, dx at the weak columns with each
+    const int dww_rows = (g.d_out + 31) / 32, ntt = p.kp32 <= 2 ? p.kp32 : 4;
+    const int dww_blocks = want_dww && n0 == 0 ? dww_rows * ((p.kp32 + ntt - 1) / ntt) : 0;
+    const int wp_blocks = dx && p.weak_staged ? p.kp32 * p.wsplit * passes : 0;
+    if (dww_blocks + wp_blocks > 0) {
+      const DwwArgs da = {static_cast<const _Float16 *>(dy), xw_st, dww, g.d_out, g.k, p.kp32, batch, p.x_steps};
+      const WeakProdArgs wp = {a_st, wst, pw, g.n_rt, p.kp32, p.wsplit};
+      hipLaunchKernelGGL(ntt == 1 ? owq_bwd_small<1> : ntt == 2 ? owq_bwd_small<2> : owq_bwd_small<4>,
+                         dim3((unsigned)(dww_blocks + wp_blocks)), dim3(256), 0, st, da, wp, dww_rows, dww_blocks);
+    }
     if (dx) {
       ProdArgs pa;
       pa.codes = reinterpret_cast<const u32 *>(blob + g.off_codes);
       pa.sz = reinterpret_cast<const u32 *>(blob + g.off_sz);
       pa.a_st = a_st;
       pa.part = part;
-      pa.wst = wst;
-      pa.pw = pw;
-      pa.kp32 = p.kp32;
       pa.n_rt = g.n_rt;
       pa.nbp = g.nbp;
       pa.chunks = g.chunks;
@@ -717,30 +818,18 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
       pa.split = p.split;
       pa.rt_per_split = p.rt_per_split;
       const dim3 grid((unsigned)(g.nbp * p.split * passes));
-      const dim3 block(kBwdWaves * 64);
-      if (g.bits == 3 && p.weak_in_product) hipLaunchKernelGGL((owq_bwd_product<3, true>), grid, block, 0, st, pa);
-      else if (g.bits == 3) hipLaunchKernelGGL((owq_bwd_product<3, false>), grid, block, 0, st, pa);
-      else if (p.weak_in_product) hipLaunchKernelGGL((owq_bwd_product<4, true>), grid, block, 0, st, pa);
-      else hipLaunchKernelGGL((owq_bwd_product<4, false>), grid, block, 0, st, pa);
-      const int dense_blocks = (g.d_in + 1023) / 1024, weak_blocks = p.weak_in_product ? (g.k + 255) / 256 : 0;
+      hipLaunchKernelGGL(g.bits == 3 ? owq_bwd_product<3> : owq_bwd_product<4>, grid, dim3(512), kProdLds, st, pa);
+      const int dense_blocks = (g.d_in + 1023) / 1024, weak_blocks = p.weak_staged ? (g.k + 255) / 256 : 0;
       SumArgs su = {part, pw, blob + g.off_wmask, reinterpret_cast<const int *>(blob + g.off_weak_idx),
-                    static_cast<_Float16 *>(dx), g.d_in, g.nbp * 256, p.split, n0, ntok, g.k, p.kp32, dense_blocks, kword};
+                    static_cast<_Float16 *>(dx), g.d_in, g.nbp * 256, p.split, p.wsplit, n0, ntok, g.k, p.kp32, dense_blocks, kword};
       hipLaunchKernelGGL(owq_bwd_sum, dim3((unsigned)(dense_blocks + weak_blocks), (unsigned)ntok), dim3(256), 0, st, su);
-      if (g.k > 0 && !p.weak_in_product) {
+      if (g.k > 0 && !p.weak_staged) {
         WeakArgs wa = {static_cast<const _Float16 *>(dy), reinterpret_cast<const _Float16 *>(blob + g.off_weak_w),
                        reinterpret_cast<const int *>(blob + g.off_weak_idx), static_cast<_Float16 *>(dx),
                        g.d_out, g.d_in, g.kp, n0, ntok};
         hipLaunchKernelGGL(owq_bwd_weak, dim3((unsigned)(g.kp / 8), (unsigned)((ntok + 7) / 8)), dim3(256), 0, st, wa);
       }
     }
-    err = hipGetLastError();
-  }
-  if (want_dww && err == hipSuccess) {
-    DwwArgs da = {static_cast<const _Float16 *>(dy), xw_st, dww, g.d_out, g.k, p.kp32, batch, p.x_steps};
-    const unsigned rows32 = (unsigned)((g.d_out + 31) / 32);
-    if (p.kp32 == 1) hipLaunchKernelGGL(owq_bwd_dww<1>, dim3(rows32, 1), dim3(256), 0, st, da);
-    else if (p.kp32 == 2) hipLaunchKernelGGL(owq_bwd_dww<2>, dim3(rows32, 1), dim3(256), 0, st, da);
-    else hipLaunchKernelGGL(owq_bwd_dww<4>, dim3(rows32, (unsigned)((p.kp32 + 3) / 4)), dim3(256), 0, st, da);
     err = hipGetLastError();
   }
   if (err != hipSuccess) {

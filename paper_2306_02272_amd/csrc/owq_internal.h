@@ -112,6 +112,7 @@ int launch_tile_small(const owq_layer_info_t &g, void *blob, void *part, uint64_
 int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, const void *x, void *y,
                      int32_t batch, void *stream);
 int prepare_tile_wide_kernels(const owq_layer_info_t &g, int32_t lds_limit);   // LDS opt-in
+int prepare_backward_kernels(const owq_layer_info_t &g, int32_t lds_limit);    // LDS opt-in (owq_backward.hip)
 bool tile_small_split_ok(const owq_layer_info_t &g, int32_t split);
 int prepare_tile_small_kernels();   // LDS opt-in
 // scratch_bytes = size of the scratch memory in use, 0 = the blob's own scratch area

@@ -61,4 +61,39 @@ __device__ __forceinline__ f16_t mma(h8_t a, h8_t b, f16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
+// Sixteen bytes per lane from sbase + voff to LDS at lds + 16 * lane.  Not known to the compiler's counting of
+// loads: wait_loads() below is what makes the data valid.
+__device__ __forceinline__ void load_to_lds(const void *sbase, u32 voff, u32 lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ u32 lds_address(const void *p) {
+  return (u32)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+
+__device__ __forceinline__ u32 pk_add(u32 a, u32 b) {
+  return __builtin_bit_cast(u32, __builtin_bit_cast(h2_t, a) + __builtin_bit_cast(h2_t, b));
+}
+__device__ __forceinline__ u32 pk_sub(u32 a, u32 b) {
+  return __builtin_bit_cast(u32, __builtin_bit_cast(h2_t, a) - __builtin_bit_cast(h2_t, b));
+}
+__device__ __forceinline__ u32 pk_dup(float v) {
+  const u32 h = __builtin_bit_cast(unsigned short, (_Float16)v);
+  return h | (h << 16);
+}
+
+// q - z of k-step S (0..7) of a block: the mask-and-OR operand plus nb[o] = -(2^(10-o) + z), exact.
+template <int BITS, int S>
+__device__ __forceinline__ h8_t a_exact(const u32 *wd, const Magic &M, const u32 *nb) {
+  u32x4 v = __builtin_bit_cast(u32x4, a_operand<BITS, S>(wd, M));
+  v.x = pk_add(v.x, nb[pair_offset(BITS, S, 0)]);
+  v.y = pk_add(v.y, nb[pair_offset(BITS, S, 1)]);
+  v.z = pk_add(v.z, nb[pair_offset(BITS, S, 2)]);
+  v.w = pk_add(v.w, nb[pair_offset(BITS, S, 3)]);
+  return __builtin_bit_cast(h8_t, v);
+}
+
 }  // namespace owq

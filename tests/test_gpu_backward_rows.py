@@ -1,0 +1,46 @@
+"""Backward of the dense part where its product's ranges of rows and its zero points can go wrong: rows that are no
+multiple of a step of 128, ranges with an empty second half, one row tile, zero points that are fractions or beyond
+what leaves with the unpack constant.  Bar as in test_gpu_backward: relative L2 error <= 1e-3, max-abs <= 1e-2 rms."""
+import numpy as np
+import pytest
+
+from oracle import backward, owq_ref
+from synth import LayerSpec, make_layer, make_x
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2306_02272_amd import binding
+    binding.lib()
+    torch.cuda.set_device(0)
+    return torch, binding
+
+
+@pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens", [
+    (256, 1, 3, 0, 4, 3), (256, 32, 4, 128, 4, 40), (300, 33, 3, 128, 9, 130), (512, 129, 4, 256, 5, 128),
+    (1000, 260, 3, 0, 7, 65), (640, 999, 4, 128, 40, 257), (128, 1500, 3, 128, 3, 520), (768, 640, 4, 0, 200, 100)])
+@pytest.mark.parametrize("zeros", ["integers", "any"])
+def test_rows_and_zero_points(env, d_in, d_out, bits, group, k, tokens, zeros):
+    torch, B = env
+    layer = make_layer(LayerSpec("bwd", d_in, d_out, bits, group, k, d_in + d_out))
+    rng = np.random.default_rng(d_out)
+    if zeros == "any":
+        z = layer.zero.astype(np.float32) + rng.normal(0, 2, layer.zero.shape)
+        z[rng.random(z.shape) < 0.02] = 1100.5
+        layer.zero[:] = z.astype(np.float16)
+    x = make_x(layer, tokens)
+    dy = rng.normal(0, 0.05, (tokens, d_out)).astype(np.float16)
+    print(f"{d_in} -> {d_out}, {bits} bit, group {group}, k {k}, {tokens} tokens, zero points: {zeros}", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    dx, dww = lin.backward(torch.from_numpy(dy).cuda(), torch.from_numpy(x).cuda())
+    want_dx, want_dww = backward.owq_backward_ref(layer.codes, layer.scale, layer.zero, group, layer.weak_idx, layer.weak_w, x, dy)
+    rel, mx = owq_ref.parity_errors(dx.cpu().numpy(), want_dx)
+    assert rel <= 1e-3 and mx <= 1e-2, (rel, mx)
+    rel, _ = owq_ref.parity_errors(dww.cpu().numpy(), want_dww)
+    assert rel <= 1e-5, rel
+    lin.close()
