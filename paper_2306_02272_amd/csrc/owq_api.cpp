@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "owq_internal.h"
@@ -9,6 +10,27 @@
 using namespace owq;
 
 static bool live(owq_handle_t h) { return h && h->magic == kMagic; }
+
+// The LDS opt-in of every kernel a tile-layout handle may launch, once per device and kind of layer (a handle would
+// otherwise spend half a millisecond on two dozen attribute calls).  Returns a hipError_t as int.
+static int opt_in_tile_kernels(const owq_layer_info_t &g, int32_t lds_limit) {
+  constexpr int kMaxDevices = 64;
+  static std::mutex lock;
+  static bool done[kMaxDevices][4];
+  int dev = 0;
+  const hipError_t err = hipGetDevice(&dev);
+  if (err != hipSuccess) return (int)err;
+  const int kind = (g.bits == 4 ? 2 : 0) + (g.n_groups > 1 ? 1 : 0);
+  std::lock_guard<std::mutex> guard(lock);
+  if (dev >= 0 && dev < kMaxDevices && done[dev][kind]) return 0;
+  int e = prepare_tile_kernels(g, lds_limit);
+  if (e == 0) e = prepare_tile_small_kernels();
+  if (e == 0) e = prepare_tile_few_kernels(g, lds_limit);
+  if (e == 0) e = prepare_tile_wide_kernels(g, lds_limit);
+  if (e == 0) e = prepare_backward_kernels(g, lds_limit);
+  if (e == 0 && dev >= 0 && dev < kMaxDevices) done[dev][kind] = true;
+  return e;
+}
 
 extern "C" {
 
@@ -21,11 +43,9 @@ static owq_status_t make_handle(const owq_layer_info_t &g, void *dev_buf, owq_ha
     if (lds_limit < 65536) return OWQ_ERR_UNSUPPORTED;
     tile_default_shape(g, tile_waves, &tile_grid, &tile_split);
     if (tile_grid < 1) return OWQ_ERR_UNSUPPORTED;
-    const int e = prepare_tile_kernels(g, lds_limit);
+    const int e = opt_in_tile_kernels(g, lds_limit);
     if (e == (int)hipErrorInvalidValue) return OWQ_ERR_UNSUPPORTED;
     if (e != 0) return OWQ_ERR_HIP;
-    if (prepare_tile_small_kernels() != 0) return OWQ_ERR_HIP;
-    if (prepare_tile_wide_kernels(g, lds_limit) != 0 || prepare_backward_kernels(g, lds_limit) != 0) return OWQ_ERR_HIP;
   } else {
     shape = default_shape(g, lds_limit);
     if (shape.rtw < 1) return OWQ_ERR_UNSUPPORTED;
@@ -104,7 +124,7 @@ static owq_status_t run_linear(owq_handle_t h, const TaskSets &tasks, const void
   if (reinterpret_cast<uintptr_t>(x) % 2 != 0 || reinterpret_cast<uintptr_t>(y) % 2 != 0) return OWQ_ERR_BUFFER;
   const int herr = h->info.layout == OWQ_LAYOUT_TILE
                        ? launch_tile(h->info, h->dev_buf, sc ? sc->mem : nullptr, sc ? sc->bytes : 0, sc ? sc->grid : h->tile_grid,
-                                     sc ? sc->split : h->tile_split, h->tile_waves, h->tile_small_split, tasks, x, y, batch, stream)
+                                     sc ? sc->split : h->tile_split, h->tile_waves, h->tile_small_split, h->lds_limit, tasks, x, y, batch, stream)
                        : launch_gemv(h->info, h->shape, h->dev, tasks, x, y, batch, h->lds_limit, stream);
   if (herr == -2) return OWQ_ERR_SHAPE;     // a launch shape set by the caller does not fit this batch
   if (herr != 0) {

@@ -97,7 +97,7 @@ int prepare_multi_kernels(int32_t lds_bytes);
 // scratch_bytes bytes (at least TileScratch::off_slots plus the slots the grid needs);
 // nullptr = the scratch area inside the blob.
 int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, int32_t grid, int32_t split,
-                int32_t waves, int32_t small_split, const TaskSets &tasks, const void *x, void *y, int32_t batch,
+                int32_t waves, int32_t small_split, int32_t lds_limit, const TaskSets &tasks, const void *x, void *y, int32_t batch,
                 void *stream);
 // Device address of the library's static scratch array on the current device (looked up once
 // per device).  Returns a hipError_t as int.
@@ -107,6 +107,10 @@ int static_scratch(void **ptr);
 // part = DEVICE memory of part_bytes bytes for fp32 partial sums when the columns are split.
 int launch_tile_small(const owq_layer_info_t &g, void *blob, void *part, uint64_t part_bytes, int32_t shape, const void *x,
                       void *y, int32_t ntok, void *stream);
+// 32 tokens or fewer of one task, rows of x on the 16-byte grid (defined in owq_tile_few.hip).  Returns a hipError_t as
+// int, or -1 when the layer or x does not fit it.
+int launch_tile_few(const owq_layer_info_t &g, void *blob, int32_t lds_limit, const void *x, void *y, int32_t ntok, void *stream);
+int prepare_tile_few_kernels(const owq_layer_info_t &g, int32_t lds_limit);    // LDS opt-in
 // More than 64 tokens of one task (defined in owq_tile_wide.hip): scratch = DEVICE memory of scratch_bytes bytes.
 // Returns a hipError_t as int, or -1 when that memory cannot hold the gathered activations of 128 tokens.
 int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, const void *x, void *y,

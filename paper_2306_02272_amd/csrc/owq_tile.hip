@@ -772,7 +772,7 @@ void tile_default_shape(const owq_layer_info_t &g, int32_t waves, int32_t *grid,
 }
 
 int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, int32_t grid, int32_t split,
-                int32_t waves, int32_t small_split, const TaskSets &tasks, const void *x, void *y, int32_t batch,
+                int32_t waves, int32_t small_split, int32_t lds_limit, const TaskSets &tasks, const void *x, void *y, int32_t batch,
                 void *stream) {
   const TileScratch ts = tile_scratch(g);
   uint8_t *base = static_cast<uint8_t *>(blob);
@@ -827,7 +827,12 @@ int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t s
   for (int32_t t0 = 0; t0 < batch; t0 += kScratchBatch) {
     const int ntok = batch - t0 < kScratchBatch ? batch - t0 : kScratchBatch;
     const int nt = ntok > 32 ? 2 : 1;
-    if (ntok <= 32 && small_split >= 0 && tasks.task_id == nullptr) {   // few tokens, one task: one launch
+    if (small_split == 0 && tasks.task_id == nullptr) {                 // few tokens, one task: one launch
+      const int r = launch_tile_few(g, blob, lds_limit, xp + (size_t)t0 * g.d_in, yp + (size_t)t0 * g.d_out, ntok, stream);
+      if (r > 0) return r;
+      if (r == 0) continue;
+    }
+    if (ntok <= 32 && small_split >= 0 && tasks.task_id == nullptr) {
       const int r = launch_tile_small(g, blob, scr + ts.off_slots, scr_bytes - ts.off_slots, small_split,
                                       xp + (size_t)t0 * g.d_in, yp + (size_t)t0 * g.d_out, ntok, stream);
       if (r > 0 || r == -2) return r;

@@ -205,12 +205,13 @@ __device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *l
   };
   // ---- codes and scales --------------------------------------------------------------------------------
   u32 cb[2][2][8];
-  u32 szr[2];
+  u32 szr[2], mkr[2];     // scale and zero point of a row; weak mask of 32 columns (a quarter wave each)
   const int rt0 = min(rg * 8 + 2 * w, a.n_rt - 1), rt1 = min(rg * 8 + 2 * w + 1, a.n_rt - 1);
   const int szrow = min((rg * 8 + 2 * w) * 32 + lane, a.d_out_pad - 1);
   constexpr int CH = BITS == 3 ? 3 : 4;
   const unsigned char *tile0 = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)(rt0 * a.nbp) * (CH * 1024);
   const unsigned char *tile1 = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)(rt1 * a.nbp) * (CH * 1024);
+  const u32 *mask32 = reinterpret_cast<const u32 *>(a.wmask) + (lane >> 4);
   int fg = b0 / a.bpg, frem = b0 - fg * a.bpg;      // group of the block that is fetched
   typedef u32 u32x2 __attribute__((ext_vector_type(2)));
   // codes of block H of pair bp (3-bit: whole and half chunks) and the scales of its group
@@ -235,6 +236,7 @@ __device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *l
         dst[6] = dst[7] = 0u;
       }
     }
+    mkr[H] = mask32[min(2 * bp + H, a.nblk - 1) * 4];
     if (GROUPED) szr[H] = a.sz[(u32)min(fg, a.n_groups - 1) * (u32)a.d_out_pad + szrow];
     const bool wrap = frem + 1 == a.bpg;
     fg += wrap ? 1 : 0;
@@ -267,21 +269,17 @@ __device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *l
   for (int i = 0; i < 4; ++i) tot[i] = zero;
 
   const u32 xsw = (u32)(lane & 31) * 256u + (u32)((kg ^ (lane & 15)) << 4);
-  typedef const __attribute__((address_space(4))) u32x4 *mask_t;
-  const mask_t wm = (mask_t)(uintptr_t)a.wmask;
-
   if (!GROUPED) take_sz(a.sz[szrow]);
   fetch_x(b0, 0);
   fetch_codes(p0, WideBuf<0>{});
 
   auto step = [&](int b, auto tag) __attribute__((always_inline)) {
     constexpr int J = decltype(wide_buf_index(tag))::value;
-    const u32x4 mk = wm[b];
     wait_loads<0>();            // this wave's part of block b is in LDS, its codes are in registers
     const int left = a.d_in - b * 128;
-    if ((mk.x | mk.y | mk.z | mk.w) != 0u || left < 128) {
+    if (__ballot(mkr[J] != 0u) != 0ull || left < 128) {
       const int d = lane >> 4, n = w * 16 + (lane & 15);
-      u32 m = d == 0 ? mk.x : d == 1 ? mk.y : d == 2 ? mk.z : mk.w;
+      u32 m = mkr[J];
       const int lv = left - 32 * d;
       if (lv < 32) m |= lv <= 0 ? 0xffffffffu : 0xffffffffu << lv;
       _Float16 *row = reinterpret_cast<_Float16 *>(lds + (J * kWideBufUnits + n * 16) * 16);
@@ -351,7 +349,7 @@ __global__ __launch_bounds__(256, 2) void owq_wide_mma(const WideArgs a) {
   const int g4 = rem / (4 * a.n_tt), gh = min(4, a.n_rg - 4 * g4), r2 = rem - g4 * 4 * a.n_tt;
   const int tt = r2 / gh, rg = 4 * g4 + (r2 - tt * gh);
   const int n0 = tt * kWideTokens;
-  const int p0 = (int)((long long)s * a.nbp / a.split), p1 = (int)((long long)(s + 1) * a.nbp / a.split);
+  const int p0 = s * a.nbp / a.split, p1 = (s + 1) * a.nbp / a.split;
 
   f16_t tot[4];
   int rest = 0;
