@@ -534,9 +534,6 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   for (int r = 0; r < 16; ++r) wk[r] = 0.f;
   const int kunits = a.kp >> 3;
   if (kunits > 0) {
-    int row = row_base + rtl * 32 + (lane & 31);
-    if (row > a.d_out_pad - 1) row = a.d_out_pad - 1;
-    const u32x4 *xsrc = a.xw + (size_t)n * kunits;
     const int kg = lane >> 5;
     // the set of weak columns of this lane's token: -1 = the layer's own, -2 = no token
     int mine = n < a.ntok ? -1 : -2;
@@ -579,41 +576,60 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
           wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
         }
       }
-    } else
-    for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
-      // the gathered activations of these K-steps are the same for every set: fetched once
-      u32x4 bv[KS];
+    } else {
+      // Several sets.  All waves of the workgroup look at the same 32 tokens (the launch sees to that), so they agree on
+      // the sets these use: in ascending order, one pass of K-steps per set, with the other tokens' operands zeroed.
+      // A set's 64 rows x 16 units go through LDS as above; those of the next set are fetched meanwhile (lanes reading
+      // operands of their own rows straight from memory, pointer first, then weights, one set after the other: 12.9 us
+      // for six sets of 72 columns, 37 tokens and 3333 rows; this: 11.3, with fewer partial results to add 10).
+      const u32x4 *own = a.weak_w;
+      const u32x4 *base = mine >= 0 ? static_cast<const u32x4 *>(a.weak_sets[mine]) : own;      // of this lane's token
+      const int cu = tid & 15, cr = tid >> 4;
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
+        const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
+        int pending = mine, t = -2;
+        // the least index still pending and, by one of its lanes, where its weights lie
+        auto next_set = [&](u32x4 (&ta)[4]) __attribute__((always_inline)) {
+          int cand = pending >= -1 ? pending : 0x7fffffff;
 #pragma unroll
-      for (int j = 0; j < KS; ++j) {
-        const int u = 2 * (s0 + j) + kg;
-        bv[j] = xsrc[u < kunits ? u : 0];
-        if (u >= kunits) bv[j] = (u32x4){0u, 0u, 0u, 0u};
-      }
-      // one pass per set that some token of the tile uses, in ascending order of the set index (at most
-      // 33 passes however many sets the table holds): the least index still pending in the wave is next
-      int pending = mine;
-      for (;;) {
-        int cand = pending >= -1 ? pending : 0x7fffffff;
+          for (int d = 1; d < 64; d <<= 1) cand = min(cand, __shfl_xor(cand, d));
+          const int c = __builtin_amdgcn_readfirstlane(cand);
+          if (c == 0x7fffffff) return c;
+          const int src = __builtin_ctzll(__ballot(pending == c));
+          const unsigned long long at = (unsigned long long)(uintptr_t)base;
+          const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)at, src), hi = (u32)__builtin_amdgcn_readlane((int)(u32)(at >> 32), src);
+          const gptr_t w0 = (gptr_t)(uintptr_t)(((unsigned long long)hi << 32) | lo);
+          if (pending == c) pending = -2;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) cand = min(cand, __shfl_xor(cand, d));
-        const int t = __builtin_amdgcn_readfirstlane(cand);
-        if (t == 0x7fffffff) break;
-        if (pending == t) pending = -2;
-        const gptr_t wbase = t < 0 ? (gptr_t)a.weak_w : (gptr_t)static_cast<const u32x4 *>(a.weak_sets[t]);
-        const gptr_t wsrc = wbase + (size_t)row * kunits;
-        const bool use = mine == t;
-        u32x4 av[KS];
+          for (int i4 = 0; i4 < 4; ++i4) {
+            int r = row_base + cr + 16 * i4;
+            if (r > a.d_out_pad - 1) r = a.d_out_pad - 1;
+            ta[i4] = w0[(size_t)r * kunits + uc];
+          }
+          return c;
+        };
+        u32x4 ta[4], tb[4];
+        t = next_set(ta);
 #pragma unroll
-        for (int j = 0; j < KS; ++j) {
-          const int u = 2 * (s0 + j) + kg;
-          av[j] = wsrc[u < kunits ? u : 0];
-          if (u >= kunits) av[j] = (u32x4){0u, 0u, 0u, 0u};
-        }
+        for (int i4 = 0; i4 < 4; ++i4) tb[i4] = a.xw[(size_t)(cr + 16 * i4) * kunits + uc];
+        __syncthreads();                             // the operands of the last chunk have been read
 #pragma unroll
-        for (int j = 0; j < KS; ++j) {
-          if (2 * (s0 + j) >= kunits) continue;      // same for the whole wave
-          const u32x4 zero = {0u, 0u, 0u, 0u};
-          wk = mma(__builtin_bit_cast(h8_t, av[j]), __builtin_bit_cast(h8_t, use ? bv[j] : zero), wk);
+        for (int i4 = 0; i4 < 4; ++i4) wstage[1][(cr + 16 * i4) * kWeakPitch + cu] = (u < kunits && cr + 16 * i4 < a.ntok) ? tb[i4] : zero;
+        while (t != 0x7fffffff) {
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) wstage[0][(cr + 16 * i4) * kWeakPitch + cu] = u < kunits ? ta[i4] : zero;
+          __syncthreads();
+          const bool use = mine == t;
+          t = next_set(ta);
+#pragma unroll
+          for (int j = 0; j < KS; ++j) {
+            if (2 * (s0 + j) >= kunits) continue;    // same for the whole workgroup
+            const u32x4 av = wstage[0][(rtl * 32 + (lane & 31)) * kWeakPitch + 2 * j + kg];
+            const u32x4 bw = wstage[1][n * kWeakPitch + 2 * j + kg];
+            wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, use ? bw : zero), wk);
+          }
+          __syncthreads();                           // read before the next set's rows are written
         }
       }
     }
@@ -634,24 +650,27 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
 #pragma unroll
   for (int qq = 0; qq < 4; ++qq) sum[qq] = (f4_t){0.f, 0.f, 0.f, 0.f};
   const f4_t *src = a.slots + (size_t)((w * 4 + i) * 4 + q0) * 64 + lane;
-  constexpr int kInFlight = 4;                       // partial results fetched together (x up to 4 row groups)
-  for (int p = p_first; p <= p_last; p += kInFlight) {     // fixed order of additions
-    f4_t v[kInFlight][4];
+  // partial results fetched together: four of four groups of rows, or eight of two
+  auto add = [&](auto in_flight, auto groups) __attribute__((always_inline)) {
+    constexpr int J = decltype(in_flight)::value, Q = decltype(groups)::value;
+    for (int p = p_first; p <= p_last; p += J) {     // fixed order of additions
+      f4_t v[J][Q];
 #pragma unroll
-    for (int j = 0; j < kInFlight; ++j) {
-      if (p + j > p_last) continue;                 // same for the whole workgroup
+      for (int j = 0; j < J; ++j) {
+        if (p + j > p_last) continue;               // same for the whole workgroup
 #pragma unroll
-      for (int qq = 0; qq < 4; ++qq)
-        if (qq < qn) v[j][qq] = src[(size_t)(p + j + rg) * slot_units + qq * 64];
-    }
-#pragma unroll
-    for (int j = 0; j < kInFlight; ++j)
-      if (p + j <= p_last) {
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq)
-          if (qq < qn) sum[qq] += v[j][qq];
+        for (int qq = 0; qq < Q; ++qq) v[j][qq] = src[(size_t)(p + j + rg) * slot_units + qq * 64];
       }
-  }
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (p + j <= p_last) {
+#pragma unroll
+          for (int qq = 0; qq < Q; ++qq) sum[qq] += v[j][qq];
+        }
+    }
+  };
+  if (two) add(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+  else add(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
 #pragma unroll
   for (int qq = 0; qq < 4; ++qq) {
     if (qq >= qn) continue;
@@ -760,10 +779,15 @@ void tile_default_shape(const owq_layer_info_t &g, int32_t waves, int32_t *grid,
   *grid = cap;
   *split = 0;
   if (cap < 1) return;
+  // no more workgroups than the longest of them needs: with two steps for some of 252 workgroups and one for the others,
+  // 196 of two steps take as long and leave a quarter less to add up (3333 x 7000 at 37 tokens)
+  const int64_t equal = (steps + cap - 1) / cap;
+  *grid = (int32_t)((steps + equal - 1) / equal);
   int64_t sa = cap / n_rg;
   if (sa > g.nbp) sa = g.nbp;
   if (sa >= 1) {
-    const int64_t aligned = (g.nbp + sa - 1) / sa, equal = (steps + cap - 1) / cap;
+    const int64_t aligned = (g.nbp + sa - 1) / sa;
+    sa = (g.nbp + aligned - 1) / aligned;
     if (aligned * 10 <= equal * 11) {
       *grid = (int32_t)(n_rg * sa);
       *split = (int32_t)sa;
@@ -850,7 +874,8 @@ int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t s
     fa.ntok = ntok;
     fa.task_id = tasks.task_id ? tasks.task_id + t0 : nullptr;
     // few rows: one workgroup per (64 rows, token tile), so that the launch fills more of the chip
-    const unsigned per_tile = (ntok > 32 && n_rg * waves <= 384) ? 2u : 1u;
+    // (several tasks: always, the workgroup's waves share their tokens)
+    const unsigned per_tile = (ntok > 32 && (n_rg * waves <= 384 || tasks.task_id != nullptr)) ? 2u : 1u;
     hipLaunchKernelGGL(owq_tile_finish, dim3((unsigned)(n_rg * waves), per_tile, 1), dim3(256, 1, 1), 0, st, fa);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
