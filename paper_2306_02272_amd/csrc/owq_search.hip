@@ -12,7 +12,11 @@
 // interpolation (a chord of a concave function lies under it).  The point with the least bound is evaluated in full,
 // and then those whose bound, less a bound on its own rounding, does not exceed the least error found: five of 256
 // on groups of 128, one or two on long rows.  These evaluations take the same binary32 decisions per weight as the
-// plain search and share their sums among the lanes.
+// plain search and share their sums among the lanes; points whose sums come out too close to tell are summed again in
+// the order of the columns, so that the choice is that of the plain search.
+// 16384 x 4096, 3-bit, groups of 128, 16 x 16 points: 1780 -> 620 us (bound by vector instructions, about 950 per group
+// of which the plain search spent 2900); 5120 x 5120, 4-bit, one scale per row: 717 -> 137 us (of which 30 are the few
+// rows with points to tell apart).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -219,12 +223,12 @@ __device__ __forceinline__ float wave_sum(float v) {
 // the range, the histogram, the evaluations and the codes: one global read per weight.
 // Bins: 4 per lane of the team.  256 for a wave (groups of at most 1024: the bounds are within 0.7 % at 3 bits and
 // groups of 128, 512 bins would leave 4 points instead of 5 and cost a longer scan), 1024 for four waves.
-template <int TW, int NT>
+template <int TW, int NT, int POINTS>
 struct Team {
   static constexpr int V = NT < 8 ? NT : 8;
   static constexpr int LANES = 64 * TW;
   static constexpr int F = 4 * LANES;
-  static constexpr int CPL = 4 / TW;               // grid points per lane
+  static constexpr int CPL = POINTS;               // grid points per lane: at most 64 TW POINTS of them
   static __device__ __forceinline__ int column(int t, int lane) { return ((t / V) * LANES + lane) * V + t % V; }
 };
 
@@ -249,9 +253,9 @@ struct TeamShared {
   float scan_f[4];
 };
 
-template <int TW, int NT>
+template <int TW, int NT, int POINTS>
 __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
-  using T = Team<TW, NT>;
+  using T = Team<TW, NT, POINTS>;
   constexpr int V = T::V, LANES = T::LANES, F = T::F, CPL = T::CPL, TEAMS = 4 / TW;
   __shared__ __attribute__((aligned(16))) unsigned long long hist[TEAMS][F + 2];
   __shared__ TeamShared sh[1];                     // four waves only
@@ -499,6 +503,72 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
           }
         }
       }
+      // The error of a grid point as one sum in the order of the columns, which is what ranks points whose errors agree to
+      // the rounding of such sums: the residuals go through LDS (where the bins were), the sum runs on every lane.
+      auto residual = [&](const Cand &p, int t) __attribute__((always_inline)) {
+        const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(cur[t] * p.inv), p.a, p.b);
+        return (kept >> t) & 1u ? __builtin_fmaf(-p.s, q, cur[t]) : 0.f;
+      };
+      float *res = reinterpret_cast<float *>(bins);
+      auto add4 = [](float e, f4v d) __attribute__((always_inline)) {
+        return __builtin_fmaf(d[3], d[3], __builtin_fmaf(d[2], d[2], __builtin_fmaf(d[1], d[1], __builtin_fmaf(d[0], d[0], e))));
+      };
+      auto in_order = [&](const Cand &p) __attribute__((always_inline)) {           // one wave
+        float e = 0.f;
+#pragma unroll
+        for (int t0 = 0; t0 < NT; t0 += V) {
+          wave_lds_fence();
+#pragma unroll
+          for (int t = t0; t < t0 + V; ++t) res[lane * V + t - t0] = residual(p, t);
+          wave_lds_fence();
+          const int n4 = min(V * 64, (len - t0 * 64 + 3) & ~3) >> 2;
+          for (int i = 0; i < n4; ++i) e = add4(e, reinterpret_cast<const f4v *>(res)[i]);
+        }
+        return e;
+      };
+      // Four waves: wave c sums point c of up to four; the residuals come 512 columns (one wave's run of them) at a time, 32
+      // in registers while the next 32 come from LDS.  One point after the other, a chain of LDS reads each, took 87 us
+      // per point on a row of 5120 columns.
+      auto in_order4 = [&](const int (&ids)[4], int count) __attribute__((always_inline)) {
+        float e = 0.f;
+#pragma unroll
+        for (int t0 = 0; t0 < NT; t0 += V)
+          for (int k = 0; k < 4; ++k) {
+            const int left = len - t0 * LANES - k * 512;
+            if (left <= 0) break;                   // the same for all
+            __syncthreads();
+            if (wv == k) {
+#pragma unroll
+              for (int c = 0; c < 4; ++c)
+                if (c < count) {
+                  const Cand p = sh[0].cand[ids[c]];
+#pragma unroll
+                  for (int t = t0; t < t0 + V; ++t) res[c * 512 + lane * V + t - t0] = residual(p, t);
+                }
+            }
+            __syncthreads();
+            if (wv < count) {
+              const f4v *r4 = reinterpret_cast<const f4v *>(res) + wv * 128;
+              const int n4 = min(128, (left + 31) / 32 * 8);
+              f4v d[8], nx[8];
+#pragma unroll
+              for (int j = 0; j < 8; ++j) d[j] = r4[j];
+              for (int i = 0; i < n4; i += 8) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) nx[j] = r4[(i + 8 < 128 ? i + 8 : i) + j];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) e = add4(e, d[j]);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) d[j] = nx[j];
+              }
+            }
+          }
+        if (lane == 0) sh[0].wave[wv][3] = e;
+        __syncthreads();
+      };
+      // errors this close may change places: four deviations of the rounding of two sums of cnt terms (0.3 sqrt(cnt / 3) units in
+      // the 24th place each)
+      const float close = 1.f + 0x1p-24f * (__builtin_sqrtf((float)cnt) + 8.f);
       // ---- the grid point with the least value first, then all that may be better ----
       const float to_bins = any_odd ? 1.f : idelta * idelta * (1.f + 0x1p-12f);
       best.e = INFINITY;
@@ -517,6 +587,12 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
           best.z = 0.f - p.a;
         }
       };
+      // Points of one width often have the same step size and zero point: their errors are the same, the lower index wins
+      auto same_as_best = [&](const Cand &p, int id) __attribute__((always_inline)) {
+        const bool same = p.s == best.s && 0.f - p.a == best.z && best.id != 0x7fffffff;
+        if (same && id < best.id) best.id = id;
+        return same;
+      };
       if constexpr (TW == 1) {
         auto cand_of = [&](int id) __attribute__((always_inline)) {
           const int src = id & 63, slot = id >> 6;
@@ -527,9 +603,15 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
           return p;
         };
         wf = __builtin_amdgcn_readfirstlane(wf);
+        float mine[CPL];                            // errors of this lane's points that were evaluated
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) mine[c] = INFINITY;
         if (wf != 0x7fffffff) {
           const Cand p = cand_of(wf);
-          take(evaluate(p), wf, p);
+          const float e = evaluate(p);
+          take(e, wf, p);
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) mine[c] = wf == lane + 64 * c ? e : mine[c];
         }
         if (any_odd) {
           // weights that are no numbers: every grid point, and if none has an error that is one, the values of point 63
@@ -545,7 +627,34 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
             const int id = src + 64 * c;
             if (id == wf || !(lane_of(bound[c], src) <= best.e * to_bins)) continue;
             const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
-            take(evaluate(p), id, p);
+            if (same_as_best(p, id)) continue;
+            const float e = evaluate(p);
+            take(e, id, p);
+            mine[c] = lane == src ? e : mine[c];
+          }
+        }
+        if (!any_odd && best.e > 0.f) {
+          const float lim = best.e * close;
+          int close_ones = 0;
+#pragma unroll
+          for (int c = 0; c < CPL; ++c)
+            close_ones += __builtin_popcountll(__ballot(mine[c] <= lim && !(cd[c].s == best.s && 0.f - cd[c].a == best.z)));
+          if (close_ones > 0) {
+            // of all points that may be meant by one of these, also those that were taken for the same as another
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) mine[c] = bound[c] <= lim * to_bins && lane + 64 * c < ncand && mine[c] == INFINITY ? lim : mine[c];
+            best.e = INFINITY;
+            best.id = 0x7fffffff;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+              unsigned long long m = __ballot(mine[c] <= lim);
+              while (m) {
+                const int src = __builtin_ctzll(m);
+                m &= m - 1;
+                const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+                if (!same_as_best(p, src + 64 * c)) take(in_order(p), src + 64 * c, p);
+              }
+            }
           }
         }
       } else {
@@ -605,6 +714,58 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
             left &= left - 1;
             take((S.part[na][0] + S.part[na][1]) + (S.part[na][2] + S.part[na][3]), id, S.cand[id]);
             ++na;
+          }
+        }
+        if (!any_odd && best.e > 0.f && na > 0) {
+          // the points whose errors are close to the least, in ascending order: the first one evaluated and those listed
+          const float near = best.e * close;
+          float ef = INFINITY;
+          if (wf != 0x7fffffff) ef = (S.wave[0][2] + S.wave[1][2]) + (S.wave[2][2] + S.wave[3][2]);
+          const float bs = best.s, bz = best.z;
+          for (int pass = 0; pass < 2; ++pass) {    // looks for one beside the best, then ranks them, four at a time
+            int k = 0, found = 0, count = 0;
+            int ids[4] = {0, 0, 0, 0};
+            bool first_due = ef <= near;
+            if (pass == 1) {
+              best.e = INFINITY;
+              best.id = 0x7fffffff;
+            }
+            auto rank = [&]() __attribute__((always_inline)) {
+              in_order4(ids, count);
+              for (int c = 0; c < count; ++c) {
+                const int id = c == 0 ? ids[0] : c == 1 ? ids[1] : c == 2 ? ids[2] : ids[3];
+                take(S.wave[c][3], id, S.cand[id]);
+              }
+              count = 0;
+            };
+            auto due = [&](int id) __attribute__((always_inline)) {
+              const Cand p = S.cand[id];
+              found += p.s == bs && 0.f - p.a == bz ? 0 : 1;
+#pragma unroll
+              for (int c = 0; c < 4; ++c) ids[c] = c == count ? id : ids[c];
+              ++count;
+            };
+            for (int i = 0; i < 4; ++i) {
+              unsigned long long left = uniform(S.alive[i]);
+              while (left) {
+                const int id = i * 64 + __builtin_ctzll(left);
+                const bool close_one = (S.part[k][0] + S.part[k][1]) + (S.part[k][2] + S.part[k][3]) <= near;
+                const bool first_now = first_due && wf < id;
+                if (!first_now) {
+                  left &= left - 1;
+                  ++k;
+                }
+                first_due = first_due && !first_now;
+                if (first_now || close_one) due(first_now ? wf : id);
+                if (count == 4) {
+                  if (pass == 1) rank();
+                  count = 0;
+                }
+              }
+            }
+            if (first_due) due(wf);
+            if (found == 0) break;
+            if (pass == 1 && count > 0) rank();
           }
         }
       }
@@ -779,17 +940,22 @@ __global__ __launch_bounds__(kWaves * 64) void owq_search_kernel(const SearchArg
 }
 
 typedef void (*search_fn)(const SearchArgs);
-search_fn pick_bounds(int g) {
-  if (g <= 128) return owq_search_bounds<1, 2>;
-  if (g <= 256) return owq_search_bounds<1, 4>;
-  if (g <= 512) return owq_search_bounds<1, 8>;
-  if (g <= 1024) return owq_search_bounds<1, 16>;
-  if (g <= 2048) return owq_search_bounds<4, 8>;
-  if (g <= 4096) return owq_search_bounds<4, 16>;
-  if (g <= 6144) return owq_search_bounds<4, 24>;
-  if (g <= 8192) return owq_search_bounds<4, 32>;
-  if (g <= 12288) return owq_search_bounds<4, 48>;
-  return owq_search_bounds<4, 64>;
+template <int POINTS>
+search_fn pick_bounds_wave(int g) {
+  if (g <= 128) return owq_search_bounds<1, 2, POINTS>;
+  if (g <= 256) return owq_search_bounds<1, 4, POINTS>;
+  if (g <= 512) return owq_search_bounds<1, 8, POINTS>;
+  return owq_search_bounds<1, 16, POINTS>;
+}
+search_fn pick_bounds(int g, int ncand) {
+  if (g <= 1024)
+    return ncand <= 64 ? pick_bounds_wave<1>(g) : ncand <= 128 ? pick_bounds_wave<2>(g) : ncand <= 192 ? pick_bounds_wave<3>(g) : pick_bounds_wave<4>(g);
+  if (g <= 2048) return owq_search_bounds<4, 8, 1>;
+  if (g <= 4096) return owq_search_bounds<4, 16, 1>;
+  if (g <= 6144) return owq_search_bounds<4, 24, 1>;
+  if (g <= 8192) return owq_search_bounds<4, 32, 1>;
+  if (g <= 12288) return owq_search_bounds<4, 48, 1>;
+  return owq_search_bounds<4, 64, 1>;
 }
 constexpr int kBoundsMax = 16384;    // columns of the longest group four waves keep in registers
 
@@ -844,7 +1010,7 @@ extern "C" owq_status_t owq_search_config(const owq_search_desc_t *d, const uint
   const dim3 grid((unsigned)((teams + per_wg - 1) / per_wg)), block(kWaves * 64);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int ncand = d->n_lo * d->n_hi;
-  const search_fn fn = bounds ? pick_bounds(g)
+  const search_fn fn = bounds ? pick_bounds(g, ncand)
                        : ncand <= 64 ? owq_search_kernel<1> : ncand <= 128 ? owq_search_kernel<2> : ncand <= 192 ? owq_search_kernel<3> : owq_search_kernel<4>;
   hipLaunchKernelGGL(fn, grid, block, mask_bytes, st, a);
   return hipGetLastError() == hipSuccess ? OWQ_OK : OWQ_ERR_HIP;
