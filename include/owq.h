@@ -85,8 +85,8 @@ typedef struct {
  * Two packed layouts hold the same content.  OWQ_LAYOUT_GEMV is built for single tokens
  * (one lane streams 128 columns of one row; a batch is one pass over the weights per two tokens, where the shape allows, else per token).
  * OWQ_LAYOUT_TILE is built for batches: 32 rows by 256 columns per tile, unpacked straight
- * into matrix-core operands, one pass over the weights per 64 tokens (half the matrix work
- * for 32 tokens or fewer).  Either layout accepts any batch and gives the same result up to
+ * into matrix-core operands, one pass over the weights per 64 tokens (one launch for 32 tokens
+ * or fewer, no passes for more than 64).  Either layout accepts any batch and gives the same result up to
  * rounding; they differ in speed only.  The blob of the tile layout ends in a scratch area
  * (staged activations, sums, fp32 partial results) that owq_linear uses at run time, so that
  * the call needs neither an allocation nor a workspace argument.
