@@ -112,7 +112,7 @@ int launch_tile_small(const owq_layer_info_t &g, void *blob, void *part, uint64_
 int launch_tile_few(const owq_layer_info_t &g, void *blob, int32_t lds_limit, const void *x, void *y, int32_t ntok, void *stream);
 int prepare_tile_few_kernels(const owq_layer_info_t &g, int32_t lds_limit);    // LDS opt-in
 // More than 64 tokens of one task (defined in owq_tile_wide.hip): scratch = DEVICE memory of scratch_bytes bytes.
-// Returns a hipError_t as int, or -1 when that memory cannot hold the gathered activations of 128 tokens.
+// Returns a hipError_t as int, or -1 when that memory cannot hold the gathered activations of 64 tokens.
 int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, const void *x, void *y,
                      int32_t batch, void *stream);
 int prepare_tile_wide_kernels(const owq_layer_info_t &g, int32_t lds_limit);   // LDS opt-in

@@ -4,7 +4,8 @@
 //
 // The passes of owq_tile.hip read the layer once per 64 tokens and spend half their time on launches, on
 // partial results and on matrix instructions that one wave per SIMD cannot keep fed.  Here a workgroup of
-// eight waves (two per SIMD) owns 256 rows x 64 tokens and walks along the columns in blocks of 128:
+// four waves owns 256 rows x 64 tokens and walks along the columns in blocks of 128; two workgroups share a compute
+// unit and are not in step, so one's matrix instructions run under the other's vector instructions and waits:
 //
 //   x       goes from memory straight into LDS (16-byte direct loads, two buffers, one block ahead), in
 //           rows of 256 bytes whose 16-byte units are exchanged by the low bits of the token, so that
@@ -23,6 +24,11 @@
 // One workgroup writes y itself when it owns all columns; when there are too few tiles for the chip the
 // columns are cut into `split` ranges, fp32 partial results go to the scratch area and owq_wide_sum adds them
 // in a fixed order.  No atomics: results are reproducible.
+//
+// What bounds it: beside its 32 matrix instructions a wave issues about 145 instructions of unpacking and 64 of scaling
+// per block.  4096 -> 16384 -> 4096, 3-bit, groups of 128, 2048 tokens: 2000 us in passes, 580-600 us here (920-950
+// TFLOP/s; a large fp16 library product reaches 1200 on the same card).  One workgroup of eight waves on 256 x 128 tokens
+// per compute unit took 636, weak masks by a scalar load per block instead of with the codes 612.
 #include <hip/hip_runtime.h>
 
 #include "owq_internal.h"
@@ -491,7 +497,8 @@ WidePlan wide_plan(int tiles, int nbp, int64_t slots) {
   for (int s = 1; s <= 32 && s * 2 <= nbp + 1; ++s) {
     const int n = tiles * s, left = n % 512, pairs = (nbp + s - 1) / s;
     if (s > 1 && n > slots) break;
-    // two workgroups per compute unit: a pair of blocks takes them kPair2, one alone kPair1
+    // Two workgroups per compute unit: a pair of blocks takes them kPair2 us, one alone kPair1.  4096 x 16384 at 2048 tokens:
+    // four rounds of 16 pairs in 310 us.  A split adds the sum's launch and the traffic of a partial result.
     constexpr float kPair1 = 1.5f, kPair2 = 2.0f;
     const float us = (n / 512) * (pairs * kPair2 + 4.f) + (left == 0 ? 0.f : pairs * (left > 256 ? kPair2 : kPair1) + 4.f) +
                      (s > 1 ? 4.f + 0.03f * n : 0.f);
