@@ -779,15 +779,19 @@ void tile_default_shape(const owq_layer_info_t &g, int32_t waves, int32_t *grid,
   *grid = cap;
   *split = 0;
   if (cap < 1) return;
-  // no more workgroups than the longest of them needs: with two steps for some of 252 workgroups and one for the others,
-  // 196 of two steps take as long and leave a quarter less to add up (3333 x 7000 at 37 tokens)
+  // A range that is as long as the longest one may as well take its neighbours' steps, if that leaves an eighth or more of
+  // the workgroups out: less to write and to add up.  At 252 -> 196 workgroups of at most two steps (3333 x 7000 at 37
+  // tokens) 24.8 -> 23.0 us, 252 -> 192 (2900 x 12000, 64 tokens) 27.9 -> 25.1, 240 -> 200 (5120 x 5120) 23.5 -> 22.6;
+  // where less is saved the compute units are missed: 240 -> 220 (5120 x 13824, 40 tokens) 29.1 -> 30.0, 250 -> 225
+  // (6400 x 6400) 25.9 -> 26.5, and 256 -> 247 (36864 x 9216) loses or gains a hundredth.
+  auto fewer = [](int64_t full, int64_t trimmed) { return (int32_t)(8 * (full - trimmed) >= full ? trimmed : full); };
   const int64_t equal = (steps + cap - 1) / cap;
-  *grid = (int32_t)((steps + equal - 1) / equal);
+  *grid = fewer(cap, (steps + equal - 1) / equal);
   int64_t sa = cap / n_rg;
   if (sa > g.nbp) sa = g.nbp;
   if (sa >= 1) {
     const int64_t aligned = (g.nbp + sa - 1) / sa;
-    sa = (g.nbp + aligned - 1) / aligned;
+    sa = fewer(sa, (g.nbp + aligned - 1) / aligned);
     if (aligned * 10 <= equal * 11) {
       *grid = (int32_t)(n_rg * sa);
       *split = (int32_t)sa;
