@@ -48,14 +48,14 @@ template <int N>
 __device__ __forceinline__ void loads_to_lds(const void *sbase, const u32 *voff, u32 lds) {
   static_assert(N == 1 || N == 2 || N == 4, "the offset field holds 3072");
   if constexpr (N == 1)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff[0]), "s"(sbase) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(voff[0]), "s"(sbase) : "memory");
   else if constexpr (N == 2)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
-                 ::"s"(lds), "v"(voff[0]), "v"(voff[1]), "s"(sbase) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
+                 ::"{m0}"(lds), "v"(voff[0]), "v"(voff[1]), "s"(sbase) : "memory");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
                  "global_load_lds_dwordx4 %3, %5 offset:2048\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072"
-                 ::"s"(lds), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(sbase) : "memory");
+                 ::"{m0}"(lds), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(sbase) : "memory");
 }
 
 template <int BITS, int RT, int S>
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(512, 2) void owq_tile_few(const FewArgs a) {
     const int t = RT == 1 ? 0 : q & 1, gp = RT == 1 ? q : q >> 1;
     const int g = min(2 * gp + kg, a.n_groups - 1), row = min((rg * RT + t) * 32 + n32, a.d_out_pad - 1);
     const u32 off = ((u32)g * (u32)a.d_out_pad + (u32)row) * 4u;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(ldsb + (u32)(a.off_sz + (t * ((a.n_groups + 1) & ~1) + 2 * gp) * 128)),
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, %2" ::"{m0}"(ldsb + (u32)(a.off_sz + (t * ((a.n_groups + 1) & ~1) + 2 * gp) * 128)),
                  "v"(off), "s"(a.sz) : "memory");
   }
   const int kunits = a.kp >> 3, ksteps = (kunits + 1) >> 1;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(512, 2) void owq_tile_few(const FewArgs a) {
     const int e = min(e0 + lane, pairs - 1), n = e & (np - 1);
     const int j = idx[e >> a.lg_tok];
     const u32 at = ((u32)(n < a.ntok ? n : 0) * (u32)a.d_in + (u32)(j >= 0 ? j : 0)) * 2u;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(ldsb + (u32)(a.off_xd + e0 * 4)), "v"(at & ~3u), "s"(a.x)
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, %2" ::"{m0}"(ldsb + (u32)(a.off_xd + e0 * 4)), "v"(at & ~3u), "s"(a.x)
                  : "memory");
   }
 
