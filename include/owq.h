@@ -279,16 +279,18 @@ owq_status_t owq_export_packed(owq_handle_t h, void *host_buf, size_t bytes);
  *     row_splits = 0 and row_tiles_per_wg = P > 0: the flattened (row group, 256-column step)
  *     sequence is cut into P equal ranges.  Both 0: the default for the chosen waves_per_wg.
  *     The number of workgroups is limited by the partial-result slots of the scratch area.
- *     These three shape the three-launch path, which takes passes of more than 16 tokens.
- *     prefetch_depth shapes the one-launch kernel for passes of few tokens: 0 = the library
- *     uses it for passes of 16 tokens or fewer and chooses its work split; -1 = never use it;
- *     S + 100 c with S in [1, 99], c in [0, 3] = use it for every pass of 32 tokens or fewer,
- *     with every row tile's columns cut into S ranges (S <= d_in / 128) and, for c = 1, 2, 3,
- *     1, 2 or 4 row tiles per workgroup (c = 0: the library chooses).  A shape that does not
- *     fit a later call's number of tokens (the activations of a range must fit LDS) makes
- *     that owq_linear return OWQ_ERR_SHAPE.  The kernel needs x 16-byte aligned, d_in a
- *     multiple of 128, a group size of 128 * 2^n or none, and one task; other calls take the
- *     three-launch path.
+ *     These three shape the three-launch path.  If any of them is given, that path takes every pass of more than 16
+ *     tokens, and batches above 64 tokens run as passes of 64; with all three 0 it takes calls of 33 to 64 tokens
+ *     and the passes of owq_linear_multi, and the library's other kernels take the rest.
+ *     prefetch_depth chooses the one-launch kernels for few tokens: 0 = the library chooses (for passes of 16 tokens or
+ *     fewer where the three launches are shaped as above, else of 32 or fewer); -1 = never use one of them;
+ *     S + 100 c with S in [0, 99], c in [0, 3], not 0 = use the kernel that spreads columns over workgroups for every
+ *     pass of 32 tokens or fewer, with every row tile's columns cut into S ranges (S <= d_in / 128; S = 0: the library
+ *     chooses) and, for c = 1, 2, 3, 1, 2 or 4 row tiles per workgroup (c = 0: the library chooses).  With a value
+ *     other than 0, batches above 64 tokens run as passes of 64 too.  A shape that does not fit a
+ *     later call's number of tokens (the activations of a range must fit LDS) makes that owq_linear
+ *     return OWQ_ERR_SHAPE.  The kernel needs x 16-byte aligned, d_in a multiple of 128, a group
+ *     size of 128 * 2^n or none, and one task; other calls take the three-launch path.
  */
 owq_status_t owq_set_launch(owq_handle_t h, int32_t row_tiles_per_wg, int32_t row_splits,
                             int32_t waves_per_wg, int32_t prefetch_depth);

@@ -60,6 +60,7 @@ static owq_status_t make_handle(const owq_layer_info_t &g, void *dev_buf, owq_ha
   h->tile_waves = tile_waves;
   h->tile_split = tile_split;
   h->tile_small_split = 0;
+  h->tile_shaped = false;
   h->dev_buf = dev_buf;
   h->lds_limit = lds_limit;
   const uint8_t *base = static_cast<const uint8_t *>(dev_buf);
@@ -124,7 +125,8 @@ static owq_status_t run_linear(owq_handle_t h, const TaskSets &tasks, const void
   if (reinterpret_cast<uintptr_t>(x) % 2 != 0 || reinterpret_cast<uintptr_t>(y) % 2 != 0) return OWQ_ERR_BUFFER;
   const int herr = h->info.layout == OWQ_LAYOUT_TILE
                        ? launch_tile(h->info, h->dev_buf, sc ? sc->mem : nullptr, sc ? sc->bytes : 0, sc ? sc->grid : h->tile_grid,
-                                     sc ? sc->split : h->tile_split, h->tile_waves, h->tile_small_split, h->lds_limit, tasks, x, y, batch, stream)
+                                     sc ? sc->split : h->tile_split, h->tile_waves, h->tile_small_split, h->tile_shaped, h->lds_limit, tasks, x, y,
+                                     batch, stream)
                        : launch_gemv(h->info, h->shape, h->dev, tasks, x, y, batch, h->lds_limit, stream);
   if (herr == -2) return OWQ_ERR_SHAPE;     // a launch shape set by the caller does not fit this batch
   if (herr != 0) {
@@ -317,6 +319,7 @@ owq_status_t owq_set_launch(owq_handle_t h, int32_t rtw, int32_t rsplit, int32_t
     h->tile_split = sp;
     h->tile_waves = wv;
     h->tile_small_split = depth;
+    h->tile_shaped = rtw != 0 || rsplit != 0 || waves != 0;
     return OWQ_OK;
   }
   LaunchShape s = h->shape;

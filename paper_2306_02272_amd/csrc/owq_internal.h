@@ -93,12 +93,14 @@ int prepare_multi_kernels(int32_t lds_bytes);
 // split = 0: the flattened (row group, column step) sequence cut into `grid` equal ranges.
 // small_shape: work split of the one-launch kernel that takes passes of 32 tokens or fewer
 // (0 = the library's choice, -1 = never use that kernel, else S + 100 c, see launch_tile_small).
+// shaped: grid, split or waves were asked for by the caller, so every pass of more than 16 tokens takes the three launches
+// they shape.  shaped or small_shape != 0: more than 64 tokens run in passes.
 // scratch = DEVICE memory for the intermediate results laid out as tile_scratch() says, of
 // scratch_bytes bytes (at least TileScratch::off_slots plus the slots the grid needs);
 // nullptr = the scratch area inside the blob.
 int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, int32_t grid, int32_t split,
-                int32_t waves, int32_t small_split, int32_t lds_limit, const TaskSets &tasks, const void *x, void *y, int32_t batch,
-                void *stream);
+                int32_t waves, int32_t small_split, bool shaped, int32_t lds_limit, const TaskSets &tasks, const void *x, void *y,
+                int32_t batch, void *stream);
 // Device address of the library's static scratch array on the current device (looked up once
 // per device).  Returns a hipError_t as int.
 int static_scratch(void **ptr);
@@ -144,4 +146,5 @@ struct owq_layer_s {
   int32_t tile_waves;    // its waves per workgroup: 4 or 8
   int32_t tile_split;    // column ranges per row group, 0 = equal ranges of the whole sequence
   int32_t tile_small_split;  // 32 tokens or fewer: column ranges per row tile, 0 = default, -1 = three-launch path
+  bool tile_shaped;          // workgroups, ranges or waves were set by owq_set_launch
 };

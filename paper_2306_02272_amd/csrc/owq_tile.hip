@@ -800,8 +800,8 @@ void tile_default_shape(const owq_layer_info_t &g, int32_t waves, int32_t *grid,
 }
 
 int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t scratch_bytes, int32_t grid, int32_t split,
-                int32_t waves, int32_t small_split, int32_t lds_limit, const TaskSets &tasks, const void *x, void *y, int32_t batch,
-                void *stream) {
+                int32_t waves, int32_t small_split, bool shaped, int32_t lds_limit, const TaskSets &tasks, const void *x, void *y,
+                int32_t batch, void *stream) {
   const TileScratch ts = tile_scratch(g);
   uint8_t *base = static_cast<uint8_t *>(blob);
   uint8_t *scr = scratch ? static_cast<uint8_t *>(scratch) : base + g.off_scratch;
@@ -847,15 +847,16 @@ int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t s
 
   const _Float16 *xp = static_cast<const _Float16 *>(x);
   _Float16 *yp = static_cast<_Float16 *>(y);
-  // more tokens than a pass takes: the kernels that read the layer once per 128 tokens and need no such passes
-  if (batch > kScratchBatch && tasks.task_id == nullptr) {
+  // more tokens than a pass takes: the kernels of owq_tile_wide.hip, which need no such passes, unless the caller has
+  // asked for a launch shape of the passes
+  if (batch > kScratchBatch && tasks.task_id == nullptr && small_split == 0 && !shaped) {
     const int r = launch_tile_wide(g, blob, scr, scr_bytes, x, y, batch, stream);
     if (r >= 0) return r;
   }
   for (int32_t t0 = 0; t0 < batch; t0 += kScratchBatch) {
     const int ntok = batch - t0 < kScratchBatch ? batch - t0 : kScratchBatch;
     const int nt = ntok > 32 ? 2 : 1;
-    if (small_split == 0 && tasks.task_id == nullptr) {                 // few tokens, one task: one launch
+    if (small_split == 0 && tasks.task_id == nullptr && !(shaped && ntok > 16)) {      // few tokens, one task: one launch
       const int r = launch_tile_few(g, blob, lds_limit, xp + (size_t)t0 * g.d_in, yp + (size_t)t0 * g.d_out, ntok, stream);
       if (r > 0) return r;
       if (r == 0) continue;
