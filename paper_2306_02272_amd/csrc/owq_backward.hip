@@ -14,7 +14,7 @@
 // product, whose A operand is dy times the step size, staged in operand order.  No LDS and no
 // shuffles are needed for the turn.
 //
-// Per group of up to four passes of 128 tokens: staging (dy into operand order, on the first group also the weak
+// Per group of passes of 128 tokens (four, or up to sixteen of a small layer): staging (dy into operand order, on the first group also the weak
 // columns and the activations at the weak columns); the small products (dww of the whole batch on the first group,
 // dx at the weak columns in partial results); the product into fp32 partial results per range of rows; the sum of
 // the partial results into fp16 dx.  A layer whose weak columns are more than an eighth of all takes a plain
@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "owq_internal.h"
 #include "owq_tile_device.h"
@@ -32,7 +33,12 @@ namespace {
 constexpr int kPassTokens = 128;     // tokens per pass: four accumulator tiles of 32 per wave
 constexpr int kSplitMax = 16;        // most ranges of rows per block pair
 constexpr int kWeakSplit = 32;       // ranges of rows of the product with the weak columns
-constexpr int kLaunchPasses = 4;     // passes (of 128 tokens) that one set of launches takes
+constexpr int kLaunchPasses = 4;     // passes (of 128 tokens) that one set of launches takes, or
+constexpr int kMorePasses = 16;      // up to so many where they do not fill the chip and their staged dy stays within
+constexpr size_t kMoreBytes = 64u << 20;
+// Fewer staging blocks of four token tiles than this do not fill the chip and take one tile each (2048 -> 640 at 200
+// tokens, 22 blocks: 3.1 instead of 4.4 us; 4096 -> 16384 at 512, 1028 blocks: 11.1 us in blocks of one, 10.0 of four).
+constexpr int kStageBlocks = 512;
 constexpr size_t kScanBytes = 2048;  // end of the workspace: the magnitude scan's 256 words, then the exponent
 
 // N 2-byte loads whose results get a use of their own after all of them have been issued, so
@@ -64,17 +70,23 @@ __global__ __launch_bounds__(256) void owq_bwd_absmax(const u32x4 *dy, size_t n1
     const u32 lo = w & 0x7fffu, hi = (w >> 16) & 0x7fffu;
     m = max(m, max(lo, hi));
   };
-  // eight loads in flight per thread (one at a time: 9.7 instead of 6.1 us on 27 MB); past the end the last one again
+  // eight loads in flight per thread (one at a time: 9.7 instead of 6.1 us on 27 MB), the last one again past the end;
+  // where a thread has one at most, that one
   constexpr size_t kStep = (size_t)kMaxBlocks * 256;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += 8 * kStep) {
-    u32x4 v[8];
+  auto scan = [&](auto in_flight) __attribute__((always_inline)) {
+    constexpr int J = decltype(in_flight)::value;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += J * kStep) {
+      u32x4 v[J];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = dy[i + j * kStep < n16 ? i + j * kStep : n16 - 1];
+      for (int j = 0; j < J; ++j) v[j] = dy[i + j * kStep < n16 ? i + j * kStep : n16 - 1];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      take(v[j].x); take(v[j].y); take(v[j].z); take(v[j].w);
+      for (int j = 0; j < J; ++j) {
+        take(v[j].x); take(v[j].y); take(v[j].z); take(v[j].w);
+      }
     }
-  }
+  };
+  if (n16 <= kStep) scan(std::integral_constant<int, 1>{});
+  else scan(std::integral_constant<int, 8>{});
   for (size_t i = n16 * 8 + (size_t)blockIdx.x * 256 + threadIdx.x; i < n_halves; i += (size_t)kMaxBlocks * 256)
     take(dy_h[i]);
 #pragma unroll
@@ -97,8 +109,10 @@ struct StageArgs {
 
 // A unit: token 32 m + lane % 32 of the pass, rows 32 rt + 16 s + 4 h + {0..3} and
 // the same + 8 (h = lane / 32): the order in which the turned codes hold their rows.  Block b of
-// the staging takes two row tiles of a pass, a thread one unit of each of its four tiles of 32 tokens: the 64 rows x
-// 2 bytes that its four waves read of a token are one 128-byte line, fetched by this block only.
+// the staging takes two row tiles and NM tiles of 32 tokens of a pass (four, or one where there are few blocks), a thread
+// one unit of each: the 64 rows x 2 bytes that its four waves read of a token are one 128-byte line, fetched by this
+// block only.
+template <int NM>
 __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) {
   // the scale: every workgroup reduces the scan's 256 entries again (cheaper than one more launch)
   __shared__ u32 red[4];
@@ -111,26 +125,28 @@ __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) 
   const float scale = __builtin_ldexpf(1.0f, kexp);
   if (b == 0 && t == 0) *a.kword = kexp;
   const int pairs = (a.n_st + 1) >> 1;
+  const int m0 = NM == 1 ? (int)(b & 3) : 0;
+  if (NM == 1) b >>= 2;
   const int pr = (int)(b % (unsigned)pairs), pass = (int)(b / (unsigned)pairs);
   const int l = t & 63, s = (t >> 6) & 1, rt = 2 * pr + (t >> 7), h = l >> 5;
   if (pass >= a.passes || rt >= a.n_st) return;
-  u32x4 *dst = a.a_st + (size_t)pass * a.n_st * 512 + ((size_t)rt * 2 + s) * 256 + l;
-  const int n0 = a.n0 + kPassTokens * pass + (l & 31);
-  h8_t v[4];
+  u32x4 *dst = a.a_st + (size_t)pass * a.n_st * 512 + ((size_t)rt * 2 + s) * 256 + m0 * 64 + l;
+  const int n0 = a.n0 + kPassTokens * pass + 32 * m0 + (l & 31);
+  h8_t v[NM];
   const int ia = 32 * rt + 16 * s + 4 * h;          // rows ia .. ia + 3 and ia + 8 .. ia + 11
   if (ia + 11 < a.d_out && (a.d_out & 3) == 0) {
     // both runs of four rows inside the matrix and 8-byte aligned (dy is 16-byte aligned)
     typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
-    h4_t lo[4], hi[4];
+    h4_t lo[NM], hi[NM];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
+    for (int m = 0; m < NM; ++m) {
       const int n = n0 + 32 * m;
       const _Float16 *row = a.dy + (size_t)(n < a.batch ? n : a.batch - 1) * a.d_out + ia;
       lo[m] = *reinterpret_cast<const h4_t *>(row);
       hi[m] = *reinterpret_cast<const h4_t *>(row + 8);
     }
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+    for (int m = 0; m < NM; ++m)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const bool in = n0 + 32 * m < a.batch;
@@ -139,7 +155,7 @@ __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) 
       }
   } else {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
+    for (int m = 0; m < NM; ++m) {
       const int n = n0 + 32 * m;
       const _Float16 *p[8];
       _Float16 x[8];
@@ -157,7 +173,7 @@ __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) 
     }
   }
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
+  for (int m = 0; m < NM; ++m) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[m][e] = (_Float16)((float)v[m][e] * scale);      // a power of two, below 1024 afterwards: exact
     dst[m * 64] = __builtin_bit_cast(u32x4, v[m]);
@@ -214,9 +230,11 @@ constexpr int kProdLds = kProdPlanes + 8 * kProdPlane;
 // codes 16, dy times step size 32), so two waves per SIMD keep the matrix cores busy if nothing else is in the way.
 // Hence: staged dy comes in operand order by direct loads to LDS (no registers, no copies between register sets), step
 // sizes lie in LDS in the order a lane multiplies them, zero points leave with the unpack constant (exactly: integers
-// of at most 1024, what they lack is taken off by a side loop where a layer has other ones).  4096 -> 16384, 3-bit, 512
-// tokens: 92 us, 745 TFLOP/s beside a turn of a quarter more; with one wave per SIMD, all of that in registers and the
-// zero points summed beside the product 135 us.  5120 -> 13824, 4-bit, 512 tokens: 91 us against 175.
+// of at most 1024, what they lack is taken off by a side loop where a layer has other ones).  Row tiles past the end of a
+// range are left out one by one (whole steps with tiles of zeros: 11.1 instead of 8.6 us on 512 x 512, 24.0 instead of
+// 20.0 on 2432 -> 2086 at 432 tokens; the branches also keep each tile's loads of codes in place).  4096 -> 16384, 3-bit,
+// 512 tokens: 88 us, 780 TFLOP/s beside a turn of a quarter more; with one wave per SIMD, all of that in registers and
+// the zero points summed beside the product 135 us.  5120 -> 13824, 4-bit, 1000 tokens: 189 us against 346.
 template <int BITS>
 __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   extern __shared__ u32x4 lds_units[];
@@ -278,7 +296,8 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   auto fetch_dy = [&](int rt, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < kStepTiles; ++i) {
-      const unsigned char *src = a_st + (size_t)(rt + i < rt1 ? rt + i : a.n_rt) * 8192;
+      if (rt + i >= rt1) break;
+      const unsigned char *src = a_st + (size_t)(rt + i) * 8192;
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         load_to_lds(src, (u32)((2 * cw + j) * 1024 + lane * 16), ldsb + (u32)((2 * kh + buf) * kStepBytes + i * 8192 + (2 * cw + j) * 1024));
@@ -309,7 +328,7 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
     fetch_sz(nx);
     const unsigned char *dyb = lds + (2 * kh + (st & 1)) * kStepBytes + lane * 16;
     if (__ballot(rest) != 0ull) {            // zero points that are no small integers: sum of dy s (z - rint z) per token
-      for (int i = 0; i < 2 * kStepTiles; ++i) {
+      for (int i = 0; i < 2 * min(kStepTiles, rt1 - rt); ++i) {
         const u32x4 s4 = *reinterpret_cast<const u32x4 *>(splane + (2 * i + h) * 8), r4 = *reinterpret_cast<const u32x4 *>(rplane + (2 * i + h) * 8);
         const u32 sv[4] = {s4.x, s4.y, s4.z, s4.w}, rv[4] = {r4.x, r4.y, r4.z, r4.w};
 #pragma unroll
@@ -322,8 +341,7 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
         }
       }
     }
-#pragma unroll
-    for (int i = 0; i < kStepTiles; ++i) {
+    auto row_tile = [&](int i) __attribute__((always_inline)) {
       // ---- turn: q - z of 32 rows x 64 columns from (row, eight columns) to (column, eight rows) per lane ----
       const _Float16 z1 = zplane[32 * i + n32];
       const u32 zz = (u32)__builtin_bit_cast(unsigned short, z1) * 0x00010001u ^ 0x80008000u;
@@ -368,6 +386,11 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
           acc[m][1] = mma(aop, __builtin_bit_cast(h8_t, wb[1][s]), acc[m][1]);
         }
       }
+    };
+#pragma unroll
+    for (int i = 0; i < kStepTiles; ++i) {
+      if (rt + i >= rt1) break;
+      row_tile(i);
     }
   }
   wait_loads<0>();
@@ -585,12 +608,14 @@ struct StageAllArgs {
   StageWeakArgs weak;
   StageXArgs x;
   unsigned dy_blocks, weak_blocks;   // blocks [0, dy_blocks) stage dy, the next weak_blocks the weak columns, the rest x
+  int narrow;                        // a block of dy takes one tile of 32 tokens instead of four
 };
 
 // All staging of a call in one launch: the three parts are independent of each other.
 __global__ __launch_bounds__(256) void owq_bwd_stage_all(const StageAllArgs a) {
   const unsigned b = blockIdx.x;
-  if (b < a.dy_blocks) stage_dy(a.dy, b, (int)threadIdx.x);
+  if (b < a.dy_blocks && a.narrow) stage_dy<1>(a.dy, b, (int)threadIdx.x);
+  else if (b < a.dy_blocks) stage_dy<4>(a.dy, b, (int)threadIdx.x);
   else if (b < a.dy_blocks + a.weak_blocks) stage_weak(a.weak, (long long)(b - a.dy_blocks) * 256 + threadIdx.x);
   else stage_x(a.x, (long long)(b - a.dy_blocks - a.weak_blocks) * 256 + threadIdx.x);
 }
@@ -695,7 +720,14 @@ struct BwdPlan {
 BwdPlan plan(const owq_layer_info_t &g, int batch) {
   BwdPlan p;
   const int all_passes = (batch + kPassTokens - 1) / kPassTokens;
-  p.passes = all_passes < kLaunchPasses ? (all_passes < 1 ? 1 : all_passes) : kLaunchPasses;
+  // Every set of launches costs the small kernels of its own (staging, weak columns, sum; 20 us and more where the product
+  // takes 15), so layers whose block pairs leave compute units free take more passes at once: 1664 -> 768 at 1017 tokens
+  // 58 -> 38 us.  The product's partial results do not grow: more passes, fewer ranges of rows.
+  const size_t pass_bytes = (size_t)(g.n_rt + 1) * 8192;
+  int most = 256 / g.nbp < kMorePasses ? 256 / g.nbp : kMorePasses;
+  if (most * pass_bytes > kMoreBytes) most = (int)(kMoreBytes / pass_bytes);
+  if (most < kLaunchPasses) most = kLaunchPasses;
+  p.passes = all_passes < most ? (all_passes < 1 ? 1 : all_passes) : most;
   // Ranges of rows per block pair.  A compute unit holds one workgroup at a time, so the product takes rounds of 256
   // workgroups, each as long as its row tiles (0.7 us) and a fixed part; every range costs the sum kernel a read of its
   // partial results.  In us, fitted to measurements on MI355X.
@@ -716,7 +748,8 @@ BwdPlan plan(const owq_layer_info_t &g, int batch) {
   p.part_bytes = (size_t)p.passes * p.split * kPassTokens * ((size_t)g.nbp * 256) * 4;
   p.kp32 = (g.kp + 31) / 32;
   p.weak_staged = g.k > 0 && p.kp32 <= g.nbp;
-  p.wsplit = g.n_rt < kWeakSplit ? g.n_rt : kWeakSplit;
+  // weak columns: ranges of at least the four row tiles whose loads go out together
+  p.wsplit = (g.n_rt + 3) / 4 < kWeakSplit ? (g.n_rt + 3) / 4 : kWeakSplit;
   p.wst_bytes = p.weak_staged ? (size_t)g.n_rt * 2 * p.kp32 * 64 * 16 : 0;
   p.pw_bytes = p.weak_staged ? (size_t)p.passes * p.wsplit * kPassTokens * 32 * p.kp32 * 4 : 0;
   p.x_steps = (batch + 15) / 16;
@@ -787,7 +820,9 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
     sa.weak = {reinterpret_cast<const _Float16 *>(blob + g.off_weak_w), wst, g.kp, p.kp32, g.n_rt};
     sa.x = {static_cast<const _Float16 *>(x), reinterpret_cast<const int *>(blob + g.off_weak_idx), xw_st,
             g.d_in, g.k, p.kp32, batch, p.x_steps};
-    sa.dy_blocks = dx ? (unsigned)(((g.n_rt + 2) / 2) * passes) : 0u;
+    const int wide_blocks = ((g.n_rt + 2) / 2) * passes;
+    sa.narrow = wide_blocks < kStageBlocks ? 1 : 0;
+    sa.dy_blocks = dx ? (unsigned)(sa.narrow ? 4 * wide_blocks : wide_blocks) : 0u;
     sa.weak_blocks = dx && n0 == 0 && p.weak_staged ? (unsigned)(((long long)g.n_rt * 2 * p.kp32 * 64 + 255) / 256) : 0u;
     const unsigned x_blocks = want_dww && n0 == 0 ? (unsigned)(((long long)p.x_steps * p.kp32 * 64 + 255) / 256) : 0u;
     if (sa.dy_blocks + sa.weak_blocks + x_blocks > 0)

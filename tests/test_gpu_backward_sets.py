@@ -1,0 +1,48 @@
+"""Backward where the work of one set of launches is cut: every remainder of a range's last step of four row tiles, in
+either half of the range; staging blocks of one and of four token tiles; five and more passes of 128 tokens at once, and
+batches that still need several sets.  Bar as in test_gpu_backward: relative L2 error <= 1e-3, max-abs <= 1e-2 rms."""
+import numpy as np
+import pytest
+
+from oracle import backward, owq_ref
+from synth import LayerSpec, make_layer, make_x
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2306_02272_amd import binding
+    binding.lib()
+    torch.cuda.set_device(0)
+    return torch, binding
+
+
+@pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens", [
+    # ranges of 1 to 9 row tiles (16 ranges at most)
+    (256, 16 * 32, 3, 0, 4, 20), (256, 33 * 32, 4, 128, 4, 20), (256, 47 * 32, 3, 128, 4, 20), (256, 64 * 32 - 7, 4, 0, 4, 20),
+    (200, 80 * 32, 3, 128, 4, 20), (256, 95 * 32, 4, 128, 4, 20), (256, 110 * 32 + 1, 3, 0, 4, 20), (256, 128 * 32, 4, 128, 4, 20),
+    (256, 141 * 32, 3, 128, 4, 20),
+    (512, 96, 4, 128, 5, 700), (300, 200, 3, 0, 9, 2300),          # six passes in one set; sixteen and then two
+    (128, 33000, 4, 0, 3, 140), (128, 66000, 3, 0, 2, 800),        # staging blocks of four token tiles; sets of four passes
+])
+def test_cuts(env, d_in, d_out, bits, group, k, tokens):
+    torch, B = env
+    layer = make_layer(LayerSpec("sets", d_in, d_out, bits, group, k, d_in + d_out))
+    rng = np.random.default_rng(d_out)
+    x = make_x(layer, tokens)
+    dy = rng.normal(0, 0.05, (tokens, d_out)).astype(np.float16)
+    print(f"{d_in} -> {d_out}, {bits} bit, group {group}, {tokens} tokens", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    dx, dww = lin.backward(torch.from_numpy(dy).cuda(), torch.from_numpy(x).cuda())
+    want_dx, want_dww = backward.owq_backward_ref(layer.codes, layer.scale, layer.zero, group, layer.weak_idx, layer.weak_w, x, dy)
+    rel, mx = owq_ref.parity_errors(dx.cpu().numpy(), want_dx)
+    assert rel <= 1e-3 and mx <= 1e-2, (rel, mx)
+    rel, _ = owq_ref.parity_errors(dww.cpu().numpy(), want_dww)
+    assert rel <= 1e-5, rel
+    again, _ = lin.backward(torch.from_numpy(dy).cuda(), torch.from_numpy(x).cuda())
+    np.testing.assert_array_equal(dx.cpu().numpy().view(np.uint16), again.cpu().numpy().view(np.uint16))
+    lin.close()
