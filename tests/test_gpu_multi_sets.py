@@ -1,0 +1,50 @@
+"""Several sets of weak columns on the tile layout: more than one chunk of 128 weak columns (a last one that is whole, ragged,
+of one unit), passes of 32 tokens or fewer and of more, rows that are no multiple of 64, tokens that use no set, one set or
+all of them.  Bar as in test_gpu_multi: relative L2 error <= 1e-3, max-abs <= 1e-2 rms, per token."""
+import numpy as np
+import pytest
+
+from oracle import owq_ref
+from synth import LayerSpec, make_layer, make_x
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2306_02272_amd import binding
+    binding.lib()
+    torch.cuda.set_device(0)
+    return torch, binding
+
+
+@pytest.mark.parametrize("k", [130, 200, 256, 300])
+@pytest.mark.parametrize("batch", [3, 17, 32, 33, 64, 100])
+@pytest.mark.parametrize("use", ["none", "one", "all"])
+def test_chunks_of_weak_columns(env, k, batch, use):
+    torch, B = env
+    d_in, d_out, n_sets = 900, 170 if batch % 2 else 333, 6
+    bits, group = (3, 0) if k in (130, 256) else (4, 128)
+    layer = make_layer(LayerSpec("chunks", d_in, d_out, bits, group, k, k + batch))
+    rng = np.random.default_rng(k * batch)
+    sets = [rng.normal(0, 0.02, size=(d_out, k)).astype(np.float16) for _ in range(n_sets)]
+    if use == "none":
+        task = np.full(batch, -1, dtype=np.int32)
+    elif use == "one":
+        task = np.where(rng.random(batch) < 0.5, 4, n_sets).astype(np.int32)         # n_sets: the layer's own
+    else:
+        task = ((np.arange(batch) + rng.integers(0, 2, batch)) % (n_sets + 1) - 1).astype(np.int32)
+    x = make_x(layer, batch)
+    print(f"k {k}, batch {batch}, sets: {use}", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    table, bufs = lin.add_weak_sets(sets)
+    y = lin.multi(torch.from_numpy(x).cuda(), table, torch.from_numpy(task).cuda()).cpu().numpy()
+    want = owq_ref.owq_linear_multi_ref(layer.codes, layer.scale, layer.zero, layer.group_size, layer.weak_idx, sets + [layer.weak_w],
+                                        [t if 0 <= t < n_sets else n_sets for t in task], x)
+    for n in range(batch):
+        rel, mx = owq_ref.parity_errors(y[n], want[n])
+        assert rel <= 1e-3 and mx <= 1e-2, (n, task[n], rel, mx)
+    lin.close()
