@@ -33,6 +33,7 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;            // waves per workgroup, each with its own LDS area
 constexpr int kChunk = 1024;         // columns moved through LDS at a time
+constexpr u32 kLeastStep = 0x38800000u;    // 2^-14 in binary32
 constexpr int kMaskBytesMax = 47 * 1024;   // LDS left for the weak-column bit mask of a row: 64 KiB less the kernel's static 16.1 KiB
 
 struct SearchArgs {
@@ -627,6 +628,9 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
             const int id = src + 64 * c;
             if (id == wf || !(lane_of(bound[c], src) <= best.e * to_bins)) continue;
             const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+            // Step sizes at their least value span more than the group: bounds rule nothing out, but most points are the
+            // same as one before and go with it (one by one they took longer than the plain search)
+            if (__builtin_bit_cast(u32, p.s) == kLeastStep) m &= ~__ballot(cd[c].s == p.s && cd[c].a == p.a);
             if (same_as_best(p, id)) continue;
             const float e = evaluate(p);
             take(e, id, p);
@@ -652,6 +656,7 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
                 const int src = __builtin_ctzll(m);
                 m &= m - 1;
                 const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+                m &= ~__ballot(cd[c].s == p.s && cd[c].a == p.a);
                 if (!same_as_best(p, src + 64 * c)) take(in_order(p), src + 64 * c, p);
               }
             }
@@ -722,11 +727,14 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
           float ef = INFINITY;
           if (wf != 0x7fffffff) ef = (S.wave[0][2] + S.wave[1][2]) + (S.wave[2][2] + S.wave[3][2]);
           const float bs = best.s, bz = best.z;
+          int found = 0, count = 0;
+          bool more = false;                        // than four of them
+          int ids[4] = {0, 0, 0, 0};
           for (int pass = 0; pass < 2; ++pass) {    // looks for one beside the best, then ranks them, four at a time
-            int k = 0, found = 0, count = 0;
-            int ids[4] = {0, 0, 0, 0};
+            int k = 0;
             bool first_due = ef <= near;
             if (pass == 1) {
+              if (more) count = 0;
               best.e = INFINITY;
               best.id = 0x7fffffff;
             }
@@ -738,14 +746,19 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
               }
               count = 0;
             };
+            // at the least step size the points of one lower end are the same: the first of a run stands for it
+            float last_s = 0.f, last_a = 0.f;
             auto due = [&](int id) __attribute__((always_inline)) {
               const Cand p = S.cand[id];
+              if (p.s == last_s && p.a == last_a) return;
+              last_s = p.s;
+              last_a = p.a;
               found += p.s == bs && 0.f - p.a == bz ? 0 : 1;
 #pragma unroll
               for (int c = 0; c < 4; ++c) ids[c] = c == count ? id : ids[c];
               ++count;
             };
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < 4 && (pass == 0 || more); ++i) {
               unsigned long long left = uniform(S.alive[i]);
               while (left) {
                 const int id = i * 64 + __builtin_ctzll(left);
@@ -759,11 +772,12 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
                 if (first_now || close_one) due(first_now ? wf : id);
                 if (count == 4) {
                   if (pass == 1) rank();
+                  more = true;
                   count = 0;
                 }
               }
             }
-            if (first_due) due(wf);
+            if (first_due && (pass == 0 || more)) due(wf);
             if (found == 0) break;
             if (pass == 1 && count > 0) rank();
           }
