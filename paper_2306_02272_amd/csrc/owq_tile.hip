@@ -779,13 +779,14 @@ void tile_default_shape(const owq_layer_info_t &g, int32_t waves, int32_t *grid,
   *grid = cap;
   *split = 0;
   if (cap < 1) return;
-  // A range that is as long as the longest one may as well take its neighbours' steps, if that leaves an eighth or more of
-  // the workgroups out: less to write and to add up.  At 252 -> 196 workgroups of at most two steps (3333 x 7000 at 37
-  // tokens) 24.8 -> 23.0 us, 252 -> 192 (2900 x 12000, 64 tokens) 27.9 -> 25.1, 240 -> 200 (5120 x 5120) 23.5 -> 22.6;
-  // where less is saved the compute units are missed: 240 -> 220 (5120 x 13824, 40 tokens) 29.1 -> 30.0, 250 -> 225
-  // (6400 x 6400) 25.9 -> 26.5, and 256 -> 247 (36864 x 9216) loses or gains a hundredth.
-  auto fewer = [](int64_t full, int64_t trimmed) { return (int32_t)(8 * (full - trimmed) >= full ? trimmed : full); };
+  // Joining ranges until all are as long as the longest had to be writes and adds up fewer partial results and idles compute
+  // units.  With up to four steps per workgroup it pays almost always (50 shapes with weights from HBM, 33 to 64 tokens, 0 to
+  // 43 % of the workgroups joined away: 0.98 to 1.13 times as fast, 47 of them faster): 252 -> 196 workgroups (3333 x 7000) 24.8 ->
+  // 23.0 us, 256 -> 192 (3968 x 8576) 27.1 -> 24.3, 256 -> 242 (11617 x 5248) 28.8 -> 28.4.  With more steps only if it leaves an
+  // eighth of them out: 240 -> 220 (5120 x 13824, five steps) 29.1 -> 30.0, 256 -> 247 (36864 x 9216, 21 steps) a hundredth
+  // either way.
   const int64_t equal = (steps + cap - 1) / cap;
+  auto fewer = [&](int64_t full, int64_t joined) { return (int32_t)(equal <= 4 || 8 * (full - joined) >= full ? joined : full); };
   *grid = fewer(cap, (steps + equal - 1) / equal);
   int64_t sa = cap / n_rg;
   if (sa > g.nbp) sa = g.nbp;
