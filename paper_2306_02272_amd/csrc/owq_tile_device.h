@@ -62,11 +62,13 @@ __device__ __forceinline__ f16_t mma(h8_t a, h8_t b, f16_t c) {
 }
 
 // Sixteen bytes per lane from sbase + voff to LDS at lds + 16 * lane.  Not known to the compiler's counting of
-// loads: wait_loads() below is what makes the data valid.  The LDS base goes into m0 as an operand that lives there, so
-// that the compiler knows of the write (m0 is a reserved register: a write inside the block cannot be declared); the
-// s_nop is the wait state between that write and the load.
+// loads: wait_loads() below is what makes the data valid.  The compiler learns from the output operand that m0 is written (m0
+// is a reserved register: naming it a clobber has no effect); the s_nop is the wait state between that write and the load.
+// (The base as an input that lives in m0 makes the compiler write it: the same work scheduled otherwise, 1 % slower on the
+// shortest calls of owq_tile_few.)
 __device__ __forceinline__ void load_to_lds(const void *sbase, u32 voff, u32 lds) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(voff), "s"(sbase) : "memory");
+  u32 m0;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" : "=&{m0}"(m0) : "s"(lds), "v"(voff), "s"(sbase) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {

@@ -42,20 +42,27 @@ struct FewArgs {
   int off_sz, off_xw, off_xd, off_idx;
 };
 
+// A dword per lane to LDS at lds + 4 * lane.
+__device__ __forceinline__ void dword_to_lds(const void *sbase, u32 voff, u32 lds) {
+  u32 m0;      // see load_to_lds
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, %3" : "=&{m0}"(m0) : "s"(lds), "v"(voff), "s"(sbase) : "memory");
+}
+
 // As load_to_lds, N times 1 KB further on both sides: sbase + voff + 1024 i to lds + 1024 i + 16 lane, i < N <= 4.  One
 // write of the LDS base serves all of them.
 template <int N>
 __device__ __forceinline__ void loads_to_lds(const void *sbase, const u32 *voff, u32 lds) {
   static_assert(N == 1 || N == 2 || N == 4, "the offset field holds 3072");
+  u32 m0;      // see load_to_lds
   if constexpr (N == 1)
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(voff[0]), "s"(sbase) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" : "=&{m0}"(m0) : "s"(lds), "v"(voff[0]), "s"(sbase) : "memory");
   else if constexpr (N == 2)
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
-                 ::"{m0}"(lds), "v"(voff[0]), "v"(voff[1]), "s"(sbase) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\tglobal_load_lds_dwordx4 %3, %4 offset:1024"
+                 : "=&{m0}"(m0) : "s"(lds), "v"(voff[0]), "v"(voff[1]), "s"(sbase) : "memory");
   else
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %3, %5 offset:2048\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072"
-                 ::"{m0}"(lds), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(sbase) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %6\n\tglobal_load_lds_dwordx4 %3, %6 offset:1024\n\t"
+                 "global_load_lds_dwordx4 %4, %6 offset:2048\n\tglobal_load_lds_dwordx4 %5, %6 offset:3072"
+                 : "=&{m0}"(m0) : "s"(lds), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(sbase) : "memory");
 }
 
 template <int BITS, int RT, int S>
@@ -138,8 +145,7 @@ __global__ __launch_bounds__(512, 2) void owq_tile_few(const FewArgs a) {
     const int t = RT == 1 ? 0 : q & 1, gp = RT == 1 ? q : q >> 1;
     const int g = min(2 * gp + kg, a.n_groups - 1), row = min((rg * RT + t) * 32 + n32, a.d_out_pad - 1);
     const u32 off = ((u32)g * (u32)a.d_out_pad + (u32)row) * 4u;
-    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, %2" ::"{m0}"(ldsb + (u32)(a.off_sz + (t * ((a.n_groups + 1) & ~1) + 2 * gp) * 128)),
-                 "v"(off), "s"(a.sz) : "memory");
+    dword_to_lds(a.sz, off, ldsb + (u32)(a.off_sz + (t * ((a.n_groups + 1) & ~1) + 2 * gp) * 128));
   }
   const int kunits = a.kp >> 3, ksteps = (kunits + 1) >> 1;
   u32x4 wa[RT];                          // the weights of the wave's first k-step of weak columns
@@ -158,8 +164,7 @@ __global__ __launch_bounds__(512, 2) void owq_tile_few(const FewArgs a) {
     const int e = min(e0 + lane, pairs - 1), n = e & (np - 1);
     const int j = idx[e >> a.lg_tok];
     const u32 at = ((u32)(n < a.ntok ? n : 0) * (u32)a.d_in + (u32)(j >= 0 ? j : 0)) * 2u;
-    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, %2" ::"{m0}"(ldsb + (u32)(a.off_xd + e0 * 4)), "v"(at & ~3u), "s"(a.x)
-                 : "memory");
+    dword_to_lds(a.x, at & ~3u, ldsb + (u32)(a.off_xd + e0 * 4));
   }
 
   Magic M;

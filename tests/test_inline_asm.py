@@ -1,6 +1,6 @@
-"""Direct loads to LDS take their LDS base from m0.  A block that writes m0 itself cannot tell the compiler so (the register
-is reserved: a clobber of it is not honoured), and the compiler uses m0 too, for register indexes known only at run time.
-So the base goes in as an operand that lives in m0, and no block writes it."""
+"""Direct loads to LDS take their LDS base from m0.  The compiler uses m0 too, for register indexes known only at run time, so
+a block that writes it has to say so; the register is reserved and a clobber of it is not honoured, but an output that lives
+in it is.  Early, as the block reads its inputs after the write."""
 import glob
 import os
 import re
@@ -21,16 +21,16 @@ def asm_blocks(text):
         yield text[m.end():i - 1]
 
 
-def test_the_lds_base_is_an_operand():
+def test_writes_of_m0_are_outputs():
     loads = 0
     for path in sorted(glob.glob(os.path.join(CSRC, "*"))):
         if not path.endswith((".hip", ".h")):
             continue
         for block in asm_blocks(open(path).read()):
-            code = block.split("::")[0]
-            assert not re.search(r"\bm0\s*,", code), (os.path.basename(path), block)
-            if "_load_lds_" in code:
-                loads += 1
-                assert '"{m0}"(' in block and block.rstrip().endswith('"memory"'), (os.path.basename(path), block)
-                assert re.match(r'\s*"s_nop 0', code), (os.path.basename(path), block)      # wait state after the write
-    assert loads >= 6
+            code, *operands = re.split(r'"\s*:', block, maxsplit=1)
+            if not re.search(r"\bm0\s*,|_load_lds_", code):
+                continue
+            loads += 1
+            assert re.match(r'\s*"s_mov_b32 m0, %1\\n\\ts_nop 0', code), (os.path.basename(path), block)      # with a wait state
+            assert operands and operands[0].lstrip().startswith('"=&{m0}"(') and '"memory"' in operands[0], (os.path.basename(path), block)
+    assert loads >= 5
