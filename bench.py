@@ -10,8 +10,8 @@ that the weights really come from HBM.
 
 The workloads named search-* time the other entry point, owq_search_config (the configuration
 search that produces a layer's step sizes, zero points and codes from fp16 weights): a step is one
-call over the whole matrix, the bound is the vector units (fp32 operations against the published
-fp32 vector peak).
+call over the whole matrix, the bound is the vector units (instructions of the call, counted once by
+rocprofv3 and kept in profiles/instructions.json, against what the units issue).
 
 Prints ONE JSON line.  value = algorithmic bytes of a step / time of a step (GB/s);
 roofline.achieved = algorithmic bytes (or, on the tile layout, floating-point operations) per
@@ -86,7 +86,15 @@ def stored_traffic(workload):
         return None
 
 
-FP32_VECTOR_PEAK_TFLOPS = 157.3
+def stored_instructions(workload):
+    """Vector instructions per call (times 64 lanes) that rocprofv3's SQ_INSTS_VALU counted for this workload, or None."""
+    try:
+        return json.load(open(os.path.join(ROOT, "profiles", "instructions.json"))).get(workload)
+    except Exception:
+        return None
+
+
+FP32_VECTOR_PEAK_TIPS = 78.6      # T lane-instructions/s: 157.3 TFLOP/s of the data sheet at two operations per instruction
 SEARCH_WORKLOADS = {
     # name: (d_out, d_in, k, bits, group size, grid n_lo x n_hi, shrink, description)
     "search-opt6.7b-fc1": (16384, 4096, 32, 3, 128, 16, 16, 0.4,
@@ -96,7 +104,6 @@ SEARCH_WORKLOADS = {
                                "configuration search for an OPT-6.7B-like fc1 (16384 x 4096 fp16 weights, k=32 weak "
                                "columns left out), 3-bit, one scale per row, 16 x 16 grid of narrowed ranges"),
 }
-SEARCH_FLOP = 7          # per weight and grid point: multiply, round, clamp, two fused multiply-adds
 
 
 def bench_search(args) -> int:
@@ -157,9 +164,9 @@ def bench_search(args) -> int:
     wall_s, event_s = t1 - t0, ev0.elapsed_time(ev1) * 1e-3
     assert torch.isfinite(err).all() and int(codes.max()) <= (1 << bits) - 1
     weights = d_out * (d_in - k)
-    flops = SEARCH_FLOP * weights * n_lo * n_hi
     avg_launch_s = event_s / steps
-    tflops = flops / avg_launch_s / 1e12
+    instructions = stored_instructions(args.workload)
+    tips = None if instructions is None else instructions / avg_launch_s / 1e12
     result = {
         "metric": f"configuration search, G weights/s ({n_lo} x {n_hi} grid points each), {bits}-bit",
         "value": round(weights * steps / wall_s / 1e9, 3), "unit": "Gweights/s", "n_gpus": 1, "steps": steps,
@@ -167,16 +174,13 @@ def bench_search(args) -> int:
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": desc, "d_out": d_out, "d_in": d_in, "k": k, "group_size": gs, "grid": [n_lo, n_hi],
                    "shrink": shrink, "launch_mode": "eager"},
-        "roofline": {"bound": "alu", "achieved": round(tflops, 1), "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(tflops / FP32_VECTOR_PEAK_TFLOPS, 4), "traffic": stored_traffic(args.workload),
-                     "kernel": "owq_search_bounds",
-                     "note": "operations of a plain search that sums every weight at every grid point; most points are ruled "
-                             "out by bounds and not summed, so the rate may pass the peak",
-                     "avg_launch_us": round(avg_launch_s * 1e6, 1), "flops_per_launch": flops,
-                     "instructions_per_s": round(5 * weights * n_lo * n_hi / avg_launch_s / 1e12, 2),
-                     "achievable": {"kind": "register-only loop of the same five fp32 instructions (T lane-instructions/s), same run",
+        "roofline": {"bound": "alu", "achieved": None if tips is None else round(tips, 2), "peak": FP32_VECTOR_PEAK_TIPS,
+                     "unit": "T lane-instructions/s", "frac": None if tips is None else round(tips / FP32_VECTOR_PEAK_TIPS, 4),
+                     "traffic": stored_traffic(args.workload), "kernel": "owq_search_bounds",
+                     "avg_launch_us": round(avg_launch_s * 1e6, 1), "instructions_per_launch": instructions,
+                     "achievable": {"kind": "register-only loop of the five fp32 instructions that evaluate a weight, same run",
                                     "instructions_per_s": round(bare_tips, 2),
-                                    "frac_of_it": round(5 * weights * n_lo * n_hi / avg_launch_s / 1e12 / bare_tips, 4)}},
+                                    "frac_of_it": None if tips is None else round(tips / bare_tips, 4)}},
     }
     if not args.no_cpu_baseline:
         from oracle import search
@@ -528,13 +532,16 @@ def main() -> int:
     traffic = stored_traffic(args.workload)
     info = first[0].info()
     flops_per_step = sum(2 * batch * sp.d_out * (sp.d_in + sp.k) for sp in specs)
-    small = layout == 1 and batch <= 16 and not args.launch     # the one-launch kernel of the tile layout: bound by the weight stream
+    # the one-launch kernels of the tile layout: bound by the weight stream
+    small = layout == 1 and batch <= 32 and not args.launch and args.tasks == 0
+    wide = layout == 1 and batch > 64 and not args.launch and args.tasks == 0
     if layout == 1 and not small:
-        # three kernels per call; the matrix kernel dominates.  The figure charges the whole call to it.
+        # several kernels per call; the matrix kernel dominates.  The figure charges the whole call to it.
         tflops = flops_per_step / len(specs) / avg_launch_s / 1e12
         roofline = {"bound": "mfma", "achieved": round(tflops, 1), "peak": MFMA_F16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(tflops / MFMA_F16_PEAK_TFLOPS, 4), "traffic": traffic,
-                    "kernel": f"owq_tile_mma<{specs[0].bits},{2 if batch > 32 else 1}> (+ stage, finish)",
+                    "kernel": (f"owq_wide_mma<{specs[0].bits}> (+ prep, sum)" if wide
+                               else f"owq_tile_mma<{specs[0].bits},{2 if batch > 32 else 1}> (+ stage, finish)"),
                     "avg_launch_us": round(avg_launch_s * 1e6, 3),
                     "flops_per_launch": flops_per_step // len(specs),
                     "hbm_gbs": round(achieved, 1), "hbm_frac": round(achieved / HBM_PEAK_GBS, 4),
@@ -552,7 +559,8 @@ def main() -> int:
     else:
         roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                    "kernel": (f"owq_tile_small<{specs[0].bits}> (+ owq_tile_small_sum)" if small
+                    "kernel": (f"owq_tile_few<{specs[0].bits}> (owq_tile_small<{specs[0].bits}> + sum, or the three launches, "
+                               "where the library expects them to be faster)" if small
                                else f"owq_gemv_kernel<{specs[0].bits},{info.prefetch_depth}>"),
                     "avg_launch_us": round(avg_launch_s * 1e6, 3),
                     "bytes_per_launch": step_bytes // len(specs)}

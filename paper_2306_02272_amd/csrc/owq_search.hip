@@ -14,9 +14,9 @@
 // on groups of 128, one or two on long rows.  These evaluations take the same binary32 decisions per weight as the
 // plain search and share their sums among the lanes; points whose sums come out too close to tell are summed again in
 // the order of the columns, so that the choice is that of the plain search.
-// 16384 x 4096, 3-bit, groups of 128, 16 x 16 points: 1780 -> 620 us (bound by vector instructions, about 950 per group
-// of which the plain search spent 2900); 5120 x 5120, 4-bit, one scale per row: 717 -> 137 us (of which 30 are the few
-// rows with points to tell apart).
+// 16384 x 4096, 3-bit, groups of 128, 16 x 16 points: 1780 -> 620 us (bound by vector instructions, 815 per group by the
+// counter where the plain search spent 3000); 5120 x 5120, 4-bit, one scale per row: 717 -> 127-138 us from box to box (of
+// which 30 are the few rows with points to tell apart).
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -7,8 +7,9 @@
 // four waves owns 256 rows x 64 tokens and walks along the columns in blocks of 128; two workgroups share a compute
 // unit and are not in step, so one's matrix instructions run under the other's vector instructions and waits:
 //
-//   x       goes from memory straight into LDS (16-byte direct loads, two buffers, one block ahead), in
-//           rows of 256 bytes whose 16-byte units are exchanged by the low bits of the token, so that
+//   x       goes from memory straight into LDS (16-byte direct loads, two buffers, asked for one block ahead; in layers
+//           with groups the wait for the block's scales, which counts only the loads the compiler knows of, waits for
+//           the next block's x as well, and only the other workgroup of the compute unit covers that), in rows of 256 bytes whose 16-byte units are exchanged by the low bits of the token, so that
 //           operand reads are free of bank conflicts; the weak columns of a block are then overwritten
 //           with zeros by the wave that fetched them (the dense term must not see them, whatever they hold);
 //   codes   go from registers into the A operand: a pair is masked out of a dword and OR-ed into the
@@ -26,9 +27,10 @@
 // in a fixed order.  No atomics: results are reproducible.
 //
 // What bounds it: beside its 32 matrix instructions a wave issues about 145 instructions of unpacking and 64 of scaling
-// per block.  4096 -> 16384 -> 4096, 3-bit, groups of 128, 2048 tokens: 2000 us in passes, 580-600 us here (920-950
-// TFLOP/s; a large fp16 library product reaches 1200 on the same card).  One workgroup of eight waves on 256 x 128 tokens
-// per compute unit took 636, weak masks by a scalar load per block instead of with the codes 612.
+// per block (by the counter 280 vector instructions in all).  4096 -> 16384 -> 4096, 3-bit, groups of 128, 2048 tokens: 2000 us in passes, 600-625 us here from box to box
+// (915-880 TFLOP/s; a large fp16 library product reaches 1200 on the same card), the matrix cores busy 46 % of the cycles.
+// On a box where this took 580, one workgroup of eight waves on 256 x 128 tokens per compute unit took 636, weak masks by a
+// scalar load per block instead of with the codes 612.
 #include <hip/hip_runtime.h>
 
 #include "owq_internal.h"
@@ -497,8 +499,10 @@ WidePlan wide_plan(int tiles, int nbp, int64_t slots) {
   for (int s = 1; s <= 32 && s * 2 <= nbp + 1; ++s) {
     const int n = tiles * s, left = n % 512, pairs = (nbp + s - 1) / s;
     if (s > 1 && n > slots) break;
-    // Two workgroups per compute unit: a pair of blocks takes them kPair2 us, one alone kPair1.  4096 x 16384 at 2048 tokens:
-    // four rounds of 16 pairs in 310 us.  A split adds the sum's launch and the traffic of a partial result.
+    // Two workgroups per compute unit: what a pair of blocks weighs with two of them (kPair2) and with one alone (kPair1),
+    // against a split's launch of the sum and the traffic of a partial result.  These are not the times of this kernel
+    // (4.8 us per pair: 4096 x 16384 at 2048 tokens, four rounds of 16 pairs in 310 us), so columns are split, and token tiles
+    // divided, less often than those would have it.
     constexpr float kPair1 = 1.5f, kPair2 = 2.0f;
     const float us = (n / 512) * (pairs * kPair2 + 4.f) + (left == 0 ? 0.f : pairs * (left > 256 ? kPair2 : kPair1) + 4.f) +
                      (s > 1 ? 4.f + 0.03f * n : 0.f);
