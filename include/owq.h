@@ -280,8 +280,8 @@ owq_status_t owq_export_packed(owq_handle_t h, void *host_buf, size_t bytes);
  *     sequence is cut into P equal ranges.  Both 0: the default for the chosen waves_per_wg.
  *     The number of workgroups is limited by the partial-result slots of the scratch area.
  *     These three shape the three-launch path.  If any of them is given, that path takes every pass of more than 16
- *     tokens, and batches above 64 tokens run as passes of 64; with all three 0 it takes calls of 33 to 64 tokens
- *     and the passes of owq_linear_multi, and the library's other kernels take the rest.
+ *     tokens, and batches above 64 tokens run as passes of 64; with all three 0 it takes calls of 33 to 64 tokens,
+ *     the passes of owq_linear_multi, and what the library's kernels for fewer and for more tokens do not take.
  *     prefetch_depth chooses the one-launch kernels for few tokens: 0 = the library chooses (for passes of 16 tokens or
  *     fewer where the three launches are shaped as above, else of 32 or fewer); -1 = never use one of them;
  *     S + 100 c with S in [0, 99], c in [0, 3], not 0 = use the kernel that spreads columns over workgroups for every

@@ -37,7 +37,7 @@ constexpr int kLaunchPasses = 4;     // passes (of 128 tokens) that one set of l
 constexpr int kMorePasses = 16;      // up to so many where they do not fill the chip and their staged dy stays within
 constexpr size_t kMoreBytes = 64u << 20;
 // Fewer staging blocks of four token tiles than this do not fill the chip and take one tile each (2048 -> 640 at 200
-// tokens, 22 blocks: about 1 us of 4.4; 4096 -> 16384 at 512, 1028 blocks: 11.1 us in blocks of one, 10.0 of four).
+// tokens, 22 blocks: 4.4 -> 3.3 us; 4096 -> 16384 at 512, 1028 blocks: 11.1 us in blocks of one, 10.0 of four).
 constexpr int kStageBlocks = 512;
 constexpr size_t kScanBytes = 2048;  // end of the workspace: the magnitude scan's 256 words, then the exponent
 
