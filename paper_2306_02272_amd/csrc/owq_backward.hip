@@ -717,7 +717,8 @@ struct BwdPlan {
   size_t a_st_bytes, part_bytes, wst_bytes, pw_bytes, xw_bytes, total;
 };
 
-BwdPlan plan(const owq_layer_info_t &g, int batch) {
+// passes > 0: that many per set of launches
+BwdPlan plan(const owq_layer_info_t &g, int batch, int passes = 0) {
   BwdPlan p;
   const int all_passes = (batch + kPassTokens - 1) / kPassTokens;
   // Every set of launches costs the small kernels of its own (staging, weak columns, sum; 20 us and more where the product
@@ -727,7 +728,7 @@ BwdPlan plan(const owq_layer_info_t &g, int batch) {
   int most = 256 / g.nbp < kMorePasses ? 256 / g.nbp : kMorePasses;
   if (most * pass_bytes > kMoreBytes) most = (int)(kMoreBytes / pass_bytes);
   if (most < kLaunchPasses) most = kLaunchPasses;
-  p.passes = all_passes < most ? (all_passes < 1 ? 1 : all_passes) : most;
+  p.passes = passes > 0 ? passes : all_passes < most ? (all_passes < 1 ? 1 : all_passes) : most;
   // Ranges of rows per block pair.  A compute unit holds one workgroup at a time, so the product takes rounds of 256
   // workgroups, each as long as its row tiles (0.7 us) and a fixed part; every range costs the sum kernel a read of its
   // partial results.  In us, fitted to measurements on MI355X.
@@ -776,7 +777,14 @@ extern "C" owq_status_t owq_backward_workspace_bytes(owq_handle_t h, int32_t bat
   if (h->info.layout != OWQ_LAYOUT_TILE) return OWQ_ERR_LAYOUT;
   if (!bytes) return OWQ_ERR_NULL;
   if (batch < 0 || batch > OWQ_MAX_BATCH) return OWQ_ERR_BATCH;
-  *bytes = plan(h->info, batch).total;
+  // A plan of more passes may need less than one of fewer (fewer ranges of rows).  From four passes on the answer covers
+  // those in between, so that a workspace for a large batch serves smaller ones too.
+  const BwdPlan p = plan(h->info, batch);
+  *bytes = p.total;
+  for (int n = kLaunchPasses; n < p.passes; ++n) {
+    const size_t need = plan(h->info, batch, n).total;
+    if (need > *bytes) *bytes = need;
+  }
   return OWQ_OK;
 }
 

@@ -46,3 +46,15 @@ def test_cuts(env, d_in, d_out, bits, group, k, tokens):
     again, _ = lin.backward(torch.from_numpy(dy).cuda(), torch.from_numpy(x).cuda())
     np.testing.assert_array_equal(dx.cpu().numpy().view(np.uint16), again.cpu().numpy().view(np.uint16))
     lin.close()
+
+
+@pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (1664, 768), (5120, 5120), (2048, 2048), (768, 7040), (16384, 512), (1024, 30000)])
+def test_a_workspace_serves_smaller_batches(env, d_in, d_out):
+    # from four passes of 128 tokens on, as a caller that asks once for its largest batch has it
+    torch, B = env
+    desc = B.make_desc(d_out, d_in, 4, 128, d_in // 100, layout=1)
+    buf = torch.empty(B.owq_packed_bytes(desc), dtype=torch.uint8, device="cuda")
+    handle = B.owq_open_packed(desc, buf.data_ptr(), buf.numel())
+    sizes = [B.owq_backward_workspace_bytes(handle, b) for b in range(385, 2600, 43)]
+    B.owq_free_layer(handle)
+    assert sizes == sorted(sizes)
