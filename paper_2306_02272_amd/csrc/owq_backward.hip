@@ -710,7 +710,7 @@ __global__ __launch_bounds__(256) void owq_bwd_small(const DwwArgs da, const Wea
 }
 
 struct BwdPlan {
-  int passes;                    // passes per set of launches
+  int passes, most;              // passes per set of launches; the most that this batch or a smaller one takes
   int split, rt_per_split, wsplit, kp32;
   bool weak_staged;              // weak columns staged in operand order: at most an eighth of the columns
   int x_steps;                   // steps of 16 tokens of the whole batch
@@ -723,12 +723,16 @@ BwdPlan plan(const owq_layer_info_t &g, int batch, int passes = 0) {
   const int all_passes = (batch + kPassTokens - 1) / kPassTokens;
   // Every set of launches costs the small kernels of its own (staging, weak columns, sum; 20 us and more where the product
   // takes 15), so layers whose block pairs leave compute units free take more passes at once: 1664 -> 768 at 1017 tokens
-  // 58 -> 38 us.  The product's partial results do not grow: more passes, fewer ranges of rows.
+  // 58 -> 38 us.  The product's partial results do not grow: more passes, fewer ranges of rows.  Where one set does not hold
+  // them all, equal sets of more than six (10752 x 6144, 13 passes as 7 + 6: 472 -> 358 us), else four as on large layers: a short
+  // last set has the others' ranges of rows and leaves the chip idle (9856 -> 6400, eight passes as 6 + 2: 255 -> 287).
   const size_t pass_bytes = (size_t)(g.n_rt + 1) * 8192;
   int most = 256 / g.nbp < kMorePasses ? 256 / g.nbp : kMorePasses;
   if (most * pass_bytes > kMoreBytes) most = (int)(kMoreBytes / pass_bytes);
   if (most < kLaunchPasses) most = kLaunchPasses;
-  p.passes = passes > 0 ? passes : all_passes < most ? (all_passes < 1 ? 1 : all_passes) : most;
+  const int sets = (all_passes + most - 1) / most, equal = sets > 1 ? (all_passes + sets - 1) / sets : all_passes;
+  p.most = all_passes < most ? all_passes : most;
+  p.passes = passes > 0 ? passes : sets > 1 && equal <= 6 ? kLaunchPasses : equal < 1 ? 1 : equal;
   // Ranges of rows per block pair.  A compute unit holds one workgroup at a time, so the product takes rounds of 256
   // workgroups, each as long as its row tiles (0.7 us) and a fixed part; every range costs the sum kernel a read of its
   // partial results.  In us, fitted to measurements on MI355X.
@@ -778,10 +782,10 @@ extern "C" owq_status_t owq_backward_workspace_bytes(owq_handle_t h, int32_t bat
   if (!bytes) return OWQ_ERR_NULL;
   if (batch < 0 || batch > OWQ_MAX_BATCH) return OWQ_ERR_BATCH;
   // A plan of more passes may need less than one of fewer (fewer ranges of rows).  From four passes on the answer covers
-  // those in between, so that a workspace for a large batch serves smaller ones too.
+  // those of smaller batches, so that a workspace for a large batch serves them too.
   const BwdPlan p = plan(h->info, batch);
   *bytes = p.total;
-  for (int n = kLaunchPasses; n < p.passes; ++n) {
+  for (int n = kLaunchPasses; n <= p.most; ++n) {
     const size_t need = plan(h->info, batch, n).total;
     if (need > *bytes) *bytes = need;
   }

@@ -26,7 +26,7 @@ def env():
     (256, 16 * 32, 3, 0, 4, 20), (256, 33 * 32, 4, 128, 4, 20), (256, 47 * 32, 3, 128, 4, 20), (256, 64 * 32 - 7, 4, 0, 4, 20),
     (200, 80 * 32, 3, 128, 4, 20), (256, 95 * 32, 4, 128, 4, 20), (256, 110 * 32 + 1, 3, 0, 4, 20), (256, 128 * 32, 4, 128, 4, 20),
     (256, 141 * 32, 3, 128, 4, 20),
-    (512, 96, 4, 128, 5, 700), (300, 200, 3, 0, 9, 2300),          # six passes in one set; sixteen and then two
+    (512, 96, 4, 128, 5, 700), (300, 200, 3, 0, 9, 2300),          # six passes in one set; nine, twice
     (128, 33000, 4, 0, 3, 140), (128, 66000, 3, 0, 2, 800),        # staging blocks of four token tiles; sets of four passes
 ])
 def test_cuts(env, d_in, d_out, bits, group, k, tokens):
