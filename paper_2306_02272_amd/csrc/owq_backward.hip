@@ -36,9 +36,10 @@ constexpr int kWeakSplit = 32;       // ranges of rows of the product with the w
 constexpr int kLaunchPasses = 4;     // passes (of 128 tokens) that one set of launches takes, or
 constexpr int kMorePasses = 16;      // up to so many where they do not fill the chip and their staged dy stays within
 constexpr size_t kMoreBytes = 64u << 20;
-// Fewer staging blocks of four token tiles than this do not fill the chip and take one tile each (2048 -> 640 at 200
-// tokens, 22 blocks: 4.4 -> 3.3 us; 4096 -> 16384 at 512, 1028 blocks: 11.1 us in blocks of one, 10.0 of four).
-constexpr int kStageBlocks = 512;
+// Fewer staging blocks of four token tiles than this do not fill the chip and take one tile each: 2048 -> 640 at 200 tokens, 22
+// blocks, 4.4 -> 3.3 us; 4096 -> 4096 at 512, 260 blocks, 6.0 -> 5.6; but 7680 -> 10368 at 354, 489 blocks, 6.6 -> 8.0, and with rows
+// of dy off the 8-byte grid 12032 -> 11155 at 65, 175 blocks, 5.1 -> 6.0.
+constexpr int kStageBlocks = 320, kStageBlocksOff = 160;
 constexpr size_t kScanBytes = 2048;  // end of the workspace: the magnitude scan's 256 words, then the exponent
 
 // N 2-byte loads whose results get a use of their own after all of them have been issued, so
@@ -833,7 +834,7 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
     sa.x = {static_cast<const _Float16 *>(x), reinterpret_cast<const int *>(blob + g.off_weak_idx), xw_st,
             g.d_in, g.k, p.kp32, batch, p.x_steps};
     const int wide_blocks = ((g.n_rt + 2) / 2) * passes;
-    sa.narrow = wide_blocks < kStageBlocks ? 1 : 0;
+    sa.narrow = wide_blocks < ((g.d_out & 3) == 0 ? kStageBlocks : kStageBlocksOff) ? 1 : 0;
     sa.dy_blocks = dx ? (unsigned)(sa.narrow ? 4 * wide_blocks : wide_blocks) : 0u;
     sa.weak_blocks = dx && n0 == 0 && p.weak_staged ? (unsigned)(((long long)g.n_rt * 2 * p.kp32 * 64 + 255) / 256) : 0u;
     const unsigned x_blocks = want_dww && n0 == 0 ? (unsigned)(((long long)p.x_steps * p.kp32 * 64 + 255) / 256) : 0u;
