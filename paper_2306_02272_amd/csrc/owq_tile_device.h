@@ -100,4 +100,45 @@ __device__ __forceinline__ h8_t a_exact(const u32 *wd, const Magic &M, const u32
   return __builtin_bit_cast(h8_t, v);
 }
 
+// Pair I of k-step S, masked, at the offset pair_offset() of its 16-bit window.
+template <int BITS, int S, int I>
+__device__ __forceinline__ u32 a_field(const u32 *wd) {
+  if (BITS == 3) {
+    constexpr int u = S >> 2, o = S & 3;
+    const u32 d0 = wd[3 * u], d1 = wd[3 * u + 1], d2 = wd[3 * u + 2];
+    if (o == 0) return I == 3 ? __builtin_amdgcn_perm(d1, d0, 0x06030401u) & field(3, 1) : d0 & field(3, 3 * I);
+    if (o == 1) return I < 2 ? __builtin_amdgcn_perm(d1, d0, 0x06030401u) & field(3, 4 + 3 * I) : d1 & field(3, 2 + 3 * (I - 2));
+    if (o == 2) return I == 3 ? d2 & field(3, 1) : __builtin_amdgcn_perm(d2, d1, 0x06030401u) & field(3, 3 * I);
+    return (I < 2 ? d2 : d2 >> 6) & field(3, 4 + 3 * (I & 1));
+  }
+  return (I < 2 ? wd[S] : wd[S] >> 6) & field(4, I < 2 ? 4 * I : 2 + 4 * (I - 2));
+}
+
+// Pair I of (q - z) 2^-9 of k-step S (0..7) of a block, nz = -z 2^-9 in both halves, z an integer of at most 1024.  A masked
+// pair read as fp16 is the subnormal q 2^(o-24), and one packed multiply-add by 2^(15-o) moves it and takes the zero point
+// off, exactly.  As many instructions as mask-and-OR and an add, but one constant per row instead of one per offset.
+template <int BITS, int S, int I>
+__device__ __forceinline__ u32 a_small_pair(const u32 *wd, u32 nz) {
+  constexpr int o = pair_offset(BITS, S, I);
+  const _Float16 m = __builtin_bit_cast(_Float16, (unsigned short)((30 - o) << 10));      // 2^(15-o)
+  return __builtin_bit_cast(u32, __builtin_elementwise_fma(__builtin_bit_cast(h2_t, a_field<BITS, S, I>(wd)), (h2_t){m, m},
+                                                          __builtin_bit_cast(h2_t, nz)));
+}
+template <int BITS, int S>
+__device__ __forceinline__ h8_t a_small(const u32 *wd, u32 nz) {
+  return __builtin_bit_cast(h8_t, (u32x4){a_small_pair<BITS, S, 0>(wd, nz), a_small_pair<BITS, S, 1>(wd, nz),
+                                          a_small_pair<BITS, S, 2>(wd, nz), a_small_pair<BITS, S, 3>(wd, nz)});
+}
+
+// Eight rows of y, or the `left` that there are, from LDS to any element of memory (rows of y need no alignment; an element at a
+// time costs the kernels for prompts up to a third on layers whose rows are no multiple of eight).
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+__device__ __forceinline__ void store_rows(_Float16 *to, const _Float16 *from, int left) {
+  if (left >= 8) {
+    *reinterpret_cast<u32x4_any *>(to) = *reinterpret_cast<const u32x4 *>(from);
+  } else {
+    for (int q = 0; q < left; ++q) to[q] = from[q];
+  }
+}
+
 }  // namespace owq
