@@ -14,9 +14,11 @@
 //   codes   go from registers into the A operand (q - z) 2^-9, exactly (a_small);
 //   groups  the accumulators hold the sums in units of the block's step size: before a block of another group they are
 //           multiplied by (last step size / next), in fp32, and by the last one at the end.  With a second set of tiles that
-//           takes the scaled blocks (as many vector instructions, 64 registers more) 128 tokens do not fit the registers;
+//           takes the scaled blocks (as many vector instructions, 64 registers more) 128 tokens do not fit the registers.
+//           What a ratio's rounding leaves goes into the next ratio, so all of them together are off by no more than one;
+//           the rounding to y then takes the result as the multiplications leave it, good to 19 bits (settled);
 //   weak    the fp16 weak columns are one more K range at the end, operands of both sides from LDS.
-// Row groups with a zero point that is no integer of at most 1024, or with a step size of zero or none that is finite, take
+// Row groups with a zero point that is no integer of at most 1024 (groups: 240), or with a step size of zero or none that is finite, take
 // wide_columns instead (found by the prep kernel): second set of tiles, rests of the zero points by a second set of matrix
 // instructions with the constant operand rint(z) - z, 64 tokens at a time.
 //
@@ -50,6 +52,9 @@ static_assert(2 * kWideBufUnits + kWideWaves * kWideWeakUnits <= 4 * kWideBufUni
 static_assert(kWideTokens * kWideOutPitch * 2 <= wide_planes(2), "64 tokens of the result are transposed in the staging buffers");
 constexpr int kWideSlotUnits = kWideWaves * 16 * 64;   // 16-byte units of a partial result (256 rows x 64 tokens, fp32)
 
+// |q - z| that wide_fast takes: what fp16 holds exactly; in groups, what is 19 bits times a step size (settled)
+constexpr float kZeroLimit = 1024.f, kZeroLimitGroups = 240.f;
+
 constexpr int kFlagGroups = 16;          // groups of a row group that one workgroup of the prep kernel looks through
 
 struct PrepArgs {
@@ -60,9 +65,10 @@ struct PrepArgs {
   _Float16 *xw;          // [ntok][xwpitch], zero beyond kp
   _Float16 *xcopy;       // [ntok][pitch], or nullptr
   int n_rg, n_fl, n_groups, d_out, d_out_pad, d_in, ntok, kp, xwpitch, pitch;
+  float zero_limit;      // largest zero point that wide_fast takes
 };
 
-// The first n_rg x n_fl workgroups: does a row group hold a zero point that is no integer of at most 1024, or a step
+// The first n_rg x n_fl workgroups: does a row group hold a zero point that is no integer of at most zero_limit, or a step
 // size that is zero or no finite number?  The
 // others take four tokens each, a wave per token: the gather of x at the weak columns and, for rows that are no
 // multiple of 16 bytes, a copy of x that is.  Latency is what it costs (a chain of two loads per element), so every
@@ -84,7 +90,7 @@ __global__ __launch_bounds__(256) void owq_wide_prep(const PrepArgs a) {
       const u32 v = a.sz[(size_t)g * a.d_out_pad + row];
       const float z = half_hi(v), sc = __builtin_fabsf(half_lo(v));
       // (no short cuts: the compiler would wait for each load in a branch of its own)
-      bad |= !((int)(__builtin_fabsf(z) <= 1024.f) & (int)(z == __builtin_rintf(z)) & (int)(sc > 0.f) & (int)(sc < INFINITY));
+      bad |= !((int)(__builtin_fabsf(z) <= a.zero_limit) & (int)(z == __builtin_rintf(z)) & (int)(sc > 0.f) & (int)(sc < INFINITY));
     }
     if (bad) any = 1;
     __syncthreads();
@@ -301,15 +307,18 @@ __device__ __forceinline__ void wide_fast(const WideArgs &a, unsigned char *lds,
   };
 
   u32 nz[2];              // -z 2^-9 of the lane's two rows
-  float last;             // step size of the lane's row in the blocks so far: what the accumulators are in units of
+  float last;             // step size of the lane's row in the blocks so far: what the accumulators are in units of,
+  float over = 0.f;       // and what the ratios' roundings have left of it
   auto take_sz = [&](u32 v, bool first) __attribute__((always_inline)) {
     const float s = half_lo(v);
     if (GROUPED) {
-      // last / s, to the last bit or the one before it
+      // (last + over) / s, and what its rounding leaves, in units of s
       float rc = __builtin_amdgcn_rcpf(s);
       rc = __builtin_fmaf(__builtin_fmaf(-s, rc, 1.f), rc, rc);
-      const float r = last * rc;
-      splane[lane] = first ? 1.f : __builtin_fmaf(__builtin_fmaf(-r, s, last), rc, r);
+      float r = last * rc;
+      r = __builtin_fmaf(__builtin_fmaf(-r, s, last) + over, rc, r);
+      over = first ? 0.f : (__builtin_fmaf(-r, s, last) + over) * __builtin_amdgcn_rcpf(r);
+      splane[lane] = first ? 1.f : r;
     }
     last = s;
     zplane[lane] = half_hi(v) * -0x1p-9f;
@@ -562,9 +571,18 @@ __device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *l
   __syncthreads();
 }
 
+// A result of wide_fast in groups as the rounding to fp16 takes it: to 19 bits.  One column by itself gives s (q - z) x, 19 bits at
+// most where x is a power of two, which often lies on a tie of fp16; the multiplications by the ratios leave some units of 2^-24
+// there, which would break the tie either way.  To a sum that is not short it adds 2^-19 under fp16's own 2^-11.
+__device__ __forceinline__ float settled(float v) {
+  const u32 u = __builtin_bit_cast(u32, v), r = (u + 16u) & ~31u;
+  return __builtin_bit_cast(float, (u & 0x7f800000u) == 0x7f800000u ? u : r);
+}
+
 // What follows the columns: the weak columns of the first column range, then y or a partial result.  NT token tiles from
 // token n0 on, tot in the order of wide_fast; every wave of the workgroup is past its reads of the staging buffers.
-template <int NT>
+// SETTLE: they come from ratios (settled).
+template <int NT, bool SETTLE>
 __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *lds, int tid, int rg, int n0, int s, f16_t *tot) {
   constexpr int kBuf = NT * 512;
   const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 5;
@@ -635,7 +653,9 @@ __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *ld
       const f16_t &v = tot[(i >> 1) * NT + 2 * half + (i & 1)];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const h4_t hv = {(_Float16)v[4 * q], (_Float16)v[4 * q + 1], (_Float16)v[4 * q + 2], (_Float16)v[4 * q + 3]};
+        h4_t hv;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) hv[e] = (_Float16)(SETTLE ? settled(v[4 * q + e]) : v[4 * q + e]);
         *reinterpret_cast<h4_t *>(out + ((i & 1) * 32 + (lane & 31)) * kWideOutPitch + w * 64 + (i >> 1) * 32 + 8 * q + 4 * kg) = hv;
       }
     }
@@ -668,7 +688,7 @@ __global__ __launch_bounds__(256, 2) void owq_wide_mma(const WideArgs a) {
   if (general == 0) {
     f16_t acc[2 * NT];
     wide_fast<BITS, GROUPED, NT>(a, lds, rg, n0, p0, p1, acc);
-    wide_finish<NT>(a, lds, (int)threadIdx.x, rg, n0, s, acc);
+    wide_finish<NT, GROUPED>(a, lds, (int)threadIdx.x, rg, n0, s, acc);
     return;
   }
   for (int half = 0; half < NT / 2 && n0 < a.ntok; ++half, n0 += kWideTokens) {
@@ -677,13 +697,15 @@ __global__ __launch_bounds__(256, 2) void owq_wide_mma(const WideArgs a) {
     asm volatile("" : "+v"(tid));           // what is made from it is made again for each half: kept over the loop it does not fit the registers
     if (half > 0) __syncthreads();          // the previous half's result has been read from where the next blocks go
     wide_columns<BITS, GROUPED, true, wide_planes(NT)>(a, lds, tid, rg, n0, p0, p1, tot);
-    wide_finish<2>(a, lds, tid, rg, n0, s, tot);
+    wide_finish<2, false>(a, lds, tid, rg, n0, s, tot);
   }
 }
 
 // Adds the partial results of a tile in a fixed order: one workgroup per 64 rows x 64 tokens (what one wave of
 // owq_wide_mma wrote), a wave per accumulator tile.
-__global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 *y, int n_tt, int split, int ntok, int d_out) {
+// flags: those of owq_wide_prep where the accumulators were in units of step sizes, or nullptr.
+__global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 *y, const int *flags, int n_fl, int n_tt, int split, int ntok,
+                                                    int d_out) {
   __shared__ __align__(16) _Float16 out[64][72];
   const int tid = threadIdx.x, lane = tid & 63, i = tid >> 6;
   const int w = blockIdx.x & 3, tile = blockIdx.x >> 2, rg = tile / n_tt, tt = tile - rg * n_tt;
@@ -698,10 +720,12 @@ __global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 
 #pragma unroll
     for (int q = 0; q < 4; ++q) sum[q] += src[(size_t)s * kWideSlotUnits + q * 64];
   const int n = (i & 1) * 32 + (lane & 31), r = (i >> 1) * 32 + 4 * (lane >> 5);
+  int general = flags == nullptr;
+  for (int f = 0; f < n_fl && flags != nullptr; ++f) general |= flags[rg * n_fl + f];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) out[n][r + 8 * q + e] = (_Float16)sum[q][e];
+    for (int e = 0; e < 4; ++e) out[n][r + 8 * q + e] = (_Float16)(general ? sum[q][e] : settled(sum[q][e]));
   __syncthreads();
   const int nn = min(64, ntok - n0);
   for (int e = tid; e < nn * 8; e += 256) {
@@ -790,6 +814,7 @@ int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint6
     pa.xcopy = copy ? reinterpret_cast<_Float16 *>(scr + flag_bytes + xw_bytes) : nullptr;
     pa.n_rg = n_rg; pa.n_fl = n_fl; pa.n_groups = g.n_groups; pa.d_out = g.d_out; pa.d_out_pad = g.d_out_pad; pa.d_in = g.d_in;
     pa.ntok = pass; pa.kp = g.kp; pa.xwpitch = xwpitch; pa.pitch = pitch;
+    pa.zero_limit = g.n_groups > 1 ? kZeroLimitGroups : kZeroLimit;
     const int gather = xwpitch > 0 || copy ? (pass + 3) / 4 : 0;
     WideArgs wa;
     wa.codes = reinterpret_cast<const u32x4 *>(base + g.off_codes);
@@ -828,8 +853,8 @@ int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint6
       hipLaunchKernelGGL(pick_wide(g.bits, grouped, plan.nt), dim3((unsigned)(n_rg * n_wt * wa.split)), dim3(256),
                          wide_lds(plan.nt), st, wa);
       if (wa.split > 1)
-        hipLaunchKernelGGL(owq_wide_sum, dim3((unsigned)(n_rg * wa.n_tt * 4)), dim3(256), 0, st, (const f4_t *)wa.slots, wa.y, wa.n_tt,
-                           wa.split, wa.ntok, g.d_out);
+        hipLaunchKernelGGL(owq_wide_sum, dim3((unsigned)(n_rg * wa.n_tt * 4)), dim3(256), 0, st, (const f4_t *)wa.slots, wa.y,
+                           grouped ? pa.flags : (const int *)nullptr, n_fl, wa.n_tt, wa.split, wa.ntok, g.d_out);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

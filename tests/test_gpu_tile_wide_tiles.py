@@ -76,3 +76,22 @@ def test_step_sizes_of_neighbouring_groups_of_any_size(env, d_in, d_out, bits, k
     layer.scale[:] = s.astype(np.float16)
     print(d_in, d_out, tokens, flush=True)
     compare(env, layer, make_x(layer, tokens), (d_in, d_out, tokens))
+
+
+@pytest.mark.parametrize("bits,k,d_out,tokens", [(3, 1500, 300, 512), (4, 30, 8192, 1100)])
+def test_one_column_by_itself_is_exact(env, bits, k, d_out, tokens):
+    # x = a column of the identity in 24 groups: s (q - z) has 15 bits at most, so often a tie of fp16. 23 ratios, each
+    # multiplication off by half a unit of the last place and all ratios together by one or two, leave less than the
+    # 16 units within which the result is settled.
+    torch, B = env
+    layer = make_layer(LayerSpec("columns", 3072, d_out, bits, 128, k, 23))
+    cols = np.random.default_rng(9).integers(0, 3072, tokens)
+    x = np.zeros((tokens, 3072), np.float16)
+    x[np.arange(tokens), cols] = 1
+    lin = B.OwqLinear(layer, layout=1)
+    got = lin(torch.from_numpy(x).cuda()).cpu().numpy()
+    lin.close()
+    pick = np.random.default_rng(2).integers(0, d_out, 200)
+    want = owq_ref.to_fp16(owq_ref.owq_linear_ref(layer.codes[pick], layer.scale[pick], layer.zero[pick], layer.group_size,
+                                                  layer.weak_idx, layer.weak_w[pick], x))
+    np.testing.assert_array_equal(got[:, pick].view(np.uint16), want.view(np.uint16))
