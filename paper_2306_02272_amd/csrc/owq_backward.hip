@@ -8,11 +8,10 @@
 // The dense part contracts over the rows i, while a lane of a packed tile holds eight
 // consecutive COLUMNS of one row, which is what the forward product wants as a matrix-core
 // operand and the wrong way round here.  The codes are therefore sent through the matrix core
-// twice.  First as the A operand against a selection matrix (ones on a diagonal): the result is
-// the same 32 x 32 block of q - z, but in the accumulator layout, where a lane holds one column
-// and sixteen rows.  Converted to fp16 (small integers, exact) they are the B operand of the real
-// product, whose A operand is dy times the step size, staged in operand order.  No LDS and no
-// shuffles are needed for the turn.
+// twice.  First as the A operand s (q - z), rounded to fp16 once, against a selection matrix (ones on a diagonal): the
+// result is the same 32 x 32 block, but in the accumulator layout, where a lane holds one column and sixteen rows.
+// Converted back to fp16 (exact) it is the B operand of the real product, whose A operand is dy, staged in operand
+// order.  No LDS and no shuffles are needed for the turn.
 //
 // Per group of passes of 128 tokens (four, or up to sixteen of a small layer): staging (dy into operand order, on the first group also the weak
 // columns and the activations at the weak columns); the small products (dww of the whole batch on the first group,
@@ -40,7 +39,6 @@ constexpr size_t kMoreBytes = 64u << 20;
 // blocks, 4.4 -> 3.3 us; 4096 -> 4096 at 512, 260 blocks, 6.0 -> 5.6; but 7680 -> 10368 at 354, 489 blocks, 6.6 -> 8.0, and with rows
 // of dy off the 8-byte grid 12032 -> 11155 at 65, 175 blocks, 5.1 -> 6.0.
 constexpr int kStageBlocks = 320, kStageBlocksOff = 160;
-constexpr size_t kScanBytes = 2048;  // end of the workspace: the magnitude scan's 256 words, then the exponent
 
 // N 2-byte loads whose results get a use of their own after all of them have been issued, so
 // that the compiler cannot move a load under the branch of a later select (loads under branches
@@ -56,56 +54,10 @@ __device__ __forceinline__ void load_h(const _Float16 *const (&p)[N], _Float16 (
   for (int e = 0; e < N; ++e) out[e] = __builtin_bit_cast(_Float16, (unsigned short)r[e]);
 }
 
-constexpr int kMaxBlocks = 256;      // workgroups of the magnitude scan = entries of its result
-
-// Largest magnitude of dy, as fp16 bit patterns without sign (Inf and NaN count as the largest
-// finite number): one entry per workgroup, no atomics.  The product forms dy * s in fp16; with
-// gradients of 1e-3 and step sizes of 1e-3 that product is a subnormal number and loses most of
-// its bits, so dy is first scaled by a power of two (exact) that brings its largest magnitude
-// into [512, 1024), and the sums are scaled back at the end (also exact).
-__global__ __launch_bounds__(256) void owq_bwd_absmax(const u32x4 *dy, size_t n16, size_t n_halves, const unsigned short *dy_h,
-                                                      u32 *out) {
-  __shared__ u32 red[4];
-  u32 m = 0;
-  auto take = [&](u32 w) {
-    const u32 lo = w & 0x7fffu, hi = (w >> 16) & 0x7fffu;
-    m = max(m, max(lo, hi));
-  };
-  // eight loads in flight per thread (one at a time: 9.7 instead of 6.1 us on 27 MB), the last one again past the end;
-  // where a thread has one at most, that one
-  constexpr size_t kStep = (size_t)kMaxBlocks * 256;
-  auto scan = [&](auto in_flight) __attribute__((always_inline)) {
-    constexpr int J = decltype(in_flight)::value;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += J * kStep) {
-      u32x4 v[J];
-#pragma unroll
-      for (int j = 0; j < J; ++j) v[j] = dy[i + j * kStep < n16 ? i + j * kStep : n16 - 1];
-#pragma unroll
-      for (int j = 0; j < J; ++j) {
-        take(v[j].x); take(v[j].y); take(v[j].z); take(v[j].w);
-      }
-    }
-  };
-  if (n16 <= kStep) scan(std::integral_constant<int, 1>{});
-  else scan(std::integral_constant<int, 8>{});
-  for (size_t i = n16 * 8 + (size_t)blockIdx.x * 256 + threadIdx.x; i < n_halves; i += (size_t)kMaxBlocks * 256)
-    take(dy_h[i]);
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) m = max(m, (u32)__shfl_xor((int)m, d));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) out[blockIdx.x] = min(max(max(red[0], red[1]), max(red[2], red[3])), 0x7bffu);
-}
-
-// The power of two dy is scaled by: 2^k brings the largest magnitude into [2^9, 2^10).
-__device__ __forceinline__ int scale_exponent(u32 max_bits) { return 24 - (int)(max_bits >> 10); }
-
 struct StageArgs {
   const _Float16 *dy;   // [batch][d_out]
   u32x4 *a_st;          // [pass][n_st][2][4 token tiles][64 lanes] units of 8 fp16
   int d_out, n_st, n0, batch, passes;      // n_st: row tiles staged per pass, the last one all zeros
-  const u32 *maxima;    // [kMaxBlocks] from owq_bwd_absmax
-  int *kword;           // the exponent, for the kernel that scales the sums back
 };
 
 // A unit: token 32 m + lane % 32 of the pass, rows 32 rt + 16 s + 4 h + {0..3} and
@@ -115,16 +67,6 @@ struct StageArgs {
 // block only.
 template <int NM>
 __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) {
-  // the scale: every workgroup reduces the scan's 256 entries again (cheaper than one more launch)
-  __shared__ u32 red[4];
-  u32 mx = a.maxima[t];
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) mx = max(mx, (u32)__shfl_xor((int)mx, d));
-  if ((t & 63) == 0) red[t >> 6] = mx;
-  __syncthreads();
-  const int kexp = scale_exponent(max(max(red[0], red[1]), max(red[2], red[3])));
-  const float scale = __builtin_ldexpf(1.0f, kexp);
-  if (b == 0 && t == 0) *a.kword = kexp;
   const int pairs = (a.n_st + 1) >> 1;
   const int m0 = NM == 1 ? (int)(b & 3) : 0;
   if (NM == 1) b >>= 2;
@@ -174,11 +116,7 @@ __device__ __forceinline__ void stage_dy(const StageArgs &a, unsigned b, int t) 
     }
   }
 #pragma unroll
-  for (int m = 0; m < NM; ++m) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[m][e] = (_Float16)((float)v[m][e] * scale);      // a power of two, below 1024 afterwards: exact
-    dst[m * 64] = __builtin_bit_cast(u32x4, v[m]);
-  }
+  for (int m = 0; m < NM; ++m) dst[m * 64] = __builtin_bit_cast(u32x4, v[m]);
 }
 
 struct StageWeakArgs {
@@ -220,22 +158,33 @@ struct ProdArgs {
 constexpr int kStepTiles = 4;                          // row tiles between two barriers
 constexpr int kStepBytes = kStepTiles * 8192;          // staged dy of a step: 128 tokens x 128 rows
 constexpr int kProdPlanes = 4 * kStepBytes;            // two buffers for either half of the rows; then per wave:
-constexpr int kProdPlane = kStepTiles * 32 * 6;        // step sizes and rests in operand order, zero points, of a step's rows
+constexpr int kProdPlane = 2 * kStepTiles * 32 * 8;    // step sizes with zero points, and rests in operand order, of the rows of two steps
 constexpr int kProdLds = kProdPlanes + 8 * kProdPlane;
+
+template <int S> using KStep = std::integral_constant<int, S>;
+
+// Eight values of a row times its step size.
+__device__ __forceinline__ h8_t scaled(h8_t v, u32 ss) {
+  const u32x4 u = __builtin_bit_cast(u32x4, v);
+  auto mul = [&](u32 p) { return __builtin_bit_cast(u32, __builtin_bit_cast(h2_t, p) * __builtin_bit_cast(h2_t, ss)); };
+  return __builtin_bit_cast(h8_t, (u32x4){mul(u.x), mul(u.y), mul(u.z), mul(u.w)});
+}
 
 // dx in partial results: a workgroup of eight waves takes 256 columns (a block pair) x 128 tokens x a range of row
 // tiles; waves 0..3 take 64 columns each over the first half of the range, waves 4..7 the same columns over the second.
 //
 // What bounds it: per 32 rows x 64 columns x 128 tokens a wave issues 16 matrix instructions for the product and 4 for
-// the turn, and about 100 vector instructions (mask-and-OR with -(2^(10-o) + z) added: 56, conversion of the turned
-// codes 16, dy times step size 32), so two waves per SIMD keep the matrix cores busy if nothing else is in the way.
-// Hence: staged dy comes in operand order by direct loads to LDS (no registers, no copies between register sets), step
-// sizes lie in LDS in the order a lane multiplies them, zero points leave with the unpack constant (exactly: integers
-// of at most 1024, what they lack is taken off by a side loop where a layer has other ones).  Row tiles past the end of a
-// range are left out one by one (whole steps with tiles of zeros: 11.1 instead of 8.6 us on 512 x 512, 24.0 instead of
-// 20.0 on 2432 -> 2086 at 432 tokens; the branches also keep each tile's loads of codes in place).  4096 -> 16384, 3-bit,
-// 512 tokens: 88 us, 780 TFLOP/s beside a turn of a quarter more; with one wave per SIMD, all of that in registers and
-// the zero points summed beside the product 135 us.  5120 -> 13824, 4-bit, 1000 tokens: 189 us against 346.
+// the turn: 1.05 PFLOP/s of both at 4096 -> 16384, 3-bit, 512 tokens, where a large fp16 library product on random data
+// reaches 1.2 on the same card.  The step size leaves with the codes: s (q - z) is rounded to fp16 once, before the turn
+// (relative error of 2^-11 at most, q - z being an integer, whatever s is), so dy is an operand as it is.  (It used to be
+// multiplied by s in the loop, 32 instructions per row tile instead of 16, and needed a launch that finds its largest magnitude
+// and a power of two against underflow.)  About 80 vector instructions per row tile, among the matrix instructions of the tile
+// before: a turn in front of its own product leaves the matrix cores waiting for it, 86.5 against 82 us here, 183 against 173
+// on 5120 -> 13824, 4-bit, 1000 tokens.  Operands of dy are read two reads ahead of their use.
+// Staged dy comes in operand order by direct loads to LDS (no registers, no copies between register sets), step sizes
+// and zero points lie in LDS by row; what a zero point lacks of an integer of at most 1024 is taken off by a side loop.
+// Row tiles past the end of a range are left out one by one (whole steps with tiles of zeros: 11.1 instead of 8.6 us on
+// 512 x 512, 24.0 instead of 20.0 on 2432 -> 2086 at 432 tokens).
 template <int BITS>
 __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   extern __shared__ u32x4 lds_units[];
@@ -252,10 +201,8 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   const int rt0 = kh ? mid : lo, rt1 = kh ? hi : mid;
   const int steps = (mid - lo + kStepTiles - 1) / kStepTiles;             // of either half (the first is not the shorter)
   const u32 ldsb = lds_address(lds);
-  _Float16 *splane = reinterpret_cast<_Float16 *>(lds + kProdPlanes + w * kProdPlane), *rplane = splane + kStepTiles * 32,
-           *zplane = rplane + kStepTiles * 32;
-  Magic M;
-  M.init();
+  u32 *szplane = reinterpret_cast<u32 *>(lds + kProdPlanes + w * kProdPlane);             // [2][128]
+  float *rplane = reinterpret_cast<float *>(szplane + 2 * kStepTiles * 32);               // [2][128]
   // this wave's 64 columns lie in one block (128 columns), hence in one group
   int g = (2 * bp + (cw >> 1)) / a.blocks_per_group;
   g = g < a.n_groups ? g : a.n_groups - 1;                          // columns past d_in: any group, they are not stored
@@ -304,101 +251,124 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
         load_to_lds(src, (u32)((2 * cw + j) * 1024 + lane * 16), ldsb + (u32)((2 * kh + buf) * kStepBytes + i * 8192 + (2 * cw + j) * 1024));
     }
   };
-  fetch_dy(rt0, 0);
-#pragma unroll
-  for (int i = 0; i < kStepTiles; ++i) fetch_codes(i, rt0 + i);
-  fetch_sz(rt0);
-  for (int st = 0; st < steps; ++st) {
-    const int rt = rt0 + st * kStepTiles, nx = st + 1 < steps ? rt + kStepTiles : rt;
-    wait_loads<0>();
-    __syncthreads();
-    fetch_dy(nx, (st + 1) & 1);
-    // step sizes to where the lanes of either half of the wave read eight of them at once: row 16 s + 8 b + 4 h + e of
-    // a row tile is element 4 b + e of unit (s, h)
+  // Step sizes with the zero points rounded; what those lack, times the step size, to where the lanes of either half of the
+  // wave read eight of them at once: row 16 s + 8 b + 4 h + e of a row tile is element 4 b + e of unit (s, h).  True: some
+  // zero point is no small integer.
+  auto put_sz = [&](int buf) __attribute__((always_inline)) {
     bool rest = false;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int r = 64 * i + lane, q = r & 15;
       const int at = (r >> 4) * 16 + ((q >> 2) & 1) * 8 + (q >> 3) * 4 + (q & 3);
       const float z = half_hi(szr[i]), z1 = __builtin_amdgcn_fmed3f(__builtin_rintf(z), -1024.f, 1024.f);
-      splane[at] = __builtin_bit_cast(_Float16, (unsigned short)szr[i]);
-      rplane[at] = (_Float16)(z - z1);
-      zplane[r] = (_Float16)z1;
+      const h2_t sz2 = {(_Float16)(half_lo(szr[i]) * 0x1p9f), (_Float16)(z1 * -0x1p-9f)};
+      szplane[buf * 128 + r] = __builtin_bit_cast(u32, sz2);
+      rplane[buf * 128 + at] = half_lo(szr[i]) * (z - z1);
       rest |= z != z1;
     }
-    fetch_sz(nx);
-    const unsigned char *dyb = lds + (2 * kh + (st & 1)) * kStepBytes + lane * 16;
-    if (__ballot(rest) != 0ull) {            // zero points that are no small integers: sum of dy s (z - rint z) per token
+    return __ballot(rest) != 0ull;
+  };
+  // s (q - z) of a K-step of the forward numbering (16 columns) of the lane's row, rounded once; sz as put_sz left it
+  auto weights = [&](int i, u32 szv, auto k_step) __attribute__((always_inline)) {
+    constexpr int S = decltype(k_step)::value;
+    return scaled(a_small<BITS, S>(cd[i], __builtin_amdgcn_perm(szv, szv, 0x03020302u)), __builtin_amdgcn_perm(szv, szv, 0x01000100u));
+  };
+  auto turned = [&](const f16_t &t, u32x4 *wb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      u32 pk[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)       // fp16 numbers: exact whatever the rounding
+        pk[e] = __builtin_bit_cast(u32, __builtin_amdgcn_cvt_pkrtz(t[8 * s + 2 * e], t[8 * s + 2 * e + 1]));
+      wb[s] = (u32x4){pk[0], pk[1], pk[2], pk[3]};
+    }
+  };
+  // ---- turn of the first row tile: s (q - z) from (row, eight columns) to (column, eight rows) per lane ----
+  fetch_dy(rt0, 0);
+  fetch_sz(rt0);
+#pragma unroll
+  for (int i = 0; i < kStepTiles; ++i) fetch_codes(i, rt0 + i);
+  bool rest = put_sz(0);
+  fetch_sz(rt0 + kStepTiles);
+  u32x4 wb[2][2], wn[2][2];
+  {
+    const u32 szv = szplane[n32];
+    const f16_t t0 = mma(weights(0, szv, KStep<1>{}), sel1, mma(weights(0, szv, KStep<0>{}), sel0, zero));
+    const f16_t t1 = mma(weights(0, szv, KStep<3>{}), sel1, mma(weights(0, szv, KStep<2>{}), sel0, zero));
+    turned(t0, wb[0]);
+    turned(t1, wb[1]);
+  }
+  fetch_codes(0, rt0 + kStepTiles);
+  for (int st = 0; st < steps; ++st) {
+    const int rt = rt0 + st * kStepTiles, nx = rt + kStepTiles, buf = st & 1;
+    // The codes of the next step's first tile, asked for last, may be on their way.  (The compiler does not count the direct
+    // loads: its own waits for the others would stand behind the next step's direct loads and wait for them too.)
+    wait_loads<BITS == 3 ? 3 : 1>();
+#pragma unroll
+    for (int i = 1; i < kStepTiles; ++i)
+#pragma unroll
+      for (int v = 0; v < BITS; ++v) asm volatile("" : "+v"(cd[i][v]));
+    asm volatile("" : "+v"(szr[0]), "+v"(szr[1]));
+    __syncthreads();
+    fetch_dy(nx, buf ^ 1);
+    const bool rest_next = put_sz(buf ^ 1);
+    fetch_sz(nx + kStepTiles);
+    u32 szv[kStepTiles];                     // of the row tiles that are turned in this step: 1, 2, 3 and the next one's 0
+#pragma unroll
+    for (int i = 0; i < kStepTiles; ++i) szv[i] = szplane[(i + 1 < kStepTiles ? buf * 128 + 32 * (i + 1) : (buf ^ 1) * 128) + n32];
+    const unsigned char *dyb = lds + (2 * kh + buf) * kStepBytes + lane * 16;
+    if (rest) {                              // sum of dy s (z - rint z) per token
+      const float *rp = rplane + buf * 128;
       for (int i = 0; i < 2 * min(kStepTiles, rt1 - rt); ++i) {
-        const u32x4 s4 = *reinterpret_cast<const u32x4 *>(splane + (2 * i + h) * 8), r4 = *reinterpret_cast<const u32x4 *>(rplane + (2 * i + h) * 8);
-        const u32 sv[4] = {s4.x, s4.y, s4.z, s4.w}, rv[4] = {r4.x, r4.y, r4.z, r4.w};
+        const f4_t r0 = *reinterpret_cast<const f4_t *>(rp + (2 * i + h) * 8), r1 = *reinterpret_cast<const f4_t *>(rp + (2 * i + h) * 8 + 4);
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
-          const u32x4 d4 = *reinterpret_cast<const u32x4 *>(dyb + (i * 4 + m) * 1024);
-          const u32 dv[4] = {d4.x, d4.y, d4.z, d4.w};
+          const h8_t d = *reinterpret_cast<const h8_t *>(dyb + (i * 4 + m) * 1024);
 #pragma unroll
-          for (int p = 0; p < 4; ++p)
-            zacc[m] = dot2(__builtin_bit_cast(u32, __builtin_bit_cast(h2_t, dv[p]) * __builtin_bit_cast(h2_t, sv[p])), rv[p], zacc[m]);
+          for (int e = 0; e < 4; ++e) zacc[m] = __builtin_fmaf((float)d[4 + e], r1[e], __builtin_fmaf((float)d[e], r0[e], zacc[m]));
         }
       }
     }
-    auto row_tile = [&](int i) __attribute__((always_inline)) {
-      // ---- turn: q - z of 32 rows x 64 columns from (row, eight columns) to (column, eight rows) per lane ----
-      const _Float16 z1 = zplane[32 * i + n32];
-      const u32 zz = (u32)__builtin_bit_cast(unsigned short, z1) * 0x00010001u ^ 0x80008000u;
-      u32 nb[8];
-#pragma unroll
-      for (int o = 0; o < 8; ++o) nb[o] = pk_sub(zz, M.m[o]);
-      u32x4 wb[2][2];
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        f16_t t;
-        if (c == 0) {
-          t = mma(a_exact<BITS, 0>(cd[i], M, nb), sel0, zero);
-          t = mma(a_exact<BITS, 1>(cd[i], M, nb), sel1, t);
-        } else {
-          t = mma(a_exact<BITS, 2>(cd[i], M, nb), sel0, zero);
-          t = mma(a_exact<BITS, 3>(cd[i], M, nb), sel1, t);
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          u32 pk[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e)       // small integers: exact whatever the rounding
-            pk[e] = __builtin_bit_cast(u32, __builtin_amdgcn_cvt_pkrtz(t[8 * s + 2 * e], t[8 * s + 2 * e + 1]));
-          wb[c][s] = (u32x4){pk[0], pk[1], pk[2], pk[3]};
-        }
-      }
-      fetch_codes(i, nx + i);
-      // ---- product: dy times step size (one rounding to fp16) against the turned codes ----
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const u32x4 s4 = *reinterpret_cast<const u32x4 *>(splane + ((2 * i + s) * 2 + h) * 8);
-        const u32 sv[4] = {s4.x, s4.y, s4.z, s4.w};
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const u32x4 d4 = *reinterpret_cast<const u32x4 *>(dyb + ((2 * i + s) * 4 + m) * 1024);
-          const u32 dv[4] = {d4.x, d4.y, d4.z, d4.w};
-          u32 ap[4];
-#pragma unroll
-          for (int p = 0; p < 4; ++p) ap[p] = __builtin_bit_cast(u32, __builtin_bit_cast(h2_t, dv[p]) * __builtin_bit_cast(h2_t, sv[p]));
-          const h8_t aop = __builtin_bit_cast(h8_t, (u32x4){ap[0], ap[1], ap[2], ap[3]});
-          acc[m][0] = mma(aop, __builtin_bit_cast(h8_t, wb[0][s]), acc[m][0]);
-          acc[m][1] = mma(aop, __builtin_bit_cast(h8_t, wb[1][s]), acc[m][1]);
-        }
-      }
-    };
+    rest = rest_next;
+    auto dy_of = [&](int i, int q) __attribute__((always_inline)) { return *reinterpret_cast<const h8_t *>(dyb + (i * 8 + q) * 1024); };
+    // ---- product: dy against the turned weights of a row tile, and the turn of the next one (slot j) in between ----
 #pragma unroll
     for (int i = 0; i < kStepTiles; ++i) {
       if (rt + i >= rt1) break;
-      row_tile(i);
+      const int j = (i + 1) % kStepTiles;
+      h8_t d0 = dy_of(i, 0), d1 = dy_of(i, 1), a0, a1;
+      f16_t t;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int s = q >> 2, m = q & 3;
+        const h8_t d2 = dy_of(i, q < 6 ? q + 2 : 7);
+        acc[m][0] = mma(d0, __builtin_bit_cast(h8_t, wb[0][s]), acc[m][0]);
+        acc[m][1] = mma(d0, __builtin_bit_cast(h8_t, wb[1][s]), acc[m][1]);
+        if (q == 0) a0 = weights(j, szv[i], KStep<0>{});
+        if (q == 1) a1 = weights(j, szv[i], KStep<1>{});
+        if (q == 2) t = mma(a1, sel1, mma(a0, sel0, zero));
+        if (q == 2) a0 = weights(j, szv[i], KStep<2>{});
+        if (q == 3) a1 = weights(j, szv[i], KStep<3>{});
+        if (q == 4) turned(t, wn[0]);
+        if (q == 4) fetch_codes(j, nx + i + 1);
+        if (q == 5) t = mma(a1, sel1, mma(a0, sel0, zero));
+        if (q == 7) turned(t, wn[1]);
+        d0 = d1;
+        d1 = d2;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        wb[0][s] = wn[0][s];
+        wb[1][s] = wn[1][s];
+      }
     }
   }
   wait_loads<0>();
   __syncthreads();
   // The rest of the zero points per token: both halves of the lanes, then from the operand layout (token = lane % 32)
   // to the accumulator layout (tokens along the registers); the planes of this wave have been read
-  float *zbuf = reinterpret_cast<float *>(splane);
+  float *zbuf = reinterpret_cast<float *>(szplane);
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     const float z = zacc[m] + __shfl_xor(zacc[m], 32);
@@ -482,7 +452,6 @@ struct SumArgs {
   const int *weak_idx;
   _Float16 *dx;         // [batch][d_in]
   int d_in, d_in_pad, split, wsplit, n0, ntok, k, kp32, dense_blocks;
-  const int *kword;     // dy was scaled by 2^*kword
 };
 
 // dx: the partial results added in a fixed order.  Blocks below dense_blocks take 1024 columns
@@ -491,7 +460,6 @@ __global__ __launch_bounds__(256) void owq_bwd_sum(const SumArgs a) {
   if ((int)blockIdx.y >= a.ntok) return;
   const int pass = blockIdx.y / kPassTokens, nl = blockIdx.y % kPassTokens;
   const size_t base = (size_t)pass * a.split * kPassTokens;           // first (range, token) row of this pass
-  const float back = __builtin_ldexpf(1.0f, -*a.kword);                // undo the scaling of dy
   if ((int)blockIdx.x < a.dense_blocks) {
     const int j = (blockIdx.x * 256 + threadIdx.x) * 4;            // four columns per thread (d_in_pad is a multiple of 256)
     if (j >= a.d_in) return;
@@ -512,7 +480,7 @@ __global__ __launch_bounds__(256) void owq_bwd_sum(const SumArgs a) {
     _Float16 *out = a.dx + (size_t)(a.n0 + blockIdx.y) * a.d_in + j;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (j + e < a.d_in && !((weak >> e) & 1u)) out[e] = (_Float16)(v[e] * back);
+      if (j + e < a.d_in && !((weak >> e) & 1u)) out[e] = (_Float16)v[e];
   } else {
     const int t = ((int)blockIdx.x - a.dense_blocks) * 256 + threadIdx.x;
     if (a.pw == nullptr || t >= a.k) return;
@@ -522,7 +490,7 @@ __global__ __launch_bounds__(256) void owq_bwd_sum(const SumArgs a) {
     const size_t wbase = (size_t)pass * a.wsplit * kPassTokens;
 #pragma unroll 8
     for (int s = 0; s < a.wsplit; ++s) v += a.pw[(wbase + (size_t)s * kPassTokens + nl) * (32 * a.kp32) + t];
-    a.dx[(size_t)(a.n0 + blockIdx.y) * a.d_in + col] = (_Float16)(v * back);
+    a.dx[(size_t)(a.n0 + blockIdx.y) * a.d_in + col] = (_Float16)v;
   }
 }
 
@@ -760,7 +728,7 @@ BwdPlan plan(const owq_layer_info_t &g, int batch, int passes = 0) {
   p.pw_bytes = p.weak_staged ? (size_t)p.passes * p.wsplit * kPassTokens * 32 * p.kp32 * 4 : 0;
   p.x_steps = (batch + 15) / 16;
   p.xw_bytes = g.k > 0 ? (size_t)p.x_steps * p.kp32 * 64 * 16 : 0;
-  p.total = p.a_st_bytes + p.part_bytes + p.wst_bytes + p.pw_bytes + p.xw_bytes + kScanBytes;
+  p.total = p.a_st_bytes + p.part_bytes + p.wst_bytes + p.pw_bytes + p.xw_bytes;
   return p;
 }
 
@@ -815,21 +783,14 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
   u32x4 *wst = p.weak_staged ? reinterpret_cast<u32x4 *>(ws + p.a_st_bytes + p.part_bytes) : nullptr;
   float *pw = p.weak_staged ? reinterpret_cast<float *>(ws + p.a_st_bytes + p.part_bytes + p.wst_bytes) : nullptr;
   u32x4 *xw_st = reinterpret_cast<u32x4 *>(ws + p.a_st_bytes + p.part_bytes + p.wst_bytes + p.pw_bytes);
-  u32 *maxima = reinterpret_cast<u32 *>(ws + p.total - kScanBytes);
-  int *kword = reinterpret_cast<int *>(maxima + kMaxBlocks);
   const bool want_dww = dww && g.k > 0;
   const int per_launch = p.passes * kPassTokens;
-  if (dx) {
-    const size_t halves = (size_t)batch * g.d_out;
-    hipLaunchKernelGGL(owq_bwd_absmax, dim3(kMaxBlocks), dim3(256), 0, st, static_cast<const u32x4 *>(dy), halves / 8, halves,
-                       static_cast<const unsigned short *>(dy), maxima);
-  }
   // The first launch stages everything the call needs; later groups of passes stage their dy only.
   for (int n0 = 0; n0 < batch && err == hipSuccess && (dx || n0 == 0); n0 += per_launch) {
     const int ntok = batch - n0 < per_launch ? batch - n0 : per_launch;
     const int passes = (ntok + kPassTokens - 1) / kPassTokens;
     StageAllArgs sa = {};
-    sa.dy = {static_cast<const _Float16 *>(dy), a_st, g.d_out, g.n_rt + 1, n0, batch, passes, maxima, kword};
+    sa.dy = {static_cast<const _Float16 *>(dy), a_st, g.d_out, g.n_rt + 1, n0, batch, passes};
     sa.weak = {reinterpret_cast<const _Float16 *>(blob + g.off_weak_w), wst, g.kp, p.kp32, g.n_rt};
     sa.x = {static_cast<const _Float16 *>(x), reinterpret_cast<const int *>(blob + g.off_weak_idx), xw_st,
             g.d_in, g.k, p.kp32, batch, p.x_steps};
@@ -869,7 +830,7 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
       hipLaunchKernelGGL(g.bits == 3 ? owq_bwd_product<3> : owq_bwd_product<4>, grid, dim3(512), kProdLds, st, pa);
       const int dense_blocks = (g.d_in + 1023) / 1024, weak_blocks = p.weak_staged ? (g.k + 255) / 256 : 0;
       SumArgs su = {part, pw, blob + g.off_wmask, reinterpret_cast<const int *>(blob + g.off_weak_idx),
-                    static_cast<_Float16 *>(dx), g.d_in, g.nbp * 256, p.split, p.wsplit, n0, ntok, g.k, p.kp32, dense_blocks, kword};
+                    static_cast<_Float16 *>(dx), g.d_in, g.nbp * 256, p.split, p.wsplit, n0, ntok, g.k, p.kp32, dense_blocks};
       hipLaunchKernelGGL(owq_bwd_sum, dim3((unsigned)(dense_blocks + weak_blocks), (unsigned)ntok), dim3(256), 0, st, su);
       if (g.k > 0 && !p.weak_staged) {
         WeakArgs wa = {static_cast<const _Float16 *>(dy), reinterpret_cast<const _Float16 *>(blob + g.off_weak_w),

@@ -44,3 +44,28 @@ def test_rows_and_zero_points(env, d_in, d_out, bits, group, k, tokens, zeros):
     rel, _ = owq_ref.parity_errors(dww.cpu().numpy(), want_dww)
     assert rel <= 1e-5, rel
     lin.close()
+
+
+@pytest.mark.parametrize("lo,hi,grad", [(6e-8, 2e-6, 300.0), (20.0, 100.0, 1e-4), (0.3, 1.0, 2e-5)])
+@pytest.mark.parametrize("zeros", ["integers", "any"])
+def test_step_sizes_and_gradients_of_any_size(env, lo, hi, grad, zeros):
+    # s (q - z) is rounded to fp16 by itself, with a relative error of 2^-11 at most also where s is subnormal, and dy is
+    # not scaled: the same bar holds, dx being a normal number in all of these.
+    torch, B = env
+    layer = make_layer(LayerSpec("bwds", 600, 1000, 4, 128, 8, 3))
+    rng = np.random.default_rng(11)
+    layer.scale[:] = (rng.uniform(lo, hi, layer.scale.shape) * rng.choice([-1, 1], layer.scale.shape)).astype(np.float16)
+    if zeros == "any":
+        layer.zero[:] = (layer.zero.astype(np.float32) + rng.normal(0, 2, layer.zero.shape)).astype(np.float16)
+    layer.weak_w[:] = 0
+    x = make_x(layer, 150)
+    dy = rng.normal(0, grad, (150, 1000)).astype(np.float16)
+    print(f"step sizes {lo} to {hi}, gradients {grad}, zero points: {zeros}", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    dx, _ = lin.backward(torch.from_numpy(dy).cuda(), torch.from_numpy(x).cuda())
+    want, _ = backward.owq_backward_ref(layer.codes, layer.scale, layer.zero, 128, layer.weak_idx, layer.weak_w, x, dy)
+    keep = np.ones(600, bool)
+    keep[layer.weak_idx] = False
+    rel, mx = owq_ref.parity_errors(dx.cpu().numpy()[:, keep], want[:, keep])
+    assert rel <= 1e-3 and mx <= 1e-2, (rel, mx)
+    lin.close()
