@@ -672,10 +672,15 @@ __device__ __forceinline__ void dww_product(const DwwArgs &a, int bx, int by) {
 
 // The two small products of a call in one launch: dww in the first blocks of the grid, dx at the weak columns in the
 // others (either may be absent).
+// Both move as many bytes as they wait: blocks that read the same lines (neighbouring row tiles of dy, the weak tiles of a range)
+// land on one die, whose L2 then serves them.  5120 -> 13824, 1000 tokens: 22.2 -> 18.8 us, 4096 -> 16384, 512 tokens 11.9 -> 10.8.
 template <int NTT>
 __global__ __launch_bounds__(256) void owq_bwd_small(const DwwArgs da, const WeakProdArgs wa, int dww_rows, int dww_blocks) {
-  if ((int)blockIdx.x < dww_blocks) dww_product<NTT>(da, (int)blockIdx.x % dww_rows, (int)blockIdx.x / dww_rows);
-  else weak_product(wa, (int)blockIdx.x - dww_blocks);
+  const bool dww = (int)blockIdx.x < dww_blocks;
+  const int b0 = dww ? (int)blockIdx.x : (int)blockIdx.x - dww_blocks, n = dww ? dww_blocks : (int)gridDim.x - dww_blocks;
+  const int x = b0 & 7, b = x * (n >> 3) + min(x, n & 7) + (b0 >> 3);
+  if (dww) dww_product<NTT>(da, b % dww_rows, b / dww_rows);
+  else weak_product(wa, b);
 }
 
 struct BwdPlan {
