@@ -152,6 +152,8 @@ struct ProdArgs {
   const u32 *sz;        // [G][d_out_pad] step size | zero point << 16
   const u32x4 *a_st;
   float *part;          // [pass][split][128][d_in_pad]
+  _Float16 *dx;         // [ntok][d_in] instead, where one workgroup has all rows; or nullptr
+  int d_in, ntok;
   int n_rt, nbp, chunks, d_out_pad, d_in_pad, blocks_per_group, n_groups, split, rt_per_split;
 };
 
@@ -159,6 +161,7 @@ constexpr int kStepTiles = 4;                          // row tiles between two 
 constexpr int kStepBytes = kStepTiles * 8192;          // staged dy of a step: 128 tokens x 128 rows
 constexpr int kProdPlanes = 4 * kStepBytes;            // two buffers for either half of the rows; then per wave:
 constexpr int kProdPlane = 2 * kStepTiles * 32 * 8;    // step sizes with zero points, and rests in operand order, of the rows of two steps
+constexpr int kOutPitch = 72;                          // halves per token of 64 columns of the result
 constexpr int kProdLds = kProdPlanes + 8 * kProdPlane;
 
 template <int S> using KStep = std::integral_constant<int, S>;
@@ -183,6 +186,8 @@ __device__ __forceinline__ h8_t scaled(h8_t v, u32 ss) {
 // on 5120 -> 13824, 4-bit, 1000 tokens.  Operands of dy are read two reads ahead of their use.
 // Staged dy comes in operand order by direct loads to LDS (no registers, no copies between register sets), step sizes
 // and zero points lie in LDS by row; what a zero point lacks of an integer of at most 1024 is taken off by a side loop.
+// A workgroup that has all rows of its columns stores dx itself, by way of LDS (fp32 partial results and their sum: 4096 rows
+// of codes x 16384 columns, 512 tokens, 12.5 us for the sum, 5.1 now for the weak columns alone, the product 81.6 as before).
 // Row tiles past the end of a range are left out one by one (whole steps with tiles of zeros: 11.1 instead of 8.6 us on
 // 512 x 512, 24.0 instead of 20.0 on 2432 -> 2086 at 432 tokens).
 template <int BITS>
@@ -388,6 +393,30 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   __syncthreads();
   if (kh == 1) return;
   const float *zother = reinterpret_cast<const float *>(lds + kProdPlanes + (w + 4) * kProdPlane);
+  if (a.dx != nullptr) {
+    // 32 tokens at a time through what has been read of the exchange, so that eight columns are stored at once
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      f4_t o[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) o[q] = xch[(m * 8 + q) * 64];
+      _Float16 *out = reinterpret_cast<_Float16 *>(lds + cw * 32768 + m * 8192);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int nl = 8 * (q & 3) + 4 * h + e;
+          out[nl * kOutPitch + 32 * (q >> 2) + n32] =
+              (_Float16)((acc[m][q >> 2][4 * (q & 3) + e] + o[q][e]) - (zbuf[32 * m + nl] + zother[32 * m + nl]));
+        }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int nl = 8 * i + (lane >> 3), n = pass * kPassTokens + 32 * m + nl, j = 256 * bp + 64 * cw + 8 * (lane & 7);
+        if (n < a.ntok) store_rows(a.dx + (size_t)n * a.d_in + j, out + nl * kOutPitch + 8 * (lane & 7), a.d_in - j);
+      }
+    }
+    return;
+  }
   float *part = a.part + ((size_t)pass * a.split + sp) * kPassTokens * a.d_in_pad;
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -708,14 +737,14 @@ BwdPlan plan(const owq_layer_info_t &g, int batch, int passes = 0) {
   p.most = all_passes < most ? all_passes : most;
   p.passes = passes > 0 ? passes : sets > 1 && equal <= 6 ? kLaunchPasses : equal < 1 ? 1 : equal;
   // Ranges of rows per block pair.  A compute unit holds one workgroup at a time, so the product takes rounds of 256
-  // workgroups, each as long as its row tiles (0.7 us) and a fixed part; every range costs the sum kernel a read of its
-  // partial results.  In us, fitted to measurements on MI355X.
+  // workgroups, each as long as its row tiles (0.7 us) and a fixed part; ranges cost a write and a read of
+  // their partial results, a single one the store of dx.  In us, fitted to measurements on MI355X.
   int split = 1;
   double best = 1e30;
   for (int sp = 1; sp <= kSplitMax && sp <= g.n_rt; ++sp) {
     const long long wgs = (long long)g.nbp * sp * p.passes;
     const double rounds = (double)((wgs + 255) / 256);
-    const double cost = rounds * (0.7 * ((g.n_rt + sp - 1) / sp) + 6.0) + sp * (p.passes * kPassTokens * 256.0 * g.nbp * 8.0 / 4e6);
+    const double cost = rounds * (0.7 * ((g.n_rt + sp - 1) / sp) + 6.0) + sp * (p.passes * kPassTokens * 256.0 * g.nbp * (sp > 1 ? 8.0 : 2.0) / 4e6);
     if (cost < best) {
       best = cost;
       split = sp;
@@ -724,7 +753,7 @@ BwdPlan plan(const owq_layer_info_t &g, int batch, int passes = 0) {
   p.rt_per_split = (g.n_rt + split - 1) / split;
   p.split = (g.n_rt + p.rt_per_split - 1) / p.rt_per_split;
   p.a_st_bytes = (size_t)p.passes * (g.n_rt + 1) * 2 * 4 * 64 * 16;
-  p.part_bytes = (size_t)p.passes * p.split * kPassTokens * ((size_t)g.nbp * 256) * 4;
+  p.part_bytes = p.split == 1 ? 0 : (size_t)p.passes * p.split * kPassTokens * ((size_t)g.nbp * 256) * 4;
   p.kp32 = (g.kp + 31) / 32;
   p.weak_staged = g.k > 0 && p.kp32 <= g.nbp;
   // weak columns: ranges of at least the four row tiles whose loads go out together
@@ -822,6 +851,9 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
       pa.sz = reinterpret_cast<const u32 *>(blob + g.off_sz);
       pa.a_st = a_st;
       pa.part = part;
+      pa.dx = p.split == 1 ? static_cast<_Float16 *>(dx) + (size_t)n0 * g.d_in : nullptr;
+      pa.d_in = g.d_in;
+      pa.ntok = ntok;
       pa.n_rt = g.n_rt;
       pa.nbp = g.nbp;
       pa.chunks = g.chunks;
@@ -833,10 +865,11 @@ extern "C" owq_status_t owq_linear_backward(owq_handle_t h, const void *dy, cons
       pa.rt_per_split = p.rt_per_split;
       const dim3 grid((unsigned)(g.nbp * p.split * passes));
       hipLaunchKernelGGL(g.bits == 3 ? owq_bwd_product<3> : owq_bwd_product<4>, grid, dim3(512), kProdLds, st, pa);
-      const int dense_blocks = (g.d_in + 1023) / 1024, weak_blocks = p.weak_staged ? (g.k + 255) / 256 : 0;
+      const int dense_blocks = p.split == 1 ? 0 : (g.d_in + 1023) / 1024, weak_blocks = p.weak_staged ? (g.k + 255) / 256 : 0;
       SumArgs su = {part, pw, blob + g.off_wmask, reinterpret_cast<const int *>(blob + g.off_weak_idx),
                     static_cast<_Float16 *>(dx), g.d_in, g.nbp * 256, p.split, p.wsplit, n0, ntok, g.k, p.kp32, dense_blocks};
-      hipLaunchKernelGGL(owq_bwd_sum, dim3((unsigned)(dense_blocks + weak_blocks), (unsigned)ntok), dim3(256), 0, st, su);
+      if (dense_blocks + weak_blocks > 0)
+        hipLaunchKernelGGL(owq_bwd_sum, dim3((unsigned)(dense_blocks + weak_blocks), (unsigned)ntok), dim3(256), 0, st, su);
       if (g.k > 0 && !p.weak_staged) {
         WeakArgs wa = {static_cast<const _Float16 *>(dy), reinterpret_cast<const _Float16 *>(blob + g.off_weak_w),
                        reinterpret_cast<const int *>(blob + g.off_weak_idx), static_cast<_Float16 *>(dx),

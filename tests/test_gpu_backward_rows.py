@@ -69,3 +69,27 @@ def test_step_sizes_and_gradients_of_any_size(env, lo, hi, grad, zeros):
     rel, mx = owq_ref.parity_errors(dx.cpu().numpy()[:, keep], want[:, keep])
     assert rel <= 1e-3 and mx <= 1e-2, (rel, mx)
     lin.close()
+
+
+@pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens", [
+    (4100, 40, 3, 128, 33, 2000),         # one range of rows, two sets of launches, columns off the 8-column grid
+    (4099, 64, 4, 0, 0, 129),             # odd rows of dx, no weak columns, a pass of one token
+    (8192, 260, 4, 128, 64, 300)])
+def test_dx_stored_by_the_product(env, d_in, d_out, bits, group, k, tokens):
+    torch, B = env
+    layer = make_layer(LayerSpec("bwd1", d_in, d_out, bits, group, k, d_in))
+    x = make_x(layer, tokens)
+    dy = np.random.default_rng(d_in).normal(0, 0.05, (tokens, d_out)).astype(np.float16)
+    print(f"{d_in} -> {d_out}, {tokens} tokens", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    guard = torch.full((tokens + 1, d_in), 7.0, dtype=torch.float16, device="cuda")
+    dyt, xt = torch.from_numpy(dy).cuda(), torch.from_numpy(x).cuda()
+    ws = torch.empty(B.owq_backward_workspace_bytes(lin.handle, tokens), dtype=torch.uint8, device="cuda")
+    B.owq_linear_backward(lin.handle, dyt.data_ptr(), xt.data_ptr(), guard.data_ptr(), 0, tokens, ws.data_ptr(), ws.numel())
+    torch.cuda.synchronize()
+    want, _ = backward.owq_backward_ref(layer.codes, layer.scale, layer.zero, group, layer.weak_idx, layer.weak_w, x, dy)
+    got = guard.cpu().numpy()
+    rel, mx = owq_ref.parity_errors(got[:tokens], want)
+    assert rel <= 1e-3 and mx <= 1e-2, (rel, mx)
+    assert (got[tokens] == 7).all()
+    lin.close()
