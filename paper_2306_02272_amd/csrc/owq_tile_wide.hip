@@ -309,22 +309,26 @@ __device__ __forceinline__ void wide_fast(const WideArgs &a, unsigned char *lds,
   u32 nz[2];              // -z 2^-9 of the lane's two rows
   float last;             // step size of the lane's row in the blocks so far: what the accumulators are in units of,
   float over = 0.f;       // and what the ratios' roundings have left of it
+  float ratio = 1.f, was = 1.f;
   auto take_sz = [&](u32 v, bool first) __attribute__((always_inline)) {
     const float s = half_lo(v);
     if (GROUPED) {
-      // (last + over) / s, and what its rounding leaves, in units of s
+      // (last + over) / s
       float rc = __builtin_amdgcn_rcpf(s);
       rc = __builtin_fmaf(__builtin_fmaf(-s, rc, 1.f), rc, rc);
-      float r = last * rc;
-      r = __builtin_fmaf(__builtin_fmaf(-r, s, last) + over, rc, r);
-      over = first ? 0.f : (__builtin_fmaf(-r, s, last) + over) * __builtin_amdgcn_rcpf(r);
-      splane[lane] = first ? 1.f : r;
+      const float r = last * rc;
+      ratio = first ? 1.f : __builtin_fmaf(__builtin_fmaf(-r, s, last) + over, rc, r);
+      was = first ? s : last;
+      splane[lane] = ratio;
     }
     last = s;
     zplane[lane] = half_hi(v) * -0x1p-9f;
 #pragma unroll
     for (int t = 0; t < 2; ++t) nz[t] = pk_dup(zplane[t * 32 + (lane & 31)]);
   };
+  // what the ratio's rounding leaves, in units of the new step size; not in front of the accumulators' multiplications, which wait
+  // for the ratio (1 % of the whole there)
+  auto carry = [&]() __attribute__((always_inline)) { over = (__builtin_fmaf(-ratio, last, was) + over) * __builtin_amdgcn_rcpf(ratio); };
 #pragma unroll
   for (int i = 0; i < 2 * NT; ++i)
 #pragma unroll
@@ -388,6 +392,7 @@ __device__ __forceinline__ void wide_fast(const WideArgs &a, unsigned char *lds,
     if (GROUPED) {
       scale_acc();
       __builtin_amdgcn_sched_barrier(0);
+      carry();
     }
     FastSteps<BITS, NT, 0>::run(first, cb[J], xb, xsw, nz, acc);
   };
