@@ -265,7 +265,7 @@ def bench_backward(args) -> int:
         "metric": f"backward of the {specs[0].bits}-bit OWQ linear (dX, dWw), tokens/s, {batch} tokens",
         "value": round(batch * steps / wall_s, 1), "unit": "tokens/s", "n_gpus": 1, "steps": steps, "warmup": warmup,
         "ms_per_step": round(wall_s / steps * 1e3, 6), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f16 operands (dy x step size rounded to f16), f32 accumulate", "data": "synthetic",
+        "dtype": "f16 operands (weights rounded to f16), f32 accumulate", "data": "synthetic",
         "config": {"workload": desc, "batch": batch, "layers": [s.name for s in specs], "launch_mode": "eager"},
         "us_per_call": round(wall_s / calls * 1e6, 3),
         "roofline": {"bound": "mfma", "achieved": round(tflops, 1), "peak": MFMA_F16_PEAK_TFLOPS, "unit": "TFLOP/s",
