@@ -11,16 +11,15 @@
 //           of 256 bytes whose 16-byte units are exchanged by the low bits of the token, so that operand reads are
 //           free of bank conflicts; the weak columns of a block are then overwritten with zeros by the wave that
 //           fetched them (the dense term must not see them, whatever they hold);
-//   codes   go from registers into the A operand (q - z) 2^-9, exactly (a_small);
-//   groups  the accumulators hold the sums in units of the block's step size: before a block of another group they are
-//           multiplied by (last step size / next), in fp32, and by the last one at the end.  With a second set of tiles that
-//           takes the scaled blocks (as many vector instructions, 64 registers more) 128 tokens do not fit the registers.
-//           What a ratio's rounding leaves goes into the next ratio, so all of them together are off by no more than one;
-//           the rounding to y then takes the result as the multiplications leave it, good to 19 bits (settled);
+//   codes   go from registers into the operand (q - z) 2^-9, exactly (a_small); it is the B operand, so that a lane holds one
+//           row of the result and sixteen tokens, and a row's step size is one register;
+//   groups  the sums of a block start from zero and end on one multiply-add per value with the step size, in fp32, as many
+//           roundings as blocks.  128 tokens of those sums and of the result would be all registers there are: the block is
+//           worked through a token tile of 32 at a time, which keeps the weight operands (64 registers) instead of seven
+//           eighths of the sums, and what follows from the lane is worked out where it is used;
 //   weak    the fp16 weak columns are one more K range at the end, operands of both sides from LDS.
-// Row groups with a zero point that is no integer of at most 1024 (groups: 240), or with a step size of zero or none that is finite, take
-// wide_columns instead (found by the prep kernel): second set of tiles, rests of the zero points by a second set of matrix
-// instructions with the constant operand rint(z) - z, 64 tokens at a time.
+// Row groups with a zero point that is no integer of at most 1024 (found by the prep kernel) take what the rounded zero points
+// lack off by a second set of matrix instructions with the constant operand rint(z) - z.
 //
 // One workgroup writes y itself when it owns all columns; when there are too few tiles for the chip the
 // columns are cut into `split` ranges, fp32 partial results go to the scratch area and owq_wide_sum adds them
@@ -28,9 +27,11 @@
 //
 // What bounds it: power.  The card lowers its clock under matrix work on random data (4096 x 16384 at 2048 tokens, 3-bit,
 // groups of 128: 304 us with 64-token tiles, 239 with x zero; a large fp16 library product of that size 224 and, on zeros,
-// about 160), so every instruction beside the matrix work costs.  128 tokens per unpacked code instead of 64 take the
-// vector instructions per matrix instruction from 7.9 to 4.7: 304 -> 248 us; 5120 -> 13824, 4-bit, 1500 tokens 270 -> 225.
-// A schedule asked for with group barriers (five vector instructions behind every matrix instruction) 252, without 246.
+// about 160), so every instruction beside the matrix work costs.  128 tokens per unpacked code instead of 64: 304 -> 241-250 us
+// there, 16384 x 4096 293 -> 275, 4-bit 5120 -> 13824 at 777 tokens 154 -> 145; vector instructions per matrix instruction
+// 7.9 -> 5.4.  With a spill of two to five registers, which waits for the direct loads too, 275 becomes 304-324.
+// (Sums kept in units of the block's step size and multiplied by ratios of step sizes instead: 266, 244 and 141, but a rounding
+// per block on all of the sums, which does not leave a single column's weight exact beyond some 100 groups.)
 #include <hip/hip_runtime.h>
 
 #include "owq_internal.h"
@@ -43,17 +44,12 @@ constexpr int kWideRows = 256, kWideTokens = 64, kWideWaves = 4;
 constexpr int kWideBufUnits = kWideTokens * 16;        // 16-byte units of one staged block: [token][16]
 constexpr int kWideWeakUnits = 32 * 16;                // of 128 weak columns of a row tile
 constexpr int kWideOutPitch = 264;                     // halves per token of the transposed result
-// A workgroup's tile has NT / 2 times 64 tokens.  After the two block buffers (later: x at the weak columns and the weights):
-// step sizes and zero points of a block, per wave.
-constexpr int wide_planes(int NT) { return (NT == 2 ? 3 : 4) * kWideBufUnits * 16; }
-constexpr int wide_lds(int NT) { return wide_planes(NT) + kWideWaves * 128 * 4; }
+// A workgroup's tile has NT / 2 times 64 tokens: two block buffers, later x at the weak columns and the weights.
+constexpr int wide_lds(int NT) { return (NT == 2 ? 3 : 4) * kWideBufUnits * 16; }
 static_assert(kWideBufUnits + kWideWaves * kWideWeakUnits <= 3 * kWideBufUnits, "a row tile's weak weights per wave beside x");
 static_assert(2 * kWideBufUnits + kWideWaves * kWideWeakUnits <= 4 * kWideBufUnits, "the same beside x of 128 tokens");
-static_assert(kWideTokens * kWideOutPitch * 2 <= wide_planes(2), "64 tokens of the result are transposed in the staging buffers");
+static_assert(kWideTokens * kWideOutPitch * 2 <= wide_lds(2), "64 tokens of the result are transposed in the staging buffers");
 constexpr int kWideSlotUnits = kWideWaves * 16 * 64;   // 16-byte units of a partial result (256 rows x 64 tokens, fp32)
-
-// |q - z| that wide_fast takes: what fp16 holds exactly; in groups, what is 19 bits times a step size (settled)
-constexpr float kZeroLimit = 1024.f, kZeroLimitGroups = 240.f;
 
 constexpr int kFlagGroups = 16;          // groups of a row group that one workgroup of the prep kernel looks through
 
@@ -64,12 +60,10 @@ struct PrepArgs {
   int *flags;            // [n_rg][n_fl]
   _Float16 *xw;          // [ntok][xwpitch], zero beyond kp
   _Float16 *xcopy;       // [ntok][pitch], or nullptr
-  int n_rg, n_fl, n_groups, d_out, d_out_pad, d_in, ntok, kp, xwpitch, pitch;
-  float zero_limit;      // largest zero point that wide_fast takes
+  int n_rg, n_fl, n_groups, d_out_pad, d_in, ntok, kp, xwpitch, pitch;
 };
 
-// The first n_rg x n_fl workgroups: does a row group hold a zero point that is no integer of at most zero_limit, or a step
-// size that is zero or no finite number?  The
+// The first n_rg x n_fl workgroups: does a row group hold a zero point that is no integer of at most 1024?  The
 // others take four tokens each, a wave per token: the gather of x at the weak columns and, for rows that are no
 // multiple of 16 bytes, a copy of x that is.  Latency is what it costs (a chain of two loads per element), so every
 // wave has one token and independent loads (a grid-stride loop over all elements took 11.9 us on 2048 tokens).
@@ -81,16 +75,14 @@ __global__ __launch_bounds__(256) void owq_wide_prep(const PrepArgs a) {
     __syncthreads();
     const int rg = blockIdx.x / a.n_fl, g0 = (blockIdx.x - rg * a.n_fl) * kFlagGroups;
     int row = rg * kWideRows + tid;
-    if (row > a.d_out - 1) row = a.d_out - 1;         // rows past the end have step size 0, and results that are dropped
+    if (row > a.d_out_pad - 1) row = a.d_out_pad - 1;
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < kFlagGroups; ++i) {
       int g = g0 + i;
       if (g > a.n_groups - 1) g = a.n_groups - 1;
-      const u32 v = a.sz[(size_t)g * a.d_out_pad + row];
-      const float z = half_hi(v), sc = __builtin_fabsf(half_lo(v));
-      // (no short cuts: the compiler would wait for each load in a branch of its own)
-      bad |= !((int)(__builtin_fabsf(z) <= a.zero_limit) & (int)(z == __builtin_rintf(z)) & (int)(sc > 0.f) & (int)(sc < INFINITY));
+      const float z = half_hi(a.sz[(size_t)g * a.d_out_pad + row]);
+      bad |= !(__builtin_fabsf(z) <= 1024.f && z == __builtin_rintf(z));
     }
     if (bad) any = 1;
     __syncthreads();
@@ -129,231 +121,131 @@ struct WideArgs {
   int nbp, nblk, n_rt, n_groups, bpg, kunits, n_rg, n_fl, n_tt, split;
 };
 
-// The operands of one k-step: q - z of the wave's two row tiles, x of its two token tiles.
-struct WideOps {
-  h8_t a0, a1, b0, b1;
-};
-template <int BITS, int S>
-__device__ __forceinline__ WideOps wide_ops(const u32 (*wd)[8], const unsigned char *xb, u32 xsw, const Magic &M, const u32 (*nb)[8]) {
-  const unsigned char *p = xb + (xsw ^ (S << 5));
-  WideOps o;
-  o.b0 = *reinterpret_cast<const h8_t *>(p);
-  o.b1 = *reinterpret_cast<const h8_t *>(p + 32 * 256);
-  o.a0 = a_exact<BITS, S>(wd[0], M, nb[0]);
-  o.a1 = a_exact<BITS, S>(wd[1], M, nb[1]);
-  return o;
-}
-
-// K-steps S..7 of a block: the operands of step S + 1 are made while the matrix instructions of step S run.  The
-// scheduling barriers keep the compiler from making all eight steps' operands first, which does not fit the registers.
-// wd: the block's dwords of the wave's two row tiles; xb + xsw: the lane's token row, its units exchanged;
-// acc 0,1 = row tile 0, token tiles 0,1; 2,3 = row tile 1.
-template <int BITS, bool GROUPED, bool REST, int S>
-struct WideSteps {
-  static __device__ __forceinline__ void run(const WideOps &o, const u32 (*wd)[8], const unsigned char *xb, u32 xsw, const Magic &M,
-                                             const u32 (*nb)[8], const u32 *nr, f16_t *acc, const f16_t &zero) {
-    WideOps nx = o;
-    if constexpr (S < 7) nx = wide_ops<BITS, (S < 7 ? S + 1 : 0)>(wd, xb, xsw, M, nb);
-    constexpr bool kFirst = GROUPED && S == 0;
-    acc[0] = mma(o.a0, o.b0, kFirst ? zero : acc[0]);
-    acc[2] = mma(o.a1, o.b0, kFirst ? zero : acc[2]);
-    acc[1] = mma(o.a0, o.b1, kFirst ? zero : acc[1]);
-    acc[3] = mma(o.a1, o.b1, kFirst ? zero : acc[3]);
-    if (REST) {
-      const h8_t r0 = __builtin_bit_cast(h8_t, (u32x4){nr[0], nr[0], nr[0], nr[0]});
-      const h8_t r1 = __builtin_bit_cast(h8_t, (u32x4){nr[1], nr[1], nr[1], nr[1]});
-      acc[0] = mma(r0, o.b0, acc[0]);
-      acc[1] = mma(r0, o.b1, acc[1]);
-      acc[2] = mma(r1, o.b0, acc[2]);
-      acc[3] = mma(r1, o.b1, acc[3]);
-    }
-    if (!REST) {
-      // operand reads first, then a few vector instructions behind every matrix instruction
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    WideSteps<BITS, GROUPED, REST, S + 1>::run(nx, wd, xb, xsw, M, nb, nr, acc, zero);
+template <int J> using Int = std::integral_constant<int, J>;
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void each(F &&f) {
+  if constexpr (I < N) {
+    f(Int<I>{});
+    each<N, I + 1>(f);
   }
-};
-template <int BITS, bool GROUPED, bool REST>
-struct WideSteps<BITS, GROUPED, REST, 8> {
-  static __device__ __forceinline__ void run(const WideOps &, const u32 (*)[8], const unsigned char *, u32, const Magic &,
-                                             const u32 (*)[8], const u32 *, f16_t *, const f16_t &) {}
-};
-
-template <int J> struct WideBuf {};
-template <int J> __device__ std::integral_constant<int, J> wide_buf_index(WideBuf<J>);
-
-// The operands of one k-step of wide_fast: (q - z) 2^-9 of the wave's two row tiles, x of its NT token tiles.
-template <int NT>
-struct FastOps {
-  h8_t a[2], b[NT];
-};
-template <int NT, int S>
-__device__ __forceinline__ void fast_x(FastOps<NT> &o, const unsigned char *xb, u32 xsw) {
-#pragma unroll
-  for (int i = 0; i < NT; ++i) o.b[i] = *reinterpret_cast<const h8_t *>(xb + (xsw ^ (S << 5)) + i * 32 * 256);
-}
-template <int BITS, int NT, int S>
-__device__ __forceinline__ void fast_codes(FastOps<NT> &o, const u32 (*wd)[8], const u32 *nz) {
-#pragma unroll
-  for (int t = 0; t < 2; ++t) o.a[t] = a_small<BITS, S>(wd[t], nz[t]);
 }
 
-// K-steps S..7 of a block: the operands of step S + 1 are made while the matrix instructions of step S run.  SCALE: the
-// accumulators are brought to the step sizes of the block first (ratio: LDS, of the wave's 64 rows), a tile's share in front
-// of its first matrix instruction.
-template <int BITS, int NT, int S>
-struct FastSteps {
-  static __device__ __forceinline__ void run(const FastOps<NT> &o, const u32 (*wd)[8], const unsigned char *xb, u32 xsw, const u32 *nz,
-                                             f16_t *acc) {
-    FastOps<NT> nx = o;
-    if constexpr (S < 7) {
-      fast_x<NT, S + 1>(nx, xb, xsw);
-      fast_codes<BITS, NT, S + 1>(nx, wd, nz);
-    }
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) acc[t * NT + i] = mma(o.a[t], o.b[i], acc[t * NT + i]);
-    __builtin_amdgcn_sched_barrier(0);
-    FastSteps<BITS, NT, S + 1>::run(nx, wd, xb, xsw, nz, acc);
-  }
-};
-template <int BITS, int NT>
-struct FastSteps<BITS, NT, 8> {
-  static __device__ __forceinline__ void run(const FastOps<NT> &, const u32 (*)[8], const unsigned char *, u32, const u32 *, f16_t *) {}
-};
+// The weight operand of k-step S of a lane's row: (q - z) 2^-9, or q - z where rests of zero points are taken off too (2^-9
+// of those may be none of fp16's numbers).
+template <int BITS, bool REST, int S>
+__device__ __forceinline__ h8_t wide_weights(const u32 *wd, u32 nz) {
+  const h8_t v = a_small<BITS, S>(wd, nz);
+  return REST ? v * (_Float16)512 : v;
+}
 
-// The columns [p0, p1) in blocks of 128 of the workgroup's tile, zero points integers of at most 1024 and step sizes finite
-// and not zero: on return acc holds, per row tile and token tile of the wave, the scaled sums.
-template <int BITS, bool GROUPED, int NT>
-__device__ __forceinline__ void wide_fast(const WideArgs &a, unsigned char *lds, int rg, int n0, int p0, int p1, f16_t *acc) {
+// The columns [p0, p1) in blocks of 128 of the workgroup's tile: on return tot holds, per row tile and token tile of the
+// wave, the scaled sums, a lane having one row (lane mod 32) and sixteen tokens.
+template <int BITS, bool GROUPED, bool REST, int NT>
+__device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *lds, int rg, int n0, int p0, int p1, f16_t *tot) {
   constexpr int kBuf = NT * 512;                // 16-byte units of a buffer
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = lane >> 5, b0 = 2 * p0, b1 = min(2 * p1, a.nblk);
+  constexpr bool kRolled = GROUPED;             // one body for even and odd blocks, whose codes come late and into the same registers
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b0 = 2 * p0, b1 = min(2 * p1, a.nblk);
   const u32 ldsb = lds_address(lds);
-  float *splane = reinterpret_cast<float *>(lds + wide_planes(NT)) + w * 128, *zplane = splane + 64;
 
-  // ---- x: this wave fetches 8 NT tokens of the tile, four per load (a quarter wave per row) -----
-  const int fn = w * 8 * NT + (lane >> 4);      // + 4i
-  u32 xoff[2 * NT];
-#pragma unroll
-  for (int i = 0; i < 2 * NT; ++i) {
-    const int n = fn + 4 * i;
-    int gn = n0 + n;
-    if (gn > a.ntok - 1) gn = a.ntok - 1;       // tokens past the end: any row will do, their results are dropped
-    xoff[i] = (u32)(gn - n0) * (u32)(a.pitch * 2) + (u32)(((lane & 15) ^ (n & 15)) * 16);
-  }
+  // What follows from the lane is worked out anew where it is used (here()): kept, it does not fit the registers of 128 tokens.
+  auto here = [&]() __attribute__((always_inline)) {
+    u32 t = threadIdx.x;
+    if (GROUPED && NT == 4) asm volatile("" : "+v"(t));
+    return t & 63;
+  };
+  // ---- x: this wave fetches 8 NT tokens of the tile, four per load (a quarter wave per row); row n's units lie at ^ n.  (Sixteen
+  // rows of 64 bytes per load and units in order would save the exclusive or per read: 4096 x 4096, 2048 tokens, 75 -> 82 us) ----
   const unsigned char *xtile = reinterpret_cast<const unsigned char *>(a.x) + (size_t)n0 * a.pitch * 2;
+  const u32 pitch2 = (u32)(a.pitch * 2);
+  const bool whole = n0 + 32 * NT <= a.ntok;
   auto fetch_x = [&](int b, int buf) __attribute__((always_inline)) {
     const unsigned char *src = xtile + (size_t)b * 256;
-    const int left = a.d_in - b * 128;          // columns past the end of the row: unit 0 instead, cleared below
-    const u32 dst = ldsb + (u32)(buf * kBuf + w * 8 * NT * 16) * 16u;
-    if (left >= 128) {
+    const int left = a.d_in - b * 128;
+    const u32 dst = ldsb + (u32)(buf * kBuf + w * 8 * NT * 16) * 16u, l = here();
+    const u32 unit = (l & 15) ^ (l >> 4);       // of the first row; 4i rows on: ^ 4i
+    if (whole && left >= 128) {
+      const u32 xrow = (u32)(w * 8 * NT + (int)(l >> 4)) * pitch2;
 #pragma unroll
-      for (int i = 0; i < 2 * NT; ++i) load_to_lds(src, xoff[i], dst + i * 1024u);
+      for (int i = 0; i < 2 * NT; ++i)
+        load_to_lds(src + (size_t)(4 * i) * pitch2, xrow + ((unit ^ (4 * i & 15)) << 4), dst + i * 1024u);
     } else {
+      // tokens past the end: any row will do, their results are dropped; columns past the end of the row: unit 0 instead,
+      // cleared below
 #pragma unroll
       for (int i = 0; i < 2 * NT; ++i) {
-        const int oct = (lane & 15) ^ ((fn + 4 * i) & 15);
-        load_to_lds(src, oct * 8 < left ? xoff[i] : xoff[i] - (u32)oct * 16u, dst + i * 1024u);
+        const u32 n = (u32)min(w * 8 * NT + 4 * i + (int)(l >> 4), a.ntok - 1 - n0), oct = unit ^ (4 * i & 15);
+        load_to_lds(src, n * pitch2 + ((int)oct * 8 < left ? oct << 4 : 0u), dst + i * 1024u);
       }
     }
   };
   // ---- codes and scales --------------------------------------------------------------------------------
   u32 cb[2][2][8];
   u32 szr[2], mkr[2];     // scale and zero point of a row; weak mask of 32 columns (a quarter wave each)
-  const int rt0 = min(rg * 8 + 2 * w, a.n_rt - 1), rt1 = min(rg * 8 + 2 * w + 1, a.n_rt - 1);
-  const int szrow = min((rg * 8 + 2 * w) * 32 + lane, a.d_out_pad - 1);
+  const int rt0 = min(rg * 8 + 2 * w, a.n_rt - 1), rt1 = min(rg * 8 + 2 * w + 1, a.n_rt - 1), row0 = (rg * 8 + 2 * w) * 32;
   constexpr int CH = BITS == 3 ? 3 : 4;
   const unsigned char *tile0 = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)(rt0 * a.nbp) * (CH * 1024);
   const unsigned char *tile1 = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)(rt1 * a.nbp) * (CH * 1024);
-  const u32 *mask32 = reinterpret_cast<const u32 *>(a.wmask) + (lane >> 4);
   int fg = b0 / a.bpg, frem = b0 - fg * a.bpg;      // group of the block that is fetched
   typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-  // codes of block H of pair bp (3-bit: whole and half chunks) and the scales of its group
-  auto fetch_codes = [&](int bp, auto tag) __attribute__((always_inline)) {
-    constexpr int H = decltype(wide_buf_index(tag))::value;
+  // codes of block b (3-bit: one and a half of the three chunks of a pair of blocks) and the scales of its group
+  auto fetch_codes = [&](int b, auto tag) __attribute__((always_inline)) {
+    constexpr int R = decltype(tag)::value;
+    const u32 l = here();
+    u32 unit = l * 16u;         // (opaque: as a shift of the lane it becomes part of 64-bit address arithmetic)
+    asm volatile("" : "+v"(unit));
+    const bool odd = kRolled ? (b & 1) != 0 : R != 0;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const unsigned char *tile = (t ? tile1 : tile0) + (u32)bp * (u32)(CH * 1024) + lane * 16;
-      u32 *dst = cb[H][t];
-      const u32x4 v = *reinterpret_cast<const u32x4 *>(tile + (H ? 2048 : 0));
+      const unsigned char *tile = (t ? tile1 : tile0) + (u32)(b >> 1) * (u32)(CH * 1024);
+      u32 *dst = cb[R][t];
       if (BITS == 4) {
-        const u32x4 u = *reinterpret_cast<const u32x4 *>(tile + (H ? 3072 : 1024));
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(tile + (odd ? 2048u : 0u) + unit);
+        const u32x4 u = *reinterpret_cast<const u32x4 *>(tile + (odd ? 3072u : 1024u) + unit);
         dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
         dst[4] = u.x; dst[5] = u.y; dst[6] = u.z; dst[7] = u.w;
       } else {
-        const u32x2 u = *reinterpret_cast<const u32x2 *>(tile + 1024 + (H ? 8 : 0));
-        if (H == 0) {
-          dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w; dst[4] = u.x; dst[5] = u.y;
-        } else {
-          dst[0] = u.x; dst[1] = u.y; dst[2] = v.x; dst[3] = v.y; dst[4] = v.z; dst[5] = v.w;
+        const u32 at[3] = {odd ? 1032u : 0u, odd ? 2048u : 8u, odd ? 2056u : 1024u};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const u32x2 v = *reinterpret_cast<const u32x2 *>(tile + at[c] + unit);
+          dst[2 * c] = v.x;
+          dst[2 * c + 1] = v.y;
         }
-        dst[6] = dst[7] = 0u;
       }
     }
-    if (GROUPED) szr[H] = a.sz[(u32)min(fg, a.n_groups - 1) * (u32)a.d_out_pad + szrow];
-    mkr[H] = mask32[min(2 * bp + H, a.nblk - 1) * 4];
+    if (GROUPED) szr[R] = (a.sz + (size_t)min(fg, a.n_groups - 1) * (u32)a.d_out_pad)[(u32)min(row0 + (int)l, a.d_out_pad - 1)];
+    mkr[R] = (reinterpret_cast<const u32 *>(a.wmask) + min(b, a.nblk - 1) * 4)[l >> 4];
     const bool wrap = frem + 1 == a.bpg;
     fg += wrap ? 1 : 0;
     frem = wrap ? 0 : frem + 1;
   };
 
-  u32 nz[2];              // -z 2^-9 of the lane's two rows
-  float last;             // step size of the lane's row in the blocks so far: what the accumulators are in units of,
-  float over = 0.f;       // and what the ratios' roundings have left of it
-  float ratio = 1.f, was = 1.f;
-  auto take_sz = [&](u32 v, bool first) __attribute__((always_inline)) {
-    const float s = half_lo(v);
-    if (GROUPED) {
-      // (last + over) / s
-      float rc = __builtin_amdgcn_rcpf(s);
-      rc = __builtin_fmaf(__builtin_fmaf(-s, rc, 1.f), rc, rc);
-      const float r = last * rc;
-      ratio = first ? 1.f : __builtin_fmaf(__builtin_fmaf(-r, s, last) + over, rc, r);
-      was = first ? s : last;
-      splane[lane] = ratio;
+  u32 nz[2], nr[2];       // of the lane's two rows, in both halves: -z 2^-9, z rounded where it is no integer; what that lacks
+  float sc[2];            // their step sizes
+  auto take_sz = [&](u32 v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const u32 u = (u32)__builtin_amdgcn_ds_bpermute((int)(t * 32 + (here() & 31)) * 4, (int)v);
+      const float z = half_hi(u), z1 = REST ? __builtin_amdgcn_fmed3f(__builtin_rintf(z), -1024.f, 1024.f) : z;
+      sc[t] = REST ? half_lo(u) : half_lo(u) * 0x1p9f;
+      nz[t] = pk_dup(z1 * -0x1p-9f);
+      if (REST) nr[t] = pk_dup(z1 - z);
     }
-    last = s;
-    zplane[lane] = half_hi(v) * -0x1p-9f;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) nz[t] = pk_dup(zplane[t * 32 + (lane & 31)]);
   };
-  // what the ratio's rounding leaves, in units of the new step size; not in front of the accumulators' multiplications, which wait
-  // for the ratio (1 % of the whole there)
-  auto carry = [&]() __attribute__((always_inline)) { over = (__builtin_fmaf(-ratio, last, was) + over) * __builtin_amdgcn_rcpf(ratio); };
+  f16_t zero, part[GROUPED && REST ? 4 : 1];
 #pragma unroll
-  for (int i = 0; i < 2 * NT; ++i)
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-  auto scale_acc = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f4_t sc = *reinterpret_cast<const f4_t *>(splane + t * 32 + 8 * q + 4 * kg);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < NT; ++i) acc[t * NT + i][4 * q + e] *= sc[e];
-      }
-  };
+  for (int i = 0; i < 2 * NT; ++i) tot[i] = zero;
 
-  const u32 xsw = (u32)(lane & 31) * 256u + (u32)((kg ^ (lane & 15)) << 4);
-  last = 1.f;
-  if (!GROUPED) take_sz(a.sz[szrow], true);
+  if (!GROUPED) take_sz(a.sz[min(row0 + (int)here(), a.d_out_pad - 1)]);
   fetch_x(b0, 0);
-  fetch_codes(p0, WideBuf<0>{});
+  fetch_codes(b0, Int<0>{});
 
   auto step = [&](int b, auto tag) __attribute__((always_inline)) {
-    constexpr int J = decltype(wide_buf_index(tag))::value;
+    constexpr int J = decltype(tag)::value;     // registers, and where the loop is not rolled the buffer too, of the block
+    const int buf = kRolled ? b & 1 : J;
     wait_loads<0>();            // this wave's part of block b is in LDS, its codes are in registers
     // (said here to the compiler, which does not count the direct loads: its own wait, wherever a register of these is used
     // first, would be behind the next block's direct loads and wait for them too)
@@ -365,7 +257,7 @@ __device__ __forceinline__ void wide_fast(const WideArgs &a, unsigned char *lds,
     asm volatile("" : "+v"(mkr[J]));
     const int left = a.d_in - b * 128;
     if (__ballot(mkr[J] != 0u) != 0ull || left < 128) {
-      const int d = lane >> 4;
+      const int l = (int)here(), d = l >> 4;
       u32 m = mkr[J];
       const int lv = left - 32 * d;
       if (lv < 32) m |= lv <= 0 ? 0xffffffffu : 0xffffffffu << lv;
@@ -374,223 +266,160 @@ __device__ __forceinline__ void wide_fast(const WideArgs &a, unsigned char *lds,
         m &= m - 1;
 #pragma unroll
         for (int i = 0; i < NT / 2; ++i) {
-          const int n = w * 8 * NT + 16 * i + (lane & 15);
-          _Float16 *row = reinterpret_cast<_Float16 *>(lds + (J * kBuf + n * 16) * 16);
+          const int n = w * 8 * NT + 16 * i + (l & 15);
+          _Float16 *row = reinterpret_cast<_Float16 *>(lds + (buf * kBuf + n * 16) * 16);
           row[(((col >> 3) ^ (n & 15)) << 3) + (col & 7)] = (_Float16)0;
         }
       }
     }
     __syncthreads();
-    // what the first k-step needs of LDS is asked for before the next block's loads go out
-    const unsigned char *xb = lds + J * kBuf * 16;
-    FastOps<NT> first;
-    fast_x<NT, 0>(first, xb, xsw);
-    if (GROUPED) take_sz(szr[J], b == b0);
-    fetch_x(min(b + 1, b1 - 1), J ^ 1);
-    fetch_codes(min((b + 1) >> 1, p1 - 1), WideBuf<(J ^ 1)>{});
-    fast_codes<BITS, NT, 0>(first, cb[J], nz);
-    if (GROUPED) {
-      scale_acc();
-      __builtin_amdgcn_sched_barrier(0);
-      carry();
-    }
-    FastSteps<BITS, NT, 0>::run(first, cb[J], xb, xsw, nz, acc);
-  };
-  int b = b0;
-  while (b + 2 <= b1) {
-    step(b, WideBuf<0>{});
-    step(b + 1, WideBuf<1>{});
-    b += 2;
-  }
-  if (b < b1) step(b, WideBuf<0>{});
-  splane[lane] = last * 0x1p9f;
-  scale_acc();
-  wait_loads<0>();            // the loads past the end must not land in what the buffers are used for next
-  __syncthreads();
-}
-
-// The columns [b0, b1) in blocks of 128 of the workgroup's tile: on return tot holds, per row tile and token
-// tile of the wave, the scaled sums (grouped) or the raw ones.
-template <int BITS, bool GROUPED, bool REST, int PLANES>
-__device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *lds, int tid, int rg, int n0, int p0, int p1, f16_t *tot) {
-  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = lane >> 5, b0 = 2 * p0, b1 = min(2 * p1, a.nblk);
-  const u32 ldsb = lds_address(lds);
-  float *splane = reinterpret_cast<float *>(lds + PLANES) + w * 128;
-  u32 *zplane = reinterpret_cast<u32 *>(splane + 64);
-
-  // ---- x: this wave fetches tokens 16w .. 16w+15 of the tile, four per load (a quarter wave per row) -----
-  const int fn = w * 16 + (lane >> 4);          // + 4i
-  u32 xoff[4];
-  int xoct[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int n = fn + 4 * i;
-    int gn = n0 + n;
-    if (gn > a.ntok - 1) gn = a.ntok - 1;       // tokens past the end: any row will do, their results are dropped
-    xoct[i] = (lane & 15) ^ (n & 15);
-    xoff[i] = (u32)(gn - n0) * (u32)(a.pitch * 2) + (u32)xoct[i] * 16u;
-  }
-  const unsigned char *xtile = reinterpret_cast<const unsigned char *>(a.x) + (size_t)n0 * a.pitch * 2;
-  auto fetch_x = [&](int b, int buf) __attribute__((always_inline)) {
-    const unsigned char *src = xtile + (size_t)b * 256;
-    const int left = a.d_in - b * 128;          // columns past the end of the row: unit 0 instead, cleared below
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const u32 off = xoct[i] * 8 < left ? xoff[i] : xoff[i] - (u32)xoct[i] * 16u;
-      load_to_lds(src, off, ldsb + (u32)(buf * kWideBufUnits + (w * 16 + 4 * i) * 16) * 16u);
-    }
-  };
-  // ---- codes and scales --------------------------------------------------------------------------------
-  u32 cb[2][2][8];
-  u32 szr[2], mkr[2];     // scale and zero point of a row; weak mask of 32 columns (a quarter wave each)
-  const int rt0 = min(rg * 8 + 2 * w, a.n_rt - 1), rt1 = min(rg * 8 + 2 * w + 1, a.n_rt - 1);
-  const int szrow = min((rg * 8 + 2 * w) * 32 + lane, a.d_out_pad - 1);
-  constexpr int CH = BITS == 3 ? 3 : 4;
-  const unsigned char *tile0 = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)(rt0 * a.nbp) * (CH * 1024);
-  const unsigned char *tile1 = reinterpret_cast<const unsigned char *>(a.codes) + (size_t)(rt1 * a.nbp) * (CH * 1024);
-  const u32 *mask32 = reinterpret_cast<const u32 *>(a.wmask) + (lane >> 4);
-  int fg = b0 / a.bpg, frem = b0 - fg * a.bpg;      // group of the block that is fetched
-  typedef u32 u32x2 __attribute__((ext_vector_type(2)));
-  // codes of block H of pair bp (3-bit: whole and half chunks) and the scales of its group
-  auto fetch_codes = [&](int bp, auto tag) __attribute__((always_inline)) {
-    constexpr int H = decltype(wide_buf_index(tag))::value;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const unsigned char *tile = (t ? tile1 : tile0) + (u32)bp * (u32)(CH * 1024) + lane * 16;
-      u32 *dst = cb[H][t];
-      const u32x4 v = *reinterpret_cast<const u32x4 *>(tile + (H ? 2048 : 0));
-      if (BITS == 4) {
-        const u32x4 u = *reinterpret_cast<const u32x4 *>(tile + (H ? 3072 : 1024));
-        dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-        dst[4] = u.x; dst[5] = u.y; dst[6] = u.z; dst[7] = u.w;
-      } else {
-        const u32x2 u = *reinterpret_cast<const u32x2 *>(tile + 1024 + (H ? 8 : 0));
-        if (H == 0) {
-          dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w; dst[4] = u.x; dst[5] = u.y;
-        } else {
-          dst[0] = u.x; dst[1] = u.y; dst[2] = v.x; dst[3] = v.y; dst[4] = v.z; dst[5] = v.w;
+    const u32 xl = here();
+    // (the dynamic LDS is all there is and begins at 0, so that the exchange of units is one of address bits)
+    u32 xsw = ldsb + (kRolled ? buf * kBuf * 16 : 0) + (xl & 31) * 256u + (((xl >> 5) ^ (xl & 15)) << 4);
+    auto x_of = [&](int i, int S) __attribute__((always_inline)) {
+      if (GROUPED && NT == 4) asm volatile("" : "+v"(xsw));
+      const u32 at = (xsw ^ (u32)(S << 5)) + (u32)((kRolled ? 0 : buf * kBuf * 16) + i * 32 * 256);
+      return *reinterpret_cast<const __attribute__((address_space(3))) h8_t *>(at);
+    };
+    const int next = min(b + 1, 2 * p1 - 1);
+    if constexpr (GROUPED && !REST) {
+      // A token tile at a time.  The block's weight operands are made with the first one and kept for the others; the next
+      // block's codes are asked for when those begin to be used up (a tile earlier, or a k-step, does not fit the registers).
+      // The second row tile is one k-step behind, so that the matrix instructions of one run under the multiply-adds of the
+      // other (16384 x 4096, a workgroup per compute unit: 286 -> 275 us).  The empty blocks keep the compiler from moving a
+      // chain of pure operations past the scheduling barriers, which costs its sums' registers.
+      h8_t xp, x0 = x_of(0, 0), av[2][8];
+      f16_t s0, s1;
+      take_sz(szr[J]);
+      fetch_x(min(b + 1, b1 - 1), buf ^ 1);
+      each<8 * NT + 1>([&](auto step_q) __attribute__((always_inline)) {
+        constexpr int q = decltype(step_q)::value, i = q >> 3, S = q & 7, ip = (q - 1) >> 3, Sp = (q - 1) & 7;
+        h8_t x1;
+        if constexpr (q + 1 < 8 * NT) x1 = x_of((q + 1) >> 3, (q + 1) & 7);
+        if constexpr (i == NT - 1 && S == 1) fetch_codes(next, Int<0>{});
+        if constexpr (q < 8) av[0][S] = wide_weights<BITS, false, S>(cb[J][0], nz[0]);
+        if constexpr (q > 0 && q <= 8) av[1][Sp] = wide_weights<BITS, false, Sp>(cb[J][1], nz[1]);
+        if constexpr (q > 0) {
+          s1 = mma(xp, av[1][Sp], Sp == 0 ? zero : s1);
+          asm volatile("" : "+v"(s1));
         }
-        dst[6] = dst[7] = 0u;
-      }
-    }
-    // The mask last: the compiler does not count the direct loads, and its wait for the mask covers every load before it,
-    // so that the scale, which is used behind the next block's direct loads, does not wait for those (5120 -> 13824 ->
-    // 5120, 4-bit, 777 tokens: 312 -> 302 us; 4096 -> 16384 -> 4096, 3-bit, 2048 tokens: 605 -> 598)
-    if (GROUPED) szr[H] = a.sz[(u32)min(fg, a.n_groups - 1) * (u32)a.d_out_pad + szrow];
-    mkr[H] = mask32[min(2 * bp + H, a.nblk - 1) * 4];
-    const bool wrap = frem + 1 == a.bpg;
-    fg += wrap ? 1 : 0;
-    frem = wrap ? 0 : frem + 1;
-  };
-
-  Magic M;
-  M.init();
-  u32 nb[2][8], nr[2];
-  // scale and zero point of the wave's 64 rows (a lane each) to LDS; each lane takes the zero points of its
-  // two rows back and makes the constants that turn the mask-and-OR operand into q - z
-  auto take_sz = [&](u32 v) __attribute__((always_inline)) {
-    const float z = half_hi(v);
-    splane[lane] = half_lo(v);
-    reinterpret_cast<float *>(zplane)[lane] = z;
+        if constexpr (q > 0 && S == 0) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const float zt = reinterpret_cast<float *>(zplane)[t * 32 + (lane & 31)];
-      const float z1 = __builtin_amdgcn_fmed3f(__builtin_rintf(zt), -1024.f, 1024.f);
-      const u32 zz = pk_dup(-z1);
-#pragma unroll
-      for (int o = 0; o < 8; ++o) nb[t][o] = pk_sub(zz, M.m[o]);
-      nr[t] = pk_dup(z1 - zt);
-    }
-  };
-  f16_t acc[GROUPED ? 4 : 1], zero;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) tot[i] = zero;
-
-  const u32 xsw = (u32)(lane & 31) * 256u + (u32)((kg ^ (lane & 15)) << 4);
-  if (!GROUPED) take_sz(a.sz[szrow]);
-  fetch_x(b0, 0);
-  fetch_codes(p0, WideBuf<0>{});
-
-  auto step = [&](int b, auto tag) __attribute__((always_inline)) {
-    constexpr int J = decltype(wide_buf_index(tag))::value;
-    wait_loads<0>();            // this wave's part of block b is in LDS, its codes are in registers
-    const int left = a.d_in - b * 128;
-    if (__ballot(mkr[J] != 0u) != 0ull || left < 128) {
-      const int d = lane >> 4, n = w * 16 + (lane & 15);
-      u32 m = mkr[J];
-      const int lv = left - 32 * d;
-      if (lv < 32) m |= lv <= 0 ? 0xffffffffu : 0xffffffffu << lv;
-      _Float16 *row = reinterpret_cast<_Float16 *>(lds + (J * kWideBufUnits + n * 16) * 16);
-      while (m) {
-        const int col = 32 * d + __builtin_ctz(m);
-        m &= m - 1;
-        row[(((col >> 3) ^ (n & 15)) << 3) + (col & 7)] = (_Float16)0;
-      }
-    }
-    __syncthreads();
-    fetch_x(min(b + 1, b1 - 1), J ^ 1);
-    fetch_codes(min((b + 1) >> 1, p1 - 1), WideBuf<(J ^ 1)>{});
-    if (GROUPED) take_sz(szr[J]);
-    const unsigned char *xb = lds + J * kWideBufUnits * 16;
-    if constexpr (GROUPED) {
-      __builtin_amdgcn_sched_barrier(0);
-      WideSteps<BITS, true, REST, 0>::run(wide_ops<BITS, 0>(cb[J], xb, xsw, M, nb), cb[J], xb, xsw, M, nb, nr, acc, zero);
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f4_t sc = *reinterpret_cast<const f4_t *>(splane + t * 32 + 8 * q + 4 * kg);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-              tot[t * 2 + nt][4 * q + e] = __builtin_fmaf(sc[e], acc[t * 2 + nt][4 * q + e], tot[t * 2 + nt][4 * q + e]);
+          for (int r = 0; r < 16; ++r) tot[ip][r] = __builtin_fmaf(s0[r], sc[0], tot[ip][r]);
+          asm volatile("" : "+v"(tot[ip]));
+          __builtin_amdgcn_sched_barrier(0);
         }
+        if constexpr (q < 8 * NT) {
+          s0 = mma(x0, av[0][S], S == 0 ? zero : s0);
+          asm volatile("" : "+v"(s0));
+        }
+        if constexpr (q > 0 && S == 0) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) tot[NT + ip][r] = __builtin_fmaf(s1[r], sc[1], tot[NT + ip][r]);
+          asm volatile("" : "+v"(tot[NT + ip]));
+        }
+        xp = x0;
+        x0 = x1;
+        __builtin_amdgcn_sched_barrier(0);
+      });
     } else {
-      WideSteps<BITS, false, REST, 0>::run(wide_ops<BITS, 0>(cb[J], xb, xsw, M, nb), cb[J], xb, xsw, M, nb, nr, tot, zero);
+      // KT token tiles at a time share a weight operand; without groups the sums go on from block to block.  With groups
+      // (and rests) the operands are made again for the next tiles: kept beside two tiles' sums they do not fit.
+      constexpr int KT = GROUPED ? 2 : NT;
+      h8_t xv[KT], av[2];
+#pragma unroll
+      for (int i = 0; i < KT; ++i) xv[i] = x_of(i, 0);
+      if (GROUPED) take_sz(szr[J]);
+      fetch_x(min(b + 1, b1 - 1), buf ^ 1);
+      if (!kRolled) fetch_codes(next, Int<(J ^ 1)>{});
+#pragma unroll
+      for (int t = 0; t < 2; ++t) av[t] = wide_weights<BITS, REST, 0>(cb[J][t], nz[t]);
+      each<8 * (NT / KT)>([&](auto step_q) __attribute__((always_inline)) {
+        constexpr int q = decltype(step_q)::value, i0 = (q >> 3) * KT, S = q & 7, qn = q + 1 < 8 * (NT / KT) ? q + 1 : q, Sn = qn & 7;
+        h8_t xn[KT];
+        if constexpr (qn > q) {
+#pragma unroll
+          for (int i = 0; i < KT; ++i) xn[i] = x_of((qn >> 3) * KT + i, Sn);
+        }
+        if constexpr (kRolled && qn == q) fetch_codes(next, Int<0>{});
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < KT; ++i) {
+            f16_t &c = GROUPED ? part[t * KT + i] : tot[t * NT + i];
+            c = mma(xv[i], av[t], GROUPED && S == 0 ? zero : c);
+          }
+        if (REST) {
+          asm volatile("" : "+v"(nr[0]), "+v"(nr[1]));
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < KT; ++i) {
+              f16_t &c = GROUPED ? part[t * KT + i] : tot[t * NT + i];
+              c = mma(xv[i], __builtin_bit_cast(h8_t, (u32x4){nr[t], nr[t], nr[t], nr[t]}), c);
+            }
+        }
+        if constexpr (qn > q) {
+          // (or the compiler keeps the first token tiles' operands for the next ones)
+          if constexpr (Sn == 0) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+              for (int c = 0; c < (BITS == 3 ? 6 : 8); ++c) asm volatile("" : "+v"(cb[J][t][c]));
+          }
+#pragma unroll
+          for (int t = 0; t < 2; ++t) av[t] = wide_weights<BITS, REST, Sn>(cb[J][t], nz[t]);
+#pragma unroll
+          for (int i = 0; i < KT; ++i) xv[i] = xn[i];
+        }
+        if constexpr (GROUPED) {
+#pragma unroll
+          for (int i = 0; i < 2 * KT; ++i) asm volatile("" : "+v"(part[i]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (GROUPED && S == 7) {
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < KT; ++i) {
+#pragma unroll
+              for (int r = 0; r < 16; ++r)
+                tot[t * NT + i0 + i][r] = __builtin_fmaf(part[t * KT + i][r], sc[t], tot[t * NT + i0 + i][r]);
+              asm volatile("" : "+v"(tot[t * NT + i0 + i]));
+            }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      });
     }
   };
-  int b = b0;
-  while (b + 2 <= b1) {
-    step(b, WideBuf<0>{});
-    step(b + 1, WideBuf<1>{});
-    b += 2;
+  if constexpr (kRolled) {
+    for (int b = b0; b < b1; ++b) step(b, Int<0>{});
+  } else {
+    int b = b0;
+    while (b + 2 <= b1) {
+      step(b, Int<0>{});
+      step(b + 1, Int<1>{});
+      b += 2;
+    }
+    if (b < b1) step(b, Int<0>{});
   }
-  if (b < b1) step(b, WideBuf<0>{});
   if (!GROUPED) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int i = 0; i < 2 * NT; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f4_t sc = *reinterpret_cast<const f4_t *>(splane + t * 32 + 8 * q + 4 * kg);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt) tot[t * 2 + nt][4 * q + e] *= sc[e];
-      }
+      for (int r = 0; r < 16; ++r) tot[i][r] *= sc[i / NT];
   }
   wait_loads<0>();            // the loads past the end must not land in what the buffers are used for next
   __syncthreads();
-}
-
-// A result of wide_fast in groups as the rounding to fp16 takes it: to 19 bits.  One column by itself gives s (q - z) x, 19 bits at
-// most where x is a power of two, which often lies on a tie of fp16; the multiplications by the ratios leave some units of 2^-24
-// there, which would break the tie either way.  To a sum that is not short it adds 2^-19 under fp16's own 2^-11.
-__device__ __forceinline__ float settled(float v) {
-  const u32 u = __builtin_bit_cast(u32, v), r = (u + 16u) & ~31u;
-  return __builtin_bit_cast(float, (u & 0x7f800000u) == 0x7f800000u ? u : r);
 }
 
 // What follows the columns: the weak columns of the first column range, then y or a partial result.  NT token tiles from
-// token n0 on, tot in the order of wide_fast; every wave of the workgroup is past its reads of the staging buffers.
-// SETTLE: they come from ratios (settled).
-template <int NT, bool SETTLE>
-__device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *lds, int tid, int rg, int n0, int s, f16_t *tot) {
+// token n0 on, tot in the order of wide_columns; every wave of the workgroup is past its reads of the staging buffers.
+template <int NT>
+__device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *lds, int rg, int n0, int s, f16_t *tot) {
   constexpr int kBuf = NT * 512;
-  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 5;
   // ---- weak columns: 128 at a time, the gathered activations in the first buffer, each wave's weights (of one
   // row tile after the other) behind it ----
   if (s == 0) {
@@ -628,7 +457,7 @@ __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *ld
           for (int i = 0; i < NT; ++i) bv[i] = *reinterpret_cast<const h8_t *>(xb + i * 32 * 256 + off);
           const h8_t av = __builtin_bit_cast(h8_t, 16 * c + u < a.kunits ? wv : zero4);
 #pragma unroll
-          for (int i = 0; i < NT; ++i) tot[NT * t + i] = mma(av, bv[i], tot[NT * t + i]);
+          for (int i = 0; i < NT; ++i) tot[NT * t + i] = mma(bv[i], av, tot[NT * t + i]);
         }
         // the next row tile's weights go where these were read from
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -637,7 +466,6 @@ __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *ld
     __syncthreads();
   }
 
-  typedef _Float16 h4_t __attribute__((ext_vector_type(4)));
   _Float16 *out = reinterpret_cast<_Float16 *>(lds);
 #pragma unroll
   for (int half = 0; half < NT / 2; ++half, n0 += kWideTokens) {
@@ -657,12 +485,8 @@ __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *ld
     for (int i = 0; i < 4; ++i) {
       const f16_t &v = tot[(i >> 1) * NT + 2 * half + (i & 1)];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        h4_t hv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) hv[e] = (_Float16)(SETTLE ? settled(v[4 * q + e]) : v[4 * q + e]);
-        *reinterpret_cast<h4_t *>(out + ((i & 1) * 32 + (lane & 31)) * kWideOutPitch + w * 64 + (i >> 1) * 32 + 8 * q + 4 * kg) = hv;
-      }
+      for (int r = 0; r < 16; ++r)
+        out[((i & 1) * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * kWideOutPitch + w * 64 + (i >> 1) * 32 + (lane & 31)] = (_Float16)v[r];
     }
     __syncthreads();
     const int row0 = rg * kWideRows, ntok = min(kWideTokens, a.ntok - n0);
@@ -685,32 +509,22 @@ __global__ __launch_bounds__(256, 2) void owq_wide_mma(const WideArgs a) {
   const int tiles = a.n_rg * n_wt, s = lin / tiles, rem = lin - s * tiles;
   const int g4 = rem / (4 * n_wt), gh = min(4, a.n_rg - 4 * g4), r2 = rem - g4 * 4 * n_wt;
   const int tt = r2 / gh, rg = 4 * g4 + (r2 - tt * gh);
-  int n0 = tt * 32 * NT;
+  const int n0 = tt * 32 * NT;
   const int p0 = s * a.nbp / a.split, p1 = (s + 1) * a.nbp / a.split;
 
-  int general = 0;
-  for (int i = 0; i < a.n_fl; ++i) general |= a.flags[rg * a.n_fl + i];
-  if (general == 0) {
-    f16_t acc[2 * NT];
-    wide_fast<BITS, GROUPED, NT>(a, lds, rg, n0, p0, p1, acc);
-    wide_finish<NT, GROUPED>(a, lds, (int)threadIdx.x, rg, n0, s, acc);
-    return;
-  }
-  for (int half = 0; half < NT / 2 && n0 < a.ntok; ++half, n0 += kWideTokens) {
-    f16_t tot[4];
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));           // what is made from it is made again for each half: kept over the loop it does not fit the registers
-    if (half > 0) __syncthreads();          // the previous half's result has been read from where the next blocks go
-    wide_columns<BITS, GROUPED, true, wide_planes(NT)>(a, lds, tid, rg, n0, p0, p1, tot);
-    wide_finish<2, false>(a, lds, tid, rg, n0, s, tot);
-  }
+  int rest = 0;
+  for (int i = 0; i < a.n_fl; ++i) rest |= a.flags[rg * a.n_fl + i];
+  f16_t tot[2 * NT];
+  if (rest != 0)
+    wide_columns<BITS, GROUPED, true, NT>(a, lds, rg, n0, p0, p1, tot);
+  else
+    wide_columns<BITS, GROUPED, false, NT>(a, lds, rg, n0, p0, p1, tot);
+  wide_finish<NT>(a, lds, rg, n0, s, tot);
 }
 
 // Adds the partial results of a tile in a fixed order: one workgroup per 64 rows x 64 tokens (what one wave of
 // owq_wide_mma wrote), a wave per accumulator tile.
-// flags: those of owq_wide_prep where the accumulators were in units of step sizes, or nullptr.
-__global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 *y, const int *flags, int n_fl, int n_tt, int split, int ntok,
-                                                    int d_out) {
+__global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 *y, int n_tt, int split, int ntok, int d_out) {
   __shared__ __align__(16) _Float16 out[64][72];
   const int tid = threadIdx.x, lane = tid & 63, i = tid >> 6;
   const int w = blockIdx.x & 3, tile = blockIdx.x >> 2, rg = tile / n_tt, tt = tile - rg * n_tt;
@@ -724,13 +538,11 @@ __global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 
   for (int s = 1; s < split; ++s)
 #pragma unroll
     for (int q = 0; q < 4; ++q) sum[q] += src[(size_t)s * kWideSlotUnits + q * 64];
-  const int n = (i & 1) * 32 + (lane & 31), r = (i >> 1) * 32 + 4 * (lane >> 5);
-  int general = flags == nullptr;
-  for (int f = 0; f < n_fl && flags != nullptr; ++f) general |= flags[rg * n_fl + f];
+  const int n = (i & 1) * 32 + 4 * (lane >> 5), r = (i >> 1) * 32 + (lane & 31);
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) out[n][r + 8 * q + e] = (_Float16)(general ? sum[q][e] : settled(sum[q][e]));
+    for (int e = 0; e < 4; ++e) out[n + 8 * q + e][r] = (_Float16)sum[q][e];
   __syncthreads();
   const int nn = min(64, ntok - n0);
   for (int e = tid; e < nn * 8; e += 256) {
@@ -756,8 +568,9 @@ constexpr float kWideLaunchUs = 14.f;     // start, first loads and end of a sec
 WidePlan wide_plan(bool grouped, int n_rg, int n_tt, int nbp, int64_t slots) {
   WidePlan best{2, 1, 1e30f};
   if (n_tt == 0) return WidePlan{2, 1, 0.f};
-  // us per pair of blocks: up to 128 workgroups, one and two on every compute unit.  Fitted to 352 whole calls (2048 to 13824
-  // columns, 2904 to 13824 rows, 160 to 1702 tokens, 1 to 6 ranges; 4.3 % root mean square).
+  // us per pair of blocks: up to 128 workgroups, one and two on every compute unit, as costs to choose by.  30 whole calls (2048
+  // to 16384 columns, 2048 to 13824 rows, 100 to 2048 tokens) took 0.94 to 1.19 of this and 14 us around it.  Row groups whose
+  // zero points are no integers have twice the matrix work, which the host does not know of.
   constexpr float kPair[4][3] = {{1.65f, 1.85f, 3.7f}, {2.7f, 3.0f, 6.8f}, {2.13f, 2.3f, 4.2f}, {3.5f, 3.75f, 7.25f}};
   for (int nt = 2; nt <= 4; nt += 2) {
     const float *c = kPair[(grouped ? 2 : 0) + (nt == 4 ? 1 : 0)];
@@ -817,9 +630,8 @@ int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint6
     pa.flags = reinterpret_cast<int *>(scr);
     pa.xw = reinterpret_cast<_Float16 *>(scr + flag_bytes);
     pa.xcopy = copy ? reinterpret_cast<_Float16 *>(scr + flag_bytes + xw_bytes) : nullptr;
-    pa.n_rg = n_rg; pa.n_fl = n_fl; pa.n_groups = g.n_groups; pa.d_out = g.d_out; pa.d_out_pad = g.d_out_pad; pa.d_in = g.d_in;
+    pa.n_rg = n_rg; pa.n_fl = n_fl; pa.n_groups = g.n_groups; pa.d_out_pad = g.d_out_pad; pa.d_in = g.d_in;
     pa.ntok = pass; pa.kp = g.kp; pa.xwpitch = xwpitch; pa.pitch = pitch;
-    pa.zero_limit = g.n_groups > 1 ? kZeroLimitGroups : kZeroLimit;
     const int gather = xwpitch > 0 || copy ? (pass + 3) / 4 : 0;
     WideArgs wa;
     wa.codes = reinterpret_cast<const u32x4 *>(base + g.off_codes);
@@ -858,8 +670,8 @@ int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint6
       hipLaunchKernelGGL(pick_wide(g.bits, grouped, plan.nt), dim3((unsigned)(n_rg * n_wt * wa.split)), dim3(256),
                          wide_lds(plan.nt), st, wa);
       if (wa.split > 1)
-        hipLaunchKernelGGL(owq_wide_sum, dim3((unsigned)(n_rg * wa.n_tt * 4)), dim3(256), 0, st, (const f4_t *)wa.slots, wa.y,
-                           grouped ? pa.flags : (const int *)nullptr, n_fl, wa.n_tt, wa.split, wa.ntok, g.d_out);
+        hipLaunchKernelGGL(owq_wide_sum, dim3((unsigned)(n_rg * wa.n_tt * 4)), dim3(256), 0, st, (const f4_t *)wa.slots, wa.y, wa.n_tt,
+                           wa.split, wa.ntok, g.d_out);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

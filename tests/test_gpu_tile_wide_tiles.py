@@ -1,14 +1,14 @@
 """The 256-row x 64- and 128-token tiles for prompts against the fp64 CPU oracle, on layers that only they take (more weak
 columns than the one-launch kernel's LDS holds) or that are large enough for them: last tiles that are nearly empty, odd
-numbers of blocks, rows off the 16-byte grid, zero points that are no small integers, and step sizes that one block's
-sums cannot be divided by (zero) or hardly (subnormal, the largest, negative).
+numbers of blocks, rows off the 16-byte grid, zero points that are no small integers, and step sizes of any size and sign
+in neighbouring groups (zero, subnormal, large).
 
 Bar as for the other kernels of the layout: relative L2 error <= 1e-3, max-abs error <= 1e-2 rms, whole output and per token."""
 import numpy as np
 import pytest
 
 from oracle import owq_ref
-from synth import LayerSpec, make_layer, make_x
+from synth import Layer, LayerSpec, make_layer, make_x
 
 pytestmark = pytest.mark.gpu
 
@@ -80,9 +80,8 @@ def test_step_sizes_of_neighbouring_groups_of_any_size(env, d_in, d_out, bits, k
 
 @pytest.mark.parametrize("bits,k,d_out,tokens", [(3, 1500, 300, 512), (4, 30, 8192, 1100)])
 def test_one_column_by_itself_is_exact(env, bits, k, d_out, tokens):
-    # x = a column of the identity in 24 groups: s (q - z) has 15 bits at most, so often a tie of fp16. 23 ratios, each
-    # multiplication off by half a unit of the last place and all ratios together by one or two, leave less than the
-    # 16 units within which the result is settled.
+    # x = a column of the identity in 24 groups: s (q - z) has 15 bits at most, so often a tie of fp16, and has to come out as
+    # it is, rounded once.
     torch, B = env
     layer = make_layer(LayerSpec("columns", 3072, d_out, bits, 128, k, 23))
     cols = np.random.default_rng(9).integers(0, 3072, tokens)
@@ -95,3 +94,43 @@ def test_one_column_by_itself_is_exact(env, bits, k, d_out, tokens):
     want = owq_ref.to_fp16(owq_ref.owq_linear_ref(layer.codes[pick], layer.scale[pick], layer.zero[pick], layer.group_size,
                                                   layer.weak_idx, layer.weak_w[pick], x))
     np.testing.assert_array_equal(got[:, pick].view(np.uint16), want.view(np.uint16))
+
+
+@pytest.mark.parametrize("d_in,bits,d_out,tokens", [(16384, 3, 8192, 2048), (36864, 4, 8192, 2048)])
+def test_one_column_by_itself_is_exact_whatever_the_number_of_groups(env, d_in, bits, d_out, tokens):
+    # As above with 128 and 288 groups, all in one workgroup: the others add exact zeros to the column's and nothing else.
+    torch, B = env
+    rng = np.random.default_rng(4)
+    groups = d_in // 128
+    layer = Layer(LayerSpec("manygroups", d_in, d_out, bits, 128, 0, 0), rng.integers(0, 1 << bits, (d_out, d_in), dtype=np.uint8),
+                  rng.uniform(0.001, 0.01, (d_out, groups)).astype(np.float16),
+                  rng.integers(0, 1 << bits, (d_out, groups)).astype(np.float16), np.zeros(0, np.int32), np.zeros((d_out, 0), np.float16))
+    cols = np.arange(tokens) % 512
+    x = torch.zeros((tokens, d_in), dtype=torch.float16, device="cuda")
+    x[torch.arange(tokens), torch.from_numpy(cols).cuda()] = torch.from_numpy(rng.choice([0.5, 1, 2, 3, 5, 7], tokens)).half().cuda()
+    print(d_in, d_out, tokens, flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    got = lin(x).cpu().numpy()
+    lin.close()
+    g = cols // 128
+    want = layer.scale[:, g].astype(np.float64) * (layer.codes[:, cols].astype(np.float64) - layer.zero[:, g]) * x.amax(1).cpu().numpy()
+    np.testing.assert_array_equal(got.view(np.uint16), owq_ref.to_fp16(want.T + 0.0).view(np.uint16))
+
+
+@pytest.mark.parametrize("group", [0, 128, 256])
+def test_exact_sums_are_rounded_once(env, group):
+    # Step sizes that are powers of two and small whole x: every sum is an exact binary32 number, with more than the 19 bits
+    # that decide an fp16 number and its ties, so y has to be that sum rounded once.
+    torch, B = env
+    layer = make_layer(LayerSpec("powers", 2048, 8192, 4, group, 0, 31))
+    rng = np.random.default_rng(6)
+    layer.scale[:] = np.ldexp(1.0, rng.integers(-4, 5, layer.scale.shape)).astype(np.float16)
+    x = rng.integers(-8, 9, (1100, 2048)).astype(np.float16)
+    x[:, 1024:] = 0
+    print("groups of", group, flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    got = lin(torch.from_numpy(x).cuda()).cpu().numpy()
+    lin.close()
+    want = owq_ref.to_fp16(owq_ref.owq_linear_ref(layer.codes, layer.scale, layer.zero, layer.group_size, layer.weak_idx,
+                                                  layer.weak_w, x))
+    np.testing.assert_array_equal(got.view(np.uint16), want.view(np.uint16))
