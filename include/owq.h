@@ -358,8 +358,8 @@ owq_status_t owq_search_config(const owq_search_desc_t *desc, const uint16_t *w,
  * summed over the whole batch; NULL = not wanted), workspace of at least
  * owq_backward_workspace_bytes bytes for this batch, 256-byte aligned (contents undefined before and after;
  * calls that share a workspace must not overlap).  fp32 accumulation; the step size times
- * (q - z) is rounded to fp16 once before the product: relative 2^-11 per term whatever the magnitude of step sizes and
- * gradients; step sizes of 128 and above, and products above 65504, overflow;
+ * (q - z), z rounded to an integer, is rounded to fp16 once before the product: relative 2^-11 per term whatever the
+ * magnitude of step sizes (any finite fp16), zero points and gradients; what z lacks of an integer is taken off in fp32;
  * dx is rounded to fp16 once.  Work is queued on `stream`, nothing is allocated, nothing synchronises.
  * Errors: OWQ_ERR_HANDLE, OWQ_ERR_LAYOUT, OWQ_ERR_NULL, OWQ_ERR_BATCH, OWQ_ERR_BUFFER (workspace
  * too small, a pointer misaligned), OWQ_ERR_HIP.  batch == 0 is a no-op.

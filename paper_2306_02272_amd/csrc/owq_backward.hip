@@ -162,7 +162,9 @@ constexpr int kStepBytes = kStepTiles * 8192;          // staged dy of a step: 1
 constexpr int kProdPlanes = 4 * kStepBytes;            // two buffers for either half of the rows; then per wave:
 constexpr int kProdPlane = 2 * kStepTiles * 32 * 8;    // step sizes with zero points, and rests in operand order, of the rows of two steps
 constexpr int kOutPitch = 72;                          // halves per token of 64 columns of the result
-constexpr int kProdLds = kProdPlanes + 8 * kProdPlane;
+constexpr int kProdFlags = kProdPlanes + 8 * kProdPlane;        // per wave: it has met a large step size
+constexpr int kProdLds = kProdFlags + 8 * 4;
+constexpr float kLargeStep = 32.f;                     // times |q - z| of up to 1039 is what fp16 holds
 
 template <int S> using KStep = std::integral_constant<int, S>;
 
@@ -179,7 +181,8 @@ __device__ __forceinline__ h8_t scaled(h8_t v, u32 ss) {
 // What bounds it: per 32 rows x 64 columns x 128 tokens a wave issues 16 matrix instructions for the product and 4 for
 // the turn: 1.05 PFLOP/s of both at 4096 -> 16384, 3-bit, 512 tokens, where a large fp16 library product on random data
 // reaches 1.2 on the same card.  The step size leaves with the codes: s (q - z) is rounded to fp16 once, before the turn
-// (relative error of 2^-11 at most, q - z being an integer, whatever s is), so dy is an operand as it is.  (It used to be
+// (relative error of 2^-11 at most, q - z being an integer; step sizes of 32 and above, whose products may be more than fp16
+// holds, in a sweep of their own that other layers never enter), so dy is an operand as it is.  (It used to be
 // multiplied by s in the loop, 32 instructions per row tile instead of 16, and needed a launch that finds its largest magnitude
 // and a power of two against underflow.)  About 80 vector instructions per row tile, among the matrix instructions of the tile
 // before: a turn in front of its own product leaves the matrix cores waiting for it, 86.5 against 82 us here, 183 against 173
@@ -194,8 +197,8 @@ template <int BITS>
 __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   extern __shared__ u32x4 lds_units[];
   unsigned char *lds = reinterpret_cast<unsigned char *>(lds_units);
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cw = w & 3, kh = w >> 2;
-  const int h = lane >> 5, n32 = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cw = w & 3, kh = w >> 2;
+  int lane = threadIdx.x & 63, h = lane >> 5, n32 = lane & 31;
   // Workgroups go to the eight dies (each with its own L2) in turn.  The workgroups that read the
   // same rows of the staged dy (same pass, same range of rows, different block pairs) are given
   // ids that land on one die: die d takes a contiguous eighth of the (pass, range, block pair) order.
@@ -215,16 +218,28 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   // selection matrices: K-step t of the forward numbering holds columns 16 t .. 16 t + 15 of the
   // block; two of them side by side make a 32-column tile
   h8_t sel0, sel1;
+  auto select = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    sel0[e] = (n32 == 8 * h + e) ? (_Float16)1.f : (_Float16)0.f;
-    sel1[e] = (n32 == 16 + 8 * h + e) ? (_Float16)1.f : (_Float16)0.f;
-  }
+    for (int e = 0; e < 8; ++e) {
+      sel0[e] = (n32 == 8 * h + e) ? (_Float16)1.f : (_Float16)0.f;
+      sel1[e] = (n32 == 16 + 8 * h + e) ? (_Float16)1.f : (_Float16)0.f;
+    }
+  };
+  select();
   f16_t acc[4][2], zero;
 #pragma unroll
   for (int r = 0; r < 16; ++r) zero[r] = 0.f;
 #pragma unroll
   for (int m = 0; m < 4; ++m) acc[m][0] = acc[m][1] = zero;
+  auto scale_acc = [&](float v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[m][0][r] *= v;
+        acc[m][1][r] *= v;
+      }
+  };
   float zacc[4] = {0.f, 0.f, 0.f, 0.f};
   u32 cd[kStepTiles][4];
   u32 szr[2];
@@ -259,19 +274,24 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
   // Step sizes with the zero points rounded; what those lack, times the step size, to where the lanes of either half of the
   // wave read eight of them at once: row 16 s + 8 b + 4 h + e of a row tile is element 4 b + e of unit (s, h).  True: some
   // zero point is no small integer.
-  auto put_sz = [&](int buf) __attribute__((always_inline)) {
+  int any_large = 0;
+  auto put_sz = [&](int buf, auto which) __attribute__((always_inline)) {
+    constexpr bool large = decltype(which)::value;
     bool rest = false;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int r = 64 * i + lane, q = r & 15;
       const int at = (r >> 4) * 16 + ((q >> 2) & 1) * 8 + (q >> 3) * 4 + (q & 3);
       const float z = half_hi(szr[i]), z1 = __builtin_amdgcn_fmed3f(__builtin_rintf(z), -1024.f, 1024.f);
-      const h2_t sz2 = {(_Float16)(half_lo(szr[i]) * 0x1p9f), (_Float16)(z1 * -0x1p-9f)};
+      const float sc = half_lo(szr[i]);
+      const bool l = __builtin_fabsf(sc) >= kLargeStep;
+      const h2_t sz2 = {(_Float16)(l == large ? sc * (large ? 0x1p-2f : 0x1p9f) : 0.f), (_Float16)(z1 * -0x1p-9f)};
+      any_large |= (int)(__ballot(l) != 0ull);
       szplane[buf * 128 + r] = __builtin_bit_cast(u32, sz2);
-      rplane[buf * 128 + at] = half_lo(szr[i]) * (z - z1);
+      rplane[buf * 128 + at] = sc * (z - z1);
       rest |= z != z1;
     }
-    return __ballot(rest) != 0ull;
+    return !large && __ballot(rest) != 0ull;
   };
   // s (q - z) of a K-step of the forward numbering (16 columns) of the lane's row, rounded once; sz as put_sz left it
   auto weights = [&](int i, u32 szv, auto k_step) __attribute__((always_inline)) {
@@ -288,89 +308,108 @@ __global__ __launch_bounds__(512, 2) void owq_bwd_product(const ProdArgs a) {
       wb[s] = (u32x4){pk[0], pk[1], pk[2], pk[3]};
     }
   };
-  // ---- turn of the first row tile: s (q - z) from (row, eight columns) to (column, eight rows) per lane ----
-  fetch_dy(rt0, 0);
-  fetch_sz(rt0);
+  // Over all rows, with the step sizes below kLargeStep (large: with the others).
+  auto sweep = [&](auto which) __attribute__((always_inline)) {
+    u32x4 wb[2][2], wn[2][2];
+    // ---- turn of the first row tile: s (q - z) from (row, eight columns) to (column, eight rows) per lane ----
+    fetch_dy(rt0, 0);
+    fetch_sz(rt0);
 #pragma unroll
-  for (int i = 0; i < kStepTiles; ++i) fetch_codes(i, rt0 + i);
-  bool rest = put_sz(0);
-  fetch_sz(rt0 + kStepTiles);
-  u32x4 wb[2][2], wn[2][2];
-  {
-    const u32 szv = szplane[n32];
-    const f16_t t0 = mma(weights(0, szv, KStep<1>{}), sel1, mma(weights(0, szv, KStep<0>{}), sel0, zero));
-    const f16_t t1 = mma(weights(0, szv, KStep<3>{}), sel1, mma(weights(0, szv, KStep<2>{}), sel0, zero));
-    turned(t0, wb[0]);
-    turned(t1, wb[1]);
-  }
-  fetch_codes(0, rt0 + kStepTiles);
-  for (int st = 0; st < steps; ++st) {
-    const int rt = rt0 + st * kStepTiles, nx = rt + kStepTiles, buf = st & 1;
-    // The codes of the next step's first tile, asked for last, may be on their way.  (The compiler does not count the direct
-    // loads: its own waits for the others would stand behind the next step's direct loads and wait for them too.)
-    wait_loads<BITS == 3 ? 3 : 1>();
+    for (int i = 0; i < kStepTiles; ++i) fetch_codes(i, rt0 + i);
+    bool rest = put_sz(0, which);
+    fetch_sz(rt0 + kStepTiles);
+    {
+      const u32 szv = szplane[n32];
+      const f16_t t0 = mma(weights(0, szv, KStep<1>{}), sel1, mma(weights(0, szv, KStep<0>{}), sel0, zero));
+      const f16_t t1 = mma(weights(0, szv, KStep<3>{}), sel1, mma(weights(0, szv, KStep<2>{}), sel0, zero));
+      turned(t0, wb[0]);
+      turned(t1, wb[1]);
+    }
+    fetch_codes(0, rt0 + kStepTiles);
+    for (int st = 0; st < steps; ++st) {
+      const int rt = rt0 + st * kStepTiles, nx = rt + kStepTiles, buf = st & 1;
+      // The codes of the next step's first tile, asked for last, may be on their way.  (The compiler does not count the direct
+      // loads: its own waits for the others would stand behind the next step's direct loads and wait for them too.)
+      wait_loads<BITS == 3 ? 3 : 1>();
 #pragma unroll
-    for (int i = 1; i < kStepTiles; ++i)
+      for (int i = 1; i < kStepTiles; ++i)
 #pragma unroll
-      for (int v = 0; v < BITS; ++v) asm volatile("" : "+v"(cd[i][v]));
-    asm volatile("" : "+v"(szr[0]), "+v"(szr[1]));
-    __syncthreads();
-    fetch_dy(nx, buf ^ 1);
-    const bool rest_next = put_sz(buf ^ 1);
-    fetch_sz(nx + kStepTiles);
-    u32 szv[kStepTiles];                     // of the row tiles that are turned in this step: 1, 2, 3 and the next one's 0
+        for (int v = 0; v < BITS; ++v) asm volatile("" : "+v"(cd[i][v]));
+      asm volatile("" : "+v"(szr[0]), "+v"(szr[1]));
+      __syncthreads();
+      fetch_dy(nx, buf ^ 1);
+      const bool rest_next = put_sz(buf ^ 1, which);
+      fetch_sz(nx + kStepTiles);
+      u32 szv[kStepTiles];                     // of the row tiles that are turned in this step: 1, 2, 3 and the next one's 0
 #pragma unroll
-    for (int i = 0; i < kStepTiles; ++i) szv[i] = szplane[(i + 1 < kStepTiles ? buf * 128 + 32 * (i + 1) : (buf ^ 1) * 128) + n32];
-    const unsigned char *dyb = lds + (2 * kh + buf) * kStepBytes + lane * 16;
-    if (rest) {                              // sum of dy s (z - rint z) per token
-      const float *rp = rplane + buf * 128;
-      for (int i = 0; i < 2 * min(kStepTiles, rt1 - rt); ++i) {
-        const f4_t r0 = *reinterpret_cast<const f4_t *>(rp + (2 * i + h) * 8), r1 = *reinterpret_cast<const f4_t *>(rp + (2 * i + h) * 8 + 4);
+      for (int i = 0; i < kStepTiles; ++i) szv[i] = szplane[(i + 1 < kStepTiles ? buf * 128 + 32 * (i + 1) : (buf ^ 1) * 128) + n32];
+      const unsigned char *dyb = lds + (2 * kh + buf) * kStepBytes + lane * 16;
+      if (rest) {                              // sum of dy s (z - rint z) per token
+        const float *rp = rplane + buf * 128;
+        for (int i = 0; i < 2 * min(kStepTiles, rt1 - rt); ++i) {
+          const f4_t r0 = *reinterpret_cast<const f4_t *>(rp + (2 * i + h) * 8), r1 = *reinterpret_cast<const f4_t *>(rp + (2 * i + h) * 8 + 4);
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const h8_t d = *reinterpret_cast<const h8_t *>(dyb + (i * 4 + m) * 1024);
+          for (int m = 0; m < 4; ++m) {
+            const h8_t d = *reinterpret_cast<const h8_t *>(dyb + (i * 4 + m) * 1024);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) zacc[m] = __builtin_fmaf((float)d[4 + e], r1[e], __builtin_fmaf((float)d[e], r0[e], zacc[m]));
+            for (int e = 0; e < 4; ++e) zacc[m] = __builtin_fmaf((float)d[4 + e], r1[e], __builtin_fmaf((float)d[e], r0[e], zacc[m]));
+          }
+        }
+      }
+      rest = rest_next;
+      auto dy_of = [&](int i, int q) __attribute__((always_inline)) { return *reinterpret_cast<const h8_t *>(dyb + (i * 8 + q) * 1024); };
+      // ---- product: dy against the turned weights of a row tile, and the turn of the next one (slot j) in between ----
+#pragma unroll
+      for (int i = 0; i < kStepTiles; ++i) {
+        if (rt + i >= rt1) break;
+        const int j = (i + 1) % kStepTiles;
+        h8_t d0 = dy_of(i, 0), d1 = dy_of(i, 1), a0, a1;
+        f16_t t;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int s = q >> 2, m = q & 3;
+          const h8_t d2 = dy_of(i, q < 6 ? q + 2 : 7);
+          acc[m][0] = mma(d0, __builtin_bit_cast(h8_t, wb[0][s]), acc[m][0]);
+          acc[m][1] = mma(d0, __builtin_bit_cast(h8_t, wb[1][s]), acc[m][1]);
+          if (q == 0) a0 = weights(j, szv[i], KStep<0>{});
+          if (q == 1) a1 = weights(j, szv[i], KStep<1>{});
+          if (q == 2) t = mma(a1, sel1, mma(a0, sel0, zero));
+          if (q == 2) a0 = weights(j, szv[i], KStep<2>{});
+          if (q == 3) a1 = weights(j, szv[i], KStep<3>{});
+          if (q == 4) turned(t, wn[0]);
+          if (q == 4) fetch_codes(j, nx + i + 1);
+          if (q == 5) t = mma(a1, sel1, mma(a0, sel0, zero));
+          if (q == 7) turned(t, wn[1]);
+          d0 = d1;
+          d1 = d2;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          wb[0][s] = wn[0][s];
+          wb[1][s] = wn[1][s];
         }
       }
     }
-    rest = rest_next;
-    auto dy_of = [&](int i, int q) __attribute__((always_inline)) { return *reinterpret_cast<const h8_t *>(dyb + (i * 8 + q) * 1024); };
-    // ---- product: dy against the turned weights of a row tile, and the turn of the next one (slot j) in between ----
-#pragma unroll
-    for (int i = 0; i < kStepTiles; ++i) {
-      if (rt + i >= rt1) break;
-      const int j = (i + 1) % kStepTiles;
-      h8_t d0 = dy_of(i, 0), d1 = dy_of(i, 1), a0, a1;
-      f16_t t;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int s = q >> 2, m = q & 3;
-        const h8_t d2 = dy_of(i, q < 6 ? q + 2 : 7);
-        acc[m][0] = mma(d0, __builtin_bit_cast(h8_t, wb[0][s]), acc[m][0]);
-        acc[m][1] = mma(d0, __builtin_bit_cast(h8_t, wb[1][s]), acc[m][1]);
-        if (q == 0) a0 = weights(j, szv[i], KStep<0>{});
-        if (q == 1) a1 = weights(j, szv[i], KStep<1>{});
-        if (q == 2) t = mma(a1, sel1, mma(a0, sel0, zero));
-        if (q == 2) a0 = weights(j, szv[i], KStep<2>{});
-        if (q == 3) a1 = weights(j, szv[i], KStep<3>{});
-        if (q == 4) turned(t, wn[0]);
-        if (q == 4) fetch_codes(j, nx + i + 1);
-        if (q == 5) t = mma(a1, sel1, mma(a0, sel0, zero));
-        if (q == 7) turned(t, wn[1]);
-        d0 = d1;
-        d1 = d2;
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        wb[0][s] = wn[0][s];
-        wb[1][s] = wn[1][s];
-      }
-    }
-  }
-  wait_loads<0>();
+    wait_loads<0>();
+  };
+  sweep(std::false_type{});
+  // Where the workgroup has met larger ones, whose products with q - z may be more than fp16 holds, another sweep takes
+  // those, 2^-11 of them, and the sums are in that unit meanwhile (both exact).
+  if (lane == 0) reinterpret_cast<int *>(lds + kProdFlags)[w] = any_large;
   __syncthreads();
+  const u32x4 *f = reinterpret_cast<const u32x4 *>(lds + kProdFlags);
+  const u32x4 f0 = f[0] | f[1];
+  if (__builtin_amdgcn_readfirstlane((int)(f0.x | f0.y | f0.z | f0.w)) != 0) {
+    scale_acc(0x1p-11f);
+    asm volatile("" : "+v"(lane));     // what follows from the lane is worked out again: kept over both it does not fit the registers
+    h = lane >> 5;
+    n32 = lane & 31;
+    select();
+    sweep(std::true_type{});
+    scale_acc(0x1p11f);
+    __syncthreads();
+  }
   // The rest of the zero points per token: both halves of the lanes, then from the operand layout (token = lane % 32)
   // to the accumulator layout (tokens along the registers); the planes of this wave have been read
   float *zbuf = reinterpret_cast<float *>(szplane);

@@ -320,7 +320,7 @@ __device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *l
           asm volatile("" : "+v"(tot[NT + ip]));
         }
         xp = x0;
-        x0 = x1;
+        if constexpr (q + 1 < 8 * NT) x0 = x1;
         __builtin_amdgcn_sched_barrier(0);
       });
     } else {

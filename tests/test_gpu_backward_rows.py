@@ -93,3 +93,31 @@ def test_dx_stored_by_the_product(env, d_in, d_out, bits, group, k, tokens):
     assert rel <= 1e-3 and mx <= 1e-2, (rel, mx)
     assert (got[tokens] == 7).all()
     lin.close()
+
+
+@pytest.mark.parametrize("bits,group,rows", [(3, 128, 1000), (4, 0, 70), (4, 256, 4200)])
+@pytest.mark.parametrize("zeros", ["integers", "any"])
+def test_step_sizes_up_to_the_largest(env, bits, group, rows, zeros):
+    # Whatever finite step size and zero point a row has, its weights times its gradients add to the others: rows of step
+    # sizes from 2^-6 to 65504, zero points to 1200, gradients so that all rows weigh alike.
+    torch, B = env
+    layer = make_layer(LayerSpec("bwdl", 900, rows, bits, group, 6, 7))
+    rng = np.random.default_rng(12)
+    s = np.exp2(rng.uniform(-6, 16, (rows, 1))) * np.ones(layer.scale.shape)
+    layer.scale[:] = np.minimum(s * rng.choice([-1, 1], s.shape), 65504).astype(np.float16)
+    layer.zero[rng.random(rows) < 0.2] = 1024
+    if zeros == "any":
+        layer.zero[:] = (layer.zero.astype(np.float32) + rng.normal(0, 2, layer.zero.shape)).astype(np.float16)
+        layer.zero[rng.random(rows) < 0.05] = -1199
+    layer.weak_w[:] = 0
+    x = make_x(layer, 140)
+    dy = (rng.normal(0, 0.05, (140, rows)) / np.abs(s[:, 0])).astype(np.float16)
+    print(f"{rows} rows, groups of {group}, zero points: {zeros}", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    dx, _ = lin.backward(torch.from_numpy(dy).cuda(), torch.from_numpy(x).cuda())
+    lin.close()
+    want, _ = backward.owq_backward_ref(layer.codes, layer.scale, layer.zero, group, layer.weak_idx, layer.weak_w, x, dy)
+    keep = np.ones(900, bool)
+    keep[layer.weak_idx] = False
+    rel, mx = owq_ref.parity_errors(dx.cpu().numpy()[:, keep], want[:, keep])
+    assert rel <= 1e-3 and mx <= 1e-2, (rel, mx)
