@@ -356,7 +356,7 @@ owq_status_t owq_search_config(const owq_search_desc_t *desc, const uint16_t *w,
  * [batch][d_out] (read), x fp16 [batch][d_in] (read; only its weak columns; may be NULL if dww
  * is NULL), dx fp16 [batch][d_in] (written; NULL = not wanted), dww fp32 [d_out][k] (written,
  * summed over the whole batch; NULL = not wanted), workspace of at least
- * owq_backward_workspace_bytes bytes for this batch, 256-byte aligned (contents undefined before and after;
+ * owq_backward_workspace_bytes bytes for this batch or a larger one, 256-byte aligned (contents undefined before and after;
  * calls that share a workspace must not overlap).  fp32 accumulation; the step size times
  * (q - z), z rounded to an integer, is rounded to fp16 once before the product: relative 2^-11 per term whatever the
  * magnitude of step sizes (any finite fp16), zero points and gradients; what z lacks of an integer is taken off in fp32;

@@ -823,11 +823,11 @@ extern "C" owq_status_t owq_backward_workspace_bytes(owq_handle_t h, int32_t bat
   if (h->info.layout != OWQ_LAYOUT_TILE) return OWQ_ERR_LAYOUT;
   if (!bytes) return OWQ_ERR_NULL;
   if (batch < 0 || batch > OWQ_MAX_BATCH) return OWQ_ERR_BATCH;
-  // A plan of more passes may need less than one of fewer (fewer ranges of rows).  From four passes on the answer covers
-  // those of smaller batches, so that a workspace for a large batch serves them too.
+  // A plan of more passes may need less than one of fewer (fewer ranges of rows; with one range no partial results at all).  The
+  // answer covers those of all smaller batches, so that a workspace for a large batch serves them too.
   const BwdPlan p = plan(h->info, batch);
   *bytes = p.total;
-  for (int n = kLaunchPasses; n <= p.most; ++n) {
+  for (int n = 1; n <= p.most; ++n) {
     const size_t need = plan(h->info, batch, n).total;
     if (need > *bytes) *bytes = need;
   }

@@ -58,3 +58,15 @@ def test_a_workspace_serves_smaller_batches(env, d_in, d_out):
     sizes = [B.owq_backward_workspace_bytes(handle, b) for b in range(385, 2600, 43)]
     B.owq_free_layer(handle)
     assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(16384, 4096), (13824, 5120), (11008, 4096), (4096, 16384), (640, 200)])
+def test_a_workspace_serves_every_smaller_batch(env, d_in, d_out):
+    # also those of fewer than four passes, where rows are cut into ranges that a larger batch does without
+    torch, B = env
+    desc = B.make_desc(d_out, d_in, 4, 128, d_in // 100, layout=1)
+    buf = torch.empty(B.owq_packed_bytes(desc), dtype=torch.uint8, device="cuda")
+    handle = B.owq_open_packed(desc, buf.data_ptr(), buf.numel())
+    sizes = [B.owq_backward_workspace_bytes(handle, b) for b in list(range(1, 1200, 31)) + [2048, 4096]]
+    B.owq_free_layer(handle)
+    assert sizes == sorted(sizes)
