@@ -15,8 +15,8 @@
 //
 // Per group of passes of 128 tokens (four, or up to sixteen of a small layer): staging (dy into operand order, on the first group also the weak
 // columns and the activations at the weak columns); the small products (dww of the whole batch on the first group,
-// dx at the weak columns in partial results); the product into fp32 partial results per range of rows; the sum of
-// the partial results into fp16 dx.  A layer whose weak columns are more than an eighth of all takes a plain
+// dx at the weak columns in partial results); the product into fp32 partial results per range of rows, or, where there is
+// one range, into dx; the sum of what partial results there are into fp16 dx.  A layer whose weak columns are more than an eighth of all takes a plain
 // kernel for the weak columns of dx instead.
 #include <hip/hip_runtime.h>
 

@@ -27,11 +27,13 @@
 //
 // What bounds it: power.  The card lowers its clock under matrix work on random data (4096 x 16384 at 2048 tokens, 3-bit,
 // groups of 128: 304 us with 64-token tiles, 239 with x zero; a large fp16 library product of that size 224 and, on zeros,
-// about 160), so every instruction beside the matrix work costs.  128 tokens per unpacked code instead of 64: 304 -> 241-250 us
-// there, 16384 x 4096 293 -> 275, 4-bit 5120 -> 13824 at 777 tokens 154 -> 145; vector instructions per matrix instruction
-// 7.9 -> 5.4.  With a spill of two to five registers, which waits for the direct loads too, 275 becomes 304-324.
-// (Sums kept in units of the block's step size and multiplied by ratios of step sizes instead: 266, 244 and 141, but a rounding
+// about 160), so every instruction beside the matrix work costs.  128 tokens per unpacked code instead of 64, in turn on one card:
+// 298 -> 248 us there, 16384 x 4096 293 -> 273, 4-bit 5120 -> 13824 at 777 tokens 153 -> 145; vector instructions per matrix
+// instruction 7.9 -> 5.4.  With a spill of two to five registers, which waits for the direct loads too, 275 becomes 304-324.
+// (Sums kept in units of the block's step size and multiplied by ratios of step sizes instead: 251, 267 and 142, but a rounding
 // per block on all of the sums, which does not leave a single column's weight exact beyond some 100 groups.)
+// Row groups with rests take 422 instead of 446 us, 440 instead of 446, but 234 instead of 209: 378 workgroups are one round with
+// twice the matrix work, 702 of 64 tokens were two shorter ones, and the plan does not know of the zero points.
 #include <hip/hip_runtime.h>
 
 #include "owq_internal.h"

@@ -2,7 +2,7 @@
 "PEFT with Weak Column Tuning") against the fp64 CPU oracle, through the C ABI.
 
 Tolerances.  dx: the forward path's bar (relative L2 <= 1e-3, max abs <= 1e-2 rms, whole batch and token
-by token): dy times the step size is rounded to fp16 once (2^-11 relative per term, independent signs),
+by token): the step size times (q - z) is rounded to fp16 once (2^-11 relative per term, independent signs),
 the sum is fp32 and dx is rounded to fp16 once.  dww is an fp32 sum of exact fp16 products over the
 batch: relative L2 <= 1e-5.
 """
@@ -97,9 +97,9 @@ def test_backward_matches_oracle(env, case):
 
 @pytest.mark.parametrize("sigma", [1.0, 1e-3, 1e-5])
 def test_gradient_magnitude_does_not_matter(env, sigma):
-    # Gradients of weak-column tuning are small: with dy ~ 1e-3 and step sizes of 1e-3..1e-2 the fp16 product
-    # dy * s would be a subnormal number.  The library scales dy by a power of two first; the error against the
-    # oracle must stay at the forward path's bar on top of what rounding the exact result to fp16 costs (at
+    # Gradients of weak-column tuning are small: with dy ~ 1e-3 and step sizes of 1e-3..1e-2 a product dy * s in
+    # fp16 would be a subnormal number.  The library rounds s (q - z) instead and takes dy as it is; the error against
+    # the oracle must stay at the forward path's bar on top of what rounding the exact result to fp16 costs (at
     # sigma = 1e-5 dx itself is a subnormal fp16 number).
     L = make_layer(LayerSpec("small_dy", 512, 2048, 3, 128, 8, 612))
     batch = 24

@@ -134,3 +134,28 @@ def test_exact_sums_are_rounded_once(env, group):
     want = owq_ref.to_fp16(owq_ref.owq_linear_ref(layer.codes, layer.scale, layer.zero, layer.group_size, layer.weak_idx,
                                                   layer.weak_w, x))
     np.testing.assert_array_equal(got.view(np.uint16), want.view(np.uint16))
+
+
+@pytest.mark.parametrize("bits,group,tokens", [(3, 128, 1100), (4, 128, 100), (4, 256, 1100), (3, 0, 1100), (4, 0, 100)])
+def test_zero_points_at_the_edge_of_what_the_unpack_takes(env, bits, group, tokens):
+    # Integers of up to 1024 leave with the codes, others by a rest, chosen by 256 rows: row groups with 1024 and -1024, with 1025,
+    # with 241 and with half-integers, a column of the identity (times 1 or 3) each: at most 24 bits, so exact until y is rounded.
+    torch, B = env
+    layer = make_layer(LayerSpec("edge", 640, 8200, bits, group, 0, 41))
+    rng = np.random.default_rng(8)
+    rows = np.arange(8200) // 256 % 5
+    for kind, z in enumerate([1024, 1025, 241, 240.5]):
+        pick = (rows == kind)[:, None] & (rng.random(layer.zero.shape) < 0.3)
+        layer.zero[pick] = z
+        if kind < 2:
+            layer.zero[pick & (rng.random(layer.zero.shape) < 0.5)] = -z
+    cols = np.random.default_rng(1).integers(0, 640, tokens)
+    x = np.zeros((tokens, 640), np.float16)
+    x[np.arange(tokens), cols] = rng.choice([1, 3], tokens)
+    print(bits, "bit, groups of", group, tokens, "tokens", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    got = lin(torch.from_numpy(x).cuda()).cpu().numpy()
+    lin.close()
+    g = cols // group if group else np.zeros(tokens, int)
+    want = layer.scale[:, g].astype(np.float64) * (layer.codes[:, cols].astype(np.float64) - layer.zero[:, g]) * x.max(1).astype(np.float64)
+    np.testing.assert_array_equal(got.view(np.uint16), owq_ref.to_fp16(want.T + 0.0).view(np.uint16))
