@@ -10,13 +10,16 @@
 // histogram of F bins (in LDS: a count and a sum of offsets, one 64-bit integer atomic per weight), two prefix sums
 // turn it into G at the bin edges, and every grid point is bounded from below by 2^bits - 1 lookups with linear
 // interpolation (a chord of a concave function lies under it).  The point with the least bound is evaluated in full,
-// and then those whose bound, less a bound on its own rounding, does not exceed the least error found: five of 256
-// on groups of 128, one or two on long rows.  These evaluations take the same binary32 decisions per weight as the
+// and then those whose bound, less a bound on its own rounding, does not exceed the least error found: one or two
+// different points in all.  These evaluations take the same binary32 decisions per weight as the
 // plain search and share their sums among the lanes; points whose sums come out too close to tell are summed again in
 // the order of the columns, so that the choice is that of the plain search.
-// 16384 x 4096, 3-bit, groups of 128, 16 x 16 points: 1780 -> 620 us (bound by vector instructions, 815 per group by the
-// counter where the plain search spent 3000); 5120 x 5120, 4-bit, one scale per row: 717 -> 127-138 us from box to box (of
-// which 30 are the few rows with points to tell apart).
+// Bound by vector instructions, and by how many waves a SIMD holds to issue them: a wave issues one every four or five cycles, the
+// SIMD takes more.  16384 x 4096, 3-bit, groups of 128, 16 x 16 points: plain search 1780 us, four points per lane 620 (815
+// instructions per group), the grid by diagonals with the general way in the same kernel 395 (497; five waves per SIMD), in a
+// kernel of its own 357 (eight).  5120 x 5120, 4-bit, one scale per row: 134 -> 98 us when a wave's registers went from 227 to 113
+// (two waves per SIMD -> four: columns and masks of all weights had been kept in registers from one row to the next, and masks
+// in spilled scalar registers); the same for 4096 rows of 13824: 290 -> 125.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -33,6 +36,7 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;            // waves per workgroup, each with its own LDS area
 constexpr int kChunk = 1024;         // columns moved through LDS at a time
+constexpr uint16_t kLeft = 0xffffu;  // as a step size: this group is left to the general grid's kernel
 constexpr u32 kLeastStep = 0x38800000u;    // 2^-14 in binary32
 constexpr int kMaskBytesMax = 47 * 1024;   // LDS left for the weak-column bit mask of a row: 64 KiB less the kernel's static 16.1 KiB
 
@@ -68,6 +72,23 @@ __device__ __forceinline__ T wave_all(T v, F op) {
   const T r2 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(i, 32)), r3 = __builtin_bit_cast(T, __builtin_amdgcn_readlane(i, 48));
   return op(op(r0, r1), op(r2, r3));
 }
+
+// Least (greatest) of the 64 lanes' values, none of them a NaN.  Written as instructions: from fminf the compiler makes four per
+// step (old value, move across lanes, canonicalise, minimum) where one does.  s_nop: two wait states before a value that was
+// just written is read across lanes.
+__device__ __forceinline__ float wave_min(float v) {
+  asm("s_nop 1\n\tv_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf"
+      : "+v"(v));
+  const int i = __builtin_bit_cast(int, v);
+  const int r0 = __builtin_amdgcn_readlane(i, 0), r1 = __builtin_amdgcn_readlane(i, 16), r2 = __builtin_amdgcn_readlane(i, 32);
+  float m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 48));
+  asm("v_min_f32 %0, %1, %0\n\tv_min_f32 %0, %2, %0\n\tv_min_f32 %0, %3, %0" : "+v"(m) : "s"(r0), "s"(r1), "s"(r2));
+  return m;
+}
+__device__ __forceinline__ float wave_max(float v) { return -wave_min(-v); }
 
 // Step size, reciprocal and zero point of the grid point that cuts the fractions fa and fb of
 // the range from its ends.  Every operation is a single binary32 operation in the order the
@@ -107,6 +128,33 @@ __device__ __forceinline__ Cand candidate(float lo, float hi, float fa, float fb
   c.a = 0.f - z;                     // 0 - z: no negative zero
   c.b = qmax - z;
   return c;
+}
+
+// The step size of a range of this width, as candidate<false> finds it.
+__device__ __forceinline__ float step_of(float width, float qmax, float rqmax) {
+#pragma clang fp contract(off)
+  const float q0 = width * rqmax;
+  const float s32 = __builtin_fmaf(__builtin_fmaf(-q0, qmax, width), rqmax, q0);
+  return (float)(_Float16)(s32 > 0x1p-14f ? s32 : 0x1p-14f);
+}
+// its reciprocal, and the zero point of a range that starts at lo_i
+__device__ __forceinline__ float reciprocal(float s) {
+  const float r0 = __builtin_amdgcn_rcpf(s);
+  return __builtin_fmaf(__builtin_fmaf(-s, r0, 1.f), r0, r0);
+}
+__device__ __forceinline__ float zero_of(float lo_i, float inv) {
+#pragma clang fp contract(off)
+  return __builtin_amdgcn_fmed3f(__builtin_rintf(-lo_i * inv), -2048.f, 2048.f);
+}
+__device__ __forceinline__ float cut_lo(float lo, float f, float r) {
+#pragma clang fp contract(off)
+  const float p = f * r;
+  return lo + p;
+}
+__device__ __forceinline__ float cut_hi(float hi, float f, float r) {
+#pragma clang fp contract(off)
+  const float p = f * r;
+  return hi - p;
 }
 
 // fraction of the range that grid point i of n cuts: binary32 of (shrink * i) / (n - 1) in binary64
@@ -254,8 +302,19 @@ struct TeamShared {
   float scan_f[4];
 };
 
-template <int TW, int NT, int POINTS>
-__global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
+//
+// BITS > 0 (a wave per group, as many points at either end): on a diagonal i + j of the grid the width is one value but for
+// rounding, so all its points have one step size, and their zero points are a short run of integers: of 256 points about 107
+// (3 bits) are different ones, and those of one diagonal share all midpoints but a few.  Two lanes take a diagonal, half of
+// its points each; L levels and Z zero points need L + Z - 1 lookups, of which every L in a row are a grid point's (3 bits: 10
+// lookups where four points per lane took 28).  Z covers the runs of all square grids up to 16 x 16 with cuts up to 0.45
+// almost always; a group where a lane's run is longer, where a diagonal has more than one step size (the widths'
+// rounding straddles a binary16 boundary), where a step size is at its least value, a midpoint lies beyond the table or three
+// errors are too close to tell is marked in `scale` (kLeft).
+// BITS < 0: the general grid for what is marked.  In a kernel of its own since the general way takes 30 registers more: 107 ->
+// 90 us for the 2^17 groups of 128 of a 4096 x 4096 matrix, and 5 us for the launch that looks for marks.
+template <int TW, int NT, int POINTS, int BITS>
+__global__ __launch_bounds__(256, NT <= 4 ? 5 : NT <= 24 ? 4 : 2) void owq_search_bounds(const SearchArgs a) {
   using T = Team<TW, NT, POINTS>;
   constexpr int V = T::V, LANES = T::LANES, F = T::F, CPL = T::CPL, TEAMS = 4 / TW;
   __shared__ __attribute__((aligned(16))) unsigned long long hist[TEAMS][F + 2];
@@ -264,6 +323,15 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
   const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int tl = TW == 4 ? tid : lane;             // lane within the team
   unsigned long long *bins = hist[TW == 4 ? 0 : wv];
+  const int team = TW == 4 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
+  const int u0 = team * a.units_per_wave;
+  int n_units = a.units - u0 < a.units_per_wave ? a.units - u0 : a.units_per_wave;         // same for the team
+  unsigned long long todo = 0ull;                  // BITS < 0: which of this wave's 64 or fewer groups
+  if constexpr (BITS < 0) {
+    todo = __ballot(lane < n_units && a.scale[u0 + (lane < n_units ? lane : 0)] == kLeft);
+    if (__syncthreads_or(todo != 0ull) == 0) return;
+    n_units = __builtin_popcountll(todo);
+  }
   for (int i = tid; i < (a.d_in + 31) >> 5; i += 256) mask[i] = 0u;
   __syncthreads();
   for (int p = tid; p < a.k; p += 256) {
@@ -273,16 +341,37 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
   __syncthreads();
   const int ncand = a.n_lo * a.n_hi;
   float fa[CPL], fb[CPL];
+  auto cuts = [&](int l) __attribute__((always_inline)) {
 #pragma unroll
-  for (int c = 0; c < CPL; ++c) {
-    const int id = tl + LANES * c;
-    const int i = id / a.n_hi, j = id - i * a.n_hi;
-    fa[c] = cut_fraction(a.shrink, i < a.n_lo ? i : 0, a.n_lo);
-    fb[c] = cut_fraction(a.shrink, j, a.n_hi);
+    for (int c = 0; c < CPL; ++c) {
+      const int id = l + LANES * c;
+      const int i = id / a.n_hi, j = id - i * a.n_hi;
+      fa[c] = cut_fraction(a.shrink, i < a.n_lo ? i : 0, a.n_lo);
+      fb[c] = cut_fraction(a.shrink, j, a.n_hi);
+    }
+  };
+  if constexpr (BITS <= 0) cuts(tl);
+  // what follows from the value is worked out where it is used: kept out of the registers of the rest
+  auto seldom = [](auto l) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(l));
+    return l;
+  };
+  // a lane's half of a diagonal: its first and last point (i, d - i), and their cuts
+  float f0a = 0.f, f0b = 0.f, f1a = 0.f, ft = 0.f;
+  auto half_of = [&](int l, int &i0, int &i1, int &j0) __attribute__((always_inline)) {
+    const int m = a.n_hi - 1, d = min(l >> 1, 2 * m), i_min = max(0, d - m), i_max = min(d, m), h0 = (i_max - i_min + 2) >> 1;
+    i0 = l & 1 ? min(i_min + h0, i_max) : i_min;
+    i1 = l & 1 ? i_max : i_min + h0 - 1;
+    j0 = d - i0;
+  };
+  if constexpr (BITS > 0) {
+    int i0, i1, j0;
+    half_of(lane, i0, i1, j0);
+    f0a = cut_fraction(a.shrink, i0, a.n_hi);
+    f0b = cut_fraction(a.shrink, j0, a.n_hi);
+    f1a = cut_fraction(a.shrink, i1, a.n_hi);
+    ft = cut_fraction(a.shrink, min(lane, a.n_hi - 1), a.n_hi);
   }
-  const int team = TW == 4 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wv;
-  const int u0 = team * a.units_per_wave;
-  const int n_units = a.units - u0 < a.units_per_wave ? a.units - u0 : a.units_per_wave;   // same for the team
   if (n_units <= 0) return;                        // four waves: the whole workgroup
   int row = u0 / a.n_groups, gi = u0 - row * a.n_groups;
   auto team_barrier = [&]() __attribute__((always_inline)) {
@@ -295,25 +384,35 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
     const int c0 = g * a.g, len = a.d_in - c0 < a.g ? a.d_in - c0 : a.g;
     const _Float16 *src = a.w + (size_t)r * a.d_in + c0;
     typedef _Float16 hv __attribute__((ext_vector_type(V)));
+    if (a.vec) {                                   // rows on the grid of V elements, len a multiple of V
 #pragma unroll
-    for (int t = 0; t < NT; t += V) {
-      const int c = T::column(t, tl);
-      if (a.vec) {                                 // rows on the grid of V elements, len a multiple of V
+      for (int t = 0; t < NT; t += V) {
+        const int c = T::column(t, tl);
         const hv v = *reinterpret_cast<const hv *>(src + (c < len ? c : len - V));
 #pragma unroll
         for (int e = 0; e < V; ++e) dst[t + e] = v[e];
-      } else {
+      }
+    } else {
+      const int l = seldom(tl);                    // or the columns of all weights stay in registers
 #pragma unroll
-        for (int e = 0; e < V; ++e) dst[t + e] = src[c + e < len ? c + e : len - 1];
+      for (int t = 0; t < NT; ++t) {
+        const int c = T::column(t, l);
+        dst[t] = src[c < len ? c : len - 1];
       }
     }
   };
   // a wave fetches its next group while it searches one; with four waves to a row other workgroups fill the wait
-  constexpr bool kAhead = TW == 1;
+  constexpr bool kAhead = TW == 1 && BITS >= 0;
   float cur[NT];
   _Float16 nxt[NT];
-  fetch(nxt, row, gi);
+  if (BITS >= 0) fetch(nxt, row, gi);
   for (int uu = 0; uu < n_units; ++uu) {
+    if constexpr (BITS < 0) {
+      const int u = u0 + __builtin_ctzll(todo);
+      todo &= todo - 1;
+      row = u / a.n_groups;
+      gi = u - row * a.n_groups;
+    }
     const int c0 = gi * a.g;
     const int len = a.d_in - c0 < a.g ? a.d_in - c0 : a.g;
     int nrow = row, ngi = gi + 1;
@@ -321,14 +420,13 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
       ngi = 0;
       ++nrow;
     }
-    if (!kAhead && uu > 0) fetch(nxt, row, gi);
+    if (!kAhead && (BITS < 0 || uu > 0)) fetch(nxt, row, gi);
 #pragma unroll
     for (int t = 0; t < NT; ++t) cur[t] = (float)nxt[t];
     if (kAhead && uu + 1 < n_units) fetch(nxt, nrow, ngi);
     // ---- range; an empty histogram ----
-    unsigned long long kept = 0;                   // bit t: weight t of this lane takes part
+    std::conditional_t<(NT > 32), unsigned long long, u32> kept = 0;     // bit t: weight t of this lane takes part
     float lo = INFINITY, hi = -INFINITY;
-    bool odd = false;                              // a weight that is no number
 #pragma unroll
     for (int t = 0; t < NT; t += V) {
       const int c = T::column(t, tl);
@@ -337,178 +435,158 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
         m = ~(mask[(c0 + c) >> 5] >> ((c0 + c) & 31)) & ((1u << V) - 1u);
         if (len - c < V) m &= (1u << (len - c)) - 1u;
       }
-      kept |= (unsigned long long)m << t;
+      kept |= (decltype(kept))m << t;
 #pragma unroll
       for (int e = 0; e < V; ++e) {
-        const float v = cur[t + e];
-        const bool in = (m >> e) & 1u;
-        odd |= in && !(__builtin_fabsf(v) < INFINITY);
-        lo = __builtin_fminf(lo, in ? v : INFINITY);      // ignores what is no number
-        hi = __builtin_fmaxf(hi, in ? v : -INFINITY);
+        const u32 v = __builtin_bit_cast(u32, cur[t + e]), in = (u32)__builtin_amdgcn_sbfe((int)m, e, 1);      // all ones or none
+        lo = __builtin_fminf(lo, __builtin_bit_cast(float, (in & v) | (~in & 0x7f800000u)));      // ignores what is no number
+        hi = __builtin_fmaxf(hi, __builtin_bit_cast(float, (in & v) | (~in & 0xff800000u)));
+        cur[t + e] = __builtin_bit_cast(float, in & v);
       }
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) bins[tl * 4 + i] = 0ull;
-    lo = wave_all(lo, [](float x, float y) { return __builtin_fminf(x, y); });
-    hi = wave_all(hi, [](float x, float y) { return __builtin_fmaxf(x, y); });
-    int cnt = 0;                                   // kept weights of the wave
-#pragma unroll
-    for (int t = 0; t < NT; ++t) cnt += __builtin_popcountll(__ballot((kept >> t) & 1u));
-    bool any_odd = __ballot(odd) != 0ull;
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    bool any = __ballot(kept != 0) != 0ull;
     if constexpr (TW == 4) {
       if (lane == 0) {
         sh[0].wave[wv][0] = lo;
         sh[0].wave[wv][1] = hi;
-        sh[0].wave[wv][2] = (float)cnt;
-        sh[0].wave[wv][3] = any_odd ? 1.f : 0.f;
+        sh[0].wave[wv][2] = any ? 1.f : 0.f;
       }
       __syncthreads();
-      cnt = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float l = sh[0].wave[i][0], h = sh[0].wave[i][1];
         lo = l < lo ? l : lo;
         hi = h > hi ? h : hi;
-        cnt += (int)sh[0].wave[i][2];
-        any_odd |= sh[0].wave[i][3] != 0.f;
+        any |= sh[0].wave[i][2] != 0.f;
       }
     } else {
       wave_lds_fence();
     }
-    const bool nothing = degenerate(lo, hi, cnt);
+    const bool nothing = degenerate(lo, hi, any ? 1 : 0);
     Best best = {1.f, 1.f, 0.f, 0.f, 0};
+    bool left = false;                             // for the general grid's kernel
     if (!nothing) {
-      Cand cd[CPL];
-      float bound[CPL];
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        cd[c] = candidate<false>(lo, hi, fa[c], fb[c], a.qmax, 1.f / a.qmax);
-        bound[c] = -INFINITY;
-      }
-      if (any_odd) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) cd[c] = candidate<true>(lo, hi, fa[c], fb[c], a.qmax, 0.f);
-      }
       // error of grid point (s, inv, za, zb) over this lane's weights, over the wave
       auto evaluate = [&](const Cand &p) __attribute__((always_inline)) {
         float e = 0.f;
+        // 0 is a level: what does not take part, held as 0, adds nothing.  (Few weights: a branch costs more than their masks.)
+        if (NT >= 8 && p.a <= 0.f && p.b >= 0.f) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const float v = cur[t];
-          const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(v * p.inv), p.a, p.b);   // q - z
-          float d = __builtin_fmaf(-p.s, q, v);
-          d = (kept >> t) & 1u ? d : 0.f;
-          e = __builtin_fmaf(d, d, e);
+          for (int t = 0; t < NT; ++t) {
+            const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(cur[t] * p.inv), p.a, p.b);   // q - z
+            const float d = __builtin_fmaf(-p.s, q, cur[t]);
+            e = __builtin_fmaf(d, d, e);
+            if (NT >= 16 && t % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          const auto in = NT >= 8 ? seldom(kept) : kept;
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(cur[t] * p.inv), p.a, p.b);
+            const float d = (in >> t) & 1u ? __builtin_fmaf(-p.s, q, cur[t]) : 0.f;
+            e = __builtin_fmaf(d, d, e);
+            if (NT >= 16 && t % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+          }
         }
         return wave_sum(e);
       };
-      const float idelta = (float)F / (hi - lo);
-      float least = INFINITY;                      // least value (not bound) from the table, and its grid point
-      int first = 0x7fffffff;
-      if (!any_odd) {
-        // ---- histogram: count in the upper half, sum of the offsets inside the bin (in 2^-16 bins) in the lower ----
-        float s2 = 0.f;
+      const float idelta = (float)F * __builtin_amdgcn_rcpf(hi - lo);      // bins per unit, to a unit in the last place
+      // ---- histogram: count in the upper half, sum of the offsets inside the bin (in 2^-16 bins) in the lower ----
+      float s2 = 0.f;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const float u = (cur[t] - lo) * idelta;
-          int b = (int)u;
-          b = b < 0 ? 0 : (b > F - 1 ? F - 1 : b);
-          const float f = __builtin_fminf(__builtin_fmaxf(u - (float)b, 0.f), 1.f);
-          const float uc = u - (float)(F / 2);
-          if ((kept >> t) & 1u) {
-            atomicAdd(&bins[b], (1ull << 32) | (unsigned long long)(u32)(f * 65536.f + 0.5f));
-            s2 = __builtin_fmaf(uc, uc, s2);
-          }
-        }
-        s2 = wave_sum(s2);
-        team_barrier();
-        // ---- G at the edges: the increase over bin b is -(weights below it) - (weights in it - their offsets) ----
-        unsigned long long h[4];
-        int n4 = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          h[i] = bins[tl * 4 + i];
-          n4 += (int)(h[i] >> 32);
-        }
-        const int incl = scan_lanes(n4);
-        float dg[4], d4 = 0.f;
-        int below = incl - n4;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int n = (int)(h[i] >> 32);
-          dg[i] = -(float)below - ((float)n - (float)(u32)h[i] * 0x1p-16f);
-          below += n;
-          d4 += dg[i];
-        }
-        const float ginc = scan_lanes(d4);
-        float g = ginc - d4, wbelow = 0.f;         // of the wave's own bins; weights in the waves before
-        if constexpr (TW == 4) {
-          if (lane == 63) {
-            sh[0].scan_i[wv] = incl;
-            sh[0].scan_f[wv] = ginc;
-          }
-          if (lane == 0) sh[0].wave[wv][0] = s2;
-          __syncthreads();
-          s2 = (sh[0].wave[0][0] + sh[0].wave[1][0]) + (sh[0].wave[2][0] + sh[0].wave[3][0]);
-          float goff = 0.f;
-#pragma unroll
-          for (int i = 0; i < 3; ++i)
-            if (i < wv) {
-              goff += sh[0].scan_f[i] - wbelow * 256.f;
-              wbelow += (float)sh[0].scan_i[i];
-            }
-          g += goff - wbelow * (float)(lane * 4);
-        }
-        Knot *knot = reinterpret_cast<Knot *>(bins);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float d = dg[i] - wbelow;
-          knot[tl * 4 + i + 1] = Knot{g, d};
-          g += d;
-        }
-        if (tl == 0) knot[0] = Knot{0.f, 0.f};
-        if (tl == LANES - 1) knot[F + 1] = Knot{g, -(float)cnt};
-        team_barrier();
-        const float gend = knot[F + 1].g, n = (float)cnt;
-        const float s1 = gend + n * (float)(F / 2);            // sum of the centred weights
-        // ---- bounds ----
-        // What rounding can do to a value: eight operations on terms of at most `mag`, and positions (midpoints, levels)
-        // that are off by `eps` bins, each seen by all weights
-        const float far = __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)) * idelta, half = (float)(F / 2);
-        const float mag = 2.f * (s2 + half * (half * n + 2.f * __builtin_fabsf(s1)));
-        const float eps = 3.f * (float)F + 2.f * far;
-        const float slack = 0x1p-24f * (8.f * mag + 4.f * n * (float)F * eps);
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-          const float su = cd[c].s * idelta, top = (cd[c].s * cd[c].b - lo) * idelta - half;
-          const float p1 = (cd[c].s * (cd[c].a + 0.5f) - lo) * idelta + 1.f;
-          const bool inside = p1 >= 0.f && __builtin_fmaf(a.qmax - 1.f, su, p1) < (float)(F + 2);
-          float gs = 0.f;
-          if (inside) {
-#pragma unroll
-            for (int l = 0; l < 15; ++l) {
-              if (l == 7 && a.qmax < 15.f) break;
-              const float p = __builtin_fmaf((float)l, su, p1);
-              const Knot k = knot[(u32)p];
-              gs = __builtin_fmaf(__builtin_amdgcn_fractf(p), k.dg, gs + k.g);
-            }
-          }
-          const float sq = __builtin_fmaf(top, __builtin_fmaf(top, n, -2.f * s1), s2);
-          const float e = __builtin_fmaf(2.f * su, gs, sq);
-          const int id = tl + LANES * c;
-          const bool is = id < ncand;
-          bound[c] = is ? (inside ? e - slack : -INFINITY) : INFINITY;
-          if (is && inside && e < least) {
-            least = e;
-            first = id;
-          }
+      for (int t = 0; t < NT; ++t) {
+        const float u = (cur[t] - lo) * idelta;
+        const int b = (int)__builtin_amdgcn_fmed3f(u, 0.f, (float)(F - 1));
+        const float f = u - (float)b;
+        const float uc = u - (float)(F / 2);
+        const u32 off = (u32)__builtin_fmaf(f, 65536.f, 0.5f);
+        if constexpr (NT >= 8) {                   // adds nothing for what does not take part: no branch per weight
+          const u32 in = (u32)__builtin_amdgcn_sbfe((int)(u32)(kept >> (t & 32)), t & 31, 1);
+          const float ui = __builtin_bit_cast(float, in & __builtin_bit_cast(u32, uc));
+          atomicAdd(&bins[b], ((unsigned long long)(in & 1u) << 32) | (unsigned long long)(in & off));
+          s2 = __builtin_fmaf(ui, ui, s2);
+          if (NT >= 16 && t % 8 == 7) __builtin_amdgcn_sched_barrier(0);      // or all weights' operands are in registers at once
+        } else if ((kept >> t) & 1u) {
+          atomicAdd(&bins[b], (1ull << 32) | (unsigned long long)off);
+          s2 = __builtin_fmaf(uc, uc, s2);
         }
       }
+      s2 = wave_sum(s2);
+      team_barrier();
+      // ---- G at the edges: the increase over bin b is -(weights below it) - (weights in it - their offsets) ----
+      unsigned long long h[4];
+      int n4 = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        h[i] = bins[tl * 4 + i];
+        n4 += (int)(h[i] >> 32);
+      }
+      const int incl = scan_lanes(n4);
+      int cnt = __builtin_amdgcn_readlane(incl, 63);           // weights that take part
+      float dg[4], d4 = 0.f;
+      int upto = incl - n4;                        // weights up to the bin's upper edge
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        upto += (int)(h[i] >> 32);
+        dg[i] = __builtin_fmaf((float)(u32)h[i], 0x1p-16f, -(float)upto);
+        d4 = i == 0 ? dg[0] : d4 + dg[i];
+      }
+      const float ginc = scan_lanes(d4);
+      float g = ginc - d4, wbelow = 0.f;         // of the wave's own bins; weights in the waves before
+      if constexpr (TW == 4) {
+        if (lane == 63) {
+          sh[0].scan_i[wv] = incl;
+          sh[0].scan_f[wv] = ginc;
+        }
+        if (lane == 0) sh[0].wave[wv][0] = s2;
+        __syncthreads();
+        s2 = (sh[0].wave[0][0] + sh[0].wave[1][0]) + (sh[0].wave[2][0] + sh[0].wave[3][0]);
+        cnt = (sh[0].scan_i[0] + sh[0].scan_i[1]) + (sh[0].scan_i[2] + sh[0].scan_i[3]);
+        float goff = 0.f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          if (i < wv) {
+            goff += sh[0].scan_f[i] - wbelow * 256.f;
+            wbelow += (float)sh[0].scan_i[i];
+          }
+        g += goff - wbelow * (float)(lane * 4);
+      }
+      Knot *knot = reinterpret_cast<Knot *>(bins);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float d = dg[i] - wbelow;
+        knot[tl * 4 + i + 1] = Knot{g, d};
+        g += d;
+      }
+      if (tl == 0) knot[0] = Knot{0.f, 0.f};
+      if (tl == LANES - 1) knot[F + 1] = Knot{g, -(float)cnt};
+      team_barrier();
+      const float gend = knot[F + 1].g, n = (float)cnt;
+      const float s1 = gend + n * (float)(F / 2);            // sum of the centred weights
+      const bool any_odd = !(s2 < INFINITY);       // a weight that is no number: the table says nothing
+      // ---- bounds ----
+      // What rounding can do to a value: eight operations on terms of at most `mag`, and positions (midpoints, levels)
+      // that are off by `eps` bins, each seen by all weights
+      const float far = __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)) * idelta, half = (float)(F / 2);
+      const float mag = 2.f * (s2 + half * (half * n + 2.f * __builtin_fabsf(s1)));
+      const float eps = (BITS > 0 ? 5.f : 3.f) * (float)F + 2.f * far;
+      const float slack = 0x1p-24f * (8.f * mag + 4.f * n * (float)F * eps);
+      const float to_bins = any_odd ? 1.f : idelta * idelta * (1.f + 0x1p-12f);
+      // errors this close may change places: four deviations of the rounding of two sums of cnt terms (0.3 sqrt(cnt / 3) units in
+      // the 24th place each)
+      const float close = 1.f + 0x1p-24f * (__builtin_amdgcn_sqrtf((float)cnt) + 8.f);
+      auto lane_of = [&](float v, int src) __attribute__((always_inline)) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
+      };
       // The error of a grid point as one sum in the order of the columns, which is what ranks points whose errors agree to
       // the rounding of such sums: the residuals go through LDS (where the bins were), the sum runs on every lane.
       auto residual = [&](const Cand &p, int t) __attribute__((always_inline)) {
         const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(cur[t] * p.inv), p.a, p.b);
-        return (kept >> t) & 1u ? __builtin_fmaf(-p.s, q, cur[t]) : 0.f;
+        return (seldom(kept) >> t) & 1u ? __builtin_fmaf(-p.s, q, cur[t]) : 0.f;
       };
       float *res = reinterpret_cast<float *>(bins);
       auto add4 = [](float e, f4v d) __attribute__((always_inline)) {
@@ -523,268 +601,427 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
           for (int t = t0; t < t0 + V; ++t) res[lane * V + t - t0] = residual(p, t);
           wave_lds_fence();
           const int n4 = min(V * 64, (len - t0 * 64 + 3) & ~3) >> 2;
+#pragma unroll 4
           for (int i = 0; i < n4; ++i) e = add4(e, reinterpret_cast<const f4v *>(res)[i]);
         }
         return e;
       };
-      // Four waves: wave c sums point c of up to four; the residuals come 512 columns (one wave's run of them) at a time, 32
-      // in registers while the next 32 come from LDS.  One point after the other, a chain of LDS reads each, took 87 us
-      // per point on a row of 5120 columns.
-      auto in_order4 = [&](const int (&ids)[4], int count) __attribute__((always_inline)) {
-        float e = 0.f;
+      if constexpr (BITS > 0) {
+        bool found = false;
+        constexpr int L = (1 << BITS) - 1, Z = BITS == 3 ? 4 : 7;
+        const float qmax = (float)L, rqmax = 1.f / (float)L;
+        const float r = hi - lo, lo0 = cut_lo(lo, f0a, r), width = cut_hi(hi, f0b, r) - lo0;
+        // no point's width is further from another's than 5.6 2^-24 (r + largest end): seven roundings each
+        const float tol = 0x1p-21f * (r + __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)));
+        const float s = step_of(width, qmax, rqmax);
+        const float lo_t = cut_lo(lo, ft, r);
+        bool other = !(s > 0x1p-14f);
+        if (__ballot(step_of(width - tol, qmax, rqmax) != step_of(width + tol, qmax, rqmax)) != 0ull) {
+          const float hi_t = cut_hi(hi, ft, r);
+          int i0, i1, j0;
+          half_of(seldom(lane), i0, i1, j0);
+#pragma unroll 1
+          for (int p = 1; p < 8; ++p) {
+            const int o = min(p, i1 - i0);
+            other |= step_of(__shfl(hi_t, j0 - o) - __shfl(lo_t, i0 + o), qmax, rqmax) != s;
+          }
+        }
+        const float inv = reciprocal(s), su = s * idelta;
+        const float z0 = zero_of(lo0, inv), z1 = zero_of(cut_lo(lo, f1a, r), inv), span = z0 - z1;
+        const float p1 = (s * (0.5f - z0) - lo) * idelta + 1.f;
+        other |= !(span <= (float)(Z - 1)) || !(p1 >= 0.f) || !(__builtin_fmaf(span + (float)(L - 1), su, p1) < (float)(F + 2));
+        if (!any_odd && __ballot(other) == 0ull) {
+          float v[L + Z - 1];                      // G at the midpoints of the run
+          float core = 0.f;                        // sum of those that all its zero points have
+          constexpr int AT_ONCE = BITS == 3 ? 5 : 7;     // reads in flight
 #pragma unroll
-        for (int t0 = 0; t0 < NT; t0 += V)
-          for (int k = 0; k < 4; ++k) {
-            const int left = len - t0 * LANES - k * 512;
-            if (left <= 0) break;                   // the same for all
-            __syncthreads();
-            if (wv == k) {
+          for (int t0 = 0; t0 < L + Z - 1; t0 += AT_ONCE) {
+            Knot k[AT_ONCE];
+            float f[AT_ONCE];
 #pragma unroll
-              for (int c = 0; c < 4; ++c)
-                if (c < count) {
-                  const Cand p = sh[0].cand[ids[c]];
-#pragma unroll
-                  for (int t = t0; t < t0 + V; ++t) res[c * 512 + lane * V + t - t0] = residual(p, t);
-                }
+            for (int t = 0; t < AT_ONCE; ++t) {
+              float p = __builtin_fmaf((float)(t0 + t), su, p1);
+              if (t0 + t >= L) p = __builtin_fminf(p, (float)(F + 1));      // not of this lane's zero points
+              k[t] = knot[(u32)p];
+              f[t] = __builtin_amdgcn_fractf(p);
             }
-            __syncthreads();
-            if (wv < count) {
-              const f4v *r4 = reinterpret_cast<const f4v *>(res) + wv * 128;
-              const int n4 = min(128, (left + 31) / 32 * 8);
-              f4v d[8], nx[8];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-              for (int j = 0; j < 8; ++j) d[j] = r4[j];
-              for (int i = 0; i < n4; i += 8) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) nx[j] = r4[(i + 8 < 128 ? i + 8 : i) + j];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) e = add4(e, d[j]);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) d[j] = nx[j];
-              }
+            for (int t = 0; t < AT_ONCE; ++t) {
+              v[t0 + t] = __builtin_fmaf(f[t], k[t].dg, k[t].g);
+              if (t0 + t >= Z - 1 && t0 + t < L) core += v[t0 + t];
             }
           }
-        if (lane == 0) sh[0].wave[wv][3] = e;
-        __syncthreads();
-      };
-      // errors this close may change places: four deviations of the rounding of two sums of cnt terms (0.3 sqrt(cnt / 3) units in
-      // the 24th place each)
-      const float close = 1.f + 0x1p-24f * (__builtin_sqrtf((float)cnt) + 8.f);
-      // ---- the grid point with the least value first, then all that may be better ----
-      const float to_bins = any_odd ? 1.f : idelta * idelta * (1.f + 0x1p-12f);
-      best.e = INFINITY;
-      best.id = 0x7fffffff;
-      const float wl = wave_all(least, [](float x, float y) { return __builtin_fminf(x, y); });
-      int wf = wave_all(least == wl ? first : 0x7fffffff, [](int x, int y) { return x < y ? x : y; });
-      auto lane_of = [&](float v, int src) __attribute__((always_inline)) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
-      };
-      auto take = [&](float e, int id, const Cand &p) __attribute__((always_inline)) {
-        if (e < best.e || (e == best.e && id < best.id)) {
-          best.e = e;
-          best.id = id;
-          best.s = p.s;
-          best.inv = p.inv;
-          best.z = 0.f - p.a;
-        }
-      };
-      // Points of one width often have the same step size and zero point: their errors are the same, the lower index wins
-      auto same_as_best = [&](const Cand &p, int id) __attribute__((always_inline)) {
-        const bool same = p.s == best.s && 0.f - p.a == best.z && best.id != 0x7fffffff;
-        if (same && id < best.id) best.id = id;
-        return same;
-      };
-      if constexpr (TW == 1) {
-        auto cand_of = [&](int id) __attribute__((always_inline)) {
-          const int src = id & 63, slot = id >> 6;
-          Cand p = {lane_of(cd[0].s, src), lane_of(cd[0].inv, src), lane_of(cd[0].a, src), lane_of(cd[0].b, src)};
+          float gs[Z];                             // sums of L in a row: what comes before those, and after
+          gs[Z - 1] = core;
 #pragma unroll
-          for (int c = 1; c < CPL; ++c)
-            if (slot == c) p = Cand{lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
-          return p;
-        };
-        wf = __builtin_amdgcn_readfirstlane(wf);
-        float mine[CPL];                            // errors of this lane's points that were evaluated
+          for (int k = Z - 2; k >= 0; --k) gs[k] = gs[k + 1] + v[k];
+          float after = 0.f;
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) mine[c] = INFINITY;
-        if (wf != 0x7fffffff) {
-          const Cand p = cand_of(wf);
-          const float e = evaluate(p);
-          take(e, wf, p);
+          for (int k = 1; k < Z; ++k) {
+            after += v[L + k - 1];
+            gs[k] += after;
+          }
+          const float top = (s * (qmax - z0) - lo) * idelta - half;
+          // the halves' runs often meet in one zero point, which the first half has
+          const float z1_first = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, z1), 0xA0, 0xf, 0xf, true));
+          const bool live = lane < 4 * a.n_hi - 2;
+          float bound[Z];
 #pragma unroll
-          for (int c = 0; c < CPL; ++c) mine[c] = wf == lane + 64 * c ? e : mine[c];
+          for (int k = 0; k < Z; ++k) {
+            const float tk = __builtin_fmaf((float)k, su, top);
+            const float e = __builtin_fmaf(2.f * su, gs[k], __builtin_fmaf(tk, __builtin_fmaf(tk, n, -2.f * s1), s2)) - slack;
+            const bool is = live && (k == 0 ? !((lane & 1) && z0 == z1_first) : (float)k <= span);
+            bound[k] = is ? e : INFINITY;
+          }
+          // the point with the least bound, then the next one until bounds exceed the least error found
+          best.e = INFINITY;
+          Best second = best;                      // and the next best, and the third one's error
+          float third = INFINITY;
+          const float lim = to_bins * close;
+          for (;;) {
+            float mine = bound[0];
+#pragma unroll
+            for (int k = 1; k < Z; ++k) mine = __builtin_fminf(mine, bound[k]);
+            if (__ballot(mine <= best.e * lim && mine < INFINITY) == 0ull) break;
+            const float wl = wave_min(mine);
+            const unsigned long long at = __ballot(mine == wl);
+            if (at == 0ull) break;
+            const int src = __builtin_ctzll(at);
+            float kz = 0.f;                        // which of the lane's zero points
+            bool due = lane == src;
+#pragma unroll
+            for (int k = 0; k < Z; ++k) {
+              const bool this_one = due && bound[k] == wl;
+              kz = this_one ? (float)k : kz;
+              bound[k] = this_one ? INFINITY : bound[k];
+              due = due && !this_one;
+            }
+            Cand p;
+            p.s = lane_of(s, src);
+            p.inv = lane_of(inv, src);
+            const float z = lane_of(z0 - kz, src);
+            p.a = 0.f - z;
+            p.b = qmax - z;
+            // the points of the diagonal with this zero point; none where they step over it
+            const int d = src >> 1, ia = max(0, d - (a.n_hi - 1)), ib = min(d, a.n_hi - 1);
+            const unsigned long long of = __ballot(zero_of(lo_t, p.inv) == z) & (((2ull << ib) - 1ull) & ~((1ull << ia) - 1ull));
+            if (of == 0ull) continue;
+            const int i = __builtin_ctzll(of), id = i * a.n_hi + d - i;
+            const Best b = {p.s, p.inv, 0.f - p.a, evaluate(p), id};      // no negative zero
+            third = __builtin_fminf(third, __builtin_fmaxf(b.e, second.e));
+            const bool better = b.e < best.e || (b.e == best.e && id < best.id);
+            if (better || b.e < second.e) second = better ? best : b;
+            if (better) best = b;
+          }
+          const float near = best.e * close;
+          found = best.e < INFINITY && !(best.e > 0.f && third <= near);
+          if (found && best.e > 0.f && second.e <= near) {       // two that are too close to tell
+            best.e = in_order(Cand{best.s, best.inv, 0.f - best.z, qmax - best.z});
+            second.e = in_order(Cand{second.s, second.inv, 0.f - second.z, qmax - second.z});
+            if (second.e < best.e || (second.e == best.e && second.id < best.id)) best = second;
+          }
         }
-        if (any_odd) {
-          // weights that are no numbers: every grid point, and if none has an error that is one, the values of point 63
-          const Cand p = cand_of(63);
-          best.s = p.s; best.inv = p.inv; best.z = 0.f - p.a;
-        }
+        left = !found;
+      }
+      if constexpr (BITS <= 0) {
+        Cand cd[CPL];
+        float bound[CPL];
+        float least = INFINITY;                      // least value (not bound) from the table, and its grid point
+        int first = 0x7fffffff;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-          unsigned long long m = __ballot(bound[c] <= best.e * to_bins && lane + 64 * c < ncand);
-          while (m) {
-            const int src = __builtin_ctzll(m);
-            m &= m - 1;
-            const int id = src + 64 * c;
-            if (id == wf || !(lane_of(bound[c], src) <= best.e * to_bins)) continue;
-            const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
-            // Step sizes at their least value span more than the group: bounds rule nothing out, but most points are the
-            // same as one before and go with it (one by one they took longer than the plain search)
-            if (__builtin_bit_cast(u32, p.s) == kLeastStep) m &= ~__ballot(cd[c].s == p.s && cd[c].a == p.a);
-            if (same_as_best(p, id)) continue;
-            const float e = evaluate(p);
-            take(e, id, p);
-            mine[c] = lane == src ? e : mine[c];
-          }
+          cd[c] = candidate<false>(lo, hi, fa[c], fb[c], a.qmax, 1.f / a.qmax);
+          bound[c] = -INFINITY;
         }
-        if (!any_odd && best.e > 0.f) {
-          const float lim = best.e * close;
-          int close_ones = 0;
+        if (any_odd) {
 #pragma unroll
-          for (int c = 0; c < CPL; ++c)
-            close_ones += __builtin_popcountll(__ballot(mine[c] <= lim && !(cd[c].s == best.s && 0.f - cd[c].a == best.z)));
-          if (close_ones > 0) {
-            // of all points that may be meant by one of these, also those that were taken for the same as another
+          for (int c = 0; c < CPL; ++c) cd[c] = candidate<true>(lo, hi, fa[c], fb[c], a.qmax, 0.f);
+        } else {
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) mine[c] = bound[c] <= lim * to_bins && lane + 64 * c < ncand && mine[c] == INFINITY ? lim : mine[c];
-            best.e = INFINITY;
-            best.id = 0x7fffffff;
+          for (int c = 0; c < CPL; ++c) {
+            const float su = cd[c].s * idelta, top = (cd[c].s * cd[c].b - lo) * idelta - half;
+            const float p1 = (cd[c].s * (cd[c].a + 0.5f) - lo) * idelta + 1.f;
+            const bool inside = p1 >= 0.f && __builtin_fmaf(a.qmax - 1.f, su, p1) < (float)(F + 2);
+            float gs = 0.f;
+            if (inside) {
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-              unsigned long long m = __ballot(mine[c] <= lim);
-              while (m) {
-                const int src = __builtin_ctzll(m);
-                m &= m - 1;
-                const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
-                m &= ~__ballot(cd[c].s == p.s && cd[c].a == p.a);
-                if (!same_as_best(p, src + 64 * c)) take(in_order(p), src + 64 * c, p);
+              for (int l = 0; l < 15; ++l) {
+                if (l == 7 && a.qmax < 15.f) break;
+                const float p = __builtin_fmaf((float)l, su, p1);
+                const Knot k = knot[(u32)p];
+                gs = __builtin_fmaf(__builtin_amdgcn_fractf(p), k.dg, gs + k.g);
               }
+            }
+            const float sq = __builtin_fmaf(top, __builtin_fmaf(top, n, -2.f * s1), s2);
+            const float e = __builtin_fmaf(2.f * su, gs, sq);
+            const int id = tl + LANES * c;
+            const bool is = id < ncand;
+            bound[c] = is ? (inside ? e - slack : -INFINITY) : INFINITY;
+            if (is && inside && e < least) {
+              least = e;
+              first = id;
             }
           }
         }
-      } else {
-        TeamShared &S = sh[0];
-        S.cand[tid] = cd[0];
-        __syncthreads();                            // the last reads of wave[][0] are done
-        if (lane == 0) {
-          S.wave[wv][0] = wl;
-          S.wave[wv][1] = __builtin_bit_cast(float, wf);
-        }
-        __syncthreads();
-        float l4 = INFINITY;
-        wf = 0x7fffffff;
+        // Four waves: wave c sums point c of up to four; the residuals come 512 columns (one wave's run of them) at a time, 32
+        // in registers while the next 32 come from LDS.  One point after the other, a chain of LDS reads each, took 87 us
+        // per point on a row of 5120 columns.
+        auto in_order4 = [&](const int (&ids)[4], int count) __attribute__((always_inline)) {
+          float e = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float l = S.wave[i][0];
-          const int f = __builtin_bit_cast(int, S.wave[i][1]);
-          if (l < l4 || (l == l4 && f < wf)) {
-            l4 = l;
-            wf = f;
-          }
-        }
-        wf = __builtin_amdgcn_readfirstlane(wf);
-        float lim = INFINITY;
-        if (wf != 0x7fffffff) {
-          const Cand p = S.cand[wf];
-          const float e = evaluate(p);
-          if (lane == 0) S.wave[wv][2] = e;
+          for (int t0 = 0; t0 < NT; t0 += V)
+            for (int k = 0; k < 4; ++k) {
+              const int left = len - t0 * LANES - k * 512;
+              if (left <= 0) break;                   // the same for all
+              __syncthreads();
+              if (wv == k) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                  if (c < count) {
+                    const Cand p = sh[0].cand[ids[c]];
+#pragma unroll
+                    for (int t = t0; t < t0 + V; ++t) res[c * 512 + lane * V + t - t0] = residual(p, t);
+                  }
+              }
+              __syncthreads();
+              if (wv < count) {
+                const f4v *r4 = reinterpret_cast<const f4v *>(res) + wv * 128;
+                const int n4 = min(128, (left + 15) / 16 * 4);
+                f4v d[4], nx[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d[j] = r4[j];
+                for (int i = 0; i < n4; i += 4) {
+#pragma unroll
+                  for (int j = 0; j < 4; ++j) nx[j] = r4[(i + 4 < 128 ? i + 4 : i) + j];
+#pragma unroll
+                  for (int j = 0; j < 4; ++j) e = add4(e, d[j]);
+#pragma unroll
+                  for (int j = 0; j < 4; ++j) d[j] = nx[j];
+                }
+              }
+            }
+          if (lane == 0) sh[0].wave[wv][3] = e;
           __syncthreads();
-          const float e4 = (S.wave[0][2] + S.wave[1][2]) + (S.wave[2][2] + S.wave[3][2]);
-          take(e4, wf, p);
-          lim = e4 * to_bins;
-        } else if (any_odd) {
-          const Cand p = S.cand[63];
-          best.s = p.s; best.inv = p.inv; best.z = 0.f - p.a;
-        }
-        const unsigned long long m = __ballot(bound[0] <= lim && tid < ncand && tid != wf);
-        if (lane == 0) S.alive[wv] = m;
-        __syncthreads();
-        int na = 0;
-        for (int i = 0; i < 4; ++i) {
-          unsigned long long left = uniform(S.alive[i]);
-          while (left) {
-            const int id = i * 64 + __builtin_ctzll(left);
-            left &= left - 1;
-            const float e = evaluate(S.cand[id]);
-            if (lane == 0) S.part[na][wv] = e;
-            ++na;
+        };
+        // ---- the grid point with the least value first, then all that may be better ----
+        best.e = INFINITY;
+        best.id = 0x7fffffff;
+        const float wl = wave_min(least);
+        int wf = wave_all(least == wl ? first : 0x7fffffff, [](int x, int y) { return x < y ? x : y; });
+        auto take = [&](float e, int id, const Cand &p) __attribute__((always_inline)) {
+          if (e < best.e || (e == best.e && id < best.id)) {
+            best.e = e;
+            best.id = id;
+            best.s = p.s;
+            best.inv = p.inv;
+            best.z = 0.f - p.a;
           }
-        }
-        __syncthreads();
-        na = 0;
-        for (int i = 0; i < 4; ++i) {
-          unsigned long long left = uniform(S.alive[i]);
-          while (left) {
-            const int id = i * 64 + __builtin_ctzll(left);
-            left &= left - 1;
-            take((S.part[na][0] + S.part[na][1]) + (S.part[na][2] + S.part[na][3]), id, S.cand[id]);
-            ++na;
+        };
+        // Points of one width often have the same step size and zero point: their errors are the same, the lower index wins
+        auto same_as_best = [&](const Cand &p, int id) __attribute__((always_inline)) {
+          const bool same = p.s == best.s && 0.f - p.a == best.z && best.id != 0x7fffffff;
+          if (same && id < best.id) best.id = id;
+          return same;
+        };
+        if constexpr (TW == 1) {
+          auto cand_of = [&](int id) __attribute__((always_inline)) {
+            const int src = id & 63, slot = id >> 6;
+            Cand p = {lane_of(cd[0].s, src), lane_of(cd[0].inv, src), lane_of(cd[0].a, src), lane_of(cd[0].b, src)};
+#pragma unroll
+            for (int c = 1; c < CPL; ++c)
+              if (slot == c) p = Cand{lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+            return p;
+          };
+          wf = __builtin_amdgcn_readfirstlane(wf);
+          float mine[CPL];                            // errors of this lane's points that were evaluated
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) mine[c] = INFINITY;
+          if (wf != 0x7fffffff) {
+            const Cand p = cand_of(wf);
+            const float e = evaluate(p);
+            take(e, wf, p);
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) mine[c] = wf == lane + 64 * c ? e : mine[c];
           }
-        }
-        if (!any_odd && best.e > 0.f && na > 0) {
-          // the points whose errors are close to the least, in ascending order: the first one evaluated and those listed
-          const float near = best.e * close;
-          float ef = INFINITY;
-          if (wf != 0x7fffffff) ef = (S.wave[0][2] + S.wave[1][2]) + (S.wave[2][2] + S.wave[3][2]);
-          const float bs = best.s, bz = best.z;
-          int found = 0, count = 0;
-          bool more = false;                        // than four of them
-          int ids[4] = {0, 0, 0, 0};
-          for (int pass = 0; pass < 2; ++pass) {    // looks for one beside the best, then ranks them, four at a time
-            int k = 0;
-            bool first_due = ef <= near;
-            if (pass == 1) {
-              if (more) count = 0;
+          if (any_odd) {
+            // weights that are no numbers: every grid point, and if none has an error that is one, the values of point 63
+            const Cand p = cand_of(63);
+            best.s = p.s; best.inv = p.inv; best.z = 0.f - p.a;
+          }
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) {
+            unsigned long long m = __ballot(bound[c] <= best.e * to_bins && lane + 64 * c < ncand);
+            while (m) {
+              const int src = __builtin_ctzll(m);
+              m &= m - 1;
+              const int id = src + 64 * c;
+              if (id == wf || !(lane_of(bound[c], src) <= best.e * to_bins)) continue;
+              const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+              // Step sizes at their least value span more than the group: bounds rule nothing out, but most points are the
+              // same as one before and go with it (one by one they took longer than the plain search)
+              if (__builtin_bit_cast(u32, p.s) == kLeastStep) m &= ~__ballot(cd[c].s == p.s && cd[c].a == p.a);
+              if (same_as_best(p, id)) continue;
+              const float e = evaluate(p);
+              take(e, id, p);
+              mine[c] = lane == src ? e : mine[c];
+            }
+          }
+          if (!any_odd && best.e > 0.f) {
+            const float lim = best.e * close;
+            int close_ones = 0;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c)
+              close_ones += __builtin_popcountll(__ballot(mine[c] <= lim && !(cd[c].s == best.s && 0.f - cd[c].a == best.z)));
+            if (close_ones > 0) {
+              // of all points that may be meant by one of these, also those that were taken for the same as another
+#pragma unroll
+              for (int c = 0; c < CPL; ++c) mine[c] = bound[c] <= lim * to_bins && lane + 64 * c < ncand && mine[c] == INFINITY ? lim : mine[c];
               best.e = INFINITY;
               best.id = 0x7fffffff;
-            }
-            auto rank = [&]() __attribute__((always_inline)) {
-              in_order4(ids, count);
-              for (int c = 0; c < count; ++c) {
-                const int id = c == 0 ? ids[0] : c == 1 ? ids[1] : c == 2 ? ids[2] : ids[3];
-                take(S.wave[c][3], id, S.cand[id]);
-              }
-              count = 0;
-            };
-            // at the least step size the points of one lower end are the same: the first of a run stands for it
-            float last_s = 0.f, last_a = 0.f;
-            auto due = [&](int id) __attribute__((always_inline)) {
-              const Cand p = S.cand[id];
-              if (p.s == last_s && p.a == last_a) return;
-              last_s = p.s;
-              last_a = p.a;
-              found += p.s == bs && 0.f - p.a == bz ? 0 : 1;
 #pragma unroll
-              for (int c = 0; c < 4; ++c) ids[c] = c == count ? id : ids[c];
-              ++count;
-            };
-            for (int i = 0; i < 4 && (pass == 0 || more); ++i) {
-              unsigned long long left = uniform(S.alive[i]);
-              while (left) {
-                const int id = i * 64 + __builtin_ctzll(left);
-                const bool close_one = (S.part[k][0] + S.part[k][1]) + (S.part[k][2] + S.part[k][3]) <= near;
-                const bool first_now = first_due && wf < id;
-                if (!first_now) {
-                  left &= left - 1;
-                  ++k;
-                }
-                first_due = first_due && !first_now;
-                if (first_now || close_one) due(first_now ? wf : id);
-                if (count == 4) {
-                  if (pass == 1) rank();
-                  more = true;
-                  count = 0;
+              for (int c = 0; c < CPL; ++c) {
+                unsigned long long m = __ballot(mine[c] <= lim);
+                while (m) {
+                  const int src = __builtin_ctzll(m);
+                  m &= m - 1;
+                  const Cand p = {lane_of(cd[c].s, src), lane_of(cd[c].inv, src), lane_of(cd[c].a, src), lane_of(cd[c].b, src)};
+                  m &= ~__ballot(cd[c].s == p.s && cd[c].a == p.a);
+                  if (!same_as_best(p, src + 64 * c)) take(in_order(p), src + 64 * c, p);
                 }
               }
             }
-            if (first_due && (pass == 0 || more)) due(wf);
-            if (found == 0) break;
-            if (pass == 1 && count > 0) rank();
+          }
+        } else {
+          TeamShared &S = sh[0];
+          S.cand[tid] = cd[0];
+          __syncthreads();                            // the last reads of wave[][0] are done
+          if (lane == 0) {
+            S.wave[wv][0] = wl;
+            S.wave[wv][1] = __builtin_bit_cast(float, wf);
+          }
+          __syncthreads();
+          float l4 = INFINITY;
+          wf = 0x7fffffff;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float l = S.wave[i][0];
+            const int f = __builtin_bit_cast(int, S.wave[i][1]);
+            if (l < l4 || (l == l4 && f < wf)) {
+              l4 = l;
+              wf = f;
+            }
+          }
+          wf = __builtin_amdgcn_readfirstlane(wf);
+          float lim = INFINITY;
+          if (wf != 0x7fffffff) {
+            const Cand p = S.cand[wf];
+            const float e = evaluate(p);
+            if (lane == 0) S.wave[wv][2] = e;
+            __syncthreads();
+            const float e4 = (S.wave[0][2] + S.wave[1][2]) + (S.wave[2][2] + S.wave[3][2]);
+            take(e4, wf, p);
+            lim = e4 * to_bins;
+          } else if (any_odd) {
+            const Cand p = S.cand[63];
+            best.s = p.s; best.inv = p.inv; best.z = 0.f - p.a;
+          }
+          const unsigned long long m = __ballot(bound[0] <= lim && tid < ncand && tid != wf);
+          if (lane == 0) S.alive[wv] = m;
+          __syncthreads();
+          int na = 0;
+          for (int i = 0; i < 4; ++i) {
+            unsigned long long left = uniform(S.alive[i]);
+            while (left) {
+              const int id = i * 64 + __builtin_ctzll(left);
+              left &= left - 1;
+              const float e = evaluate(S.cand[id]);
+              if (lane == 0) S.part[na][wv] = e;
+              ++na;
+            }
+          }
+          __syncthreads();
+          na = 0;
+          for (int i = 0; i < 4; ++i) {
+            unsigned long long left = uniform(S.alive[i]);
+            while (left) {
+              const int id = i * 64 + __builtin_ctzll(left);
+              left &= left - 1;
+              take((S.part[na][0] + S.part[na][1]) + (S.part[na][2] + S.part[na][3]), id, S.cand[id]);
+              ++na;
+            }
+          }
+          if (!any_odd && best.e > 0.f && na > 0) {
+            // the points whose errors are close to the least, in ascending order: the first one evaluated and those listed
+            const float near = best.e * close;
+            float ef = INFINITY;
+            if (wf != 0x7fffffff) ef = (S.wave[0][2] + S.wave[1][2]) + (S.wave[2][2] + S.wave[3][2]);
+            const float bs = best.s, bz = best.z;
+            int others = 0, count = 0;
+            bool more = false;                        // than four of them
+            int ids[4] = {0, 0, 0, 0};
+            for (int pass = 0; pass < 2; ++pass) {    // looks for one beside the best, then ranks them, four at a time
+              int k = 0;
+              bool first_due = ef <= near;
+              if (pass == 1) {
+                if (more) count = 0;
+                best.e = INFINITY;
+                best.id = 0x7fffffff;
+              }
+              auto rank = [&]() __attribute__((always_inline)) {
+                in_order4(ids, count);
+                for (int c = 0; c < count; ++c) {
+                  const int id = c == 0 ? ids[0] : c == 1 ? ids[1] : c == 2 ? ids[2] : ids[3];
+                  take(S.wave[c][3], id, S.cand[id]);
+                }
+                count = 0;
+              };
+              // at the least step size the points of one lower end are the same: the first of a run stands for it
+              float last_s = 0.f, last_a = 0.f;
+              auto due = [&](int id) __attribute__((always_inline)) {
+                const Cand p = S.cand[id];
+                if (p.s == last_s && p.a == last_a) return;
+                last_s = p.s;
+                last_a = p.a;
+                others += p.s == bs && 0.f - p.a == bz ? 0 : 1;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) ids[c] = c == count ? id : ids[c];
+                ++count;
+              };
+              for (int i = 0; i < 4 && (pass == 0 || more); ++i) {
+                unsigned long long left = uniform(S.alive[i]);
+                while (left) {
+                  const int id = i * 64 + __builtin_ctzll(left);
+                  const bool close_one = (S.part[k][0] + S.part[k][1]) + (S.part[k][2] + S.part[k][3]) <= near;
+                  const bool first_now = first_due && wf < id;
+                  if (!first_now) {
+                    left &= left - 1;
+                    ++k;
+                  }
+                  first_due = first_due && !first_now;
+                  if (first_now || close_one) due(first_now ? wf : id);
+                  if (count == 4) {
+                    if (pass == 1) rank();
+                    more = true;
+                    count = 0;
+                  }
+                }
+              }
+              if (first_due && (pass == 0 || more)) due(wf);
+              if (others == 0) break;
+              if (pass == 1 && count > 0) rank();
+            }
           }
         }
       }
     }
     team_barrier();                                // the histogram is cleared for the next group
+    if (BITS > 0 && left) {
+      if (lane == 0) a.scale[(size_t)row * a.n_groups + gi] = kLeft;
+      row = nrow;
+      gi = ngi;
+      continue;
+    }
     if (TW == 1 || wv == 0) store_choice(a, row, gi, best, lane);
     uint8_t *crow = a.codes + (size_t)row * a.d_in + c0;
     typedef uint8_t bv __attribute__((ext_vector_type(V)));
@@ -792,15 +1029,30 @@ __global__ __launch_bounds__(256) void owq_search_bounds(const SearchArgs a) {
     for (int t = 0; t < NT; t += V) {
       const int c = T::column(t, tl);
       bv q;
+      if constexpr (V >= 4) {
+        typedef u32 wv_t __attribute__((ext_vector_type(V / 4)));
+        wv_t words;
 #pragma unroll
-      for (int e = 0; e < V; ++e)
-        q[e] = (nothing || !((kept >> (t + e)) & 1u)) ? (uint8_t)0 : code_of(cur[t + e], best, a.qmax);
+        for (int e = 0; e < V; e += 4) {
+          u32 w = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) w |= (u32)code_of(cur[t + e + i], best, a.qmax) << (8 * i);
+          // four bits of `kept` to four bytes
+          const u32 in = (((nothing ? 0u : (u32)(kept >> ((t + e) & 32))) >> ((t + e) & 31)) & 15u) * 0x00204081u & 0x01010101u;
+          words[e / 4] = w & ((in << 8) - in);
+        }
+        q = __builtin_bit_cast(bv, words);
+      } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e) q[e] = (nothing || !((kept >> (t + e)) & 1u)) ? (uint8_t)0 : code_of(cur[t + e], best, a.qmax);
+      }
       if (a.vec) {
         if (c < len) *reinterpret_cast<bv *>(crow + c) = q;
       } else {
+        const int l = seldom(tl);
 #pragma unroll
         for (int e = 0; e < V; ++e)
-          if (c + e < len) crow[c + e] = q[e];
+          if (T::column(t + e, l) < len) crow[T::column(t + e, l)] = q[e];
       }
     }
     row = nrow;
@@ -954,22 +1206,22 @@ __global__ __launch_bounds__(kWaves * 64) void owq_search_kernel(const SearchArg
 }
 
 typedef void (*search_fn)(const SearchArgs);
-template <int POINTS>
+template <int POINTS, int BITS>
 search_fn pick_bounds_wave(int g) {
-  if (g <= 128) return owq_search_bounds<1, 2, POINTS>;
-  if (g <= 256) return owq_search_bounds<1, 4, POINTS>;
-  if (g <= 512) return owq_search_bounds<1, 8, POINTS>;
-  return owq_search_bounds<1, 16, POINTS>;
+  if (g <= 128) return owq_search_bounds<1, 2, POINTS, BITS>;
+  if (g <= 256) return owq_search_bounds<1, 4, POINTS, BITS>;
+  if (g <= 512) return owq_search_bounds<1, 8, POINTS, BITS>;
+  return owq_search_bounds<1, 16, POINTS, BITS>;
 }
 search_fn pick_bounds(int g, int ncand) {
   if (g <= 1024)
-    return ncand <= 64 ? pick_bounds_wave<1>(g) : ncand <= 128 ? pick_bounds_wave<2>(g) : ncand <= 192 ? pick_bounds_wave<3>(g) : pick_bounds_wave<4>(g);
-  if (g <= 2048) return owq_search_bounds<4, 8, 1>;
-  if (g <= 4096) return owq_search_bounds<4, 16, 1>;
-  if (g <= 6144) return owq_search_bounds<4, 24, 1>;
-  if (g <= 8192) return owq_search_bounds<4, 32, 1>;
-  if (g <= 12288) return owq_search_bounds<4, 48, 1>;
-  return owq_search_bounds<4, 64, 1>;
+    return ncand <= 64 ? pick_bounds_wave<1, 0>(g) : ncand <= 128 ? pick_bounds_wave<2, 0>(g) : ncand <= 192 ? pick_bounds_wave<3, 0>(g) : pick_bounds_wave<4, 0>(g);
+  if (g <= 2048) return owq_search_bounds<4, 8, 1, 0>;
+  if (g <= 4096) return owq_search_bounds<4, 16, 1, 0>;
+  if (g <= 6144) return owq_search_bounds<4, 24, 1, 0>;
+  if (g <= 8192) return owq_search_bounds<4, 32, 1, 0>;
+  if (g <= 12288) return owq_search_bounds<4, 48, 1, 0>;
+  return owq_search_bounds<4, 64, 1, 0>;
 }
 constexpr int kBoundsMax = 16384;    // columns of the longest group four waves keep in registers
 
@@ -1024,8 +1276,23 @@ extern "C" owq_status_t owq_search_config(const owq_search_desc_t *d, const uint
   const dim3 grid((unsigned)((teams + per_wg - 1) / per_wg)), block(kWaves * 64);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int ncand = d->n_lo * d->n_hi;
-  const search_fn fn = bounds ? pick_bounds(g, ncand)
-                       : ncand <= 64 ? owq_search_kernel<1> : ncand <= 128 ? owq_search_kernel<2> : ncand <= 192 ? owq_search_kernel<3> : owq_search_kernel<4>;
-  hipLaunchKernelGGL(fn, grid, block, mask_bytes, st, a);
+  // By diagonals: as many points at either end, so that the cuts of a diagonal add up to one sum; more than two points a lane
+  // (with two the general grid's kernel takes as few lookups); steps of a diagonal's width that are several steps of binary16,
+  // so that no two diagonals have the same step size; and weights enough that what it saves (0.6 us per 2^17 weights or more) is
+  // more than the second launch costs (5 us).
+  const bool diagonals = bounds && g <= 1024 && d->n_lo == d->n_hi && ncand > 128 && d->shrink * 256.f >= (float)(d->n_lo - 1) &&
+                         (long long)d->d_out * d->d_in >= (4 << 20) && units >= 16384;
+  if (diagonals) {
+    hipLaunchKernelGGL((d->bits == 3 ? pick_bounds_wave<4, 3>(g) : pick_bounds_wave<4, 4>(g)), grid, block, mask_bytes, st, a);
+    if (hipGetLastError() != hipSuccess) return OWQ_ERR_HIP;
+    const long long left = units / 8192;
+    a.units_per_wave = (int)(left < 1 ? 1 : left > 64 ? 64 : left);
+    const long long waves = (units + a.units_per_wave - 1) / a.units_per_wave;
+    hipLaunchKernelGGL((pick_bounds_wave<4, -1>(g)), dim3((unsigned)((waves + kWaves - 1) / kWaves)), block, mask_bytes, st, a);
+  } else {
+    const search_fn fn = bounds ? pick_bounds(g, ncand)
+                         : ncand <= 64 ? owq_search_kernel<1> : ncand <= 128 ? owq_search_kernel<2> : ncand <= 192 ? owq_search_kernel<3> : owq_search_kernel<4>;
+    hipLaunchKernelGGL(fn, grid, block, mask_bytes, st, a);
+  }
   return hipGetLastError() == hipSuccess ? OWQ_OK : OWQ_ERR_HIP;
 }
