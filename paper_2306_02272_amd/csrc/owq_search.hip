@@ -19,7 +19,8 @@
 // instructions per group), the grid by diagonals with the general way in the same kernel 395 (497; five waves per SIMD), in a
 // kernel of its own 357 (eight).  5120 x 5120, 4-bit, one scale per row: 134 -> 98 us when a wave's registers went from 227 to 113
 // (two waves per SIMD -> four: columns and masks of all weights had been kept in registers from one row to the next, and masks
-// in spilled scalar registers); the same for 4096 rows of 13824: 290 -> 125.
+// in spilled scalar registers), 76 to 98 with a row per workgroup, one of several equal points of a diagonal evaluated and
+// two points at a time summed in order (by whether one of the last rows has such points: 20 us); 4096 rows of 13824: 290 -> 123.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -401,6 +402,8 @@ __global__ __launch_bounds__(256, NT <= 4 ? 5 : NT <= 24 ? 4 : 2) void owq_searc
       }
     }
   };
+  // four waves: the grid point before this thread's on its diagonal, which has the same width
+  const int before = TW == 4 && tid < ncand && tid >= a.n_hi && (tid + 1) % a.n_hi != 0 ? tid - (a.n_hi - 1) : -1;
   // a wave fetches its next group while it searches one; with four waves to a row other workgroups fill the wait
   constexpr bool kAhead = TW == 1 && BITS >= 0;
   float cur[NT];
@@ -764,41 +767,44 @@ __global__ __launch_bounds__(256, NT <= 4 ? 5 : NT <= 24 ? 4 : 2) void owq_searc
             }
           }
         }
-        // Four waves: wave c sums point c of up to four; the residuals come 512 columns (one wave's run of them) at a time, 32
-        // in registers while the next 32 come from LDS.  One point after the other, a chain of LDS reads each, took 87 us
-        // per point on a row of 5120 columns.
-        auto in_order4 = [&](const int (&ids)[4], int count) __attribute__((always_inline)) {
+        // Four waves: waves 0 and 1 sum two points, whose residuals come 1024 columns (two waves' runs of them) at a time.  A chain of
+        // dependent additions is all latency: 28 of a wave's 32 values in registers are still to be added when one is read, and
+        // the wave goes first on its SIMD.  (One point after the other, a chain of LDS reads each, took 87 us per point on a row
+        // of 5120 columns; 512 columns of four points, 16 values ahead: 8 us more for a matrix of 5120 rows with a few of these.)
+        auto in_order2 = [&](int id0, int id1) __attribute__((always_inline)) {
           float e = 0.f;
 #pragma unroll
           for (int t0 = 0; t0 < NT; t0 += V)
-            for (int k = 0; k < 4; ++k) {
-              const int left = len - t0 * LANES - k * 512;
+            for (int k = 0; k < 2; ++k) {
+              const int left = len - t0 * LANES - k * 1024;
               if (left <= 0) break;                   // the same for all
               __syncthreads();
-              if (wv == k) {
+              if ((wv >> 1) == k) {
+                f4v *to = reinterpret_cast<f4v *>(res) + (wv & 1) * 128 + lane * (V / 4);
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                  if (c < count) {
-                    const Cand p = sh[0].cand[ids[c]];
-#pragma unroll
-                    for (int t = t0; t < t0 + V; ++t) res[c * 512 + lane * V + t - t0] = residual(p, t);
-                  }
+                for (int t = t0; t < t0 + 2 * V; t += 4) {
+                  const Cand p = sh[0].cand[t < t0 + V ? id0 : id1];
+                  const int u = t < t0 + V ? t : t - V;
+                  to[(t < t0 + V ? 0 : 256) + (u - t0) / 4] = (f4v){residual(p, u), residual(p, u + 1), residual(p, u + 2), residual(p, u + 3)};
+                  __builtin_amdgcn_sched_barrier(0);
+                }
               }
               __syncthreads();
-              if (wv < count) {
-                const f4v *r4 = reinterpret_cast<const f4v *>(res) + wv * 128;
-                const int n4 = min(128, (left + 15) / 16 * 4);
-                f4v d[4], nx[4];
+              if (wv < 2) {
+                const f4v *r4 = reinterpret_cast<const f4v *>(res) + wv * 256;
+                const int n4 = min(256, (left + 31) / 32 * 8);      // zeros behind the last column
+                f4v d[8];
+                __builtin_amdgcn_s_setprio(3);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) d[j] = r4[j];
-                for (int i = 0; i < n4; i += 4) {
+                for (int j = 0; j < 8; ++j) d[j] = r4[j];
+                for (int i = 8; i <= n4; i += 8) {
 #pragma unroll
-                  for (int j = 0; j < 4; ++j) nx[j] = r4[(i + 4 < 128 ? i + 4 : i) + j];
-#pragma unroll
-                  for (int j = 0; j < 4; ++j) e = add4(e, d[j]);
-#pragma unroll
-                  for (int j = 0; j < 4; ++j) d[j] = nx[j];
+                  for (int j = 0; j < 8; ++j) {
+                    e = add4(e, d[j]);
+                    d[j] = r4[min(i + j, 255)];
+                  }
                 }
+                __builtin_amdgcn_s_setprio(0);
               }
             }
           if (lane == 0) sh[0].wave[wv][3] = e;
@@ -896,6 +902,10 @@ __global__ __launch_bounds__(256, NT <= 4 ? 5 : NT <= 24 ? 4 : 2) void owq_searc
           TeamShared &S = sh[0];
           S.cand[tid] = cd[0];
           __syncthreads();                            // the last reads of wave[][0] are done
+          if (before >= 0) {                          // the same as the point before it on its diagonal: that one stands for it
+            const Cand p = S.cand[before];
+            if (p.s == cd[0].s && p.a == cd[0].a) bound[0] = INFINITY;
+          }
           if (lane == 0) {
             S.wave[wv][0] = wl;
             S.wave[wv][1] = __builtin_bit_cast(float, wf);
@@ -969,10 +979,12 @@ __global__ __launch_bounds__(256, NT <= 4 ? 5 : NT <= 24 ? 4 : 2) void owq_searc
                 best.id = 0x7fffffff;
               }
               auto rank = [&]() __attribute__((always_inline)) {
-                in_order4(ids, count);
-                for (int c = 0; c < count; ++c) {
-                  const int id = c == 0 ? ids[0] : c == 1 ? ids[1] : c == 2 ? ids[2] : ids[3];
-                  take(S.wave[c][3], id, S.cand[id]);
+                for (int c = 0; c < count; c += 2) {
+                  const int id0 = c == 0 ? ids[0] : ids[2], id1 = c == 0 ? (count > 1 ? ids[1] : id0) : (count > 3 ? ids[3] : id0);
+                  in_order2(id0, id1);
+                  take(S.wave[0][3], id0, S.cand[id0]);
+                  take(S.wave[1][3], id1, S.cand[id1]);
+                  __syncthreads();                    // read before the next two sums are written
                 }
                 count = 0;
               };
@@ -1265,7 +1277,8 @@ extern "C" owq_status_t owq_search_config(const owq_search_desc_t *d, const uint
   // per-lane grid set-up and the weak mask are then paid once per team
   const bool bounds = g <= kBoundsMax;
   const int team_waves = bounds && g > 1024 ? 4 : 1;
-  const long long upw = units / (team_waves == 4 ? 2048 : 32768);
+  // (four waves: two rows where there are 16384, 120 -> 115 us on rows of 4096; of 5120 rows, two each take 81 us and one 77)
+  const long long upw = units / (team_waves == 4 ? 8192 : 32768);
   a.units_per_wave = (int)(upw < 1 ? 1 : (upw > 16 ? 16 : upw));
   a.qmax = (float)((1 << d->bits) - 1);
   a.shrink = d->shrink;
