@@ -32,6 +32,9 @@
 // instruction 7.9 -> 5.4.  With a spill of two to five registers, which waits for the direct loads too, 275 becomes 304-324.
 // (Sums kept in units of the block's step size and multiplied by ratios of step sizes instead: 251, 267 and 142, but a rounding
 // per block on all of the sums, which does not leave a single column's weight exact beyond some 100 groups.)
+// Where there are no two workgroups for a compute unit, one has eight waves, half the columns for four of them (HALVES): 16384 ->
+// 4096 at 2048 tokens, 256 tiles, 281 -> 252 us (matrix pipe busy 43 % before); 13824 -> 5120, 4-bit, at 600 tokens 127 -> 110,
+// at 2048 322 -> 279; 9000 -> 6016 at 1500 211 -> 178.  A barrier of four waves each, through counts in LDS, changed nothing.
 // Row groups with rests take 422 instead of 446 us, 440 instead of 446, but 234 instead of 209: 378 workgroups are one round with
 // twice the matrix work, 702 of 64 tokens were two shorter ones, and the plan does not know of the zero points.
 #include <hip/hip_runtime.h>
@@ -120,8 +123,16 @@ struct WideArgs {
   f4_t *slots;
   _Float16 *y;                 // [ntok][d_out]
   int pitch, xwpitch, d_in, d_out, d_out_pad, ntok;
-  int nbp, nblk, n_rt, n_groups, bpg, kunits, n_rg, n_fl, n_tt, split;
+  int nbp, nblk, n_rt, n_groups, bpg, kunits, n_rg, n_fl, n_tt;
+  int full, split;             // the first `full` tiles have one workgroup each, the others `split` column ranges
 };
+
+// Tile `rem` of a launch: row group and tile of tokens (n_wt of them); four row groups x the token tiles are neighbours.
+__device__ __forceinline__ void wide_tile(int rem, int n_rg, int n_wt, int &rg, int &tt) {
+  const int g4 = rem / (4 * n_wt), gh = min(4, n_rg - 4 * g4), r2 = rem - g4 * 4 * n_wt;
+  tt = r2 / gh;
+  rg = 4 * g4 + (r2 - tt * gh);
+}
 
 template <int J> using Int = std::integral_constant<int, J>;
 template <int N, int I = 0, class F>
@@ -141,12 +152,13 @@ __device__ __forceinline__ h8_t wide_weights(const u32 *wd, u32 nz) {
 }
 
 // The columns [p0, p1) in blocks of 128 of the workgroup's tile: on return tot holds, per row tile and token tile of the
-// wave, the scaled sums, a lane having one row (lane mod 32) and sixteen tokens.
+// wave, the scaled sums, a lane having one row (lane mod 32) and sixteen tokens.  `idle`: steps that the workgroup's other four
+// waves have more.
 template <int BITS, bool GROUPED, bool REST, int NT>
-__device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *lds, int rg, int n0, int p0, int p1, f16_t *tot) {
+__device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *lds, int rg, int n0, int p0, int p1, int idle, f16_t *tot) {
   constexpr int kBuf = NT * 512;                // 16-byte units of a buffer
   constexpr bool kRolled = GROUPED;             // one body for even and odd blocks, whose codes come late and into the same registers
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
   const int b0 = 2 * p0, b1 = min(2 * p1, a.nblk);
   const u32 ldsb = lds_address(lds);
 
@@ -412,16 +424,19 @@ __device__ __forceinline__ void wide_columns(const WideArgs &a, unsigned char *l
 #pragma unroll
       for (int r = 0; r < 16; ++r) tot[i][r] *= sc[i / NT];
   }
+  for (int i = 0; i < idle; ++i) __syncthreads();
   wait_loads<0>();            // the loads past the end must not land in what the buffers are used for next
   __syncthreads();
 }
 
 // What follows the columns: the weak columns of the first column range, then y or a partial result.  NT token tiles from
 // token n0 on, tot in the order of wide_columns; every wave of the workgroup is past its reads of the staging buffers.
+// store = false: four waves whose tokens do not exist go the same way to the same barriers.
+// slot: the partial result of the first 64 tokens, -1 where there is none; those of the next 64 are `split` further on.
 template <int NT>
-__device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *lds, int rg, int n0, int s, f16_t *tot) {
+__device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *lds, int rg, int n0, int s, int slot, bool store, f16_t *tot) {
   constexpr int kBuf = NT * 512;
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 5;
+  const int tid = threadIdx.x & 255, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 5;
   // ---- weak columns: 128 at a time, the gathered activations in the first buffer, each wave's weights (of one
   // row tile after the other) behind it ----
   if (s == 0) {
@@ -472,8 +487,9 @@ __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *ld
 #pragma unroll
   for (int half = 0; half < NT / 2; ++half, n0 += kWideTokens) {
     if (n0 >= a.ntok) break;
-    if (a.split > 1) {
-      f4_t *dst = a.slots + ((size_t)(rg * a.n_tt + n0 / kWideTokens) * a.split + s) * kWideSlotUnits + (w * 16) * 64 + lane;
+    if (slot >= 0) {
+      if (!store) break;
+      f4_t *dst = a.slots + ((size_t)slot + half * a.split) * kWideSlotUnits + (w * 16) * 64 + lane;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const f16_t &v = tot[(i >> 1) * NT + 2 * half + (i & 1)];
@@ -491,7 +507,7 @@ __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *ld
         out[((i & 1) * 32 + 8 * (r >> 2) + 4 * kg + (r & 3)) * kWideOutPitch + w * 64 + (i >> 1) * 32 + (lane & 31)] = (_Float16)v[r];
     }
     __syncthreads();
-    const int row0 = rg * kWideRows, ntok = min(kWideTokens, a.ntok - n0);
+    const int row0 = rg * kWideRows, ntok = store ? min(kWideTokens, a.ntok - n0) : 0;
     for (int e = tid; e < ntok * 32; e += 256) {
       const int n = e >> 5, r = (e & 31) * 8;
       store_rows(a.y + (size_t)(n0 + n) * a.d_out + row0 + r, out + n * kWideOutPitch + r, a.d_out - row0 - r);
@@ -500,37 +516,91 @@ __device__ __forceinline__ void wide_finish(const WideArgs &a, unsigned char *ld
 }
 
 // One workgroup = 256 rows x 32 NT tokens x one column range (a run of block pairs); a wave = 64 rows x 32 NT tokens.
-template <int BITS, bool GROUPED, int NT>
-__global__ __launch_bounds__(256, 2) void owq_wide_mma(const WideArgs a) {
+// HALVES = 2: eight waves, the second four on the second half of the range, with buffers of their own.  The halves exchange
+// the sums of 64 tokens each through LDS and finish 64 tokens each.
+template <int BITS, bool GROUPED, int NT, int HALVES>
+__global__ __launch_bounds__(256 * HALVES, 2) void owq_wide_mma(const WideArgs a) {
+  static_assert(HALVES == 1 || NT == 4, "a half finishes 64 tokens");
   extern __shared__ u32x4 lds_units[];
   unsigned char *lds = reinterpret_cast<unsigned char *>(lds_units);
-  // workgroups of one die (id mod 8) take neighbouring tiles: four row groups x the token tiles, so that a die's
-  // L2 serves the codes and the activations to all of them
-  const int n_wt = (a.n_tt + NT / 2 - 1) / (NT / 2);
-  const int N = gridDim.x, xcd = blockIdx.x & 7, lin = xcd * (N >> 3) + min(xcd, N & 7) + (int)(blockIdx.x >> 3);
-  const int tiles = a.n_rg * n_wt, s = lin / tiles, rem = lin - s * tiles;
-  const int g4 = rem / (4 * n_wt), gh = min(4, a.n_rg - 4 * g4), r2 = rem - g4 * 4 * n_wt;
-  const int tt = r2 / gh, rg = 4 * g4 + (r2 - tt * gh);
-  const int n0 = tt * 32 * NT;
-  const int p0 = s * a.nbp / a.split, p1 = (s + 1) * a.nbp / a.split;
+  // workgroups of one die (id mod 8) take neighbouring tiles, so that a die's L2 serves the codes and the activations to all of
+  // them; the tiles with one workgroup come first
+  const int n_wt = (a.n_tt + NT / 2 - 1) / (NT / 2), tiles = a.n_rg * n_wt;
+  const int full = HALVES == 2 ? a.full : 0;
+  const bool cut = (int)blockIdx.x >= full;
+  const int id = cut ? (int)blockIdx.x - full : (int)blockIdx.x, N = cut ? (int)gridDim.x - full : full, xcd = id & 7;
+  const int lin = xcd * (N >> 3) + min(xcd, N & 7) + (id >> 3);
+  const int s = cut ? lin / (tiles - full) : 0, rel = lin - s * (tiles - full);      // of its part
+  int rg, tt;
+  wide_tile(cut ? full + rel : rel, a.n_rg, n_wt, rg, tt);
+  const int n0 = tt * 32 * NT, split = cut ? a.split : 1;
+  // partial results lie by row group and tokens, or, if only some tiles have them, in the order of these
+  const int slot = split > 1 ? (full == 0 ? rg * a.n_tt + tt * (NT / 2) : rel * (NT / 2)) * split + s : -1;
+  const int p0 = s * a.nbp / split, p1 = (s + 1) * a.nbp / split;
 
   int rest = 0;
   for (int i = 0; i < a.n_fl; ++i) rest |= a.flags[rg * a.n_fl + i];
   f16_t tot[2 * NT];
-  if (rest != 0)
-    wide_columns<BITS, GROUPED, true, NT>(a, lds, rg, n0, p0, p1, tot);
-  else
-    wide_columns<BITS, GROUPED, false, NT>(a, lds, rg, n0, p0, p1, tot);
-  wide_finish<NT>(a, lds, rg, n0, s, tot);
+  if constexpr (HALVES == 1) {
+    if (rest != 0)
+      wide_columns<BITS, GROUPED, true, NT>(a, lds, rg, n0, p0, p1, 0, tot);
+    else
+      wide_columns<BITS, GROUPED, false, NT>(a, lds, rg, n0, p0, p1, 0, tot);
+    wide_finish<NT>(a, lds, rg, n0, s, slot, true, tot);
+  } else {
+    const int h = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), pm = (p0 + p1 + 1) >> 1;      // the first half is no shorter
+    const int n_first = 2 * (pm - p0), n_second = min(2 * p1, a.nblk) - 2 * pm;
+    unsigned char *own = lds + h * wide_lds(NT);
+    if (rest != 0)
+      wide_columns<BITS, GROUPED, true, NT>(a, own, rg, n0, h ? pm : p0, h ? p1 : pm, h ? n_first - n_second : 0, tot);
+    else
+      wide_columns<BITS, GROUPED, false, NT>(a, own, rg, n0, h ? pm : p0, h ? p1 : pm, h ? n_first - n_second : 0, tot);
+    // token tiles 0 and 1 go to the first half, 2 and 3 to the second
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
+    f4_t *to = reinterpret_cast<f4_t *>(lds + (h ^ 1) * wide_lds(NT)) + w * 1024 + lane;
+    const f4_t *from = reinterpret_cast<const f4_t *>(own) + w * 1024 + lane;
+    f16_t mine[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f16_t &lo = tot[(i >> 1) * NT + (i & 1)], &hi = tot[(i >> 1) * NT + 2 + (i & 1)];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mine[i][r] = h ? hi[r] : lo[r];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f4_t v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = h ? lo[4 * q + e] : hi[4 * q + e];
+        to[(i * 4 + q) * 64] = v;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f4_t v = from[(i * 4 + q) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mine[i][4 * q + e] += v[e];
+      }
+    __syncthreads();
+    const bool store = n0 + 64 * h < a.ntok;
+    wide_finish<2>(a, own, rg, store ? n0 + 64 * h : n0, s, slot < 0 ? -1 : slot + h * split, store, mine);
+  }
 }
 
-// Adds the partial results of a tile in a fixed order: one workgroup per 64 rows x 64 tokens (what one wave of
-// owq_wide_mma wrote), a wave per accumulator tile.
-__global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 *y, int n_tt, int split, int ntok, int d_out) {
+// Adds the partial results of the tiles from `full` on in a fixed order: one workgroup per 64 rows x 64 tokens (what one wave of
+// owq_wide_mma wrote), a wave per accumulator tile.  A tile of tokens has 64 << lg2.
+__global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 *y, int full, int n_rg, int n_tt, int lg2, int split, int ntok, int d_out) {
   __shared__ __align__(16) _Float16 out[64][72];
   const int tid = threadIdx.x, lane = tid & 63, i = tid >> 6;
-  const int w = blockIdx.x & 3, tile = blockIdx.x >> 2, rg = tile / n_tt, tt = tile - rg * n_tt;
+  const int w = blockIdx.x & 3, rg = (blockIdx.x >> 2) / n_tt, tt = (blockIdx.x >> 2) - rg * n_tt;
   const int n0 = tt * kWideTokens, row0 = rg * kWideRows + w * 64;
+  int tile = rg * n_tt + tt;
+  if (full > 0) {             // its place in the order of wide_tile()
+    const int rem = (rg & ~3) * ((n_tt + lg2) >> lg2) + (tt >> lg2) * min(4, n_rg - (rg & ~3)) + (rg & 3);
+    if (rem < full) return;
+    tile = ((rem - full) << lg2) + (tt & lg2);
+  }
   if (n0 >= ntok || row0 >= d_out) return;
   const f4_t *src = slots + (size_t)tile * split * kWideSlotUnits + (w * 16 + i * 4) * 64 + lane;
   f4_t sum[4];
@@ -554,22 +624,27 @@ __global__ __launch_bounds__(256) void owq_wide_sum(const f4_t *slots, _Float16 
 }
 
 typedef void (*wide_fn)(const WideArgs);
-template <int NT>
+template <int NT, int HALVES>
 wide_fn pick_wide_tokens(int bits, bool grouped) {
-  if (bits == 3) return grouped ? owq_wide_mma<3, true, NT> : owq_wide_mma<3, false, NT>;
-  return grouped ? owq_wide_mma<4, true, NT> : owq_wide_mma<4, false, NT>;
+  if (bits == 3) return grouped ? owq_wide_mma<3, true, NT, HALVES> : owq_wide_mma<3, false, NT, HALVES>;
+  return grouped ? owq_wide_mma<4, true, NT, HALVES> : owq_wide_mma<4, false, NT, HALVES>;
 }
-wide_fn pick_wide(int bits, bool grouped, int nt) { return nt == 4 ? pick_wide_tokens<4>(bits, grouped) : pick_wide_tokens<2>(bits, grouped); }
+wide_fn pick_wide(int bits, bool grouped, int nt, int halves) {
+  return nt != 4 ? pick_wide_tokens<2, 1>(bits, grouped) : halves == 2 ? pick_wide_tokens<4, 2>(bits, grouped) : pick_wide_tokens<4, 1>(bits, grouped);
+}
 
 // Kernel and work split of n_tt token tiles of 64 over n_rg row groups and nbp block pairs, with room for `slots` partial results.
 struct WidePlan {
-  int nt, split;
+  int nt, halves, full, split;
   float us;
 };
+constexpr float kWide8 = 3.1f, kWide8Grouped = 3.6f;      // us per pair of blocks of a workgroup of eight waves, beside
+constexpr float kWide8Us = 4.f, kWide8More = 9.f;         // the exchange of its halves; start and end of a round, which nothing runs under
+constexpr int kWidePlans = 128;           // most token tiles that may go in two launches
 constexpr float kWideLaunchUs = 14.f;     // start, first loads and end of a second launch
 WidePlan wide_plan(bool grouped, int n_rg, int n_tt, int nbp, int64_t slots) {
-  WidePlan best{2, 1, 1e30f};
-  if (n_tt == 0) return WidePlan{2, 1, 0.f};
+  WidePlan best{2, 1, 0, 1, 1e30f};
+  if (n_tt == 0) return WidePlan{2, 1, 0, 1, 0.f};
   // us per pair of blocks: up to 128 workgroups, one and two on every compute unit, as costs to choose by.  30 whole calls (2048
   // to 16384 columns, 2048 to 13824 rows, 100 to 2048 tokens) took 0.94 to 1.19 of this and 14 us around it.  Row groups whose
   // zero points are no integers have twice the matrix work, which the host does not know of.
@@ -579,13 +654,24 @@ WidePlan wide_plan(bool grouped, int n_rg, int n_tt, int nbp, int64_t slots) {
     const int tiles = n_rg * (nt == 4 ? (n_tt + 1) / 2 : n_tt);
     for (int s = 1; s <= 32 && s * 2 <= nbp + 1; ++s) {
       const int n = tiles * s, left = n % 512, pairs = (nbp + s - 1) / s;
-      if (s > 1 && (int64_t)n_rg * n_tt * s > slots) break;
+      if (s > 1 && (int64_t)tiles * (nt / 2) * s > slots) break;
       const float last = left <= 128 ? c[0] : left <= 256 ? c[1] : c[1] + (c[2] - c[1]) * (0.53f + 0.47f * (left - 256) / 256);
       // rounds of 512 workgroups, which overlap at their ends, and for a split the launch of the sum
       const float us = pairs * (n / 512 * c[2] + (left ? last : 0.f)) - 2.2f * (n / 512 + (left ? 1 : 0) - 1) +
                        (s > 1 ? 1.6f + 0.009f * n_rg * n_tt * s : 0.f);
-      if (us < best.us) best = WidePlan{nt, s, us};
+      if (us < best.us) best = WidePlan{nt, 1, 0, s, us};
     }
+  }
+  // Eight waves, one workgroup per compute unit: fewer than 512 tiles, of which 256, if there are as many, are a whole round and the
+  // others are cut into column ranges that fill another.  (From 512 on two workgroups of four waves share a compute unit from
+  // start to end and lose nothing: 5120 -> 13824, 4-bit, 1500 tokens, 648 tiles: 237 us, so 259.)
+  const float c8 = grouped ? kWide8Grouped : kWide8;
+  const int tiles = n_rg * ((n_tt + 1) / 2), full = tiles / 256 * 256, rest = tiles - full, rounds = full / 256 + (rest ? 1 : 0);
+  for (int s = 1; tiles < 512 && s <= 32 && s * 2 <= nbp; ++s) {
+    if (s > 1 && (rest == 0 || rest * s > 256 || (int64_t)rest * 2 * s > slots)) break;
+    const int pairs = full / 256 * nbp + (rest ? (nbp + s - 1) / s : 0);
+    const float us = kWide8Us + kWide8More * (rounds - 1) + c8 * pairs + (s > 1 ? 1.6f + 0.018f * rest * s : 0.f);
+    if (us < best.us) best = WidePlan{4, 2, s > 1 ? full : 0, s, us};
   }
   return best;
 }
@@ -593,11 +679,13 @@ WidePlan wide_plan(bool grouped, int n_rg, int n_tt, int nbp, int64_t slots) {
 }  // namespace
 
 int prepare_tile_wide_kernels(const owq_layer_info_t &g, int32_t lds_limit) {
-  if (wide_lds(4) > lds_limit) return (int)hipErrorInvalidValue;
+  if (2 * wide_lds(4) > lds_limit) return (int)hipErrorInvalidValue;
   int e = 0;
-  for (int nt = 2; nt <= 4 && e == 0; nt += 2)
-    e = (int)hipFuncSetAttribute(reinterpret_cast<const void *>(pick_wide(g.bits, g.n_groups > 1, nt)),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds(nt));
+  for (int i = 0; i < 3 && e == 0; ++i) {
+    const int nt = i == 0 ? 2 : 4, halves = i == 2 ? 2 : 1;
+    e = (int)hipFuncSetAttribute(reinterpret_cast<const void *>(pick_wide(g.bits, g.n_groups > 1, nt, halves)),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, wide_lds(nt) * halves);
+  }
   return e;
 }
 
@@ -651,9 +739,11 @@ int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint6
     // the token tiles in one or two launches: the first `a` of them and the rest, each with its own split
     int first = n_tt;
     const bool grouped = g.n_groups > 1;
-    float us = wide_plan(grouped, n_rg, n_tt, g.nbp, slots).us;
-    for (int a = 1; a < n_tt && n_tt <= 128; ++a) {
-      const float v = wide_plan(grouped, n_rg, a, g.nbp, slots).us + wide_plan(grouped, n_rg, n_tt - a, g.nbp, slots).us + kWideLaunchUs;
+    WidePlan whole = wide_plan(grouped, n_rg, n_tt, g.nbp, slots), some[kWidePlans];       // some[a]: of a token tiles
+    float us = whole.us;
+    for (int a = 1; a < n_tt && n_tt <= kWidePlans; ++a) some[a] = wide_plan(grouped, n_rg, a, g.nbp, slots);
+    for (int a = 1; a < n_tt && n_tt <= kWidePlans; ++a) {
+      const float v = some[a].us + some[n_tt - a].us + kWideLaunchUs;
       if (v < us) { us = v; first = a; }
     }
     hipLaunchKernelGGL(owq_wide_prep, dim3((unsigned)(n_rg * n_fl + gather)), dim3(256), 0, st, pa);
@@ -663,17 +753,18 @@ int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint6
       const int p0 = ta * kWideTokens, p1 = tb * kWideTokens < pass ? tb * kWideTokens : pass;
       wa.n_tt = tb - ta;
       wa.ntok = p1 - p0;
-      const WidePlan plan = wide_plan(grouped, n_rg, wa.n_tt, g.nbp, slots);
+      const WidePlan plan = first == n_tt ? whole : some[wa.n_tt];
+      wa.full = plan.full;
       wa.split = plan.split;
       wa.x = copy ? pa.xcopy + (size_t)p0 * pitch : pa.x + (size_t)p0 * g.d_in;
       wa.xw = pa.xw + (size_t)p0 * xwpitch;
       wa.y = yp + (size_t)(t0 + p0) * g.d_out;
-      const int n_wt = plan.nt == 4 ? (wa.n_tt + 1) / 2 : wa.n_tt;
-      hipLaunchKernelGGL(pick_wide(g.bits, grouped, plan.nt), dim3((unsigned)(n_rg * n_wt * wa.split)), dim3(256),
-                         wide_lds(plan.nt), st, wa);
+      const int nt2 = plan.nt / 2, n_wt = (wa.n_tt + nt2 - 1) / nt2, cut = n_rg * n_wt - plan.full;
+      hipLaunchKernelGGL(pick_wide(g.bits, grouped, plan.nt, plan.halves), dim3((unsigned)(plan.full + cut * plan.split)),
+                         dim3((unsigned)(256 * plan.halves)), wide_lds(plan.nt) * plan.halves, st, wa);
       if (wa.split > 1)
-        hipLaunchKernelGGL(owq_wide_sum, dim3((unsigned)(n_rg * wa.n_tt * 4)), dim3(256), 0, st, (const f4_t *)wa.slots, wa.y, wa.n_tt,
-                           wa.split, wa.ntok, g.d_out);
+        hipLaunchKernelGGL(owq_wide_sum, dim3((unsigned)(n_rg * wa.n_tt * 4)), dim3(256), 0, st, (const f4_t *)wa.slots, wa.y, plan.full, n_rg,
+                           wa.n_tt, nt2 - 1, wa.split, wa.ntok, g.d_out);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

@@ -24,7 +24,7 @@ def env():
     return torch, binding
 
 
-def compare(env, layer, x, what, rows=300):
+def compare(env, layer, x, what, rows=300, rounding=False):
     torch, B = env
     lin = B.OwqLinear(layer, layout=1)
     got = lin(torch.from_numpy(x).cuda()).cpu().numpy()
@@ -38,7 +38,9 @@ def compare(env, layer, x, what, rows=300):
                                   layer.weak_w[pick], x)
     for g, w in [(got[:, pick], want)] + list(zip(got[:, pick], want)):
         rel, mx = owq_ref.parity_errors(g, w)
-        assert rel <= 1e-3 and mx <= 1e-2, (what, rel, mx)
+        # rounding: rows of large zero points can be more than 20 rms, whose rounding to fp16 alone is 2^-11 of them
+        top = max(1e-2, 2.0 ** -11 * np.abs(w).max() / np.sqrt(np.mean(np.square(w))) + 2e-3) if rounding else 1e-2
+        assert rel <= 1e-3 and mx <= top, (what, rel, mx)
 
 
 @pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens", [
@@ -51,7 +53,7 @@ def compare(env, layer, x, what, rows=300):
     (1600, 6401, 3, 128, 1400, 1000),
 ])
 @pytest.mark.parametrize("zeros", ["integers", "any"])
-def test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros):
+def test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros, rounding=False):
     layer = make_layer(LayerSpec("tiles", d_in, d_out, bits, group, k, d_in + d_out))
     if zeros == "any":
         rng = np.random.default_rng(5)
@@ -60,7 +62,17 @@ def test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros):
         z[rows & (rng.random(d_out) < 0.05)] = 1500.5
         layer.zero[:] = z.astype(np.float16)
     print(d_in, d_out, tokens, zeros, flush=True)
-    compare(env, layer, make_x(layer, tokens), (d_in, d_out, tokens, zeros))
+    compare(env, layer, make_x(layer, tokens), (d_in, d_out, tokens, zeros), rounding=rounding)
+
+
+# Workgroups of eight waves, whose halves take half the columns each: no column ranges beside, an odd number of blocks and a last
+# tile whose second 64 tokens do not exist; a round of whole tiles and the others in four ranges, rows of x off the 16-byte
+# grid; two ranges of all tiles; one scale per row.
+@pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens", [
+    (8056, 3300, 3, 128, 40, 1950), (4100, 5120, 4, 128, 40, 2000), (13824, 5100, 4, 256, 300, 590), (8192, 5120, 3, 0, 9, 2040)])
+@pytest.mark.parametrize("zeros", ["integers", "any"])
+def test_tiles_of_two_halves_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros):
+    test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros, rounding=True)
 
 
 @pytest.mark.parametrize("d_in,d_out,bits,k,tokens", [(2048, 300, 3, 1500, 70), (1152, 8192, 4, 4, 1100)])
