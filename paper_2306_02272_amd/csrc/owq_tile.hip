@@ -535,102 +535,37 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   const int kunits = a.kp >> 3;
   if (kunits > 0) {
     const int kg = lane >> 5;
-    // the set of weak columns of this lane's token: -1 = the layer's own, -2 = no token
-    int mine = n < a.ntok ? -1 : -2;
-    if (a.task_id != nullptr && n < a.ntok) {
-      const int t = a.task_id[n];
-      if ((u32)t < (u32)a.n_sets) mine = t;
-    }
-    typedef const __attribute__((address_space(1))) u32x4 *gptr_t;   // pointers read from memory: global
     constexpr int KS = 8;                            // K-steps whose loads are in flight together
-    if (a.task_id == nullptr) {
-      // One set, the layer's own.  A lane's operand is 16 bytes of its own row, so a wave reading operands
-      // straight from memory touches 64 cache lines per load, and the address path takes a cycle for each
-      // (4 of this kernel's 12 us).  Instead the workgroup copies the 64 rows x 16 units of a chunk of 8 K-steps
-      // with loads that cover whole lines (a quarter wave per row), weights and gathered activations alike,
-      // and the waves take their operands from LDS (odd pitch: no bank conflicts).
-      const int cu = tid & 15, cr = tid >> 4;
-      for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
-        const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
-        u32x4 ta[4], tb[4];
+    // A lane's operand is 16 bytes of its own row, so a wave reading operands
+    // straight from memory touches 64 cache lines per load, and the address path takes a cycle for each
+    // (4 of this kernel's 12 us).  Instead the workgroup copies the 64 rows x 16 units of a chunk of 8 K-steps
+    // with loads that cover whole lines (a quarter wave per row), weights and gathered activations alike,
+    // and the waves take their operands from LDS (odd pitch: no bank conflicts).
+    const int cu = tid & 15, cr = tid >> 4;
+    for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
+      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
+      u32x4 ta[4], tb[4];
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          int r = row_base + cr + 16 * i4;
-          if (r > a.d_out_pad - 1) r = a.d_out_pad - 1;
-          ta[i4] = a.weak_w[(size_t)r * kunits + uc];
-          tb[i4] = a.xw[(size_t)(cr + 16 * i4) * kunits + uc];
-        }
-        if (s0 > 0) __syncthreads();                 // the operands of the last chunk have been read
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const u32x4 zero = {0u, 0u, 0u, 0u};
-          wstage[0][(cr + 16 * i4) * kWeakPitch + cu] = u < kunits ? ta[i4] : zero;
-          wstage[1][(cr + 16 * i4) * kWeakPitch + cu] = (u < kunits && cr + 16 * i4 < a.ntok) ? tb[i4] : zero;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < KS; ++j) {
-          if (2 * (s0 + j) >= kunits) continue;      // same for the whole workgroup
-          const u32x4 av = wstage[0][(rtl * 32 + (lane & 31)) * kWeakPitch + 2 * j + kg];
-          const u32x4 bw = wstage[1][n * kWeakPitch + 2 * j + kg];
-          wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
-        }
+      for (int i4 = 0; i4 < 4; ++i4) {
+        int r = row_base + cr + 16 * i4;
+        if (r > a.d_out_pad - 1) r = a.d_out_pad - 1;
+        ta[i4] = a.weak_w[(size_t)r * kunits + uc];
+        tb[i4] = a.xw[(size_t)(cr + 16 * i4) * kunits + uc];
       }
-    } else {
-      // Several sets.  All waves of the workgroup look at the same 32 tokens (the launch sees to that), so they agree on
-      // the sets these use: in ascending order, one pass of K-steps per set, with the other tokens' operands zeroed.
-      // A set's 64 rows x 16 units go through LDS as above; those of the next set are fetched meanwhile (lanes reading
-      // operands of their own rows straight from memory, pointer first, then weights, one set after the other: 12.9 us
-      // for six sets of 72 columns, 37 tokens and 3333 rows; this: 11.3, with fewer partial results to add 10).
-      const u32x4 *own = a.weak_w;
-      const u32x4 *base = mine >= 0 ? static_cast<const u32x4 *>(a.weak_sets[mine]) : own;      // of this lane's token
-      const int cu = tid & 15, cr = tid >> 4;
-      const u32x4 zero = {0u, 0u, 0u, 0u};
-      for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
-        const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
-        int pending = mine, t = -2;
-        // the least index still pending and, by one of its lanes, where its weights lie
-        auto next_set = [&](u32x4 (&ta)[4]) __attribute__((always_inline)) {
-          int cand = pending >= -1 ? pending : 0x7fffffff;
+      if (s0 > 0) __syncthreads();                 // the operands of the last chunk have been read
 #pragma unroll
-          for (int d = 1; d < 64; d <<= 1) cand = min(cand, __shfl_xor(cand, d));
-          const int c = __builtin_amdgcn_readfirstlane(cand);
-          if (c == 0x7fffffff) return c;
-          const int src = __builtin_ctzll(__ballot(pending == c));
-          const unsigned long long at = (unsigned long long)(uintptr_t)base;
-          const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)at, src), hi = (u32)__builtin_amdgcn_readlane((int)(u32)(at >> 32), src);
-          const gptr_t w0 = (gptr_t)(uintptr_t)(((unsigned long long)hi << 32) | lo);
-          if (pending == c) pending = -2;
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        wstage[0][(cr + 16 * i4) * kWeakPitch + cu] = u < kunits ? ta[i4] : zero;
+        wstage[1][(cr + 16 * i4) * kWeakPitch + cu] = (u < kunits && cr + 16 * i4 < a.ntok) ? tb[i4] : zero;
+      }
+      __syncthreads();
 #pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            int r = row_base + cr + 16 * i4;
-            if (r > a.d_out_pad - 1) r = a.d_out_pad - 1;
-            ta[i4] = w0[(size_t)r * kunits + uc];
-          }
-          return c;
-        };
-        u32x4 ta[4], tb[4];
-        t = next_set(ta);
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) tb[i4] = a.xw[(size_t)(cr + 16 * i4) * kunits + uc];
-        __syncthreads();                             // the operands of the last chunk have been read
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) wstage[1][(cr + 16 * i4) * kWeakPitch + cu] = (u < kunits && cr + 16 * i4 < a.ntok) ? tb[i4] : zero;
-        while (t != 0x7fffffff) {
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) wstage[0][(cr + 16 * i4) * kWeakPitch + cu] = u < kunits ? ta[i4] : zero;
-          __syncthreads();
-          const bool use = mine == t;
-          t = next_set(ta);
-#pragma unroll
-          for (int j = 0; j < KS; ++j) {
-            if (2 * (s0 + j) >= kunits) continue;    // same for the whole workgroup
-            const u32x4 av = wstage[0][(rtl * 32 + (lane & 31)) * kWeakPitch + 2 * j + kg];
-            const u32x4 bw = wstage[1][n * kWeakPitch + 2 * j + kg];
-            wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, use ? bw : zero), wk);
-          }
-          __syncthreads();                           // read before the next set's rows are written
-        }
+      for (int j = 0; j < KS; ++j) {
+        if (2 * (s0 + j) >= kunits) continue;      // same for the whole workgroup
+        const u32x4 av = wstage[0][(rtl * 32 + (lane & 31)) * kWeakPitch + 2 * j + kg];
+        const u32x4 bw = wstage[1][n * kWeakPitch + 2 * j + kg];
+        wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
       }
     }
   }
@@ -704,6 +639,154 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   for (int e = tid; e < (n_hi - n_lo) * 64; e += 256) {
     const int nn = n_lo + (e >> 6), r = e & 63;
     if (row_base + r < a.d_out) a.y[(size_t)nn * a.d_out + row_base + r] = out[nn][r];
+  }
+}
+
+// Several tasks: one workgroup per 32 rows and 32 tokens (grid.y: token tiles).  Latency is what bounds it (37 tokens, 3333 rows,
+// six sets of 72 columns: 112 workgroups of 64 rows, which took the sets one after the other between barriers and the partial
+// results behind them, 9.6 us of a call's 24.1).  So the partial results are asked for first, and the sets that the tokens use are
+// dealt out to the four waves, which need no barrier for them: each stages its sets' rows in LDS of its own (loads that cover
+// whole lines, the next set's while one is used).  A token has one set, so of the four waves' products three are zero where
+// the fourth is not, and their sum is what one wave would have.
+__global__ __launch_bounds__(256) void owq_tile_finish_sets(const FinishArgs a) {
+  constexpr int kPitch = 17;           // 16-byte units per staged row of a chunk of 128 weak columns, odd
+  constexpr int KS = 8;
+  __shared__ u32x4 xst[32 * kPitch], wst[4][32 * kPitch];
+  _Float16(*out)[40] = reinterpret_cast<_Float16(*)[40]>(xst);      // [token][row]
+  static_assert(32 * 40 * 2 <= sizeof(xst), "the transposed result lies where the activations were");
+  static_assert(16 * 64 * 4 <= sizeof(wst[0]), "a wave's product lies where its weights were");
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 5;
+  const int rt = blockIdx.x, nt = blockIdx.y, rg = rt / (2 * a.waves), w = (rt >> 1) - rg * a.waves, row_base = rt * 32;
+  if (row_base >= a.d_out) return;
+  const int n = nt * 32 + (lane & 31);
+
+  // ---- partial results of the wave's eight rows: the first ones ----
+  const long long st0 = (long long)rg * a.nbp, st1 = st0 + a.nbp - 1;
+  int p_first, p_last;
+  if (a.split > 0) {
+    p_first = rg * a.split;
+    p_last = p_first + a.split - 1;
+  } else {
+    p_first = (int)(((st0 + 1) * a.grid - 1) / a.steps);
+    p_last = (int)(((st1 + 1) * a.grid - 1) / a.steps);
+  }
+  const size_t slot_units = (size_t)a.waves * 1024;
+  const f4_t *src = a.slots + (size_t)((w * 4 + (rt & 1) * 2 + nt) * 4 + wv) * 64 + lane;
+  constexpr int J = 8;                 // fetched together
+  f4_t part[J];
+  auto fetch = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) part[j] = src[(size_t)(min(p + j, p_last) + rg) * slot_units];
+  };
+  fetch(p_first);
+
+  // ---- weak columns: the set of this lane's token (-1 = the layer's own, -2 = no token) ----
+  f16_t wk;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) wk[r] = 0.f;
+  const int kunits = a.kp >> 3;
+  if (kunits > 0) {
+    int mine = n < a.ntok ? -1 : -2;
+    if (n < a.ntok) {
+      const int t = a.task_id[n];
+      if ((u32)t < (u32)a.n_sets) mine = t;
+    }
+    typedef const __attribute__((address_space(1))) u32x4 *gptr_t;   // pointers read from memory: global
+    const unsigned long long base = (unsigned long long)(uintptr_t)(mine >= 0 ? a.weak_sets[mine] : static_cast<const void *>(a.weak_w));
+    const int cu = lane & 15, cr = lane >> 4;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
+      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
+      u32x4 tb[2], ta[8];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) tb[i] = a.xw[(size_t)(nt * 32 + wv * 8 + i * 4 + cr) * kunits + uc];
+      // the sets in use, in the order of their first tokens; this wave's are every fourth one
+      unsigned long long pending = __ballot(mine >= -1);
+      int k = 0;
+      auto next_set = [&]() __attribute__((always_inline)) {
+        int c = -2;
+        while (pending != 0ull) {
+          const int at = __builtin_ctzll(pending), v = __builtin_amdgcn_readlane(mine, at);
+          pending &= ~__ballot(mine == v);
+          if ((k++ & 3) != wv) continue;
+          c = v;
+          const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)base, at), hi = (u32)__builtin_amdgcn_readlane((int)(u32)(base >> 32), at);
+          const gptr_t w0 = (gptr_t)(uintptr_t)(((unsigned long long)hi << 32) | lo);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) ta[i] = w0[(size_t)min(row_base + i * 4 + cr, a.d_out_pad - 1) * kunits + uc];
+          break;
+        }
+        return c;
+      };
+      int c = next_set();
+      if (s0 > 0) __syncthreads();                   // the last chunk's activations have been read
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = wv * 8 + i * 4 + cr;
+        xst[r * kPitch + cu] = (u < kunits && nt * 32 + r < a.ntok) ? tb[i] : zero;
+      }
+      __syncthreads();
+      while (c != -2) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) wst[wv][(i * 4 + cr) * kPitch + cu] = u < kunits ? ta[i] : zero;
+        const bool use = mine == c;
+        c = next_set();
+        // (LDS serves a wave's instructions in order; this keeps the compiler from moving them)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+          if (2 * (s0 + j) >= kunits) continue;      // same for the whole workgroup
+          const u32x4 av = wst[wv][(lane & 31) * kPitch + 2 * j + kg];
+          const u32x4 bw = xst[(lane & 31) * kPitch + 2 * j + kg];
+          wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, use ? bw : zero), wk);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+    }
+  }
+  float *prod = reinterpret_cast<float *>(wst[wv]);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) prod[r * 64 + lane] = wk[r];
+
+  // ---- partial results in a fixed order ----
+  f4_t sum = {0.f, 0.f, 0.f, 0.f};
+  for (int p = p_first;;) {
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (p + j <= p_last) sum += part[j];           // same for the whole workgroup
+    p += J;
+    if (p > p_last) break;
+    fetch(p);
+  }
+  const int r0 = 8 * wv + 4 * kg;                    // row within the 32
+  if (!a.scaled) {
+    const f2_t t = a.tsum[n];
+    const u32x4 szw = *reinterpret_cast<const u32x4 *>(a.sz + min(row_base + r0, a.d_out_pad - 4));
+    const u32 s4[4] = {szw.x, szw.y, szw.z, szw.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float v = sum[e] - t.y;
+      v = __builtin_fmaf(-half_hi(s4[e]), t.x, v);
+      sum[e] = v * half_lo(s4[e]);
+    }
+  }
+  __syncthreads();                                   // all products are there, the activations have been read
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v += reinterpret_cast<const float *>(wst[q])[(4 * wv + e) * 64 + lane];
+    out[lane & 31][r0 + e] = (_Float16)(sum[e] + v);
+  }
+  __syncthreads();
+  const int ntok = min(32, a.ntok - nt * 32);
+  for (int e = tid; e < ntok * 32; e += 256) {
+    const int nn = e >> 5, r = e & 31;
+    if (row_base + r < a.d_out) a.y[(size_t)(nt * 32 + nn) * a.d_out + row_base + r] = out[nn][r];
   }
 }
 
@@ -879,10 +962,13 @@ int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t s
     fa.y = yp + (size_t)t0 * g.d_out;
     fa.ntok = ntok;
     fa.task_id = tasks.task_id ? tasks.task_id + t0 : nullptr;
-    // few rows: one workgroup per (64 rows, token tile), so that the launch fills more of the chip
-    // (several tasks: always, the workgroup's waves share their tokens)
-    const unsigned per_tile = (ntok > 32 && (n_rg * waves <= 384 || tasks.task_id != nullptr)) ? 2u : 1u;
-    hipLaunchKernelGGL(owq_tile_finish, dim3((unsigned)(n_rg * waves), per_tile, 1), dim3(256, 1, 1), 0, st, fa);
+    if (tasks.task_id != nullptr) {
+      hipLaunchKernelGGL(owq_tile_finish_sets, dim3((unsigned)(n_rg * waves * 2), (unsigned)nt, 1), dim3(256, 1, 1), 0, st, fa);
+    } else {
+      // few rows: one workgroup per (64 rows, token tile), so that the launch fills more of the chip
+      const unsigned per_tile = ntok > 32 && n_rg * waves <= 384 ? 2u : 1u;
+      hipLaunchKernelGGL(owq_tile_finish, dim3((unsigned)(n_rg * waves), per_tile, 1), dim3(256, 1, 1), 0, st, fa);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }
