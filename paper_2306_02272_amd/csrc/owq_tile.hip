@@ -509,10 +509,9 @@ struct FinishArgs {
   int scaled;            // the partial results are already scaled (grouped layers)
 };
 
-// grid.x = row groups x waves of the main kernel: one workgroup per 64 rows (the part of a slot
+// More than 32 tokens, many rows.  grid.x = row groups x waves of the main kernel: one workgroup per 64 rows (the part of a slot
 // one wave of the main kernel wrote); wave i takes accumulator tile i = (row tile i >> 1,
-// token tile i & 1).  grid.y = 2 (layers with few rows, more than 32 tokens): a workgroup per token
-// tile as well, its waves sharing the row tiles as they do for 32 tokens or fewer.
+// token tile i & 1).  grid.y = 2: a workgroup per token tile as well, two waves sharing a row tile.
 __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   __shared__ _Float16 out[64][72];     // [token][row], padded pitch
   constexpr int kWeakPitch = 17;       // 16-byte units per staged row of a chunk of weak columns, odd
@@ -521,10 +520,9 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   const int rg = blockIdx.x / a.waves, w = blockIdx.x - rg * a.waves;
   const int row_base = (rg * a.waves + w) * 64;
   const size_t slot_units = (size_t)a.waves * 1024;
-  // 64 tokens: wave = accumulator tile (row tile wv >> 1, token tile wv & 1), all four groups
-  // of 8 rows; 32 tokens or fewer: two waves share a row tile, two groups of 8 rows each
-  const bool per_tile = gridDim.y == 2;
-  const bool two = a.ntok > 32 && !per_tile;
+  // both token tiles: wave = accumulator tile (row tile wv >> 1, token tile wv & 1), all four groups
+  // of 8 rows; one: two waves share a row tile, two groups of 8 rows each
+  const bool per_tile = gridDim.y == 2, two = !per_tile;
   const int i = two ? wv : (wv >> 1) * 2 + (per_tile ? (int)blockIdx.y : 0), nt = i & 1, rtl = i >> 1;
   const int q0 = two ? 0 : 2 * (wv & 1), qn = two ? 4 : 2;
   const int n = nt * 32 + (lane & 31);
@@ -642,16 +640,19 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   }
 }
 
-// Several tasks: one workgroup per 32 rows and 32 tokens (grid.y: token tiles).  Latency is what bounds it (37 tokens, 3333 rows,
-// six sets of 72 columns: 112 workgroups of 64 rows, which took the sets one after the other between barriers and the partial
-// results behind them, 9.6 us of a call's 24.1).  So the partial results are asked for first, and the sets that the tokens use are
-// dealt out to the four waves, which need no barrier for them: each stages its sets' rows in LDS of its own (loads that cover
-// whole lines, the next set's while one is used).  A token has one set, so of the four waves' products three are zero where
-// the fourth is not, and their sum is what one wave would have.
-__global__ __launch_bounds__(256) void owq_tile_finish_sets(const FinishArgs a) {
+// Several tasks (SETS), 32 tokens or fewer, or few rows: one workgroup per 32 rows and 32 tokens (grid.y: token tiles).  Latency is
+// what bounds it (37 tokens, 3333 rows, six sets of 72 columns: 112 workgroups of 64 rows, which took the sets one after the other
+// between barriers and the partial results behind them, 9.6 us of a call's 24.1; so 21.0).  The partial results are asked for
+// first, and the weak product is dealt out to the four waves: with one set two k-steps of a chunk of eight each; with several,
+// every fourth of the sets that the tokens use, which needs no barrier: each wave stages its sets' rows in LDS of its own (loads
+// that cover whole lines, the next set's while one is used).  A token has one set, so of the four waves' products three are
+// zero where the fourth is not, and their sum is what one wave would have.
+template <bool SETS>
+__global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) {
   constexpr int kPitch = 17;           // 16-byte units per staged row of a chunk of 128 weak columns, odd
+  constexpr int kWPitch = SETS ? kPitch : 8;         // (the wave's product needs 4 KB)
   constexpr int KS = 8;
-  __shared__ u32x4 xst[32 * kPitch], wst[4][32 * kPitch];
+  __shared__ u32x4 xst[32 * kPitch], wst[4][32 * kWPitch];
   _Float16(*out)[40] = reinterpret_cast<_Float16(*)[40]>(xst);      // [token][row]
   static_assert(32 * 40 * 2 <= sizeof(xst), "the transposed result lies where the activations were");
   static_assert(16 * 64 * 4 <= sizeof(wst[0]), "a wave's product lies where its weights were");
@@ -685,7 +686,35 @@ __global__ __launch_bounds__(256) void owq_tile_finish_sets(const FinishArgs a) 
 #pragma unroll
   for (int r = 0; r < 16; ++r) wk[r] = 0.f;
   const int kunits = a.kp >> 3;
-  if (kunits > 0) {
+  if constexpr (!SETS) {
+    // one set: a wave takes two of a chunk's eight k-steps
+    const int cu = lane & 15, cr = lane >> 4, wu = lane & 3, wr = lane >> 2;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
+      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0, v = 2 * s0 + 4 * wv + wu, vc = v < kunits ? v : 0;
+      u32x4 tb[2], ta[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        tb[i] = a.xw[(size_t)(nt * 32 + wv * 8 + i * 4 + cr) * kunits + uc];
+        ta[i] = a.weak_w[(size_t)min(row_base + i * 16 + wr, a.d_out_pad - 1) * kunits + vc];
+      }
+      if (s0 > 0) __syncthreads();                   // the last chunk's activations have been read
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = wv * 8 + i * 4 + cr;
+        xst[r * kPitch + cu] = (u < kunits && nt * 32 + r < a.ntok) ? tb[i] : zero;
+        wst[wv][(i * 16 + wr) * 5 + wu] = v < kunits ? ta[i] : zero;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (2 * s0 + 4 * wv + 2 * j >= kunits) continue;      // same for the wave
+        const u32x4 av = wst[wv][(lane & 31) * 5 + 2 * j + kg];
+        const u32x4 bw = xst[(lane & 31) * kPitch + 4 * wv + 2 * j + kg];
+        wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
+      }
+    }
+  } else if (kunits > 0) {
     int mine = n < a.ntok ? -1 : -2;
     if (n < a.ntok) {
       const int t = a.task_id[n];
@@ -963,10 +992,14 @@ int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t s
     fa.ntok = ntok;
     fa.task_id = tasks.task_id ? tasks.task_id + t0 : nullptr;
     if (tasks.task_id != nullptr) {
-      hipLaunchKernelGGL(owq_tile_finish_sets, dim3((unsigned)(n_rg * waves * 2), (unsigned)nt, 1), dim3(256, 1, 1), 0, st, fa);
+      hipLaunchKernelGGL(owq_tile_finish_rows<true>, dim3((unsigned)(n_rg * waves * 2), (unsigned)nt, 1), dim3(256, 1, 1), 0, st, fa);
+    } else if (ntok <= 32 || n_rg * waves <= 160) {
+      // latency (16384 -> 4096, 28 tokens: 24.9 us with 64 rows per workgroup, 22.0 so; 7000 -> 3333 at 48 tokens 23.1 and 21.9; 36864 ->
+      // 9216 57.7 and 57.0) rather than workgroups in several rounds (13824 rows at 48 tokens 28.9 and 30.0, 36864 58.0 and 58.9)
+      hipLaunchKernelGGL(owq_tile_finish_rows<false>, dim3((unsigned)(n_rg * waves * 2), (unsigned)nt, 1), dim3(256, 1, 1), 0, st, fa);
     } else {
-      // few rows: one workgroup per (64 rows, token tile), so that the launch fills more of the chip
-      const unsigned per_tile = ntok > 32 && n_rg * waves <= 384 ? 2u : 1u;
+      // one workgroup per (64 rows, token tile) where that fills more of the chip
+      const unsigned per_tile = n_rg * waves <= 384 ? 2u : 1u;
       hipLaunchKernelGGL(owq_tile_finish, dim3((unsigned)(n_rg * waves), per_tile, 1), dim3(256, 1, 1), 0, st, fa);
     }
     const hipError_t e = hipGetLastError();
