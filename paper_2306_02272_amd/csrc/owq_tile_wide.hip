@@ -527,7 +527,7 @@ __global__ __launch_bounds__(256 * HALVES, 2) void owq_wide_mma(const WideArgs a
   // them; the tiles with one workgroup come first
   const int n_wt = (a.n_tt + NT / 2 - 1) / (NT / 2), tiles = a.n_rg * n_wt;
   const int full = HALVES == 2 ? a.full : 0;
-  const bool cut = (int)blockIdx.x >= full;
+  const bool cut = HALVES == 1 || (int)blockIdx.x >= full;
   const int id = cut ? (int)blockIdx.x - full : (int)blockIdx.x, N = cut ? (int)gridDim.x - full : full, xcd = id & 7;
   const int lin = xcd * (N >> 3) + min(xcd, N & 7) + (id >> 3);
   const int s = cut ? lin / (tiles - full) : 0, rel = lin - s * (tiles - full);      // of its part
