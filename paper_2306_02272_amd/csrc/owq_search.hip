@@ -310,7 +310,7 @@ struct TeamShared {
 // its points each; L levels and Z zero points need L + Z - 1 lookups, of which every L in a row are a grid point's (3 bits: 10
 // lookups where four points per lane took 28).  Z covers the runs of all square grids up to 16 x 16 with cuts up to 0.45
 // almost always; a group where a lane's run is longer, where a diagonal has more than one step size (the widths'
-// rounding straddles a binary16 boundary), where a step size is at its least value, a midpoint lies beyond the table or three
+// rounding straddles a binary16 boundary, inside a half or between the two), where a step size is at its least value, a midpoint lies beyond the table or three
 // errors are too close to tell is marked in `scale` (kLeft).
 // BITS < 0: the general grid for what is marked.  In a kernel of its own since the general way takes 30 registers more: 107 ->
 // 90 us for the 2^17 groups of 128 of a 4096 x 4096 matrix, and 5 us for the launch that looks for marks.
@@ -623,6 +623,8 @@ __global__ __launch_bounds__(256, NT <= 4 ? 5 : NT <= 24 ? 4 : 2) void owq_searc
           const float hi_t = cut_hi(hi, ft, r);
           int i0, i1, j0;
           half_of(seldom(lane), i0, i1, j0);
+          // the diagonal's other half, of which this lane's points say nothing; then this half point by point
+          other |= __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0xB1, 0xf, 0xf, true)) != s;
 #pragma unroll 1
           for (int p = 1; p < 8; ++p) {
             const int o = min(p, i1 - i0);
