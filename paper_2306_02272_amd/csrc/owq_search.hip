@@ -76,17 +76,18 @@ __device__ __forceinline__ T wave_all(T v, F op) {
 
 // Least (greatest) of the 64 lanes' values, none of them a NaN.  Written as instructions: from fminf the compiler makes four per
 // step (old value, move across lanes, canonicalise, minimum) where one does.  s_nop: two wait states before a value that was
-// just written is read across lanes.
+// just written is read across lanes, inside the blocks and around them, and before scalar registers that v_readlane wrote are
+// used: the compiler, which adds these between its own instructions, does not look into a block.
 __device__ __forceinline__ float wave_min(float v) {
   asm("s_nop 1\n\tv_min_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
       "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
       "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-      "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf"
+      "s_nop 1\n\tv_min_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\ts_nop 1"
       : "+v"(v));
   const int i = __builtin_bit_cast(int, v);
   const int r0 = __builtin_amdgcn_readlane(i, 0), r1 = __builtin_amdgcn_readlane(i, 16), r2 = __builtin_amdgcn_readlane(i, 32);
   float m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 48));
-  asm("v_min_f32 %0, %1, %0\n\tv_min_f32 %0, %2, %0\n\tv_min_f32 %0, %3, %0" : "+v"(m) : "s"(r0), "s"(r1), "s"(r2));
+  asm("s_nop 1\n\tv_min_f32 %0, %1, %0\n\tv_min_f32 %0, %2, %0\n\tv_min_f32 %0, %3, %0\n\ts_nop 1" : "+v"(m) : "s"(r0), "s"(r1), "s"(r2));
   return m;
 }
 __device__ __forceinline__ float wave_max(float v) { return -wave_min(-v); }
