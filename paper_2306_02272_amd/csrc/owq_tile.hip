@@ -509,9 +509,10 @@ struct FinishArgs {
   int scaled;            // the partial results are already scaled (grouped layers)
 };
 
-// More than 32 tokens, many rows.  grid.x = row groups x waves of the main kernel: one workgroup per 64 rows (the part of a slot
+// Many rows.  grid.x = row groups x waves of the main kernel: one workgroup per 64 rows (the part of a slot
 // one wave of the main kernel wrote); wave i takes accumulator tile i = (row tile i >> 1,
-// token tile i & 1).  grid.y = 2: a workgroup per token tile as well, two waves sharing a row tile.
+// token tile i & 1).  32 tokens or fewer, or grid.y = 2, a workgroup per token tile as well: two waves share a row tile.
+template <bool SETS>
 __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   __shared__ _Float16 out[64][72];     // [token][row], padded pitch
   constexpr int kWeakPitch = 17;       // 16-byte units per staged row of a chunk of weak columns, odd
@@ -522,7 +523,7 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   const size_t slot_units = (size_t)a.waves * 1024;
   // both token tiles: wave = accumulator tile (row tile wv >> 1, token tile wv & 1), all four groups
   // of 8 rows; one: two waves share a row tile, two groups of 8 rows each
-  const bool per_tile = gridDim.y == 2, two = !per_tile;
+  const bool per_tile = gridDim.y == 2, two = a.ntok > 32 && !per_tile;
   const int i = two ? wv : (wv >> 1) * 2 + (per_tile ? (int)blockIdx.y : 0), nt = i & 1, rtl = i >> 1;
   const int q0 = two ? 0 : 2 * (wv & 1), qn = two ? 4 : 2;
   const int n = nt * 32 + (lane & 31);
@@ -534,36 +535,99 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   if (kunits > 0) {
     const int kg = lane >> 5;
     constexpr int KS = 8;                            // K-steps whose loads are in flight together
-    // A lane's operand is 16 bytes of its own row, so a wave reading operands
-    // straight from memory touches 64 cache lines per load, and the address path takes a cycle for each
-    // (4 of this kernel's 12 us).  Instead the workgroup copies the 64 rows x 16 units of a chunk of 8 K-steps
-    // with loads that cover whole lines (a quarter wave per row), weights and gathered activations alike,
-    // and the waves take their operands from LDS (odd pitch: no bank conflicts).
-    const int cu = tid & 15, cr = tid >> 4;
-    for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
-      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
-      u32x4 ta[4], tb[4];
+    if constexpr (!SETS) {
+      // One set, the layer's own.  A lane's operand is 16 bytes of its own row, so a wave reading operands
+      // straight from memory touches 64 cache lines per load, and the address path takes a cycle for each
+      // (4 of this kernel's 12 us).  Instead the workgroup copies the 64 rows x 16 units of a chunk of 8 K-steps
+      // with loads that cover whole lines (a quarter wave per row), weights and gathered activations alike,
+      // and the waves take their operands from LDS (odd pitch: no bank conflicts).
+      const int cu = tid & 15, cr = tid >> 4;
+      for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
+        const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
+        u32x4 ta[4], tb[4];
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        int r = row_base + cr + 16 * i4;
-        if (r > a.d_out_pad - 1) r = a.d_out_pad - 1;
-        ta[i4] = a.weak_w[(size_t)r * kunits + uc];
-        tb[i4] = a.xw[(size_t)(cr + 16 * i4) * kunits + uc];
+        for (int i4 = 0; i4 < 4; ++i4) {
+          int r = row_base + cr + 16 * i4;
+          if (r > a.d_out_pad - 1) r = a.d_out_pad - 1;
+          ta[i4] = a.weak_w[(size_t)r * kunits + uc];
+          tb[i4] = a.xw[(size_t)(cr + 16 * i4) * kunits + uc];
+        }
+        if (s0 > 0) __syncthreads();                 // the operands of the last chunk have been read
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const u32x4 zero = {0u, 0u, 0u, 0u};
+          wstage[0][(cr + 16 * i4) * kWeakPitch + cu] = u < kunits ? ta[i4] : zero;
+          wstage[1][(cr + 16 * i4) * kWeakPitch + cu] = (u < kunits && cr + 16 * i4 < a.ntok) ? tb[i4] : zero;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+          if (2 * (s0 + j) >= kunits) continue;      // same for the whole workgroup
+          const u32x4 av = wstage[0][(rtl * 32 + (lane & 31)) * kWeakPitch + 2 * j + kg];
+          const u32x4 bw = wstage[1][n * kWeakPitch + 2 * j + kg];
+          wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
+        }
       }
-      if (s0 > 0) __syncthreads();                 // the operands of the last chunk have been read
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-        wstage[0][(cr + 16 * i4) * kWeakPitch + cu] = u < kunits ? ta[i4] : zero;
-        wstage[1][(cr + 16 * i4) * kWeakPitch + cu] = (u < kunits && cr + 16 * i4 < a.ntok) ? tb[i4] : zero;
+    } else {
+      // Several sets.  All waves of the workgroup look at the same 32 tokens (the launch sees to that), so they agree on
+      // the sets these use: in ascending order, one pass of K-steps per set, with the other tokens' operands zeroed.
+      // A set's 64 rows x 16 units go through LDS as above; those of the next set are fetched meanwhile (lanes reading
+      // operands of their own rows straight from memory, pointer first, then weights, one set after the other: 12.9 us
+      // for six sets of 72 columns, 37 tokens and 3333 rows; this: 11.3, with fewer partial results to add 10).
+      typedef const __attribute__((address_space(1))) u32x4 *gptr_t;   // pointers read from memory: global
+      int mine = n < a.ntok ? -1 : -2;               // the set of this lane's token: -1 = the layer's own, -2 = no token
+      if (n < a.ntok) {
+        const int t = a.task_id[n];
+        if ((u32)t < (u32)a.n_sets) mine = t;
       }
-      __syncthreads();
+      const u32x4 *base = mine >= 0 ? static_cast<const u32x4 *>(a.weak_sets[mine]) : a.weak_w;
+      const int cu = tid & 15, cr = tid >> 4;
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
+        const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
+        int pending = mine, t = -2;
+        // the least index still pending and, by one of its lanes, where its weights lie
+        auto next_set = [&](u32x4 (&ta)[4]) __attribute__((always_inline)) {
+          int cand = pending >= -1 ? pending : 0x7fffffff;
 #pragma unroll
-      for (int j = 0; j < KS; ++j) {
-        if (2 * (s0 + j) >= kunits) continue;      // same for the whole workgroup
-        const u32x4 av = wstage[0][(rtl * 32 + (lane & 31)) * kWeakPitch + 2 * j + kg];
-        const u32x4 bw = wstage[1][n * kWeakPitch + 2 * j + kg];
-        wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
+          for (int d = 1; d < 64; d <<= 1) cand = min(cand, __shfl_xor(cand, d));
+          const int c = __builtin_amdgcn_readfirstlane(cand);
+          if (c == 0x7fffffff) return c;
+          const int src = __builtin_ctzll(__ballot(pending == c));
+          const unsigned long long at = (unsigned long long)(uintptr_t)base;
+          const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)at, src), hi = (u32)__builtin_amdgcn_readlane((int)(u32)(at >> 32), src);
+          const gptr_t w0 = (gptr_t)(uintptr_t)(((unsigned long long)hi << 32) | lo);
+          if (pending == c) pending = -2;
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) {
+            int r = row_base + cr + 16 * i4;
+            if (r > a.d_out_pad - 1) r = a.d_out_pad - 1;
+            ta[i4] = w0[(size_t)r * kunits + uc];
+          }
+          return c;
+        };
+        u32x4 ta[4], tb[4];
+        t = next_set(ta);
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) tb[i4] = a.xw[(size_t)(cr + 16 * i4) * kunits + uc];
+        __syncthreads();                             // the operands of the last chunk have been read
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) wstage[1][(cr + 16 * i4) * kWeakPitch + cu] = (u < kunits && cr + 16 * i4 < a.ntok) ? tb[i4] : zero;
+        while (t != 0x7fffffff) {
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) wstage[0][(cr + 16 * i4) * kWeakPitch + cu] = u < kunits ? ta[i4] : zero;
+          __syncthreads();
+          const bool use = mine == t;
+          t = next_set(ta);
+#pragma unroll
+          for (int j = 0; j < KS; ++j) {
+            if (2 * (s0 + j) >= kunits) continue;    // same for the whole workgroup
+            const u32x4 av = wstage[0][(rtl * 32 + (lane & 31)) * kWeakPitch + 2 * j + kg];
+            const u32x4 bw = wstage[1][n * kWeakPitch + 2 * j + kg];
+            wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, use ? bw : zero), wk);
+          }
+          __syncthreads();                           // read before the next set's rows are written
+        }
       }
     }
   }
@@ -640,7 +704,7 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
   }
 }
 
-// Several tasks (SETS), 32 tokens or fewer, or few rows: one workgroup per 32 rows and 32 tokens (grid.y: token tiles).  Latency is
+// Few rows: one workgroup per 32 rows and 32 tokens (grid.y: token tiles); SETS: several tasks.  Latency is
 // what bounds it (37 tokens, 3333 rows, six sets of 72 columns: 112 workgroups of 64 rows, which took the sets one after the other
 // between barriers and the partial results behind them, 9.6 us of a call's 24.1; so 21.0).  The partial results are asked for
 // first, and the weak product is dealt out to the four waves: with one set two k-steps of a chunk of eight each; with several,
@@ -991,16 +1055,19 @@ int launch_tile(const owq_layer_info_t &g, void *blob, void *scratch, uint64_t s
     fa.y = yp + (size_t)t0 * g.d_out;
     fa.ntok = ntok;
     fa.task_id = tasks.task_id ? tasks.task_id + t0 : nullptr;
-    if (tasks.task_id != nullptr) {
-      hipLaunchKernelGGL(owq_tile_finish_rows<true>, dim3((unsigned)(n_rg * waves * 2), (unsigned)nt, 1), dim3(256, 1, 1), 0, st, fa);
-    } else if (ntok <= 32 || n_rg * waves <= 160) {
-      // latency (16384 -> 4096, 28 tokens: 24.9 us with 64 rows per workgroup, 22.0 so; 7000 -> 3333 at 48 tokens 23.1 and 21.9; 36864 ->
-      // 9216 57.7 and 57.0) rather than workgroups in several rounds (13824 rows at 48 tokens 28.9 and 30.0, 36864 58.0 and 58.9)
-      hipLaunchKernelGGL(owq_tile_finish_rows<false>, dim3((unsigned)(n_rg * waves * 2), (unsigned)nt, 1), dim3(256, 1, 1), 0, st, fa);
+    // 32 rows and tokens per workgroup, or 64 rows.  The first is about latency (16384 -> 4096, 28 tokens: 24.9 us with 64 rows per
+    // workgroup, 22.0 so; 7000 -> 3333 at 48 tokens 23.1 and 21.9; six tasks 25.9 and 22.1), as long as its workgroups have a place
+    // each.  Past that it loses: 13824 rows at 48 tokens 28.9 and 30.0, one task by its index 29.1 and 31.0; 28672 rows at 16
+    // tokens 27.6 and 29.9 (24576 rows 27.4 and 27.3), without tasks 49152 rows 25.7 and 26.8.
+    const bool sets = tasks.task_id != nullptr;
+    const int rows64 = n_rg * waves;
+    if (rows64 <= (ntok <= 32 ? 384 : 160)) {
+      hipLaunchKernelGGL((sets ? owq_tile_finish_rows<true> : owq_tile_finish_rows<false>), dim3((unsigned)(rows64 * 2), (unsigned)nt, 1),
+                         dim3(256, 1, 1), 0, st, fa);
     } else {
-      // one workgroup per (64 rows, token tile) where that fills more of the chip
-      const unsigned per_tile = n_rg * waves <= 384 ? 2u : 1u;
-      hipLaunchKernelGGL(owq_tile_finish, dim3((unsigned)(n_rg * waves), per_tile, 1), dim3(256, 1, 1), 0, st, fa);
+      // a workgroup per token tile as well where that fills more of the chip (several tasks: always, its waves share their tokens)
+      const unsigned per_tile = ntok > 32 && (rows64 <= 384 || sets) ? 2u : 1u;
+      hipLaunchKernelGGL((sets ? owq_tile_finish<true> : owq_tile_finish<false>), dim3((unsigned)rows64, per_tile, 1), dim3(256, 1, 1), 0, st, fa);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;

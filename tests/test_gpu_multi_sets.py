@@ -48,3 +48,26 @@ def test_chunks_of_weak_columns(env, k, batch, use):
         rel, mx = owq_ref.parity_errors(y[n], want[n])
         assert rel <= 1e-3 and mx <= 1e-2, (n, task[n], rel, mx)
     lin.close()
+
+
+@pytest.mark.parametrize("d_out,batch", [(10240, 64), (10250, 33), (10250, 64), (24576, 32), (24600, 5), (24600, 32), (24600, 40)])
+@pytest.mark.parametrize("bits,group,k,used", [(3, 0, 130, 6), (4, 128, 20, 1)])
+def test_many_rows(env, d_out, batch, bits, group, k, used):
+    # either side of the rows from which a workgroup of the last launch takes 64 of them: by the number of tokens
+    torch, B = env
+    n_sets = 6
+    layer = make_layer(LayerSpec("rows", 256, d_out, bits, group, k, d_out + batch))
+    rng = np.random.default_rng(d_out + batch)
+    sets = [rng.normal(0, 0.02, size=(d_out, k)).astype(np.float16) for _ in range(n_sets)]
+    task = (rng.integers(-1, n_sets, batch) if used > 1 else np.full(batch, 2)).astype(np.int32)
+    x = make_x(layer, batch)
+    print(f"{d_out} rows, {batch} tokens, k {k}", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    table, bufs = lin.add_weak_sets(sets)
+    y = lin.multi(torch.from_numpy(x).cuda(), table, torch.from_numpy(task).cuda()).cpu().numpy()
+    want = owq_ref.owq_linear_multi_ref(layer.codes, layer.scale, layer.zero, layer.group_size, layer.weak_idx, sets + [layer.weak_w],
+                                        [t if 0 <= t < n_sets else n_sets for t in task], x)
+    for n in range(batch):
+        rel, mx = owq_ref.parity_errors(y[n], want[n])
+        assert rel <= 1e-3 and mx <= 1e-2, (n, task[n], rel, mx)
+    lin.close()

@@ -1,6 +1,6 @@
 """The last of the batched path's three launches where one task's weak columns are dealt out to its waves: no weak columns, one
 k-step, parts of a chunk of 128 and more than two of them; rows that are no multiple of 32; 32 tokens or fewer and more; and
-either side of the number of rows from which a workgroup takes 64 of them.  Bar as for the other kernels of the layout."""
+either side of the numbers of rows from which a workgroup takes 64 of them (more than 32 tokens; fewer).  Bar as for the other kernels of the layout."""
 import numpy as np
 import pytest
 
@@ -22,7 +22,7 @@ def env():
 
 
 @pytest.mark.parametrize("d_in,d_out,k", [(900, 33, 0), (900, 170, 5), (520, 65, 100), (900, 300, 130), (900, 95, 300),
-                                          (256, 10240, 9), (256, 10250, 9)])
+                                          (256, 10240, 9), (256, 10250, 9), (256, 24576, 9), (256, 24600, 9)])
 @pytest.mark.parametrize("bits,group", [(3, 0), (4, 128)])
 @pytest.mark.parametrize("batch", [1, 32, 33, 64])
 def test_weak_columns_dealt_out_to_the_waves(env, d_in, d_out, k, bits, group, batch):
