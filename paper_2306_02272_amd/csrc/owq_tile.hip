@@ -707,16 +707,16 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
 // Few rows: one workgroup per 32 rows and 32 tokens (grid.y: token tiles); SETS: several tasks.  Latency is
 // what bounds it (37 tokens, 3333 rows, six sets of 72 columns: 112 workgroups of 64 rows, which took the sets one after the other
 // between barriers and the partial results behind them, 9.6 us of a call's 24.1; so 21.0).  The partial results are asked for
-// first, and the weak product is dealt out to the four waves: with one set two k-steps of a chunk of eight each; with several,
-// every fourth of the sets that the tokens use, which needs no barrier: each wave stages its sets' rows in LDS of its own (loads
-// that cover whole lines, the next set's while one is used).  A token has one set, so of the four waves' products three are
-// zero where the fourth is not, and their sum is what one wave would have.
+// first, and the weak product is dealt out to the four waves, two k-steps of a chunk of eight each, of every set that the tokens
+// use: a wave needs no barrier from set to set, it stages its k-steps of a set's rows in LDS of its own while the next ones are
+// fetched.  A token has one set, whose k-steps add up as they do where there is no other: one task gives the bits of the
+// plain call.  (Every fourth set by a wave, which keeps a set's sum in one chain: 0.98 to 1.06 of this, 1.00 on average
+// over 100 calls.)
 template <bool SETS>
 __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) {
   constexpr int kPitch = 17;           // 16-byte units per staged row of a chunk of 128 weak columns, odd
-  constexpr int kWPitch = SETS ? kPitch : 8;         // (the wave's product needs 4 KB)
   constexpr int KS = 8;
-  __shared__ u32x4 xst[32 * kPitch], wst[4][32 * kWPitch];
+  __shared__ u32x4 xst[32 * kPitch], wst[4][256];    // a wave's weights: 32 rows x 5 units; its product: 4 KB
   _Float16(*out)[40] = reinterpret_cast<_Float16(*)[40]>(xst);      // [token][row]
   static_assert(32 * 40 * 2 <= sizeof(xst), "the transposed result lies where the activations were");
   static_assert(16 * 64 * 4 <= sizeof(wst[0]), "a wave's product lies where its weights were");
@@ -750,10 +750,26 @@ __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) 
 #pragma unroll
   for (int r = 0; r < 16; ++r) wk[r] = 0.f;
   const int kunits = a.kp >> 3;
+  // a wave takes two of a chunk's eight k-steps
+  const int cu = lane & 15, cr = lane >> 4, wu = lane & 3, wr = lane >> 2;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  auto stage_x = [&](const u32x4 (&tb)[2], bool in) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = wv * 8 + i * 4 + cr;
+      xst[r * kPitch + cu] = (in && nt * 32 + r < a.ntok) ? tb[i] : zero;
+    }
+  };
+  auto steps = [&](int s0, auto of) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (2 * s0 + 4 * wv + 2 * j >= kunits) continue;        // same for the wave
+      const u32x4 av = wst[wv][(lane & 31) * 5 + 2 * j + kg];
+      const u32x4 bw = of(xst[(lane & 31) * kPitch + 4 * wv + 2 * j + kg]);
+      wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
+    }
+  };
   if constexpr (!SETS) {
-    // one set: a wave takes two of a chunk's eight k-steps
-    const int cu = lane & 15, cr = lane >> 4, wu = lane & 3, wr = lane >> 2;
-    const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
       const int u = 2 * s0 + cu, uc = u < kunits ? u : 0, v = 2 * s0 + 4 * wv + wu, vc = v < kunits ? v : 0;
       u32x4 tb[2], ta[2];
@@ -763,20 +779,11 @@ __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) 
         ta[i] = a.weak_w[(size_t)min(row_base + i * 16 + wr, a.d_out_pad - 1) * kunits + vc];
       }
       if (s0 > 0) __syncthreads();                   // the last chunk's activations have been read
+      stage_x(tb, u < kunits);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = wv * 8 + i * 4 + cr;
-        xst[r * kPitch + cu] = (u < kunits && nt * 32 + r < a.ntok) ? tb[i] : zero;
-        wst[wv][(i * 16 + wr) * 5 + wu] = v < kunits ? ta[i] : zero;
-      }
+      for (int i = 0; i < 2; ++i) wst[wv][(i * 16 + wr) * 5 + wu] = v < kunits ? ta[i] : zero;
       __syncthreads();
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if (2 * s0 + 4 * wv + 2 * j >= kunits) continue;      // same for the wave
-        const u32x4 av = wst[wv][(lane & 31) * 5 + 2 * j + kg];
-        const u32x4 bw = xst[(lane & 31) * kPitch + 4 * wv + 2 * j + kg];
-        wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
-      }
+      steps(s0, [](u32x4 bw) __attribute__((always_inline)) { return bw; });
     }
   } else if (kunits > 0) {
     int mine = n < a.ntok ? -1 : -2;
@@ -786,58 +793,51 @@ __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) 
     }
     typedef const __attribute__((address_space(1))) u32x4 *gptr_t;   // pointers read from memory: global
     const unsigned long long base = (unsigned long long)(uintptr_t)(mine >= 0 ? a.weak_sets[mine] : static_cast<const void *>(a.weak_w));
-    const int cu = lane & 15, cr = lane >> 4;
-    const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
-      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0;
-      u32x4 tb[2], ta[8];
+      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0, v = 2 * s0 + 4 * wv + wu, vc = v < kunits ? v : 0;
+      u32x4 tb[2], ta[4][2];                         // four sets' weights in flight
+      int c[4];                                      // which
 #pragma unroll
       for (int i = 0; i < 2; ++i) tb[i] = a.xw[(size_t)(nt * 32 + wv * 8 + i * 4 + cr) * kunits + uc];
-      // the sets in use, in the order of their first tokens; this wave's are every fourth one
+      // the sets in use, in the order of their first tokens
       unsigned long long pending = __ballot(mine >= -1);
-      int k = 0;
-      auto next_set = [&]() __attribute__((always_inline)) {
-        int c = -2;
-        while (pending != 0ull) {
-          const int at = __builtin_ctzll(pending), v = __builtin_amdgcn_readlane(mine, at);
-          pending &= ~__ballot(mine == v);
-          if ((k++ & 3) != wv) continue;
-          c = v;
-          const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)base, at), hi = (u32)__builtin_amdgcn_readlane((int)(u32)(base >> 32), at);
-          const gptr_t w0 = (gptr_t)(uintptr_t)(((unsigned long long)hi << 32) | lo);
+      auto next_set = [&](u32x4 (&t)[2], int &set) __attribute__((always_inline)) {
+        set = -2;
+        if (pending == 0ull) return;
+        const int at = __builtin_ctzll(pending);
+        set = __builtin_amdgcn_readlane(mine, at);
+        pending &= ~__ballot(mine == set);
+        const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)base, at), hi = (u32)__builtin_amdgcn_readlane((int)(u32)(base >> 32), at);
+        const gptr_t w0 = (gptr_t)(uintptr_t)(((unsigned long long)hi << 32) | lo);
 #pragma unroll
-          for (int i = 0; i < 8; ++i) ta[i] = w0[(size_t)min(row_base + i * 4 + cr, a.d_out_pad - 1) * kunits + uc];
-          break;
-        }
-        return c;
+        for (int i = 0; i < 2; ++i) t[i] = w0[(size_t)min(row_base + i * 16 + wr, a.d_out_pad - 1) * kunits + vc];
       };
-      int c = next_set();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) next_set(ta[i], c[i]);
       if (s0 > 0) __syncthreads();                   // the last chunk's activations have been read
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = wv * 8 + i * 4 + cr;
-        xst[r * kPitch + cu] = (u < kunits && nt * 32 + r < a.ntok) ? tb[i] : zero;
-      }
+      stage_x(tb, u < kunits);
       __syncthreads();
-      while (c != -2) {
+      auto use_set = [&](u32x4 (&t)[2], int &set) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) wst[wv][(i * 4 + cr) * kPitch + cu] = u < kunits ? ta[i] : zero;
-        const bool use = mine == c;
-        c = next_set();
+        for (int i = 0; i < 2; ++i) wst[wv][(i * 16 + wr) * 5 + wu] = v < kunits ? t[i] : zero;
+        const bool use = mine == set;
+        next_set(t, set);
         // (LDS serves a wave's instructions in order; this keeps the compiler from moving them)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int j = 0; j < KS; ++j) {
-          if (2 * (s0 + j) >= kunits) continue;      // same for the whole workgroup
-          const u32x4 av = wst[wv][(lane & 31) * kPitch + 2 * j + kg];
-          const u32x4 bw = xst[(lane & 31) * kPitch + 2 * j + kg];
-          wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, use ? bw : zero), wk);
-        }
+        steps(s0, [&](u32x4 bw) __attribute__((always_inline)) { return use ? bw : zero; });
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      };
+      for (bool more = true; more;) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          more = c[i] != -2;
+          if (!more) break;
+          use_set(ta[i], c[i]);
+        }
       }
     }
   }

@@ -71,3 +71,23 @@ def test_many_rows(env, d_out, batch, bits, group, k, used):
         rel, mx = owq_ref.parity_errors(y[n], want[n])
         assert rel <= 1e-3 and mx <= 1e-2, (n, task[n], rel, mx)
     lin.close()
+
+
+@pytest.mark.parametrize("d_out,k", [(96, 33), (128, 130), (300, 200), (70, 300), (10300, 70)])
+@pytest.mark.parametrize("bits,group", [(3, 0), (4, 128)])
+@pytest.mark.parametrize("batch", [33, 64])
+def test_one_task_equals_the_plain_call_bit_for_bit(env, d_out, k, bits, group, batch):
+    # 33 to 64 tokens, the plain call's three launches: sums of more than two k-steps in the same order, beside tokens of other tasks too
+    torch, B = env
+    layer = make_layer(LayerSpec("same", 900, d_out, bits, group, k, d_out + k))
+    x = torch.from_numpy(make_x(layer, batch)).cuda()
+    rng = np.random.default_rng(k)
+    sets = [layer.weak_w] + [rng.normal(0, 0.02, size=(d_out, k)).astype(np.float16) for _ in range(5)]
+    print(f"{d_out} rows, {batch} tokens, k {k}", flush=True)
+    lin = B.OwqLinear(layer, layout=1)
+    table, bufs = lin.add_weak_sets(sets)
+    want = lin(x).cpu().numpy().view(np.uint16)
+    for task in (np.zeros(batch), np.full(batch, -1), np.where(rng.random(batch) < 0.4, 0, rng.integers(1, 6, batch))):
+        y = lin.multi(x, table, torch.from_numpy(task.astype(np.int32)).cuda()).cpu().numpy().view(np.uint16)
+        np.testing.assert_array_equal(y[task <= 0], want[task <= 0])
+    lin.close()
