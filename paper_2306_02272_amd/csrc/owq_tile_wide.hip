@@ -633,7 +633,8 @@ wide_fn pick_wide(int bits, bool grouped, int nt, int halves) {
   return nt != 4 ? pick_wide_tokens<2, 1>(bits, grouped) : halves == 2 ? pick_wide_tokens<4, 2>(bits, grouped) : pick_wide_tokens<4, 1>(bits, grouped);
 }
 
-// Kernel and work split of n_tt token tiles of 64 over n_rg row groups and nbp block pairs, with room for `slots` partial results.
+// Kernel and work split of n_tt token tiles of 64 over n_rg row groups and nbp block pairs, with room for `slots` partial results;
+// eight: workgroups of eight waves too.
 struct WidePlan {
   int nt, halves, full, split;
   float us;
@@ -642,7 +643,7 @@ constexpr float kWide8 = 3.1f, kWide8Grouped = 3.6f;      // us per pair of bloc
 constexpr float kWide8Us = 4.f, kWide8More = 9.f;         // the exchange of its halves; start and end of a round, which nothing runs under
 constexpr int kWidePlans = 128;           // most token tiles that may go in two launches
 constexpr float kWideLaunchUs = 14.f;     // start, first loads and end of a second launch
-WidePlan wide_plan(bool grouped, int n_rg, int n_tt, int nbp, int64_t slots) {
+WidePlan wide_plan(bool grouped, int n_rg, int n_tt, int nbp, int64_t slots, bool eight) {
   WidePlan best{2, 1, 0, 1, 1e30f};
   if (n_tt == 0) return WidePlan{2, 1, 0, 1, 0.f};
   // us per pair of blocks: up to 128 workgroups, one and two on every compute unit, as costs to choose by.  30 whole calls (2048
@@ -665,13 +666,24 @@ WidePlan wide_plan(bool grouped, int n_rg, int n_tt, int nbp, int64_t slots) {
   // Eight waves, one workgroup per compute unit: fewer than 512 tiles, of which 256, if there are as many, are a whole round and the
   // others are cut into column ranges that fill another.  (From 512 on two workgroups of four waves share a compute unit from
   // start to end and lose nothing: 5120 -> 13824, 4-bit, 1500 tokens, 648 tiles: 237 us, so 259.)
-  const float c8 = grouped ? kWide8Grouped : kWide8;
+  // What is cut has to be better by a margin than one launch of tiles of 64 tokens, which the costs above are too high for: with
+  // groups by what its workgroups' starts and ends take (14848 -> 8298, 4-bit, 903 tokens, 29 ranges: 263 us, so 248; 9600 -> 4752, 3-bit,
+  // 1690 tokens, 19 ranges and two launches otherwise: 178, 197), with one scale per row by their share (3968 -> 7345, 4-bit, 1352
+  // tokens 96, so 89).  With one scale per row two rounds of eight waves lose, too (10240 -> 10871, 3-bit, 1390 tokens 257, so 249).
+  const float c8 = grouped ? kWide8Grouped : kWide8, four = best.us;
+  float least = four;
+  const bool small_tiles = best.nt == 2 && best.split == 1;
   const int tiles = n_rg * ((n_tt + 1) / 2), full = tiles / 256 * 256, rest = tiles - full, rounds = full / 256 + (rest ? 1 : 0);
-  for (int s = 1; tiles < 512 && s <= 32 && s * 2 <= nbp; ++s) {
+  for (int s = 1; eight && tiles < 512 && s <= 32 && s * 2 <= nbp; ++s) {
     if (s > 1 && (rest == 0 || rest * s > 256 || (int64_t)rest * 2 * s > slots)) break;
+    if (s == 1 && full > 0 && !grouped) continue;
     const int pairs = full / 256 * nbp + (rest ? (nbp + s - 1) / s : 0);
     const float us = kWide8Us + kWide8More * (rounds - 1) + c8 * pairs + (s > 1 ? 1.6f + 0.018f * rest * s : 0.f);
-    if (us < best.us) best = WidePlan{4, 2, s > 1 ? full : 0, s, us};
+    const float margin = small_tiles && full > 0 && s > 1 ? (grouped ? 0.45f * s : 0.08f * four) : 0.f;
+    if (us + margin < least) {
+      least = us + margin;
+      best = WidePlan{4, 2, s > 1 ? full : 0, s, us};
+    }
   }
   return best;
 }
@@ -739,9 +751,11 @@ int launch_tile_wide(const owq_layer_info_t &g, void *blob, void *scratch, uint6
     // the token tiles in one or two launches: the first `a` of them and the rest, each with its own split
     int first = n_tt;
     const bool grouped = g.n_groups > 1;
-    WidePlan whole = wide_plan(grouped, n_rg, n_tt, g.nbp, slots), some[kWidePlans];       // some[a]: of a token tiles
+    WidePlan whole = wide_plan(grouped, n_rg, n_tt, g.nbp, slots, true), some[kWidePlans];       // some[a]: of a token tiles
     float us = whole.us;
-    for (int a = 1; a < n_tt && n_tt <= kWidePlans; ++a) some[a] = wide_plan(grouped, n_rg, a, g.nbp, slots);
+    // (one scale per row: a part of eight waves loses what the other part's launch costs, 11648 -> 7665, 3-bit, 1786 tokens 285 us, one
+    // launch of four waves 268)
+    for (int a = 1; a < n_tt && n_tt <= kWidePlans; ++a) some[a] = wide_plan(grouped, n_rg, a, g.nbp, slots, grouped);
     for (int a = 1; a < n_tt && n_tt <= kWidePlans; ++a) {
       const float v = some[a].us + some[n_tt - a].us + kWideLaunchUs;
       if (v < us) { us = v; first = a; }
