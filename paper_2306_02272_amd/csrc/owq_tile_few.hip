@@ -355,11 +355,13 @@ int launch_tile_few(const owq_layer_info_t &g, void *blob, int32_t lds_limit, co
   // 17.4 / 22.2; 4096 rows x 16384 columns, 24 tokens 36.2 / 23.2.
   const float mb = (float)g.n_rt * g.nbp * 64 * g.chunks * 16 / 1e6f;
   float best = 15.f + mb / 4.2f;
-  // (several workgroups per row tile: whole blocks only.  Layers with others went by that cost too and took three launches: 7000 ->
-  // 2048 at 4 / 16 tokens 15.2 / 15.6 us, 10.3 / 11.9 so; 9000 -> 3000 16.3 / 16.5, 12.3 / 14.1.  8192 -> 4096, 3-bit, 12.7 / 16.0,
+  // (several workgroups per row tile: whole blocks and groups of 128 2^n only.  Layers with others went by that cost too and took three
+  // launches: 7000 -> 2048 at 4 / 16 tokens 15.2 / 15.6 us, 10.3 / 11.9 so; 9000 -> 3000 16.3 / 16.5, 12.3 / 14.1; 7680 -> 2048 in
+  // groups of 384 15.7 / 16.2, 11.1 / 12.7.  8192 -> 4096, 3-bit, 12.7 / 16.0,
   // 11.4 / 12.6; 4096 -> 512 at 8 7.6, 6.7; 6144 -> 1024 stays at 8.1 at 4 tokens, 8.7 here, and takes 9.8 instead of 11.3 at 16; one token of 8192 -> 4096 10.6, 11.1)
   const float spread = (ntok > 8 ? 10.5f : ntok > 2 ? 10.f : 8.5f) + 0.38f * mb;
-  if (ntok <= 16 && g.d_in % kBlockCols == 0 && best > spread) best = spread;
+  const bool spreads = g.d_in % kBlockCols == 0 && (g.n_groups <= 1 || (g.group_size & (g.group_size - 1)) == 0);
+  if (ntok <= 16 && spreads && best > spread) best = spread;
   int rt = 0, ring = 0, sz = 0, total = 0;
   for (int r = 1; r <= 2; ++r) {
     const int wgs = (g.n_rt + r - 1) / r, rg_bytes = waves * kFewDepth * (np * 256 + r * 2048);

@@ -71,3 +71,19 @@ def test_runs_of_weak_columns(env, runs):
     x[:, idx] = np.float16(30000)
     np.testing.assert_array_equal(a.view(np.uint16), lin(torch.from_numpy(x).cuda()).cpu().numpy().view(np.uint16))
     lin.close()
+
+
+@pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens", [(4736, 549, 4, 384, 30, 1), (4352, 1645, 4, 640, 9, 2), (7680, 2048, 3, 384, 20, 4),
+                                                            (7680, 2048, 3, 384, 20, 16)])
+def test_groups_that_no_other_kernel_takes(env, d_in, d_out, bits, group, k, tokens):
+    # groups that are not 128 2^n: the kernel that spreads columns refuses them, so its cost must not count
+    from launches import launches
+    torch, B = env
+    layer = make_layer(LayerSpec("groups", d_in, d_out, bits, group, k, d_in))
+    x = make_x(layer, tokens)
+    print(f"{d_in} -> {d_out}, {bits} bit, group {group}, {tokens} tokens", flush=True)
+    lin = B.OwqLinear(layer, layout=TILE)
+    xd, y = torch.from_numpy(x).cuda(), torch.empty((tokens, d_out), dtype=torch.float16, device="cuda")
+    assert len(launches(torch, lambda: lin(xd, out=y))) == 1
+    check(y.cpu().numpy(), owq_ref.owq_linear_layer(layer, x), "groups")
+    lin.close()
