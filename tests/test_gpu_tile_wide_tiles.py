@@ -7,6 +7,7 @@ Bar as for the other kernels of the layout: relative L2 error <= 1e-3, max-abs e
 import numpy as np
 import pytest
 
+from launches import launches
 from oracle import owq_ref
 from synth import Layer, LayerSpec, make_layer, make_x
 
@@ -24,9 +25,12 @@ def env():
     return torch, binding
 
 
-def compare(env, layer, x, what, rows=300, rounding=False):
+def compare(env, layer, x, what, rows=300, rounding=False, eight=None):
     torch, B = env
     lin = B.OwqLinear(layer, layout=1)
+    if eight is not None:                  # workgroups of eight waves, 0: none
+        xd, y = torch.from_numpy(x).cuda(), torch.empty((len(x), layer.d_out), dtype=torch.float16, device="cuda")
+        assert sum(n for n, threads in launches(torch, lambda: lin(xd, out=y)) if threads == 512) == eight, what
     got = lin(torch.from_numpy(x).cuda()).cpu().numpy()
     again = lin(torch.from_numpy(x).cuda()).cpu().numpy()
     np.testing.assert_array_equal(got.view(np.uint16), again.view(np.uint16))
@@ -53,7 +57,7 @@ def compare(env, layer, x, what, rows=300, rounding=False):
     (1600, 6401, 3, 128, 1400, 1000),
 ])
 @pytest.mark.parametrize("zeros", ["integers", "any"])
-def test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros, rounding=False):
+def test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros, rounding=False, eight=None):
     layer = make_layer(LayerSpec("tiles", d_in, d_out, bits, group, k, d_in + d_out))
     if zeros == "any":
         rng = np.random.default_rng(5)
@@ -62,17 +66,19 @@ def test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros, rou
         z[rows & (rng.random(d_out) < 0.05)] = 1500.5
         layer.zero[:] = z.astype(np.float16)
     print(d_in, d_out, tokens, zeros, flush=True)
-    compare(env, layer, make_x(layer, tokens), (d_in, d_out, tokens, zeros), rounding=rounding)
+    compare(env, layer, make_x(layer, tokens), (d_in, d_out, tokens, zeros), rounding=rounding, eight=eight)
 
 
-# Workgroups of eight waves, whose halves take half the columns each: no column ranges beside, an odd number of blocks and a last
-# tile whose second 64 tokens do not exist; a round of whole tiles and the others in four ranges, rows of x off the 16-byte
-# grid; two ranges of all tiles; one scale per row.
-@pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens", [
-    (8056, 3300, 3, 128, 40, 1950), (4100, 5120, 4, 128, 40, 2000), (13824, 5100, 4, 256, 300, 590), (8192, 5120, 3, 0, 9, 2040)])
+# Workgroups of eight waves, whose halves take half the columns each, and how many of them: no column ranges beside, an odd number
+# of blocks and a last tile whose second 64 tokens do not exist; a round of whole tiles and the others in five ranges, rows of x
+# off the 16-byte grid; the same where the copied rows leave no room for partial results, four waves; two ranges of all tiles;
+# one scale per row, a round of whole tiles and the others in four ranges.
+@pytest.mark.parametrize("d_in,d_out,bits,group,k,tokens,eight", [
+    (8056, 3300, 3, 128, 40, 1950, 13 * 16), (4100, 6600, 4, 128, 40, 1300, 256 + 5 * 30), (4100, 5120, 4, 128, 40, 2000, 0),
+    (13824, 5100, 4, 256, 300, 590, 2 * 100), (8192, 5120, 3, 0, 9, 2040, 256 + 4 * 64)])
 @pytest.mark.parametrize("zeros", ["integers", "any"])
-def test_tiles_of_two_halves_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros):
-    test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros, rounding=True)
+def test_tiles_of_two_halves_match_oracle(env, d_in, d_out, bits, group, k, tokens, eight, zeros):
+    test_tiles_match_oracle(env, d_in, d_out, bits, group, k, tokens, zeros, rounding=True, eight=eight)
 
 
 @pytest.mark.parametrize("d_in,d_out,bits,k,tokens", [(2048, 300, 3, 1500, 70), (1152, 8192, 4, 4, 1100)])
