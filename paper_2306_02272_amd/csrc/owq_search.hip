@@ -88,7 +88,7 @@ __device__ __forceinline__ float wave_min(float v) {
   const int r0 = __builtin_amdgcn_readlane(i, 0), r1 = __builtin_amdgcn_readlane(i, 16), r2 = __builtin_amdgcn_readlane(i, 32);
   float m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 48));
   asm("s_nop 1\n\tv_min_f32 %0, %1, %0\n\tv_min_f32 %0, %2, %0\n\tv_min_f32 %0, %3, %0\n\ts_nop 1" : "+v"(m) : "s"(r0), "s"(r1), "s"(r2));
-  return m;
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
 }
 __device__ __forceinline__ float wave_max(float v) { return -wave_min(-v); }
 
