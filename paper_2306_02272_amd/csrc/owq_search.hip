@@ -37,6 +37,7 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;            // waves per workgroup, each with its own LDS area
 constexpr int kChunk = 1024;         // columns moved through LDS at a time
+constexpr int zero_points(int bits) { return bits == 3 ? 4 : 7; }      // longest run of them that a lane takes on a diagonal
 constexpr uint16_t kLeft = 0xffffu;  // as a step size: this group is left to the general grid's kernel
 constexpr u32 kLeastStep = 0x38800000u;    // 2^-14 in binary32
 constexpr int kMaskBytesMax = 47 * 1024;   // LDS left for the weak-column bit mask of a row: 64 KiB less the kernel's static 16.1 KiB
@@ -309,10 +310,10 @@ struct TeamShared {
 // rounding, so all its points have one step size, and their zero points are a short run of integers: of 256 points about 107
 // (3 bits) are different ones, and those of one diagonal share all midpoints but a few.  Two lanes take a diagonal, half of
 // its points each; L levels and Z zero points need L + Z - 1 lookups, of which every L in a row are a grid point's (3 bits: 10
-// lookups where four points per lane took 28).  Z covers the runs of all square grids up to 16 x 16 with cuts up to 0.45
-// almost always; a group where a lane's run is longer, where a diagonal has more than one step size (the widths'
-// rounding straddles a binary16 boundary, inside a half or between the two), where a step size is at its least value, a midpoint lies beyond the table or three
-// errors are too close to tell is marked in `scale` (kLeft).
+// lookups where four points per lane took 28).  Z covers the runs of the square grids that come here.  A group where a diagonal
+// has more than one step size (the widths' rounding straddles a binary16 boundary, inside a half or between the two), where a
+// run is longer all the same, a step size is at its least value, a midpoint lies beyond the table or three errors are too close
+// to tell is marked in `scale` (kLeft).
 // BITS < 0: the general grid for what is marked.  In a kernel of its own since the general way takes 30 registers more: 107 ->
 // 90 us for the 2^17 groups of 128 of a 4096 x 4096 matrix, and 5 us for the launch that looks for marks.
 template <int TW, int NT, int POINTS, int BITS>
@@ -612,7 +613,7 @@ __global__ __launch_bounds__(256, NT <= 4 ? 5 : NT <= 24 ? 4 : 2) void owq_searc
       };
       if constexpr (BITS > 0) {
         bool found = false;
-        constexpr int L = (1 << BITS) - 1, Z = BITS == 3 ? 4 : 7;
+        constexpr int L = (1 << BITS) - 1, Z = zero_points(BITS);
         const float qmax = (float)L, rqmax = 1.f / (float)L;
         const float r = hi - lo, lo0 = cut_lo(lo, f0a, r), width = cut_hi(hi, f0b, r) - lo0;
         // no point's width is further from another's than 5.6 2^-24 (r + largest end): seven roundings each
@@ -1296,8 +1297,16 @@ extern "C" owq_status_t owq_search_config(const owq_search_desc_t *d, const uint
   // (with two the general grid's kernel takes as few lookups); steps of a diagonal's width that are several steps of binary16,
   // so that no two diagonals have the same step size; and weights enough that what it saves (0.6 us per 2^17 weights or more) is
   // more than the second launch costs (5 us).
-  const bool diagonals = bounds && g <= 1024 && d->n_lo == d->n_hi && ncand > 128 && d->shrink * 256.f >= (float)(d->n_lo - 1) &&
-                         (long long)d->d_out * d->d_in >= (4 << 20) && units >= 16384;
+  bool diagonals = bounds && g <= 1024 && d->n_lo == d->n_hi && ncand > 128 && d->shrink * 256.f >= (float)(d->n_lo - 1) &&
+                   (long long)d->d_out * d->d_in >= (4 << 20) && units >= 16384;
+  // And no run of zero points longer than a lane takes: from 0.45 on at 4 bits (0.46 at 3) some groups have longer ones, and a
+  // launch that finds any takes 10 us more (4096 x 4096, 4-bit, 12 x 12 points of 0.45, groups of 512: 64 us, weights spread evenly 83;
+  // the general grid's kernel 57 and 54; groups of 128 134 and 152, so 135 and 132).
+  const float cut = d->shrink / (float)(d->n_lo - 1);
+  for (int c = 0; diagonals && c <= 2 * (d->n_lo - 1); ++c) {
+    const int points = (c < d->n_lo ? c : 2 * (d->n_lo - 1) - c) + 1;
+    diagonals = (float)((points - 1) / 2) * cut * a.qmax <= (float)(zero_points(d->bits) - 1) * (1.f - cut * (float)c);
+  }
   if (diagonals) {
     hipLaunchKernelGGL((d->bits == 3 ? pick_bounds_wave<4, 3>(g) : pick_bounds_wave<4, 4>(g)), grid, block, mask_bytes, st, a);
     if (hipGetLastError() != hipSuccess) return OWQ_ERR_HIP;

@@ -10,6 +10,7 @@ the lanes' loads."""
 import numpy as np
 import pytest
 
+from launches import launches
 from oracle import search
 from test_gpu_search_bounds import weights
 
@@ -33,7 +34,7 @@ KINDS = ("normal", "grid", "offset", "least_step", "sparse", "tail", "nan")
 @pytest.mark.parametrize("rows,cols,group,bits,n,shrink", [
     (1100, 4096, 128, 3, 16, 0.4), (1100, 4096, 128, 4, 16, 0.45), (1400, 3000, 128, 3, 12, 0.3), (2100, 2049, 256, 4, 16, 0.375),
     (2100, 2049, 256, 3, 16, 0.375), (2100, 4096, 512, 3, 13, 0.25), (2100, 4096, 512, 4, 16, 0.1), (4200, 4000, 1024, 3, 16, 0.4),
-    (4200, 4000, 1024, 4, 12, 0.45)])
+    (4200, 4000, 1024, 4, 12, 0.45), (1100, 4096, 128, 4, 16, 0.44), (4200, 4000, 1024, 4, 12, 0.44), (2100, 2049, 256, 3, 13, 0.45)])
 def test_same_as_in_calls_of_fewer_groups(env, rows, cols, group, bits, n, shrink):
     torch, B = env
     assert rows * -(-cols // group) >= 16384 and rows * cols >= 4 << 20      # where the library takes diagonals
@@ -46,6 +47,8 @@ def test_same_as_in_calls_of_fewer_groups(env, rows, cols, group, bits, n, shrin
     idx = torch.from_numpy(np.sort(rng.choice(cols, cols // 100, replace=False)).astype(np.int32)).cuda()
     wd = torch.from_numpy(w).cuda()
     whole = B.search_config(wd, idx, bits, group, n, n, shrink)
+    # from 0.45 on at 4 bits zero points of a diagonal's half are further apart than a lane takes: the general kernel alone
+    assert len(launches(torch, lambda: B.search_config(wd, idx, bits, group, n, n, shrink))) == (1 if bits == 4 and shrink >= 0.45 else 2)
     cut = 500 if group < 1024 else 900
     assert cut * cols < 4 << 20
     parts = [B.search_config(wd[r:r + cut].contiguous(), idx, bits, group, n, n, shrink) for r in range(0, rows, cut)]
