@@ -709,9 +709,9 @@ __global__ __launch_bounds__(256) void owq_tile_finish(const FinishArgs a) {
 // between barriers and the partial results behind them, 9.6 us of a call's 24.1; so 21.0).  The partial results are asked for
 // first, and the weak product is dealt out to the four waves, two k-steps of a chunk of eight each, of every set that the tokens
 // use: a wave needs no barrier from set to set, it stages its k-steps of a set's rows in LDS of its own while the next ones are
-// fetched.  A token has one set, whose k-steps add up as they do where there is no other: one task gives the bits of the
-// plain call.  (Every fourth set by a wave, which keeps a set's sum in one chain: 0.98 to 1.06 of this, 1.00 on average
-// over 100 calls.)
+// fetched; where one or two waves have all k-steps, every fourth or second set.  A token has one set, whose k-steps add up as
+// they do where there is no other: one task gives the bits of the plain call.  (Every fourth set by a wave, which keeps a set's sum
+// in one chain: 0.98 to 1.07 of this, 1.005 on average over 100 calls; two, three or four sets' k-steps staged together: 1.01 to 1.02.)
 template <bool SETS>
 __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) {
   constexpr int kPitch = 17;           // 16-byte units per staged row of a chunk of 128 weak columns, odd
@@ -760,12 +760,12 @@ __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) 
       xst[r * kPitch + cu] = (in && nt * 32 + r < a.ntok) ? tb[i] : zero;
     }
   };
-  auto steps = [&](int s0, auto of) __attribute__((always_inline)) {
+  auto steps = [&](int s0, int q, auto of) __attribute__((always_inline)) {     // the chunk's k-steps 2 q and 2 q + 1
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      if (2 * s0 + 4 * wv + 2 * j >= kunits) continue;        // same for the wave
+      if (2 * s0 + 4 * q + 2 * j >= kunits) continue;         // same for the wave
       const u32x4 av = wst[wv][(lane & 31) * 5 + 2 * j + kg];
-      const u32x4 bw = of(xst[(lane & 31) * kPitch + 4 * wv + 2 * j + kg]);
+      const u32x4 bw = of(xst[(lane & 31) * kPitch + 4 * q + 2 * j + kg]);
       wk = mma(__builtin_bit_cast(h8_t, av), __builtin_bit_cast(h8_t, bw), wk);
     }
   };
@@ -783,7 +783,7 @@ __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) 
 #pragma unroll
       for (int i = 0; i < 2; ++i) wst[wv][(i * 16 + wr) * 5 + wu] = v < kunits ? ta[i] : zero;
       __syncthreads();
-      steps(s0, [](u32x4 bw) __attribute__((always_inline)) { return bw; });
+      steps(s0, wv, [](u32x4 bw) __attribute__((always_inline)) { return bw; });
     }
   } else if (kunits > 0) {
     int mine = n < a.ntok ? -1 : -2;
@@ -793,20 +793,25 @@ __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) 
     }
     typedef const __attribute__((address_space(1))) u32x4 *gptr_t;   // pointers read from memory: global
     const unsigned long long base = (unsigned long long)(uintptr_t)(mine >= 0 ? a.weak_sets[mine] : static_cast<const void *>(a.weak_w));
+    // 64 weak columns or fewer are k-steps for two waves, or one: the other two take every second set, or each every fourth
+    const int parts = kunits <= 4 ? 1 : kunits <= 8 ? 2 : 4, part = wv & (parts - 1), every = 4 / parts;
     for (int s0 = 0; 2 * s0 < kunits; s0 += KS) {
-      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0, v = 2 * s0 + 4 * wv + wu, vc = v < kunits ? v : 0;
+      const int u = 2 * s0 + cu, uc = u < kunits ? u : 0, v = 2 * s0 + 4 * part + wu, vc = v < kunits ? v : 0;
       u32x4 tb[2], ta[4][2];                         // four sets' weights in flight
       int c[4];                                      // which
 #pragma unroll
       for (int i = 0; i < 2; ++i) tb[i] = a.xw[(size_t)(nt * 32 + wv * 8 + i * 4 + cr) * kunits + uc];
       // the sets in use, in the order of their first tokens
       unsigned long long pending = __ballot(mine >= -1);
+      int skip = wv / parts;                         // sets before the wave's next one
       auto next_set = [&](u32x4 (&t)[2], int &set) __attribute__((always_inline)) {
         set = -2;
+        for (; skip > 0 && pending != 0ull; --skip) pending &= ~__ballot(mine == __builtin_amdgcn_readlane(mine, __builtin_ctzll(pending)));
         if (pending == 0ull) return;
         const int at = __builtin_ctzll(pending);
         set = __builtin_amdgcn_readlane(mine, at);
         pending &= ~__ballot(mine == set);
+        skip = every - 1;
         const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)base, at), hi = (u32)__builtin_amdgcn_readlane((int)(u32)(base >> 32), at);
         const gptr_t w0 = (gptr_t)(uintptr_t)(((unsigned long long)hi << 32) | lo);
 #pragma unroll
@@ -826,7 +831,7 @@ __global__ __launch_bounds__(256) void owq_tile_finish_rows(const FinishArgs a) 
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        steps(s0, [&](u32x4 bw) __attribute__((always_inline)) { return use ? bw : zero; });
+        steps(s0, part, [&](u32x4 bw) __attribute__((always_inline)) { return use ? bw : zero; });
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

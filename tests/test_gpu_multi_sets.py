@@ -73,7 +73,7 @@ def test_many_rows(env, d_out, batch, bits, group, k, used):
     lin.close()
 
 
-@pytest.mark.parametrize("d_out,k", [(96, 33), (128, 130), (300, 200), (70, 300), (10300, 70)])
+@pytest.mark.parametrize("d_out,k", [(40, 1), (200, 30), (96, 33), (170, 64), (128, 130), (300, 200), (70, 300), (10300, 70)])
 @pytest.mark.parametrize("bits,group", [(3, 0), (4, 128)])
 @pytest.mark.parametrize("batch", [33, 64])
 def test_one_task_equals_the_plain_call_bit_for_bit(env, d_out, k, bits, group, batch):
