@@ -332,7 +332,9 @@ typedef struct {
  * of order or out of range give a wrong result, never an access out of bounds); written:
  * scale, zero fp16 bit patterns [d_out][G], codes [d_out][d_in], and, unless NULL, err [d_out][G]
  * (E of the choice) and choice [d_out][G] (i n_hi + j).  G = 1 if group_size == 0, else
- * ceil(d_in / group_size).  One launch on `stream`, no allocation, no synchronisation.
+ * ceil(d_in / group_size).  One launch on `stream`, or two: on square grids and many groups the first leaves marks in `scale`
+ * for the groups that the second searches, so scale is read by the device as well, and until the call is through, all outputs
+ * of such groups are undefined.  No allocation, no synchronisation; calls in flight at once need outputs of their own.
  * Errors: OWQ_ERR_NULL, OWQ_ERR_SHAPE (sizes below 1, d_out G above 2^31 - 1, grid or shrink out
  * of range), OWQ_ERR_BITS, OWQ_ERR_GROUP, OWQ_ERR_INDEX (k out of range), OWQ_ERR_UNSUPPORTED (d_in above
  * 385024: the weak-column bit mask of a row must fit 47 KiB of LDS), OWQ_ERR_HIP.

@@ -16,8 +16,8 @@
 // the order of the columns, so that the choice is that of the plain search.
 // Bound by vector instructions, and by how many waves a SIMD holds to issue them: a wave issues one every four or five cycles, the
 // SIMD takes more.  16384 x 4096, 3-bit, groups of 128, 16 x 16 points: plain search 1780 us, four points per lane 620 (815
-// instructions per group), the grid by diagonals with the general way in the same kernel 395 (497; five waves per SIMD), in a
-// kernel of its own 357 (eight).  5120 x 5120, 4-bit, one scale per row: 134 -> 98 us when a wave's registers went from 227 to 113
+// instructions per group), the grid by diagonals with the general way in the same kernel 395 (five waves per SIMD), in a
+// kernel of its own 357 (504; eight).  5120 x 5120, 4-bit, one scale per row: 134 -> 98 us when a wave's registers went from 227 to 112
 // (two waves per SIMD -> four: columns and masks of all weights had been kept in registers from one row to the next, and masks
 // in spilled scalar registers), 76 to 98 with a row per workgroup, one of several equal points of a diagonal evaluated and
 // two points at a time summed in order (by whether one of the last rows has such points: 20 us); 4096 rows of 13824: 290 -> 123.
